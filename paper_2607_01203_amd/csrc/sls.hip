@@ -5,8 +5,8 @@
 //
 // Responses (appendix on solving for Phi, eqs. backward_prop and
 // forward_prop; reformulated problem eq. fastsls_qp_reform): the problem
-// splits over the disturbance time j, so one workgroup owns one (trajectory,
-// j) pair and runs, with every matrix in LDS,
+// splits over the disturbance time j, so every (trajectory, j) pair runs on its
+// own, by one of three kernels chosen by size (leb_sls_responses),
 //   backward  P_{N,j} = diag(qx_{N,j}); for k = N-1 .. j+1:
 //             S = diag(qu_{k,j}) + B_k^T P B_k,  Bc = B_k^T P A_k,
 //             K_{k,j} = -S^-1 Bc (Cholesky),  P <- diag(qx_{k,j}) + A_k^T P A_k + K^T Bc
@@ -447,6 +447,269 @@ __global__ void __launch_bounds__(64) sls_riccati_mfma_kernel(RiccatiArgs a) {
             X = mm_tn(AclT, X, z4);                 // (A + B K) X
         }
     }
+}
+
+// The same recursions for larger sizes (nx <= 32, nu <= 16) on FP64 MFMA: one
+// wave per (trajectory, j), every matrix in registers as TX x TX zero-padded
+// 16 x 16 tiles (TX = 2: nx > 16) in the layout of the kernel above, every product
+// a sum of X^T Y over tiles.  The gain solves S K = -Bc by elimination: lane c
+// holds column c of [S | Bc] (NUB rows, NUB >= nu), and the pivot column is read
+// from its lane by v_readlane, so the nu steps need no LDS; the pivots are
+// the squares of the Cholesky pivots' and are tested the same way.  Only the
+// hand-over between the two layouts goes through LDS.
+//
+// What bounds it: the FP64 matrix rate and the serial chain of a wave.  At
+// nx = 30, nu = 10 a backward and a forward step issue 184 MFMA (64 cycles
+// each); the first launched waves are the longest chains (j = 0 of every
+// trajectory), so the short ones fill the end of the launch.  64 x 40 steps:
+// 0.55 ms, 34 TFLOP/s of padded products (6.48 ms with a 256-lane workgroup per
+// (trajectory, j) and every matrix in LDS).
+// Tiles are read through a buffer descriptor of the one matrix: a row past the
+// end is out of its range and reads 0, so a lane needs one offset per tile and one
+// column test instead of an address and a test for every element.
+typedef unsigned int sls_u2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t matrix_rsrc(const double* M, int elems) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(M), 0, elems * 8, 0x00027000);
+}
+
+// the 16 x 16 tile at (r0, c0) of a matrix with rows of C elements; tr: of its transpose
+__device__ __forceinline__ sls_d4 tile_at(__amdgpu_buffer_rsrc_t M, int C, int r0, int c0, int lr, int lq, bool tr) {
+    sls_d4 v;
+    const int o = 8 * (tr ? (c0 + lr) * C + r0 + lq : (r0 + lq) * C + c0 + lr);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        union { sls_u2 u; double d; } x;
+        x.u = __builtin_amdgcn_raw_buffer_load_b64(M, o + (tr ? 32 * i : 32 * i * C), 0, 0);
+        v[i] = (tr ? r0 + lq + 4 * i : c0 + lr) < C ? x.d : 0.0;
+    }
+    return v;
+}
+
+__device__ __forceinline__ double lane_value(double x, int lane) {   // x of one lane, uniform
+    union { double d; int w[2]; } u;
+    u.d = x;
+    u.w[0] = __builtin_amdgcn_readlane(u.w[0], lane);
+    u.w[1] = __builtin_amdgcn_readlane(u.w[1], lane);
+    return u.d;
+}
+
+template <int TX, int NUB>
+__global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) {
+    constexpr int W = 16 * TX, LD = 16 + W;
+    const int b = blockIdx.x, j = blockIdx.y;
+    const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
+    if (j >= N - 1) return;                      // no k with j < k < N
+    __shared__ double sT[16 * LD];               // [S | Bc], row-major
+    __shared__ double sK[16 * W];                // K_k, zero rows past nu
+    const int lane = threadIdx.x, lr = lane & 15, lq = lane >> 4;
+    const double* Ab = a.A + (size_t)b * N * nx * nx;
+    const double* Bb = a.B + (size_t)b * N * nx * nu;
+    const double* qxb = a.qx + (size_t)b * (N + 1) * N * nx;
+    const double* qub = a.qu + (size_t)b * N * N * nu;
+    double* Kb = a.K + (size_t)b * N * N * nu * nx;
+    double* phib = a.phi + (size_t)b * N * N * n * nx;
+    for (int q = lane; q < 16 * W; q += 64) sK[q] = 0.0;
+    // element of this lane on a tile's diagonal (row 4i + lq == lr), if any
+    const int di = (lr >= lq && ((lr - lq) & 3) == 0) ? (lr - lq) >> 2 : -1;
+    const sls_d4 z4 = {0.0, 0.0, 0.0, 0.0};
+    auto diag = [&](const double* q, int t) { return (di >= 0 && 16 * t + lr < nx) ? q[16 * t + lr] : 0.0; };
+    sls_d4 P[TX][TX], An[TX][TX], Bn[TX];
+    double qxn[TX], qun;
+#pragma unroll
+    for (int t = 0; t < TX; ++t) {
+        const double q = diag(qxb + ((size_t)N * N + j) * nx, t);
+#pragma unroll
+        for (int u = 0; u < TX; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) P[t][u][i] = (t == u && i == di) ? q : 0.0;
+    }
+    auto fetch = [&](int k) {
+        const auto rA = matrix_rsrc(Ab + (size_t)k * nx * nx, nx * nx), rB = matrix_rsrc(Bb + (size_t)k * nx * nu, nx * nu);
+#pragma unroll
+        for (int t = 0; t < TX; ++t) {
+#pragma unroll
+            for (int u = 0; u < TX; ++u) An[t][u] = tile_at(rA, nx, 16 * t, 16 * u, lr, lq, false);
+            Bn[t] = tile_at(rB, nu, 16 * t, 0, lr, lq, false);
+            qxn[t] = diag(qxb + ((size_t)k * N + j) * nx, t);
+        }
+        qun = (di >= 0 && lr < nu) ? qub[((size_t)k * N + j) * nu + lr] : 0.0;
+    };
+    fetch(N - 1);
+    for (int k = N - 1; k > j; --k) {
+        sls_d4 A[TX][TX], B[TX], PA[TX][TX], Bc[TX];
+        double qxd[TX];
+        const double qud = qun;
+#pragma unroll
+        for (int t = 0; t < TX; ++t) {
+#pragma unroll
+            for (int u = 0; u < TX; ++u) A[t][u] = An[t][u];
+            B[t] = Bn[t];
+            qxd[t] = qxn[t];
+        }
+        if (k - 1 > j) fetch(k - 1);
+        // S = diag(qu) + B^T (P B) first: its elimination is the longer chain
+        sls_d4 S = z4;
+#pragma unroll
+        for (int t = 0; t < TX; ++t) {
+            sls_d4 pb = z4;
+#pragma unroll
+            for (int u = 0; u < TX; ++u) pb = mm_tn(P[u][t], B[u], pb);
+            S = mm_tn(B[t], pb, S);
+        }
+#pragma unroll
+        for (int t = 0; t < TX; ++t)
+#pragma unroll
+            for (int u = 0; u < TX; ++u) {
+                sls_d4 c = z4;
+#pragma unroll
+                for (int l = 0; l < TX; ++l) c = mm_tn(P[l][t], A[l][u], c);
+                PA[t][u] = c;
+            }
+#pragma unroll
+        for (int u = 0; u < TX; ++u) {
+            Bc[u] = z4;
+#pragma unroll
+            for (int t = 0; t < TX; ++t) Bc[u] = mm_tn(B[t], PA[t][u], Bc[u]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * i + lq;
+            sT[row * LD + lr] = S[i] + (i == di ? qud : 0.0);
+#pragma unroll
+            for (int u = 0; u < TX; ++u) sT[row * LD + 16 + 16 * u + lr] = Bc[u][i];
+        }
+        lds_barrier();
+        // elimination: column `lane` of [S | Bc]
+        {
+            double col[NUB];
+            const int c = lane < LD ? lane : LD - 1;
+#pragma unroll
+            for (int r = 0; r < NUB; ++r) col[r] = sT[r * LD + c];
+            bool bad = false;
+#pragma unroll
+            for (int p = 0; p < NUB; ++p) {
+                if (p < nu) {
+                    double piv = lane_value(col[p], p);
+                    if (!(piv > 0.0) || !isfinite(piv)) { bad = true; piv = 1.0; }
+                    const double x = col[p] / piv;
+#pragma unroll
+                    for (int r = 0; r < NUB; ++r)
+                        if (r != p) col[r] = fma(-lane_value(col[r], p), x, col[r]);
+                    col[p] = x;
+                }
+            }
+            const int kc = lane - 16;
+            if (kc >= 0 && kc < W) {
+#pragma unroll
+                for (int r = 0; r < NUB; ++r) {
+                    if (r < nu) {
+                        const double kv = bad ? NAN : -col[r];
+                        sK[r * W + kc] = kv;
+                        if (kc < nx) Kb[((size_t)k * N + j) * nu * nx + r * nx + kc] = kv;
+                    }
+                }
+            }
+        }
+        lds_barrier();
+        // P <- diag(qx) + A^T (P A) + K^T Bc
+        sls_d4 K[TX];
+#pragma unroll
+        for (int t = 0; t < TX; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) K[t][i] = sK[(4 * i + lq) * W + 16 * t + lr];
+#pragma unroll
+        for (int t = 0; t < TX; ++t)
+#pragma unroll
+            for (int u = 0; u < TX; ++u) {
+                sls_d4 c;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[i] = (t == u && i == di) ? qxd[t] : 0.0;
+#pragma unroll
+                for (int l = 0; l < TX; ++l) c = mm_tn(A[l][t], PA[l][u], c);
+                P[t][u] = mm_tn(K[t], Bc[u], c);
+            }
+        lds_barrier();                           // sT, sK are rewritten by the next step
+    }
+    // forward: U = K X, X' = A X + B U.  The gains were stored by this wave, and the
+    // full barrier orders those stores before the loads
+    __syncthreads();
+    sls_d4 X[TX][TX], ATn[TX][TX], BTn[TX], KTn[TX];
+#pragma unroll
+    for (int t = 0; t < TX; ++t)
+#pragma unroll
+        for (int u = 0; u < TX; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) X[t][u][i] = (t == u && i == di && 16 * t + lr < nx) ? 1.0 : 0.0;
+    auto ffetch = [&](int k) {                   // tiles of A^T, B^T, K^T
+        const auto rA = matrix_rsrc(Ab + (size_t)k * nx * nx, nx * nx), rB = matrix_rsrc(Bb + (size_t)k * nx * nu, nx * nu),
+                   rK = matrix_rsrc(Kb + ((size_t)k * N + j) * nu * nx, nu * nx);
+#pragma unroll
+        for (int t = 0; t < TX; ++t) {
+#pragma unroll
+            for (int u = 0; u < TX; ++u) ATn[t][u] = tile_at(rA, nx, 16 * t, 16 * u, lr, lq, true);
+            BTn[t] = tile_at(rB, nu, 0, 16 * t, lr, lq, true);
+            KTn[t] = tile_at(rK, nx, 16 * t, 0, lr, lq, true);
+        }
+    };
+    ffetch(j + 1);
+    for (int k = j + 1; k < N; ++k) {
+        sls_d4 AT[TX][TX], BT[TX], KT[TX], U[TX];
+#pragma unroll
+        for (int t = 0; t < TX; ++t) {
+#pragma unroll
+            for (int u = 0; u < TX; ++u) AT[t][u] = ATn[t][u];
+            BT[t] = BTn[t];
+            KT[t] = KTn[t];
+        }
+        if (k + 1 < N) ffetch(k + 1);
+#pragma unroll
+        for (int u = 0; u < TX; ++u) {
+            U[u] = z4;
+#pragma unroll
+            for (int t = 0; t < TX; ++t) U[u] = mm_tn(KT[t], X[t][u], U[u]);
+        }
+        double* out = phib + ((size_t)k * N + j) * n * nx;
+#pragma unroll
+        for (int u = 0; u < TX; ++u) {
+            const int col = 16 * u + lr;
+            if (col < nx) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                    for (int t = 0; t < TX; ++t) {
+                        const int row = 16 * t + 4 * i + lq;
+                        if (row < nx) out[row * nx + col] = X[t][u][i];
+                    }
+                    if (4 * i + lq < nu) out[(nx + 4 * i + lq) * nx + col] = U[u][i];
+                }
+            }
+        }
+        if (k + 1 < N) {
+            sls_d4 Xn[TX][TX];
+#pragma unroll
+            for (int t = 0; t < TX; ++t)
+#pragma unroll
+                for (int u = 0; u < TX; ++u) {
+                    sls_d4 c = mm_tn(BT[t], U[u], z4);
+#pragma unroll
+                    for (int l = 0; l < TX; ++l) c = mm_tn(AT[l][t], X[l][u], c);
+                    Xn[t][u] = c;
+                }
+#pragma unroll
+            for (int t = 0; t < TX; ++t)
+#pragma unroll
+                for (int u = 0; u < TX; ++u) X[t][u] = Xn[t][u];
+        }
+    }
+}
+
+template <int TX>
+static void launch_riccati_tile(const RiccatiArgs& a, int batch, hipStream_t st) {
+    const dim3 grid((unsigned)batch, (unsigned)a.N);
+    if (a.nu <= 8) hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 8>), grid, dim3(64), 0, st, a);
+    else if (a.nu <= 12) hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 12>), grid, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 16>), grid, dim3(64), 0, st, a);
 }
 
 static size_t riccati_smem(int nx, int nu) {
@@ -1007,22 +1270,21 @@ extern "C" int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t 
     RiccatiArgs a;
     a.A = A; a.B = B; a.qx = qx; a.qu = qu; a.K = K; a.phi = phi;
     a.nx = nx; a.nu = nu; a.N = N;
-    const int threads = min(SLS_THREADS, 64 * ((nx * nx + 63) / 64));
-    // registers per thread that hold one step's prefetch
-    const int step = max(nx * nx + 2 * nx * nu, nx * (nx + nu) + nx + nu);
-    const bool small = nu <= 4 && step <= 2 * threads;
-    if (!small && step > SLS_PF * threads) return LEB_ENOTSUP;
     const dim3 grid((unsigned)N, (unsigned)batch);
     const size_t sm = riccati_smem(nx, nu);
     hipStream_t st = (hipStream_t)stream;
-    if (nx > 8 && nx <= 16 && nu <= 4)
+    // nx <= 8 and nu <= 4: a 16 x 16 tile would be mostly padding (19 times the work at
+    // nx = 6), so these stay on the VALU; everything else runs on the matrix cores
+    if (nx > 16)
+        launch_riccati_tile<2>(a, batch, st);
+    else if (nu > 4)
+        launch_riccati_tile<1>(a, batch, st);
+    else if (nx > 8)
         hipLaunchKernelGGL((sls_riccati_mfma_kernel<4>), grid, dim3(64), 0, st, a);
-    else if (nx == 6 && nu == 2 && threads == 64)
-        hipLaunchKernelGGL((sls_riccati_kernel<4, 2, 6, 2>), grid, dim3(threads), sm, st, a);
-    else if (small)
-        hipLaunchKernelGGL((sls_riccati_kernel<4, 2>), grid, dim3(threads), sm, st, a);
+    else if (nx == 6 && nu == 2)
+        hipLaunchKernelGGL((sls_riccati_kernel<4, 2, 6, 2>), grid, dim3(64), sm, st, a);
     else
-        hipLaunchKernelGGL((sls_riccati_kernel<SLS_MAX_NU, SLS_PF>), grid, dim3(threads), sm, st, a);
+        hipLaunchKernelGGL((sls_riccati_kernel<4, 2>), grid, dim3(64), sm, st, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 

@@ -375,3 +375,39 @@ def test_sls_fixed_point_bad_nominal(gpu):
     assert torch.equal(sg[0, :6], ref[1][0, :6]) and torch.equal(mu[0, :6], ref[0][0, :6])
     for t_new, t_ref in zip((mu, sg, lo, hi), ref[:4]):
         assert torch.equal(t_new[1], t_ref[1])
+
+
+@pytest.mark.parametrize("nx,nu", [(9, 5), (10, 9), (16, 16), (17, 1), (18, 6), (24, 8), (31, 9), (32, 12), (32, 16),
+                                   (8, 5), (1, 16)])
+@pytest.mark.parametrize("N", [2, 3, 8])
+def test_responses_tile_edges(gpu, sls, nx, nu, N):
+    """The tiled Riccati kernel at the edges of its tiles and row counts
+    (nx 16 / 17 / 32, nu 8 / 9 / 12 / 16) and the shortest horizons; same
+    tolerance as above, entries k <= j zero."""
+    import paper_2607_01203_amd as leb
+    A, B, qx, qu = W.random_ltv(300 + nx + nu, 2, N, nx, nu, scale=0.2)
+    print("case: responses nx=%d nu=%d N=%d" % (nx, nu, N), flush=True)
+    K, phi = leb.sls_responses(_t(A, gpu), _t(B, gpu), _t(qx, gpu), _t(qu, gpu))
+    K, phi = _np(K), _np(phi)
+    for b in range(2):
+        Ko, _ = sls.riccati(A[b], B[b], qx[b], qu[b])
+        Po, _ = sls.responses(A[b], B[b], Ko)
+        for k in range(N):
+            for j in range(N):
+                s = max(np.abs(Po[k, j]).max(), 1e-300) if k > j else 0.0
+                assert np.abs(phi[b, k, j] - Po[k, j]).max() <= 1e-9 * s, (b, k, j)
+                sk = max(np.abs(Ko[k, j]).max(), 1e-300) if k > j else 0.0
+                assert np.abs(K[b, k, j] - Ko[k, j]).max() <= 1e-9 * sk, (b, k, j)
+
+
+@pytest.mark.parametrize("nx,nu", [(12, 6), (30, 10)])
+def test_responses_tile_non_positive_pivot(gpu, nx, nu):
+    """A weight that makes S indefinite at (k, j) = (3, 1) gives NaN gains for
+    that disturbance time at k <= 3 and leaves the others finite."""
+    import paper_2607_01203_amd as leb
+    A, B, qx, qu = W.random_ltv(7, 1, 6, nx, nu, scale=0.2)
+    qu[0, 3, 1, nu - 1] = -1e6
+    K, _ = leb.sls_responses(_t(A, gpu), _t(B, gpu), _t(qx, gpu), _t(qu, gpu))
+    K = _np(K)[0]
+    assert np.isnan(K[3, 1]).all() and np.isnan(K[2, 1]).all()
+    assert np.isfinite(K[4:, 1]).all() and np.isfinite(K[:, 0]).all() and np.isfinite(K[:, 2]).all()
