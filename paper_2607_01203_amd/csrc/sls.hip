@@ -63,12 +63,10 @@ struct RiccatiArgs {
     int nx, nu, N;
 };
 
-// NXC, NUC > 0: nx and nu fixed at compile time (the short dot products are
-// then unrolled and their LDS loads issued together); 0: taken from a.
-template <int NUB, int PF, int NXC = 0, int NUC = 0>
+template <int NUB, int PF>
 __global__ void __launch_bounds__(SLS_THREADS) sls_riccati_kernel(RiccatiArgs a) {
     const int j = blockIdx.x, b = blockIdx.y;
-    const int nx = NXC ? NXC : a.nx, nu = NUC ? NUC : a.nu, N = a.N, n = nx + nu;
+    const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
     if (j >= N - 1) return;                      // no k with j < k < N
     extern __shared__ double sm[];
     double* P = sm;                              // nx*nx   cost-to-go, then X of the forward pass
@@ -266,6 +264,198 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_riccati_kernel(RiccatiArgs a)
     for (int k = j + 1; k < N; k += 2) {
         fstep(k, pfa, pfb);
         if (k + 1 < N) fstep(k + 1, pfb, pfa);
+    }
+}
+
+// The same recursions for one small size (NX <= 8, NU = 2) with eight lanes per
+// (trajectory, j): lane c of a group of eight holds column c of every matrix in
+// registers, so products with A_k and B_k from the left are local, and a wave
+// runs eight consecutive j of one trajectory in lockstep over k, sharing
+// A_k and B_k (read as broadcasts from LDS, stored there one step ahead).
+// P is symmetric, so P A = (A^T P)^T: the step's only exchanges between lanes are
+// that transpose, the 2 x NX rows of B^T P and the gain (LDS, padded strides).
+// The 2 x 2 system is solved as L D L^T; its pivots are the squares of the
+// Cholesky pivots and are tested the same way.
+//
+// What bounds it: the serial chain of a wave, 2 (N - j - 1) dependent steps; at
+// 256 trajectories a compute unit holds five waves.  Eight lanes per chain keep
+// one step's products (about 190 FMA) inside the latency that its exchanges cost
+// anyway.  256 x 40 steps at nx = 6: 0.088 ms (one 64-lane workgroup per chain with
+// the matrices in LDS: 0.280 ms); 1,024 x 40: 0.25 ms (0.857 ms).
+template <int NX, int NU>
+__global__ void __launch_bounds__(64) sls_riccati_lane_kernel(RiccatiArgs a) {
+    static_assert(NX <= 8 && NU == 2, "eight lanes per chain, 2 x 2 gain system");
+    constexpr int n = NX + NU, AB = NX * n;                    // A_k and B_k of one step
+    constexpr int ST = NX * NX + 2, SN = NU * NX + 2;          // strides of a chain's blocks in LDS
+    const int b = blockIdx.y, N = a.N;
+    const int lane = threadIdx.x, ch = lane >> 3, c = lane & 7;
+    const int j0 = 8 * blockIdx.x, j = min(j0 + ch, N - 1);   // j = N - 1 has no steps
+    const bool own = c < NX;
+    const int cc = own ? c : 0;
+    __shared__ double sAB[2][AB];
+    __shared__ double sT[8 * ST];                              // A^T P, then free
+    __shared__ double sN[8 * SN];                              // B^T P, then K
+    const double* Ab = a.A + (size_t)b * N * NX * NX;
+    const double* Bb = a.B + (size_t)b * N * NX * NU;
+    const double* qxb = a.qx + (size_t)b * (N + 1) * N * NX;
+    const double* qub = a.qu + (size_t)b * N * N * NU;
+    double* Kb = a.K + (size_t)b * N * N * NU * NX;
+    double* phib = a.phi + (size_t)b * N * N * n * NX;
+    auto ab_at = [&](int k) {
+        return lane < NX * NX ? Ab[(size_t)k * NX * NX + lane]
+                              : (lane < AB ? Bb[(size_t)k * NX * NU + (lane - NX * NX)] : 0.0);
+    };
+    static_assert(AB <= 64, "one value of A_k and B_k per lane");
+    double P[NX];
+#pragma unroll
+    for (int r = 0; r < NX; ++r) P[r] = 0.0;
+    {
+        const double q = qxb[((size_t)N * N + j) * NX + cc];
+#pragma unroll
+        for (int r = 0; r < NX; ++r) P[r] = r == c ? q : 0.0;
+    }
+    double abn = ab_at(N - 1);
+    double qxn = qxb[((size_t)(N - 1) * N + j) * NX + cc];
+    double qu0n = qub[((size_t)(N - 1) * N + j) * NU], qu1n = qub[((size_t)(N - 1) * N + j) * NU + 1];
+    if (lane < AB) sAB[(N - 1) & 1][lane] = abn;
+    if (N - 2 > j0) abn = ab_at(N - 2);
+    for (int k = N - 1; k > j0; --k) {
+        const double qx = qxn, qu0 = qu0n, qu1 = qu1n;
+        lds_barrier();                                         // A_k, B_k stored; sN free
+        if (k - 1 > j0) {
+            qxn = qxb[((size_t)(k - 1) * N + j) * NX + cc];
+            qu0n = qub[((size_t)(k - 1) * N + j) * NU];
+            qu1n = qub[((size_t)(k - 1) * N + j) * NU + 1];
+        }
+        double A[NX * NX], B[NX * NU];
+#pragma unroll
+        for (int q = 0; q < NX * NX; ++q) A[q] = sAB[k & 1][q];
+#pragma unroll
+        for (int q = 0; q < NX * NU; ++q) B[q] = sAB[k & 1][NX * NX + q];
+        // column c of A^T P (row c of P A) and of B^T P
+#pragma unroll
+        for (int r = 0; r < NX; ++r) {
+            double s = 0.0;
+#pragma unroll
+            for (int l = 0; l < NX; ++l) s = fma(A[l * NX + r], P[l], s);
+            if (own) sT[ch * ST + c * NX + r] = s;
+        }
+#pragma unroll
+        for (int m = 0; m < NU; ++m) {
+            double s = 0.0;
+#pragma unroll
+            for (int l = 0; l < NX; ++l) s = fma(B[l * NU + m], P[l], s);
+            if (own) sN[ch * SN + m * NX + c] = s;
+        }
+        lds_barrier();
+        if (k - 1 > j0) {
+            if (lane < AB) sAB[(k - 1) & 1][lane] = abn;
+            if (k - 2 > j0) abn = ab_at(k - 2);
+        }
+        double PA[NX], Bc[NU], S[3];                           // S: (0,0), (1,0), (1,1)
+#pragma unroll
+        for (int r = 0; r < NX; ++r) PA[r] = sT[ch * ST + r * NX + cc];
+        S[0] = S[1] = S[2] = 0.0;
+#pragma unroll
+        for (int l = 0; l < NX; ++l) {
+            const double n0 = sN[ch * SN + l], n1 = sN[ch * SN + NX + l];
+            S[0] = fma(n0, B[l * NU], S[0]);
+            S[1] = fma(n1, B[l * NU], S[1]);
+            S[2] = fma(n1, B[l * NU + 1], S[2]);
+        }
+#pragma unroll
+        for (int m = 0; m < NU; ++m) {
+            Bc[m] = 0.0;
+#pragma unroll
+            for (int r = 0; r < NX; ++r) Bc[m] = fma(B[r * NU + m], PA[r], Bc[m]);
+        }
+        double d0 = qu0 + S[0];
+        bool bad = !(d0 > 0.0) || !isfinite(d0);
+        if (bad) d0 = 1.0;
+        const double i0 = 1.0 / d0, l10 = S[1] * i0;
+        double d1 = fma(-l10, S[1], qu1 + S[2]);
+        if (!(d1 > 0.0) || !isfinite(d1)) { bad = true; d1 = 1.0; }
+        const double y1 = fma(-l10, Bc[0], Bc[1]) / d1;
+        const double y0 = fma(-l10, y1, Bc[0] * i0);
+        const double K0 = bad ? NAN : -y0, K1 = bad ? NAN : -y1;
+        lds_barrier();                                         // B^T P read
+        if (own) {
+            sN[ch * SN + c] = K0;
+            sN[ch * SN + NX + c] = K1;
+            if (k > j) {
+                double* Kp = Kb + ((size_t)k * N + j) * NU * NX;
+                Kp[c] = K0;
+                Kp[NX + c] = K1;
+            }
+        }
+        lds_barrier();
+        // P <- diag(qx) + A^T (P A) + K^T Bc (chains with k <= j no longer use theirs)
+#pragma unroll
+        for (int r = 0; r < NX; ++r) {
+            double s = r == c ? qx : 0.0;
+#pragma unroll
+            for (int l = 0; l < NX; ++l) s = fma(A[l * NX + r], PA[l], s);
+            s = fma(sN[ch * SN + r], Bc[0], s);
+            P[r] = fma(sN[ch * SN + NX + r], Bc[1], s);
+        }
+    }
+    // forward: U = K X, X' = A X + B U from Phi^x_{j+1,j} = I.  The gains were stored
+    // by this wave, and the full barrier orders those stores before the loads
+    __syncthreads();
+    double X[NX], Kn[NU * NX];
+#pragma unroll
+    for (int r = 0; r < NX; ++r) X[r] = 0.0;
+    auto kfetch = [&](int k) {
+        const double* Kp = Kb + ((size_t)k * N + min(j, k - 1)) * NU * NX;
+#pragma unroll
+        for (int q = 0; q < NU * NX; ++q) Kn[q] = Kp[q];
+    };
+    abn = ab_at(j0 + 1 < N ? j0 + 1 : N - 1);
+    if (j0 + 1 < N) {
+        kfetch(j0 + 1);
+        if (lane < AB) sAB[(j0 + 1) & 1][lane] = abn;
+        if (j0 + 2 < N) abn = ab_at(j0 + 2);
+    }
+    for (int k = j0 + 1; k < N; ++k) {
+        double K[NU * NX];
+#pragma unroll
+        for (int q = 0; q < NU * NX; ++q) K[q] = Kn[q];
+        lds_barrier();                                         // A_k, B_k stored
+        if (k + 1 < N) kfetch(k + 1);
+        if (k == j + 1) {
+#pragma unroll
+            for (int r = 0; r < NX; ++r) X[r] = r == c ? 1.0 : 0.0;
+        }
+        double U[NU];
+#pragma unroll
+        for (int m = 0; m < NU; ++m) {
+            U[m] = 0.0;
+#pragma unroll
+            for (int l = 0; l < NX; ++l) U[m] = fma(K[m * NX + l], X[l], U[m]);
+        }
+        if (own && k > j) {
+            double* out = phib + ((size_t)k * N + j) * n * NX + c;
+#pragma unroll
+            for (int r = 0; r < NX; ++r) out[r * NX] = X[r];
+#pragma unroll
+            for (int m = 0; m < NU; ++m) out[(NX + m) * NX] = U[m];
+        }
+        double Xn[NX];
+#pragma unroll
+        for (int r = 0; r < NX; ++r) {
+            double s = 0.0;
+#pragma unroll
+            for (int l = 0; l < NX; ++l) s = fma(sAB[k & 1][r * NX + l], X[l], s);
+#pragma unroll
+            for (int m = 0; m < NU; ++m) s = fma(sAB[k & 1][NX * NX + r * NU + m], U[m], s);
+            Xn[r] = s;
+        }
+#pragma unroll
+        for (int r = 0; r < NX; ++r) X[r] = Xn[r];
+        if (k + 1 < N) {
+            if (lane < AB) sAB[(k + 1) & 1][lane] = abn;
+            if (k + 2 < N) abn = ab_at(k + 2);
+        }
     }
 }
 
@@ -1282,7 +1472,8 @@ extern "C" int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t 
     else if (nx > 8)
         hipLaunchKernelGGL((sls_riccati_mfma_kernel<4>), grid, dim3(64), 0, st, a);
     else if (nx == 6 && nu == 2)
-        hipLaunchKernelGGL((sls_riccati_kernel<4, 2, 6, 2>), grid, dim3(64), sm, st, a);
+        hipLaunchKernelGGL((sls_riccati_lane_kernel<6, 2>), dim3((unsigned)((N + 7) / 8), (unsigned)batch), dim3(64),
+                           0, st, a);
     else
         hipLaunchKernelGGL((sls_riccati_kernel<4, 2>), grid, dim3(64), sm, st, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
