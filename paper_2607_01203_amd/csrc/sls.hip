@@ -684,12 +684,24 @@ __device__ __forceinline__ double lane_value(double x, int lane) {   // x of one
     return u.d;
 }
 
+// acc + X^T Y over the first `steps` groups of four rows (the others are padding)
+__device__ __forceinline__ sls_d4 mm_tn(const sls_d4& X, const sls_d4& Y, sls_d4 acc, int steps) {
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[0], Y[0], acc, 0, 0, 0);
+    if (steps > 1) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[1], Y[1], acc, 0, 0, 0);
+    if (steps > 2) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[2], Y[2], acc, 0, 0, 0);
+    if (steps > 3) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[3], Y[3], acc, 0, 0, 0);
+    return acc;
+}
+
 template <int TX, int NUB>
 __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) {
     constexpr int W = 16 * TX, LD = 16 + W;
     const int b = blockIdx.x, j = blockIdx.y;
     const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
     if (j >= N - 1) return;                      // no k with j < k < N
+    // k-steps of a product over states (per tile) and over inputs
+    const int sx0 = TX > 1 ? 4 : (nx + 3) >> 2, sx1 = (nx - 13) >> 2, su = (nu + 3) >> 2;
+    auto sx = [&](int t) { return t == 0 ? sx0 : sx1; };
     __shared__ double sT[16 * LD];               // [S | Bc], row-major
     __shared__ double sK[16 * W];                // K_k, zero rows past nu
     const int lane = threadIdx.x, lr = lane & 15, lq = lane >> 4;
@@ -744,8 +756,8 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
         for (int t = 0; t < TX; ++t) {
             sls_d4 pb = z4;
 #pragma unroll
-            for (int u = 0; u < TX; ++u) pb = mm_tn(P[u][t], B[u], pb);
-            S = mm_tn(B[t], pb, S);
+            for (int u = 0; u < TX; ++u) pb = mm_tn(P[u][t], B[u], pb, sx(u));
+            S = mm_tn(B[t], pb, S, sx(t));
         }
 #pragma unroll
         for (int t = 0; t < TX; ++t)
@@ -753,14 +765,14 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
             for (int u = 0; u < TX; ++u) {
                 sls_d4 c = z4;
 #pragma unroll
-                for (int l = 0; l < TX; ++l) c = mm_tn(P[l][t], A[l][u], c);
+                for (int l = 0; l < TX; ++l) c = mm_tn(P[l][t], A[l][u], c, sx(l));
                 PA[t][u] = c;
             }
 #pragma unroll
         for (int u = 0; u < TX; ++u) {
             Bc[u] = z4;
 #pragma unroll
-            for (int t = 0; t < TX; ++t) Bc[u] = mm_tn(B[t], PA[t][u], Bc[u]);
+            for (int t = 0; t < TX; ++t) Bc[u] = mm_tn(B[t], PA[t][u], Bc[u], sx(t));
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -816,8 +828,8 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) c[i] = (t == u && i == di) ? qxd[t] : 0.0;
 #pragma unroll
-                for (int l = 0; l < TX; ++l) c = mm_tn(A[l][t], PA[l][u], c);
-                P[t][u] = mm_tn(K[t], Bc[u], c);
+                for (int l = 0; l < TX; ++l) c = mm_tn(A[l][t], PA[l][u], c, sx(l));
+                P[t][u] = mm_tn(K[t], Bc[u], c, su);
             }
         lds_barrier();                           // sT, sK are rewritten by the next step
     }
@@ -857,7 +869,7 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
         for (int u = 0; u < TX; ++u) {
             U[u] = z4;
 #pragma unroll
-            for (int t = 0; t < TX; ++t) U[u] = mm_tn(KT[t], X[t][u], U[u]);
+            for (int t = 0; t < TX; ++t) U[u] = mm_tn(KT[t], X[t][u], U[u], sx(t));
         }
         double* out = phib + ((size_t)k * N + j) * n * nx;
 #pragma unroll
@@ -881,9 +893,9 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
             for (int t = 0; t < TX; ++t)
 #pragma unroll
                 for (int u = 0; u < TX; ++u) {
-                    sls_d4 c = mm_tn(BT[t], U[u], z4);
+                    sls_d4 c = mm_tn(BT[t], U[u], z4, su);
 #pragma unroll
-                    for (int l = 0; l < TX; ++l) c = mm_tn(AT[l][t], X[l][u], c);
+                    for (int l = 0; l < TX; ++l) c = mm_tn(AT[l][t], X[l][u], c, sx(l));
                     Xn[t][u] = c;
                 }
 #pragma unroll
