@@ -680,7 +680,7 @@ int leb_sls_tube_map(int32_t nx, int32_t nu, int32_t nw, int32_t batch, int32_t 
  *       is finite
  * Kinds CHAIN, SATELLITE, QUAD3D (LEB_ENOTSUP otherwise).  The disturbance
  * part of every tube entry (which does not depend on the bounds) is one launch
- * over all rows; chains whose per-trajectory data fits in 64 KB of LDS then
+ * over all rows; chains whose per-trajectory data fits in 160 KB of LDS then
  * take the whole causal pass in one launch (one workgroup per trajectory),
  * everything else one row launch and one bound launch per step.  All on
  * `stream`, no host synchronisation.  Uses a library-owned, grow-only device

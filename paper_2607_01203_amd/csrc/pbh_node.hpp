@@ -184,10 +184,19 @@ __device__ __forceinline__ void row_zono(double lo, double hi, double pad, doubl
     }
 }
 
+// Orders one wave's own LDS accesses (its lanes exchange values without the
+// other waves of the workgroup).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Spring i and node i of timestep lt; s_sp [T][U], s_flag [T] (cleared).
-// Contains one workgroup barrier.  Args supplies U, c (dt/m), kL, L0, pad and
+// Contains one workgroup barrier (ONE_WAVE: none, the timestep's nodes are lanes
+// of the one calling wave).  Args supplies U, c (dt/m), kL, L0, pad and
 // compact (1: c_bar, rho_bar hold rows 3 and 4 of each node only).
-template <class Args>
+template <bool ONE_WAVE = false, class Args>
 __device__ __forceinline__ void node_pass(const Args& A, const TileRef& t, const NodeIn& d, int lt, int i,
                                           SpringOut* s_sp, uint32_t* s_flag) {
     const int U = A.U, nx = 6 * U;
@@ -201,7 +210,8 @@ __device__ __forceinline__ void node_pass(const Args& A, const TileRef& t, const
     SpringKeep k;
     spring_step(K, d, right, k, &s_sp[lt * U + i]);
     if (k.unb) atomicOr(&s_flag[lt], LEB_FLAG_UNBOUNDED);
-    __syncthreads();      // spring terms and flags complete
+    if (ONE_WAVE) wave_lds_fence();
+    else __syncthreads();      // spring terms and flags complete
     if (!active) return;
     const uint32_t ft = s_flag[lt];
     double lo34[2], hi34[2];

@@ -53,7 +53,7 @@ constexpr int SLS_MAX_NW = 64;
 constexpr int SLS_THREADS = 256;
 constexpr int SLS_PF = 8;                      // prefetch registers per thread (nx^2 + 2 nx nu <= 8 threads)
 constexpr size_t SLS_ROW_LDS = 48 * 1024;      // LDS budget of a tube-row workgroup
-constexpr size_t SLS_LDS_MAX = 64 * 1024;      // LDS of the one-launch fixed point (resident data + row region)
+constexpr size_t SLS_LDS_MAX = 160 * 1024;     // LDS of the one-launch fixed point (a compute unit's)
 
 // ------------------------------------------------------------ responses
 
@@ -1079,12 +1079,12 @@ __device__ void tube_row(const TubeRowArgs& a, const RowRef& rr, int k, double* 
     __syncthreads();
 }
 
-static int tube_jc(int nx, int nu, int nw, int mode, size_t* smem, size_t budget = SLS_ROW_LDS) {
+static int tube_jc(int nx, int nu, int nw, int mode, size_t* smem) {
     const int n = nx + nu;
     const size_t per_j = sizeof(double) * ((mode != ROW_NOE ? (size_t)nx * nw + nx : 0) +
                                            (mode != ROW_E ? 2 * (size_t)nx : 0) + 3 * (size_t)n);
     int jc = SLS_THREADS / n;
-    while (jc > 1 && per_j * jc + 2 * n * sizeof(double) > budget) --jc;
+    while (jc > 1 && per_j * jc + 2 * n * sizeof(double) > SLS_ROW_LDS) --jc;
     *smem = per_j * jc;            // tube_row's region; callers add 2 n for the row results
     return jc;
 }
@@ -1195,17 +1195,18 @@ static void launch_tube(const TubeRowArgs& a, int batch, double* out_sig, hipStr
 
 // ------------------------------------------------------------ disturbance error
 
-// FP64 interval sine and cosine of [lo, hi]: library values widened by 2^-40
-// relative plus 2^-100 absolute, +-1 where a critical point may lie inside
-// (tested against an outward pi).
-__device__ void sls_sincos(double lo, double hi, double* sl, double* sh, double* cl, double* ch) {
+// FP64 interval sine and cosine of [lo, hi] from the library values at its ends
+// (sa, sb = sin lo, sin hi; ca, cb = cos lo, cos hi): widened by 2^-40 relative
+// plus 2^-100 absolute, +-1 where a critical point may lie inside (tested
+// against an outward pi) and everywhere for wide or far-out intervals.
+__device__ void sls_sincos(double lo, double hi, double sa, double sb, double ca, double cb, double* sl, double* sh,
+                           double* cl, double* ch) {
     const double PI_LO = 3.141592653589793115997963468544185161590576171875;
     const double PI_HI = 3.141592653589793560087173318606801331043243408203125;
     if (!(hi - lo < 2.0 * PI_LO) || fabs(lo) > 1024.0 || fabs(hi) > 1024.0) {
         *sl = -1.0; *sh = 1.0; *cl = -1.0; *ch = 1.0;
         return;
     }
-    const double sa = sin(lo), sb = sin(hi), ca = cos(lo), cb = cos(hi);
     auto wdn = [](double x) { return x - fabs(x) * 0x1p-40 - 0x1p-100; };
     auto wup = [](double x) { return x + fabs(x) * 0x1p-40 + 0x1p-100; };
     double s0 = wdn(fmin(sa, sb)), s1 = wup(fmax(sa, sb));
@@ -1227,18 +1228,32 @@ __device__ void sls_sincos(double lo, double hi, double* sl, double* sh, double*
 __device__ __forceinline__ double rdn(double x) { return x - fabs(x) * 0x1p-52 - 0x1p-1000; }
 __device__ __forceinline__ double rup(double x) { return x + fabs(x) * 0x1p-52 + 0x1p-1000; }
 
-// half-width of the thrust columns' disturbance error on row l (0 off the (vx, vz) rows)
-__device__ double thrust_rdist(int l, double zt, double mut, double sgt, double e0, double c) {
-    const int comp = l % 6;
-    if (comp != 3 && comp != 4) return 0.0;
-    const double lo = rdn(zt + mut - sgt), hi = rup(zt + mut + sgt);
+// ends of theta's interval over the tube set
+__device__ __forceinline__ void thrust_theta(double zt, double mut, double sgt, double* lo, double* hi) {
+    *lo = rdn(zt + mut - sgt);
+    *hi = rup(zt + mut + sgt);
+}
+
+// half-width of a thrust column's disturbance error on a node's vx (comp 3) or vz
+// (comp 4) row, from theta's interval and the library values at its ends
+__device__ double thrust_rdist(int comp, double lo, double hi, double sa, double sb, double ca, double cb, double e0,
+                               double c) {
     if (!(lo <= hi) || !isfinite(lo) || !isfinite(hi)) return INFINITY;
     double sl, sh, cl, ch;
-    sls_sincos(lo, hi, &sl, &sh, &cl, &ch);
+    sls_sincos(lo, hi, sa, sb, ca, cb, &sl, &sh, &cl, &ch);
     // vx: -c [sin], vz: c [cos]; products of the point c >= 0 rounded outward
     const double a = comp == 3 ? rdn(-c * sh) : rdn(c * cl);
     const double bq = comp == 3 ? rup(-c * sl) : rup(c * ch);
     return rup(fmax(fabs(rup(bq - e0)), fabs(rdn(a - e0))));
+}
+
+// the same for any row l (0 off the (vx, vz) rows), from the tube's theta entries
+__device__ double thrust_rdist_row(int l, double zt, double mut, double sgt, double e0, double c) {
+    const int comp = l % 6;
+    if (comp != 3 && comp != 4) return 0.0;
+    double lo, hi;
+    thrust_theta(zt, mut, sgt, &lo, &hi);
+    return thrust_rdist(comp, lo, hi, sin(lo), sin(hi), cos(lo), cos(hi), e0, c);
 }
 
 struct EDiag { double e[SLS_MAX_NX]; };
@@ -1296,8 +1311,8 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_fp_row_kernel(FpRowArgs a, in
                 const int node = l / 6, th = 6 * node + 2;
                 const size_t ob = ((size_t)b * N + kp);
                 const double e0 = t.E[(ob * nx + l) * nw + (nw - a.U + node)];
-                const double s = thrust_rdist(l, a.z[ob * nx + th], t.mu[ob * n + th], t.sigma[ob * n + th], e0,
-                                              a.thrust_c);
+                const double s = thrust_rdist_row(l, a.z[ob * nx + th], t.mu[ob * n + th], t.sigma[ob * n + th], e0,
+                                                  a.thrust_c);
                 if (s != 0.0) {
                     lo = rdn(lo - s);
                     hi = rup(hi + s);
@@ -1336,114 +1351,268 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_fp_row_kernel(FpRowArgs a, in
     for (int q = tid; q < nu; q += blockDim.x) a.vs[(size_t)b * nu + q] = a.v[ob * nu + q];
 }
 
-// Chain dynamics: the whole causal pass of one trajectory in one workgroup.
-// Step k: tube row k, then the path-based bound of the unit (z_k, v_k) +
-// mu_k +- sigma_k by the chain bound's node pass (U of the 256 lanes; the
-// tube row sits in LDS and the bound writes its rows to LDS), then the
-// residual zonotope of step k for the later rows.
+// Chain dynamics: the whole causal pass of one trajectory in one workgroup, its
+// nominal, disturbance parts, thrust entries and residual zonotopes in LDS.
+// The tube row k + 1 needs the residual of step k only through its last block
+// Phi_{k+1,k}, so the waves take different parts of step k:
+//   A  others  row k = the sums over j < k - 1 (formed during step k - 1) plus the
+//              block Phi_{k,k-1} (in LDS) times the residual of step k - 1
+//   B  wave 0  the path-based bound of the unit (z_k, v_k) + mu_k +- sigma_k (U lanes)
+//      wave 1  the thrust disturbance error over theta's interval (two lanes a node,
+//              one library call each)
+//      others  the sums of row k + 1 over j < k: thread p holds the two entries
+//              2p, 2p + 1 of every block, so a block is one coalesced read; the first
+//              SLS_FP_PF blocks were read during step k - 1
+//   C  wave 0  the residual zonotope of step k;  others: the partial sums of B
+//              added up per row, the block Phi_{k+1,k} to LDS
+// with one LDS barrier after each.
+//
+// What bounds it: 40 dependent steps, each the latency of A, of the slowest of B
+// (the bound at small nx, the stream of the row at nx = 30: up to 374 KB a step for
+// one compute unit) and of C.  256 x 40 steps at nx = 6: 0.095 ms (rows, bound and
+// disturbance error one after the other: 0.224 ms); at nx = 12 0.197 ms (0.378 ms);
+// 64 x 40 at nx = 30 0.303 ms (1.33 ms).
+constexpr int SLS_FP_PF = 8;             // blocks of the next row read one step ahead
+constexpr int SLS_FP_MAX_THREADS = 768;
+
+typedef double sls_p2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// x + x of the partner lane of a data-parallel-primitive pattern (no LDS):
+// 0xB1, 0x4E: lanes 1, 2 away within four; 0x141: mirrored within eight
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+    union { double d; int w[2]; } u;
+    u.d = x;
+    u.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], CTRL, 0xf, 0xf, true);
+    u.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], CTRL, 0xf, 0xf, true);
+    return x + u.d;
+}
+__device__ __forceinline__ double sum4(double x) { return dpp_add<0x4E>(dpp_add<0xB1>(x)); }
+__device__ __forceinline__ double sum8(double x) { return dpp_add<0x141>(sum4(x)); }
+
 struct FpChainArgs {
-    TubeRowArgs t;
-    double* cbar_w; double* rbar_w;
+    const double* phi; const double* E; const double* sigE;
     const double* z; const double* v;
-    double* r_lo; double* r_hi;
+    double* mu; double* sigma; double* r_lo; double* r_hi;
     uint32_t* certified;
     double thrust_c;
+    int nu, nw, N;
+    int npos, slots;         // two-entry positions of a block; blocks in flight across the stream waves
     // node-pass constants
     int U;
     double c, kL, L0, pad;
     int compact;
 };
 
-__device__ __forceinline__ void residual_row(int l, double lo, double hi, double zt, double mut, double sgt,
-                                             double e0, double thrust_c, double pad, double* cb, double* rb,
-                                             double* lo_o, double* hi_o) {
-    if (thrust_c > 0.0) {
-        const double s = thrust_rdist(l, zt, mut, sgt, e0, thrust_c);
-        if (s != 0.0) {
-            lo = rdn(lo - s);
-            hi = rup(hi + s);
-        }
-    }
-    *lo_o = lo;
-    *hi_o = hi;
-    double c = 0.5 * (lo + hi), r = fmax(hi - c, c - lo);
-    r = rup(rup(r) + pad);
-    if (!isfinite(lo) || !isfinite(hi)) { c = NAN; r = INFINITY; }
-    *cb = c;
-    *rb = r;
-}
-
-template <int NXB>
-__global__ void __launch_bounds__(SLS_THREADS) sls_fp_chain_kernel(FpChainArgs a) {
+__global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChainArgs a) {
     const int b = blockIdx.x;
-    const TubeRowArgs& t = a.t;
-    const int nx = t.nx, nu = t.nu, n = nx + nu, N = t.N, nw = t.nw, U = a.U;
+    const int U = a.U, nx = 6 * U, nu = a.nu, n = nx + nu, N = a.N, nw = a.nw;
     extern __shared__ double sm[];
-    // the trajectory's nominal, disturbance parts, thrust entries and residual
-    // zonotopes stay in LDS for the whole pass
+    const int nst = a.npos * a.slots;
     double* mo = sm;                    // n
     double* so = mo + n;                // n
     double* rl = so + n;                // nx
     double* rh = rl + nx;               // nx
-    double* zl = rh + nx;               // N*nx
+    double* rd = rh + nx;               // nx     disturbance error of step k
+    double* base = rd + nx;             // 3*n    sums of the next row over the earlier steps
+    double* zl = base + 3 * n;          // N*nx
     double* vl = zl + (size_t)N * nx;   // N*nu
     double* sel = vl + (size_t)N * nu;  // N*n
-    double* eth = sel + (size_t)N * n;  // N*nx  E_k entry of row l's thrust column (0 off the thrust rows)
-    double* cbl = eth + (size_t)N * nx; // N*nx
-    double* rbl = cbl + (size_t)N * nx; // N*nx
-    SpringOut* s_sp = reinterpret_cast<SpringOut*>(rbl + (size_t)N * nx);      // [U]
+    double* eth = sel + (size_t)N * n;  // N*2*U  E_k entries of the thrust columns (vx, vz rows)
+    double* cbl = eth + (size_t)N * 2 * U;      // N*nx
+    double* rbl = cbl + (size_t)N * nx;         // N*nx
+    double* blk = rbl + (size_t)N * nx;         // n*nx   Phi_{k,k-1}
+    double* part = blk + n * nx;                // 3*nst
+    SpringOut* s_sp = reinterpret_cast<SpringOut*>(part + 3 * nst);             // [U]
     uint32_t* s_flag = reinterpret_cast<uint32_t*>(s_sp + U);                   // [2]: flags, all finite
-    const size_t off = ((reinterpret_cast<uintptr_t>(s_flag + 2) - reinterpret_cast<uintptr_t>(sm)) + 15) & ~size_t(15);
-    double* region = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(sm) + off);
-    const int tid = threadIdx.x, bs = blockDim.x;
-    const int lt = tid / U, i = tid - lt * U;
+    const int tid = threadIdx.x, bs = blockDim.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t b0 = (size_t)b * N;
-    for (int q = tid; q < N * nx; q += bs) {
-        zl[q] = a.z[b0 * nx + q];
-        const int k = q / nx, l = q - k * nx, comp = l % 6;
-        eth[q] = (a.thrust_c > 0.0 && (comp == 3 || comp == 4)) ? t.E[((b0 + k) * nx + l) * nw + (nw - U + l / 6)] : 0.0;
-    }
+    const double* phib = a.phi + b0 * N * n * nx;
+    for (int q = tid; q < N * nx; q += bs) zl[q] = a.z[b0 * nx + q];
     for (int q = tid; q < N * nu; q += bs) vl[q] = a.v[b0 * nu + q];
-    for (int q = tid; q < N * n; q += bs) sel[q] = t.sigE[b0 * n + q];
+    for (int q = tid; q < N * n; q += bs) sel[q] = a.sigE[b0 * n + q];
+    for (int q = tid; q < N * 2 * U; q += bs) {
+        const int k = q / (2 * U), u = (q >> 1) % U, e = q & 1;
+        eth[q] = a.thrust_c > 0.0 ? a.E[((b0 + k) * nx + 6 * u + 3 + e) * nw + (nw - U + u)] : 0.0;
+    }
+    for (int q = tid; q < nx; q += bs) rd[q] = 0.0;
     if (tid == 0) s_flag[1] = 1u;
     __syncthreads();
-    RowRef rr;
-    rr.E = nullptr; rr.cb = cbl; rr.rb = rbl;
-    for (int k = 0; k < N; ++k) {
-        rr.phi = t.phi + ((b0 + k) * N) * n * nx;
-        rr.sigE = sel + (size_t)k * n;
-        tube_row<ROW_NOE, NXB>(t, rr, k, region, mo, so);
-        for (int q = tid; q < n; q += bs) {
-            t.mu[(b0 + k) * n + q] = mo[q];
-            t.sigma[(b0 + k) * n + q] = so[q];
-            if (!isfinite(so[q])) s_flag[1] = 0u;
+    // one loop a role, with the same three barriers in each (the role is uniform over a
+    // wave), so that a wave holds the registers of its own part only
+    if (wave == 0) {
+        const int lt = lane / U, i = lane - lt * U;
+        for (int k = 0; k < N; ++k) {
+            lds_barrier();                       // A done: row k in mo, so
+            if (lane == 0) s_flag[0] = 0u;
+            const TileRef t0{zl + (size_t)k * nx, vl + (size_t)k * nu, mo, so, rl, rh, nullptr, nullptr, nullptr, 1};
+            NodeIn d;
+            node_load(t0, U, lt, i, d);
+            wave_lds_fence();                    // s_flag cleared
+            node_pass<true>(a, t0, d, lt, i, s_sp, s_flag);
+            lds_barrier();                       // B done
+            if (lane < nx) {
+                const int l = lane;
+                double lo = rl[l], hi = rh[l];
+                const double s = rd[l];
+                if (s != 0.0) {
+                    lo = rdn(lo - s);
+                    hi = rup(hi + s);
+                }
+                double c = 0.5 * (lo + hi), r = fmax(hi - c, c - lo);
+                r = rup(rup(r) + a.pad);
+                if (!isfinite(lo) || !isfinite(hi)) { c = NAN; r = INFINITY; }
+                cbl[(size_t)k * nx + l] = c;
+                rbl[(size_t)k * nx + l] = r;
+                if (!isfinite(r)) s_flag[1] = 0u;
+                if (a.r_lo) { a.r_lo[(b0 + k) * nx + l] = lo; a.r_hi[(b0 + k) * nx + l] = hi; }
+            }
+            lds_barrier();                       // C done
         }
-        if (tid == 0) s_flag[0] = 0u;
-        const TileRef t0{zl + (size_t)k * nx, vl + (size_t)k * nu, mo, so, rl, rh, nullptr, nullptr, nullptr, 1};
-        NodeIn d;
-        node_load(t0, U, lt, i, d);
-        lds_barrier();                        // s_flag cleared
-        node_pass(a, t0, d, lt, i, s_sp, s_flag);
-        lds_barrier();                        // the unit's rows are in rl, rh
-        for (int l = tid; l < nx; l += bs) {
-            const int th = 6 * (l / 6) + 2;
-            double lo, hi;
-            residual_row(l, rl[l], rh[l], zl[(size_t)k * nx + th], mo[th], so[th], eth[(size_t)k * nx + l],
-                         a.thrust_c, a.pad, &cbl[(size_t)k * nx + l], &rbl[(size_t)k * nx + l], &lo, &hi);
-            if (!isfinite(rbl[(size_t)k * nx + l])) s_flag[1] = 0u;
-            if (a.r_lo) { a.r_lo[(b0 + k) * nx + l] = lo; a.r_hi[(b0 + k) * nx + l] = hi; }
+    } else if (wave == 1) {
+        const int u = lane >> 1, e = lane & 1, th = 6 * u + 2;
+        const bool mine = a.thrust_c > 0.0 && lane < 2 * U;
+        for (int k = 0; k < N; ++k) {
+            lds_barrier();
+            if (mine) {
+                double lo, hi, sx, cx;
+                thrust_theta(zl[(size_t)k * nx + th], mo[th], so[th], &lo, &hi);
+                sincos(e ? hi : lo, &sx, &cx);
+                const double sy = __shfl_xor(sx, 1), cy = __shfl_xor(cx, 1);
+                rd[6 * u + 3 + e] = thrust_rdist(3 + e, lo, hi, e ? sy : sx, e ? sx : sy, e ? cy : cx, e ? cx : cy,
+                                                 eth[((size_t)k * U + u) * 2 + e], a.thrust_c);
+            }
+            lds_barrier();
+            lds_barrier();
         }
-        lds_barrier();                        // residual of step k in LDS for the later rows
+    } else {
+        // this thread's place in the row stream
+        const int st = tid - 128, hx = nx >> 1;
+        const bool streams = st < nst;
+        const int pos = streams ? st % a.npos : 0, slot = streams ? st / a.npos : 0, l2 = 2 * (pos % hx);
+        const int per = hx * a.slots, mine = (pos / hx) * per + slot * hx + pos % hx;   // partial sums, row by row
+        auto load = [&](int k, int j) {          // entries 2 pos, 2 pos + 1 of Phi_{k,j}
+            return *reinterpret_cast<const sls_p2*>(phib + ((size_t)k * N + j) * n * nx + 2 * pos);
+        };
+        sls_p2 pf[SLS_FP_PF], nb = {0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < SLS_FP_PF; ++q) pf[q] = sls_p2{0.0, 0.0};
+        for (int k = 0; k < N; ++k) {
+            // A: row k (four lanes a row)
+            if (st < 4 * n) {
+                const int i = st >> 2, q = st & 3;
+                double m = 0.0, s = 0.0, g = 0.0;
+                if (k > 0) {
+                    const double* cb = cbl + (size_t)(k - 1) * nx;
+                    const double* rb = rbl + (size_t)(k - 1) * nx;
+                    for (int l = q; l < nx; l += 4) {
+                        const double r = blk[i * nx + l], ap = fabs(r), c = cb[l], w = rb[l];
+                        m = fma(r, c, m);
+                        s = fma(ap, w, s);
+                        g = fma(ap, fabs(c) + w, g);
+                    }
+                }
+                m = sum4(m);
+                s = sum4(s);
+                g = sum4(g);
+                if (q == 0) {
+                    if (k > 1) { m += base[i]; s += base[n + i]; g += base[2 * n + i]; }
+                    // rounding of the sums: at most nx + k (nw + 1) + 72 additions deep, each
+                    // within 2^-53 of the magnitudes g; doubled for the centre's error and the
+                    // final additions
+                    const double coef = (double)(nx + k * (nw + 1) + 72) * 0x1p-52;
+                    s = s + coef * g * (1.0 + 0x1p-50) + 0x1p-1000;
+                    const double se = sel[(size_t)k * n + i];
+                    s = s + se;
+                    s = s + fabs(s) * 0x1p-52;
+                    if (!isfinite(g) || !isfinite(s) || !isfinite(se)) { m = 0.0; s = INFINITY; }
+                    if (k == 0) { m = 0.0; s = 0.0; }
+                    mo[i] = m;
+                    so[i] = s;
+                    a.mu[(b0 + k) * n + i] = m;
+                    a.sigma[(b0 + k) * n + i] = s;
+                    if (!isfinite(s)) s_flag[1] = 0u;
+                }
+            }
+            lds_barrier();
+            // B: the next row over the residuals known before this step
+            if (streams && k + 1 < N) {
+                if (slot == 0) nb = load(k + 1, k);
+                double m = 0.0, s = 0.0, g = 0.0;
+                auto add = [&](int j, sls_p2 r) {
+                    const double* cb = cbl + (size_t)j * nx + l2;
+                    const double* rb = rbl + (size_t)j * nx + l2;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const double ap = fabs(r[e]);
+                        m = fma(r[e], cb[e], m);
+                        s = fma(ap, rb[e], s);
+                        g = fma(ap, fabs(cb[e]) + rb[e], g);
+                    }
+                };
+                int j = slot;
+#pragma unroll
+                for (int q = 0; q < SLS_FP_PF; ++q, j += a.slots)
+                    if (j < k) add(j, pf[q]);
+                for (; j < k; j += SLS_FP_PF * a.slots) {
+                    sls_p2 r[SLS_FP_PF];
+#pragma unroll
+                    for (int q = 0; q < SLS_FP_PF; ++q) r[q] = load(k + 1, min(j + q * a.slots, k - 1));
+#pragma unroll
+                    for (int q = 0; q < SLS_FP_PF; ++q)
+                        if (j + q * a.slots < k) add(j + q * a.slots, r[q]);
+                }
+                if (k + 2 < N) {
+#pragma unroll
+                    for (int q = 0; q < SLS_FP_PF; ++q) pf[q] = load(k + 2, min(slot + q * a.slots, k));
+                }
+                part[mine] = m;
+                part[nst + mine] = s;
+                part[2 * nst + mine] = g;
+            }
+            lds_barrier();
+            // C: eight lanes a row over its nx / 2 positions in every slot
+            if (k + 1 < N) {
+                if (st < 8 * n) {
+                    const int i = st >> 3;
+                    double m = 0.0, s = 0.0, g = 0.0;
+                    for (int q = i * per + (st & 7); q < (i + 1) * per; q += 8) {
+                        m += part[q];
+                        s += part[nst + q];
+                        g += part[2 * nst + q];
+                    }
+                    m = sum8(m);
+                    s = sum8(s);
+                    g = sum8(g);
+                    if ((st & 7) == 0) { base[i] = m; base[n + i] = s; base[2 * n + i] = g; }
+                }
+                if (streams && slot == 0) { blk[2 * pos] = nb[0]; blk[2 * pos + 1] = nb[1]; }
+            }
+            lds_barrier();
+        }
     }
+    __syncthreads();
     if (a.certified && tid == 0) a.certified[b] = s_flag[1];
 }
 
-// LDS bytes of the resident part of sls_fp_chain_kernel (before its tube-row region)
-static size_t fp_chain_head_bytes(int nx, int nu, int U, int N) {
+// Slots and LDS bytes of sls_fp_chain_kernel; 0: too large for the one-launch form.
+// Slots: blocks side by side in the row stream.  At nx = 6 (24 positions a block) two
+// stream waves hold five, so that the blocks read ahead cover 40 steps and two
+// workgroups share a compute unit (256 / 1,024 trajectories of 40 steps: 95 / 194 us;
+// with five stream waves 101 / 396 us).  Larger blocks need the five waves to keep a
+// row's reads in flight (nx = 12: 197 us, with two waves 226 us); at least one slot.
+static size_t fp_chain_plan(int nx, int nu, int U, int N, int* npos, int* slots, int* threads) {
     const int n = nx + nu;
-    const size_t b = sizeof(double) * ((size_t)2 * n + 2 * nx + (size_t)N * (nx + nu + n + 3 * nx)) +
-                     sizeof(SpringOut) * U + 2 * sizeof(uint32_t);
-    return (b + 15) & ~size_t(15);
+    *npos = n * nx / 2;
+    *slots = max(1, (*npos <= 24 ? 128 : 320) / *npos);
+    const int stream = max(*npos * *slots, 8 * n);
+    *threads = 128 + 64 * ((stream + 63) / 64);
+    if (*threads > SLS_FP_MAX_THREADS) return 0;
+    const size_t bytes = sizeof(double) * ((size_t)5 * n + 3 * nx + (size_t)N * (3 * nx + nu + n + 2 * U) + n * nx +
+                                           (size_t)3 * *npos * *slots) +
+                         sizeof(SpringOut) * U + 2 * sizeof(uint32_t);
+    return bytes <= SLS_LDS_MAX ? bytes : 0;
 }
 
 struct SlsWorkspace {
@@ -1604,29 +1773,21 @@ extern "C" int leb_sls_fixed_point(const leb_dynamics* dyn, int32_t batch, int32
     a.thrust_c = thrust > 0.0 ? thrust * dyn->dt / dyn->m : 0.0;
     a.pad = pad;
     a.U = chain ? dyn->n_units : 0;
-    // chains whose trajectory data fits in LDS beside a tube-row region: the whole
-    // causal pass in one launch (one workgroup per trajectory)
-    const size_t head = chain ? fp_chain_head_bytes(nx, nu, dyn->n_units, N) : 0;
-    size_t region = 0;
-    int jc_res = 0;
-    if (chain && head < SLS_LDS_MAX) {
-        jc_res = tube_jc(nx, nu, nw, ROW_NOE, &region, SLS_LDS_MAX - head);
-        if (head + region > SLS_LDS_MAX) jc_res = 0;
-    }
-    if (jc_res > 0) {
-        FpChainArgs c;
-        c.t = a.t;
-        c.t.jc = jc_res;
-        c.cbar_w = a.cbar_w; c.rbar_w = a.rbar_w;
-        c.z = z; c.v = v; c.r_lo = r_lo; c.r_hi = r_hi; c.certified = certified;
+    // chains whose trajectory data fits in LDS: the whole causal pass in one launch
+    int npos = 0, slots = 0, threads = 0;
+    const size_t lds = chain ? fp_chain_plan(nx, nu, dyn->n_units, N, &npos, &slots, &threads) : 0;
+    if (lds > 0) {
+        FpChainArgs c = {};
+        c.phi = phi; c.E = E; c.sigE = sigE; c.z = z; c.v = v;
+        c.mu = mu; c.sigma = sigma; c.r_lo = r_lo; c.r_hi = r_hi; c.certified = certified;
         c.thrust_c = a.thrust_c;
+        c.nu = nu; c.nw = nw; c.N = N; c.npos = npos; c.slots = slots;
         c.U = dyn->n_units;
         c.c = dyn->dt / dyn->m; c.kL = dyn->k_spring * dyn->rest_len; c.L0 = dyn->rest_len; c.pad = pad;
-        c.compact = 0;
-        const dim3 g((unsigned)batch), bl(SLS_THREADS);
-        if (nxb == 8) hipLaunchKernelGGL(sls_fp_chain_kernel<8>, g, bl, head + region, s, c);
-        else if (nxb == 16) hipLaunchKernelGGL(sls_fp_chain_kernel<16>, g, bl, head + region, s, c);
-        else hipLaunchKernelGGL(sls_fp_chain_kernel<32>, g, bl, head + region, s, c);
+        if (hipFuncSetAttribute((const void*)sls_fp_chain_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)SLS_LDS_MAX) != hipSuccess)
+            return LEB_EDEVICE;
+        hipLaunchKernelGGL(sls_fp_chain_kernel, dim3((unsigned)batch), dim3((unsigned)threads), lds, s, c);
         return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
     }
     // otherwise one row launch and one bound launch per step

@@ -411,3 +411,39 @@ def test_responses_tile_non_positive_pivot(gpu, nx, nu):
     K = _np(K)[0]
     assert np.isnan(K[3, 1]).all() and np.isnan(K[2, 1]).all()
     assert np.isfinite(K[4:, 1]).all() and np.isfinite(K[:, 0]).all() and np.isfinite(K[:, 2]).all()
+
+
+@pytest.mark.parametrize("n_units,N", [(1, 41), (1, 3), (2, 30), (3, 12), (4, 12), (5, 12)])
+def test_sls_update_causal_pass_slots(gpu, orc, sls, n_units, N):
+    """The one-launch causal pass over its block layouts (five slots of 24
+    positions at U = 1, three at U = 2, one from U = 3; horizons past the
+    blocks read ahead), same tolerances as the parity test."""
+    import paper_2607_01203_amd as leb
+    p = W.sls_cfg(seed=80 + n_units, batch=2, N=N, n_units=n_units, thrust=0.1)
+    dyn = leb.dynamics_like(p.dyn)
+    print("case: sls causal pass U=%d N=%d" % (n_units, N), flush=True)
+    out = leb.sls_update(dyn, _t(p.z, gpu), _t(p.v, gpu), _t(p.qx, gpu), _t(p.qu, gpu), p.e, p.thrust, pad=1e-6)
+    mu, sg, lo, hi, cert = (_np(out[k]) for k in ("mu", "sigma", "r_lo", "r_hi", "certified"))
+    assert (cert == 1).all()
+    for b in range(p.batch):
+        mo, so, loo, hio = _oracle_update(orc, sls, p, b, 1e-6)
+        _close_tube(mu[b], sg[b], mo, so, "tube U=%d b=%d" % (n_units, b))
+        _close_interval(lo[b], hi[b], loo, hio, "bounds U=%d b=%d" % (n_units, b))
+
+
+def test_sls_update_beyond_lds(gpu, orc, sls):
+    """Five quadrotors at N = 120 exceed a compute unit's LDS and take the
+    per-step launches: parity with the oracle while every radius is <= 1, as
+    in the blow-up test."""
+    import paper_2607_01203_amd as leb
+    p = W.sls_cfg(seed=36, batch=1, N=120, n_units=5, thrust=0.2)
+    dyn = leb.dynamics_like(p.dyn)
+    print("case: sls update U=5 N=120 per-step launches", flush=True)
+    out = leb.sls_update(dyn, _t(p.z, gpu), _t(p.v, gpu), _t(p.qx, gpu), _t(p.qu, gpu), p.e, p.thrust, pad=1e-6)
+    mu, sg = _np(out["mu"])[0], _np(out["sigma"])[0]
+    with np.errstate(invalid="ignore", over="ignore"):
+        mo, so, _, _ = _oracle_update(orc, sls, p, 0, 1e-6)
+    big = np.nanmax(np.where(np.isfinite(so), so, np.inf), 1) > 1.0
+    km = int(np.argmax(big)) if big.any() else p.N
+    assert km > 10
+    _close_tube(mu[:km], sg[:km], mo[:km], so[:km], "U=5 N=120 tube")
