@@ -658,6 +658,7 @@ __global__ void __launch_bounds__(64) sls_riccati_mfma_kernel(RiccatiArgs a) {
 // end is out of its range and reads 0, so a lane needs one offset per tile and one
 // column test instead of an address and a test for every element.
 typedef unsigned int sls_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned int sls_u4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t matrix_rsrc(const double* M, int elems) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(M), 0, elems * 8, 0x00027000);
@@ -1111,71 +1112,242 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_tube_kernel(TubeRowArgs a, do
     }
 }
 
-// The disturbance part sum_j |Phi_{k,j} E_j| 1 of tube row k on FP64 MFMA for
-// 8 < n <= 16, nw <= 16 (smaller blocks stay on the VALU row): one workgroup per (trajectory, k), wave w takes the blocks
-// j = w, w + 4, ...  Each block is one zero-padded 16 x 16 x 16 product
-// (A fragments from Phi_{k,j}, B fragments from E_j, both straight from
-// memory); the accumulator's entries are added up in absolute value over j,
-// and |Phi| |E| is accumulated beside it for the rounding allowance.  The
-// sixteen columns of each row are summed at the end.
+typedef double sls_p2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// x + x of the partner lane of a data-parallel-primitive pattern (no LDS):
+// 0xB1, 0x4E: lanes 1, 2 away within four; 0x141, 0x140: mirrored within eight, sixteen
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+    union { double d; int w[2]; } u;
+    u.d = x;
+    u.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], CTRL, 0xf, 0xf, true);
+    u.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], CTRL, 0xf, 0xf, true);
+    return x + u.d;
+}
+__device__ __forceinline__ double sum4(double x) { return dpp_add<0x4E>(dpp_add<0xB1>(x)); }
+__device__ __forceinline__ double sum8(double x) { return dpp_add<0x141>(sum4(x)); }
+__device__ __forceinline__ double sum16(double x) { return dpp_add<0x140>(sum8(x)); }
+
+// M[row][col] of a matrix with rows of C elements, 0 outside (a row past its end is
+// out of the descriptor's range)
+__device__ __forceinline__ double element_at(__amdgpu_buffer_rsrc_t M, int C, int row, int col) {
+    union { sls_u2 u; double d; } x;
+    x.u = __builtin_amdgcn_raw_buffer_load_b64(M, 8 * (row * C + col), 0, 0);
+    return col < C ? x.d : 0.0;
+}
+
+// The disturbance part sum_j |Phi_{k,j} E_j| 1 of tube row k on FP64 MFMA for n > 8
+// rows (RT = ceil(n / 16), CT = ceil(nw / 16) tiles): one workgroup per
+// (trajectory, k), wave w takes the blocks j = w, w + 4, ...  A block is one
+// zero-padded product (A fragments from Phi_{k,j}, B fragments from E_j, both
+// straight from memory); the absolute values of its entries are added up over
+// j.  The rounding allowance needs |Phi| |E| 1 = |Phi| (|E| 1): the row sums of
+// |E_j| come from the B fragments by additions within 16 lanes, and the product with
+// them runs on the VALU beside the MFMAs.
+//
+// What bounds it: the padded products (72 MFMA a block at nx = 30: 94 us for 64 x 40
+// steps) with the address and masking work beside them, and reading Phi (479 MB
+// there: 98 us).  The fragments of the next group of states are read during this
+// group's products.  64 x 40 at nx = 30: 0.25 ms (VALU rows: 1.24 ms), at nx = 18
+// 0.091 ms (0.305 ms); 256 x 40 at nx = 12: 0.117 ms (0.120 ms with |Phi| |E| as a
+// second MFMA product).  Several rows k a workgroup, to share E_j, was slower
+// (0.28 and 0.33 ms with two and four rows at nx = 30).
+template <int RT, int CT>
 __global__ void __launch_bounds__(256) sls_tube_e_mfma_kernel(TubeRowArgs a, double* out_sig) {
     const int k = blockIdx.x, b = blockIdx.y;
     const int nx = a.nx, nw = a.nw, N = a.N, n = nx + a.nu;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
-    __shared__ double red[2][4][4][64];
-    __shared__ double rows[2][16];
-    sls_d4 T = {0.0, 0.0, 0.0, 0.0}, G = {0.0, 0.0, 0.0, 0.0};
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ double redT[4][16 * RT];
+    __shared__ double redG[4][4][16 * RT];
     const double* prow = a.phi + (((size_t)b * N + k) * N) * n * nx;
     const double* Eb = a.E + (size_t)b * N * nx * nw;
-    // fragments of block j: A[l%16][4t + l/16] from Phi_{k,j}, B[4t + l/16][l%16] from E_j;
-    // the next block's are loaded while this one multiplies
-    double an[4], bn[4];
-    auto frag = [&](int j) {
-        const double* Pj = prow + (size_t)j * n * nx;
-        const double* Ej = Eb + (size_t)j * nx * nw;
+    const int nch = (nx + 15) >> 4;              // groups of 16 states (four k-steps)
+    const int nit = wave < k ? ((k - 1 - wave) / 4 + 1) * nch : 0;
+    // a group's fragments: k-step t of lane group lq takes state l = 16 g + 4 lq + t, so a
+    // lane's four entries of a Phi row are one 32-byte piece of a 128-byte line
+    auto fetch = [&](int it, double (&A)[RT][4], double (&B)[4][CT]) {
+        const int q = it / nch, j = wave + 4 * q, l0 = 16 * (it - q * nch) + 4 * lq;
+        const auto rP = matrix_rsrc(prow + (size_t)j * n * nx, n * nx), rE = matrix_rsrc(Eb + (size_t)j * nx * nw, nx * nw);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                union { sls_u4 u; double d[2]; } x;
+                x.u = __builtin_amdgcn_raw_buffer_load_b128(rP, 8 * ((16 * r + lr) * nx + l0 + 2 * h), 0, 0);
+                A[r][2 * h] = l0 + 2 * h < nx ? x.d[0] : 0.0;
+                A[r][2 * h + 1] = l0 + 2 * h + 1 < nx ? x.d[1] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) B[t][c] = element_at(rE, nw, l0 + t, 16 * c + lr);
+    };
+    sls_d4 T[RT], D[RT][CT];
+    double G[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        T[r] = sls_d4{0.0, 0.0, 0.0, 0.0};
+        G[r] = 0.0;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) D[r][c] = sls_d4{0.0, 0.0, 0.0, 0.0};
+    }
+    double av[RT][4], bv[4][CT], an[RT][4], bn[4][CT];
+    auto multiply = [&](int it) {
+        const int c0 = it % nch, left = nx - 16 * c0;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int kk = 4 * t + lq;
-            an[t] = (lr < n && kk < nx) ? Pj[lr * nx + kk] : 0.0;
-            bn[t] = (kk < nx && lr < nw) ? Ej[kk * nw + lr] : 0.0;
+            if (t >= left) break;
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    D[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r][t], bv[t][c], D[r][c], 0, 0, 0);
+            double e1 = 0.0;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) e1 += fabs(bv[t][c]);
+            e1 = sum16(e1);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) G[r] = fma(fabs(av[r][t]), e1, G[r]);
+        }
+        if (c0 == nch - 1) {                     // block j complete
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) T[r][i] += fabs(D[r][c][i]);
+                    D[r][c] = sls_d4{0.0, 0.0, 0.0, 0.0};
+                }
         }
     };
-    if (wave < k) frag(wave);
-    for (int j = wave; j < k; j += 4) {
-        double av[4], bv[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) { av[t] = an[t]; bv[t] = bn[t]; }
-        if (j + 4 < k) frag(j + 4);
-        sls_d4 D = {0.0, 0.0, 0.0, 0.0};
+    if (nit > 0) fetch(0, an, bn);
+    for (int it = 0; it < nit; ++it) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            D = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t], bv[t], D, 0, 0, 0);
-            G = __builtin_amdgcn_mfma_f64_16x16x4f64(fabs(av[t]), fabs(bv[t]), G, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) av[r][t] = an[r][t];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) bv[t][c] = bn[t][c];
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) T[i] += fabs(D[i]);
+        if (it + 1 < nit) fetch(it + 1, an, bn);
+        multiply(it);
     }
+    // the sixteen columns of each row (row 16 r + 4 i + lq), then the waves
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { red[0][wave][i][lane] = T[i]; red[1][wave][i][lane] = G[i]; }
-    __syncthreads();
-    if (tid < 32) {
-        // row r = 4 i + lq' of the tile: the 16 lanes lr of group lq', element i, all waves
-        const int which = tid >> 4, r = tid & 15, i = r >> 2, lqr = r & 3;
-        double acc = 0.0;
-        for (int w = 0; w < 4; ++w)
-            for (int c = 0; c < 16; ++c) acc += red[which][w][i][lqr * 16 + c];
-        rows[which][r] = acc;
+    for (int r = 0; r < RT; ++r) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double t = sum16(T[r][i]);
+            if (lr == 0) redT[wave][16 * r + 4 * i + lq] = t;
+        }
+        redG[wave][lq][16 * r + lr] = G[r];
     }
     __syncthreads();
     if (tid < n) {
-        double sv = rows[0][tid];
-        const double g = rows[1][tid];
+        double sv = 0.0, g = 0.0;
+        for (int w = 0; w < 4; ++w) {
+            sv += redT[w][tid];
+            for (int q = 0; q < 4; ++q) g += redG[w][q][tid];
+        }
         // depth of the sums: nx products per entry inside the MFMA, k blocks, 4 waves, 16 columns
         const double coef = (double)(nx + k * (nw + 1) + 64) * 0x1p-52;
         sv = sv + coef * g * (1.0 + 0x1p-50) + 0x1p-1000;
         if (!isfinite(g) || !isfinite(sv)) sv = INFINITY;
         if (k == 0) sv = 0.0;
         out_sig[((size_t)b * N + k) * n + tid] = sv;
+    }
+}
+
+template <int RT>
+static void launch_tube_e_mfma(const TubeRowArgs& a, int batch, double* out_sig, hipStream_t s) {
+    const dim3 grid((unsigned)a.N, (unsigned)batch);
+    switch ((a.nw + 15) / 16) {
+    case 1: hipLaunchKernelGGL((sls_tube_e_mfma_kernel<RT, 1>), grid, dim3(256), 0, s, a, out_sig); break;
+    case 2: hipLaunchKernelGGL((sls_tube_e_mfma_kernel<RT, 2>), grid, dim3(256), 0, s, a, out_sig); break;
+    case 3: hipLaunchKernelGGL((sls_tube_e_mfma_kernel<RT, 3>), grid, dim3(256), 0, s, a, out_sig); break;
+    default: hipLaunchKernelGGL((sls_tube_e_mfma_kernel<RT, 4>), grid, dim3(256), 0, s, a, out_sig); break;
+    }
+}
+
+// The same for one small size (n = NX + NU = 8 rows, nw <= 8) on the VALU: a lane
+// holds row i of tube row k (eight rows, eight k a wave, five waves: 40 k a
+// workgroup) and the wave walks j in step, so that E_j and |E_j| 1 are broadcasts
+// from LDS and every lane's row of Phi_{k,j} is one 48-byte read, four j ahead.
+//
+// What bounds it: reading Phi (77 MB at 256 x 40: 16 us) and one wave's walk over
+// up to 39 blocks.  256 x 40: 0.036 ms (a workgroup per row k, two barriers a chunk
+// and the sums over its slots through LDS: 0.047 ms); 1,024 x 40: 0.125 ms (0.173 ms).
+template <int NX, int NU>
+__global__ void __launch_bounds__(320) sls_tube_e_lane_kernel(TubeRowArgs a, double* out_sig) {
+    constexpr int n = NX + NU, NW = 8, KW = 40, CH = 40, JU = 4;   // k a workgroup, staged j, j read ahead
+    static_assert(n == 8 && NX % 2 == 0, "eight lanes per tube row");
+    const int b = blockIdx.y, N = a.N, nw = a.nw;
+    __shared__ double sE[CH][NX][NW];
+    __shared__ double se[CH][NX];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kw = KW * blockIdx.x + 8 * wave;               // first k of this wave
+    const int k = kw + (lane >> 3), i = lane & 7, kc = min(k, N - 1);
+    const int kend = min(kw + 7, N - 1);                     // blocks j < kend matter to the wave
+    const int kblk = min(KW * (int)blockIdx.x + KW - 1, N - 1);
+    const double* row = a.phi + ((((size_t)b * N + kc) * N) * n + i) * NX;
+    const double* Eb = a.E + (size_t)b * N * NX * nw;
+    double s = 0.0, g = 0.0;
+    sls_p2 rn[JU][NX / 2];
+    auto fetch = [&](int u, int j) {                         // entries j >= k are read but not used
+#pragma unroll
+        for (int q = 0; q < NX / 2; ++q)
+            rn[u][q] = *reinterpret_cast<const sls_p2*>(row + (size_t)min(j, N - 1) * n * NX + 2 * q);
+    };
+    for (int c0 = 0; c0 < kblk; c0 += CH) {
+        const int cnt = min(CH, kblk - c0);
+        __syncthreads();
+        for (int q = tid; q < cnt * NX * NW; q += 320) {
+            const int jl = q / (NX * NW), l = (q / NW) % NX, w = q % NW;
+            sE[jl][l][w] = w < nw ? Eb[((size_t)(c0 + jl) * NX + l) * nw + w] : 0.0;
+        }
+        __syncthreads();
+        for (int q = tid; q < cnt * NX; q += 320) {
+            const int jl = q / NX, l = q % NX;
+            double t = 0.0;
+            for (int w = 0; w < NW; ++w) t += fabs(sE[jl][l][w]);
+            se[jl][l] = t;
+        }
+        __syncthreads();
+        const int je = min(c0 + cnt, kend);
+#pragma unroll
+        for (int u = 0; u < JU; ++u) fetch(u, c0 + u);
+        for (int j = c0; j < je; j += JU) {
+#pragma unroll
+            for (int u = 0; u < JU; ++u) {
+                double r[NX];
+#pragma unroll
+                for (int q = 0; q < NX / 2; ++q) { r[2 * q] = rn[u][q][0]; r[2 * q + 1] = rn[u][q][1]; }
+                fetch(u, j + u + JU);
+                const int jl = min(j + u, je - 1) - c0;
+                double t[NW], gg = 0.0, ss = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) t[w] = 0.0;
+#pragma unroll
+                for (int l = 0; l < NX; ++l) {
+                    gg = fma(fabs(r[l]), se[jl][l], gg);
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) t[w] = fma(r[l], sE[jl][l][w], t[w]);
+                }
+#pragma unroll
+                for (int w = 0; w < NW; ++w) ss += fabs(t[w]);
+                if (j + u < k && j + u < je) { s += ss; g += gg; }
+            }
+        }
+    }
+    if (k < N) {
+        // depth of the sums: NX products, NW columns, k blocks
+        const double coef = (double)(NX + k * (nw + 1) + 64) * 0x1p-52;
+        s = s + coef * g * (1.0 + 0x1p-50) + 0x1p-1000;
+        if (!isfinite(g) || !isfinite(s)) s = INFINITY;
+        if (k == 0) s = 0.0;
+        out_sig[((size_t)b * N + k) * n + i] = s;
     }
 }
 
@@ -1374,21 +1546,6 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_fp_row_kernel(FpRowArgs a, in
 // 64 x 40 at nx = 30 0.303 ms (1.33 ms).
 constexpr int SLS_FP_PF = 8;             // blocks of the next row read one step ahead
 constexpr int SLS_FP_MAX_THREADS = 768;
-
-typedef double sls_p2 __attribute__((ext_vector_type(2), aligned(8)));
-
-// x + x of the partner lane of a data-parallel-primitive pattern (no LDS):
-// 0xB1, 0x4E: lanes 1, 2 away within four; 0x141: mirrored within eight
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double x) {
-    union { double d; int w[2]; } u;
-    u.d = x;
-    u.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], CTRL, 0xf, 0xf, true);
-    u.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], CTRL, 0xf, 0xf, true);
-    return x + u.d;
-}
-__device__ __forceinline__ double sum4(double x) { return dpp_add<0x4E>(dpp_add<0xB1>(x)); }
-__device__ __forceinline__ double sum8(double x) { return dpp_add<0x141>(sum4(x)); }
 
 struct FpChainArgs {
     const double* phi; const double* E; const double* sigE;
@@ -1754,8 +1911,15 @@ extern "C" int leb_sls_fixed_point(const leb_dynamics* dyn, int32_t batch, int32
     // so it runs over all (trajectory, step) rows at once
     double* sigE = take((size_t)batch * N * n);
     a.t.sigE = sigE;
-    if (n > 8 && n <= 16 && nw <= 16 && nw > 0)
-        hipLaunchKernelGGL(sls_tube_e_mfma_kernel, dim3((unsigned)N, (unsigned)batch), dim3(256), 0, s, a.t, sigE);
+    if (nw > 0 && n > 32)
+        launch_tube_e_mfma<3>(a.t, batch, sigE, s);
+    else if (nw > 0 && n > 16)
+        launch_tube_e_mfma<2>(a.t, batch, sigE, s);
+    else if (nw > 0 && n > 8)
+        launch_tube_e_mfma<1>(a.t, batch, sigE, s);
+    else if (nx == 6 && nu == 2 && nw > 0 && nw <= 8)
+        hipLaunchKernelGGL((sls_tube_e_lane_kernel<6, 2>), dim3((unsigned)((N + 39) / 40), (unsigned)batch), dim3(320), 0,
+                           s, a.t, sigE);
     else
         launch_tube<ROW_E>(a.t, batch, sigE, s);
     size_t smem;

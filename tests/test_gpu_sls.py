@@ -447,3 +447,37 @@ def test_sls_update_beyond_lds(gpu, orc, sls):
     km = int(np.argmax(big)) if big.any() else p.N
     assert km > 10
     _close_tube(mu[:km], sg[:km], mo[:km], so[:km], "U=5 N=120 tube")
+
+
+@pytest.mark.parametrize("n_units,N,nw", [(1, 3, 8), (1, 42, 1), (1, 9, 9), (1, 9, 64), (2, 9, 1), (2, 9, 17), (3, 9, 33),
+                                          (3, 4, 64), (5, 9, 16), (5, 9, 49)])
+def test_fixed_point_disturbance_part_tiles(gpu, sls, n_units, N, nw):
+    """The disturbance part of every tube row over its kernels' edges (the
+    lane kernel up to nw = 8 and past one workgroup's 40 rows; 1-3 row tiles by
+    1-4 column tiles): with a zero nominal-bound tube the fixed point's
+    sigma is at least, and within 1e-4 of, sum_j |Phi E| 1 + |Phi| rho of the
+    returned residuals (the tube-map bar)."""
+    import paper_2607_01203_amd as leb
+    p = W.sls_cfg(seed=90 + n_units, batch=2, N=N, n_units=n_units, thrust=0.0)
+    dyn = leb.dynamics_like(p.dyn)
+    z, v = _t(p.z, gpu), _t(p.v, gpu)
+    A, B, _ = leb.linearize(dyn, z, v)
+    _, phi = leb.sls_responses(A, B, _t(p.qx, gpu), _t(p.qu, gpu))
+    rng = np.random.default_rng(nw)
+    E = rng.normal(size=(2, N, 6 * n_units, nw)) * 1e-3
+    print("case: disturbance part U=%d N=%d nw=%d" % (n_units, N, nw), flush=True)
+    mu, sg, lo, hi, cert = leb.sls_fixed_point(dyn, z, v, phi, _t(E, gpu), 0.0, 1e-6)
+    mu, sg, lo, hi = _np(mu), _np(sg), _np(lo), _np(hi)
+    for b in range(2):
+        # rows up to the first step whose bound is not finite (many wide columns can
+        # carry the tube into a spring singularity); every later row is +inf
+        fin = np.isfinite(lo[b]).all(1) & np.isfinite(hi[b]).all(1)
+        K = N if fin.all() else int(np.argmin(fin)) + 1
+        assert K > 1 and (K < N or not fin.all() or int(_np(cert)[b]) == 1)
+        assert np.isinf(sg[b, K:]).all() and (mu[b, K:] == 0).all()
+        with np.errstate(invalid="ignore"):
+            cb, rb = 0.5 * (lo[b] + hi[b]), 0.5 * (hi[b] - lo[b]) + 1e-6
+            mo, so = sls.tube_map(_np(phi)[b], E[b], cb, rb)
+        scale = np.abs(mo[:K]) + so[:K]
+        assert (np.abs(mu[b, :K] - mo[:K]) <= 1e-11 * scale).all()
+        assert (sg[b, :K] >= so[:K] * (1 - 1e-15)).all() and (sg[b, :K] <= so[:K] + 1e-11 * scale + 1e-290).all()
