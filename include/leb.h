@@ -645,6 +645,10 @@ int leb_linearize(const leb_dynamics* dyn, int32_t batch, int32_t N, const doubl
  */
 int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t N, const double* A, const double* B,
                       const double* qx, const double* qu, double* K, double* phi, void* stream);
+/* The same, and every entry with k <= j of K and phi is written 0 (for callers
+ * that hand out whole arrays: no fill before the call). */
+int leb_sls_responses_full(int32_t nx, int32_t nu, int32_t batch, int32_t N, const double* A, const double* B,
+                           const double* qx, const double* qu, double* K, double* phi, void* stream);
 
 /*
  * leb_sls_tube_map -- tube centre and width of time-varying responses (eqs.

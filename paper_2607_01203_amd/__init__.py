@@ -215,6 +215,8 @@ def lib():
         L.leb_linearize.restype = ctypes.c_int
         L.leb_sls_responses.argtypes = [i32, i32, i32, i32] + [vp] * 7
         L.leb_sls_responses.restype = ctypes.c_int
+        L.leb_sls_responses_full.argtypes = L.leb_sls_responses.argtypes
+        L.leb_sls_responses_full.restype = ctypes.c_int
         L.leb_sls_tube_map.argtypes = [i32, i32, i32, i32, i32] + [vp] * 7
         L.leb_sls_tube_map.restype = ctypes.c_int
         L.leb_sls_fixed_point.argtypes = [ctypes.POINTER(Dynamics), i32, i32, vp, vp, vp, i32, vp, f64c_, f64c_] + \
@@ -364,11 +366,11 @@ def sls_responses(A, B, qx, qu, stream=None):
     import torch
     f64 = torch.float64
     b, N, nx, nu = (int(x) for x in B.shape)
-    K = torch.zeros((b, N, N, nu, nx), dtype=f64, device=A.device)
-    phi = torch.zeros((b, N, N, nx + nu, nx), dtype=f64, device=A.device)
-    _check(lib().leb_sls_responses(nx, nu, b, N, _dev_ptr(A, "A", f64), _dev_ptr(B, "B", f64),
-                                   _dev_ptr(qx, "qx", f64), _dev_ptr(qu, "qu", f64), _dev_ptr(K, "K", f64),
-                                   _dev_ptr(phi, "phi", f64), _stream(stream)))
+    K = torch.empty((b, N, N, nu, nx), dtype=f64, device=A.device)
+    phi = torch.empty((b, N, N, nx + nu, nx), dtype=f64, device=A.device)
+    _check(lib().leb_sls_responses_full(nx, nu, b, N, _dev_ptr(A, "A", f64), _dev_ptr(B, "B", f64),
+                                        _dev_ptr(qx, "qx", f64), _dev_ptr(qu, "qu", f64), _dev_ptr(K, "K", f64),
+                                        _dev_ptr(phi, "phi", f64), _stream(stream)))
     return K, phi
 
 

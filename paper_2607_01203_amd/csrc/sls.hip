@@ -61,13 +61,36 @@ struct RiccatiArgs {
     const double* A; const double* B; const double* qx; const double* qu;
     double* K; double* phi;
     int nx, nu, N;
+    int zero;                // 1: write 0 to the entries k <= j too
 };
+
+// Zeros of disturbance times j .. j + cnt - 1 (adjacent in memory), every k <= j: the
+// workgroup's last work.  A chain has j + 1 blocks to clear and N - j - 1 steps to run,
+// so the clearing fills the memory system while the long chains still run (as a fill of
+// the whole arrays before the launch it cost 25 us at 256 x 40, nx = 6, and 0.25 ms at
+// 64 x 40, nx = 30).
+__device__ void riccati_zero(const RiccatiArgs& a, int b, int j, int cnt) {
+    const int nk = a.nu * a.nx, np = (a.nx + a.nu) * a.nx;
+    const int last = min(j + cnt, a.N) - 1;
+    for (int k = 0; k <= last; ++k) {
+        const int j0 = max(j, k);                 // times j0 .. last have k <= j
+        const size_t o = ((size_t)b * a.N + k) * a.N + j0;
+        double* K = a.K + o * nk;
+        double* P = a.phi + o * np;
+        const int m = last - j0 + 1;
+        for (int q = threadIdx.x; q < m * nk; q += blockDim.x) K[q] = 0.0;
+        for (int q = threadIdx.x; q < m * np; q += blockDim.x) P[q] = 0.0;
+    }
+}
 
 template <int NUB, int PF>
 __global__ void __launch_bounds__(SLS_THREADS) sls_riccati_kernel(RiccatiArgs a) {
     const int j = blockIdx.x, b = blockIdx.y;
     const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
-    if (j >= N - 1) return;                      // no k with j < k < N
+    if (j >= N - 1) {                            // no k with j < k < N
+        if (a.zero) riccati_zero(a, b, j, 1);
+        return;
+    }
     extern __shared__ double sm[];
     double* P = sm;                              // nx*nx   cost-to-go, then X of the forward pass
     double* Ak = P + nx * nx;                    // nx*nx
@@ -265,6 +288,7 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_riccati_kernel(RiccatiArgs a)
         fstep(k, pfa, pfb);
         if (k + 1 < N) fstep(k + 1, pfb, pfa);
     }
+    if (a.zero) riccati_zero(a, b, j, 1);
 }
 
 // The same recursions for one small size (NX <= 8, NU = 2) with eight lanes per
@@ -457,6 +481,7 @@ __global__ void __launch_bounds__(64) sls_riccati_lane_kernel(RiccatiArgs a) {
             if (k + 2 < N) abn = ab_at(k + 2);
         }
     }
+    if (a.zero) riccati_zero(a, b, j0, 8);
 }
 
 // The same recursions on FP64 MFMA (v_mfma_f64_16x16x4f64) for nx <= 16,
@@ -494,7 +519,10 @@ template <int NUB>
 __global__ void __launch_bounds__(64) sls_riccati_mfma_kernel(RiccatiArgs a) {
     const int j = blockIdx.x, b = blockIdx.y;
     const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
-    if (j >= N - 1) return;
+    if (j >= N - 1) {
+        if (a.zero) riccati_zero(a, b, j, 1);
+        return;
+    }
     __shared__ double sS[NUB * NUB];
     __shared__ double sBc[NUB * 16];
     __shared__ double sK[16 * 16];
@@ -637,6 +665,7 @@ __global__ void __launch_bounds__(64) sls_riccati_mfma_kernel(RiccatiArgs a) {
             X = mm_tn(AclT, X, z4);                 // (A + B K) X
         }
     }
+    if (a.zero) riccati_zero(a, b, j, 1);
 }
 
 // The same recursions for larger sizes (nx <= 32, nu <= 16) on FP64 MFMA: one
@@ -699,7 +728,10 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
     constexpr int W = 16 * TX, LD = 16 + W;
     const int b = blockIdx.x, j = blockIdx.y;
     const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
-    if (j >= N - 1) return;                      // no k with j < k < N
+    if (j >= N - 1) {                            // no k with j < k < N
+        if (a.zero) riccati_zero(a, b, j, 1);
+        return;
+    }
     // k-steps of a product over states (per tile) and over inputs
     const int sx0 = TX > 1 ? 4 : (nx + 3) >> 2, sx1 = (nx - 13) >> 2, su = (nu + 3) >> 2;
     auto sx = [&](int t) { return t == 0 ? sx0 : sx1; };
@@ -905,6 +937,7 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
                 for (int u = 0; u < TX; ++u) X[t][u] = Xn[t][u];
         }
     }
+    if (a.zero) riccati_zero(a, b, j, 1);
 }
 
 template <int TX>
@@ -1786,8 +1819,8 @@ static bool dims_ok(int nx, int nu) { return nx >= 1 && nx <= SLS_MAX_NX && nu >
 
 using namespace leb;
 
-extern "C" int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t N, const double* A, const double* B,
-                                 const double* qx, const double* qu, double* K, double* phi, void* stream) {
+static int sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t N, const double* A, const double* B,
+                         const double* qx, const double* qu, double* K, double* phi, bool zero, void* stream) {
     if (!dims_ok(nx, nu) || nu < 1 || batch < 0 || N < 0) return LEB_EINVAL;
     if (batch > 65535 || N > 65535) return LEB_ENOTSUP;
     if ((int64_t)batch * N * N == 0) return LEB_OK;
@@ -1797,7 +1830,7 @@ extern "C" int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t 
         if (!aligned8(p)) return LEB_EINVAL;
     RiccatiArgs a;
     a.A = A; a.B = B; a.qx = qx; a.qu = qu; a.K = K; a.phi = phi;
-    a.nx = nx; a.nu = nu; a.N = N;
+    a.nx = nx; a.nu = nu; a.N = N; a.zero = zero ? 1 : 0;
     const dim3 grid((unsigned)N, (unsigned)batch);
     const size_t sm = riccati_smem(nx, nu);
     hipStream_t st = (hipStream_t)stream;
@@ -1815,6 +1848,17 @@ extern "C" int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t 
     else
         hipLaunchKernelGGL((sls_riccati_kernel<4, 2>), grid, dim3(64), sm, st, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
+}
+
+extern "C" int leb_sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t N, const double* A, const double* B,
+                                 const double* qx, const double* qu, double* K, double* phi, void* stream) {
+    return sls_responses(nx, nu, batch, N, A, B, qx, qu, K, phi, false, stream);
+}
+
+extern "C" int leb_sls_responses_full(int32_t nx, int32_t nu, int32_t batch, int32_t N, const double* A,
+                                      const double* B, const double* qx, const double* qu, double* K, double* phi,
+                                      void* stream) {
+    return sls_responses(nx, nu, batch, N, A, B, qx, qu, K, phi, true, stream);
 }
 
 extern "C" int leb_sls_tube_map(int32_t nx, int32_t nu, int32_t nw, int32_t batch, int32_t N, const double* phi,

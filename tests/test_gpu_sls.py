@@ -481,3 +481,27 @@ def test_fixed_point_disturbance_part_tiles(gpu, sls, n_units, N, nw):
         scale = np.abs(mo[:K]) + so[:K]
         assert (np.abs(mu[b, :K] - mo[:K]) <= 1e-11 * scale).all()
         assert (sg[b, :K] >= so[:K] * (1 - 1e-15)).all() and (sg[b, :K] <= so[:K] + 1e-11 * scale + 1e-290).all()
+
+
+@pytest.mark.parametrize("nx,nu,N", [(6, 2, 1), (6, 2, 19), (7, 3, 9), (12, 4, 9), (12, 5, 9), (30, 10, 9)])
+def test_responses_full_clears_every_entry(gpu, nx, nu, N):
+    """leb_sls_responses_full on buffers full of NaN writes every entry (0 for
+    k <= j); leb_sls_responses leaves those entries alone and writes the same
+    values elsewhere, in each of the four kernels."""
+    import ctypes
+    import torch
+    import paper_2607_01203_amd as leb
+    L = leb.lib()
+    A, B, qx, qu = (_t(x, gpu) for x in W.random_ltv(5, 2, N, nx, nu, scale=0.2))
+    vp = lambda t: ctypes.c_void_p(t.data_ptr())
+    out = {}
+    for name in ("leb_sls_responses", "leb_sls_responses_full"):
+        K = torch.full((2, N, N, nu, nx), float("nan"), dtype=torch.float64, device=gpu)
+        phi = torch.full((2, N, N, nx + nu, nx), float("nan"), dtype=torch.float64, device=gpu)
+        leb._check(getattr(L, name)(nx, nu, 2, N, vp(A), vp(B), vp(qx), vp(qu), vp(K), vp(phi), None))
+        torch.cuda.synchronize()
+        out[name] = (K, phi)
+    late = torch.tril(torch.ones(N, N, dtype=torch.bool, device=gpu), -1)       # k > j
+    for a, f in zip(out["leb_sls_responses"], out["leb_sls_responses_full"]):
+        assert torch.equal(a[:, late], f[:, late]) and torch.isfinite(f).all()
+        assert torch.isnan(a[:, ~late]).all() and (f[:, ~late] == 0).all()
