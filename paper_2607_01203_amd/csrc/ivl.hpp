@@ -124,7 +124,9 @@ __device__ __noinline__ void sincos_wide(double a, double b, SinCos* r) {
         r->s_lo = r->s_hi = r->c_lo = r->c_hi = 2;
         return;
     }
-    double sa = sin(a), sb = sin(b), ca = cos(a), cb = cos(b);
+    double sa, sb, ca, cb;
+    sincos(a, &sa, &ca);
+    sincos(b, &sb, &cb);
     auto wdn = [](double x) { return x - fabs(x) * 0x1p-40 - 0x1p-100; };
     auto wup = [](double x) { return x + fabs(x) * 0x1p-40 + 0x1p-100; };
     r->s_lo = sa <= sb ? 0 : 1;

@@ -163,3 +163,50 @@ def test_sampled_remainder(gpu, orc, name):
     assert (np.abs(slo - rlo) <= e + 1e-15).all() and (np.abs(shi - rhi) <= e + 1e-15).all()
     lo, hi, _ = _gpu_bound(leb, b, gpu, "path")
     assert (slo >= lo[0] - e).all() and (shi <= hi[0] + e).all()
+
+
+@pytest.mark.parametrize("name", ["satellite", "quad3d", "quadratic", "sincos"])
+@pytest.mark.parametrize("K", [0, 1, 256, 257, 3001])
+def test_sampled_remainder_parts(gpu, name, K):
+    """One unit (its samples spread over several workgroups, combined by atomic
+    maxima) gives bit for bit what the same unit gives among 600 (one workgroup
+    each); K at the edges of a workgroup's stride."""
+    import torch
+    import paper_2607_01203_amd as leb
+    rng = np.random.default_rng(K)
+    if name in ("satellite", "quad3d"):
+        b = W.small_batch(_sys(name), 55, 1, 0.1)
+        dyn, z, v, sg = leb.dynamics_like(b.dyn), b.z, b.v, b.sigma
+    elif name == "quadratic":
+        Q = rng.normal(size=(3, 5, 5))
+        dyn = leb.quadratic_dynamics(_t(0.5 * (Q + Q.transpose(0, 2, 1)), gpu), nu=2)
+        z, v, sg = rng.normal(size=(1, 1, 3)), rng.normal(size=(1, 1, 2)), rng.uniform(0.1, 0.2, (1, 1, 5))
+    else:
+        dyn = leb.sincos_dynamics(2)
+        z, v, sg = rng.normal(size=(1, 1, 2)), np.zeros((1, 1, 0)), rng.uniform(0.1, 0.2, (1, 1, 2))
+    t = _t(rng.uniform(-1.0, 1.0, (K, sg.shape[2])), gpu)
+    many = lambda a: _t(np.broadcast_to(a, (1, 600, a.shape[2])), gpu)
+    print("case: sampled remainder parts %s K=%d" % (name, K), flush=True)
+    lo, hi = leb.sample_remainder(dyn, _t(z, gpu), _t(v, gpu), _t(sg, gpu), t)
+    lo2, hi2 = leb.sample_remainder(dyn, many(z), many(v), many(sg), t)
+    torch.cuda.synchronize()
+    assert torch.equal(lo.expand_as(lo2), lo2) and torch.equal(hi.expand_as(hi2), hi2)
+    assert (lo <= 0).all() and (hi >= 0).all()
+
+
+@pytest.mark.parametrize("name", ["satellite", "quad3d"])
+@pytest.mark.parametrize("units", [1, 3, 5])
+@pytest.mark.parametrize("mode", MODES)
+def test_small_units_of_a_wave(gpu, orc, name, units, mode):
+    """Unit counts around the four that share a wave, one of them invalid and
+    (3-D quadrotor) one with unbounded rows: bounds and flags against the oracle."""
+    import paper_2607_01203_amd as leb
+    b = W.small_batch(_sys(name), 56, units, 0.1)
+    if units > 1:
+        b.sigma[0, 1, 2] = np.nan
+    if name == "quad3d":
+        b.z[0, units - 1, 4] = np.pi / 2 - 0.05
+    lo, hi, fl = _gpu_bound(leb, b, gpu, mode)
+    olo, ohi, ofl = orc.leb(orc.Dyn.like(b.dyn), b.z, b.v, b.sigma, mode=mode)
+    check_bounds(lo, hi, olo, ohi, "%s %s" % (name, mode))
+    assert (fl == ofl.astype(np.int32)).all()
