@@ -73,7 +73,6 @@ int launch_pbh_chain(const leb_dynamics* dyn, int64_t units, const double* z, co
                      const SweepFold* fold = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
                      bool compact = false);
 size_t pbh_smem_bytes(int U);
-size_t bwd_smem_bytes(int U);
 int launch_tube_map(int B, int N, int U, const double* phi, const double* e, const double* cbar,
                     const double* rbar, double* mu, double* sigma, hipStream_t s,
                     double scale = 1.0, double shift = 0.0);

@@ -8,30 +8,42 @@
 // gradients to refine the nominal point (Table II) and to penalise the
 // propagated error (eq. linearization_error_cost_penalty).
 //
-// Interval intermediates are recomputed, never stored:
-//   1. spring i primal (the bound kernel's own code, F = float): pieces of
-//      node i+1's shared entries go to LDS;
+// Interval intermediates are recomputed, never stored.  A lane owns node i of a
+// timestep and spring i (to node i + 1), as in the bound kernel:
+//   1. spring i primal (the bound kernel's own code): pieces of node i+1's shared
+//      entries go to LDS;
 //   2. node i primal and its hand-written reverse: adjoints of the node's
 //      displacements, nominal attitude and thrust sum, and of the shared
 //      spring pieces (the left spring's go to LDS);
-//   3. spring i tangent passes: the same spring code with a forward-mode
-//      dual type, one pass per spring input (2 separations, 8 displacement
-//      endpoints); each pass contracts the tangents with the adjoints;
+//   3. spring i tangent passes: the same spring code with a forward-mode dual type
+//      of two directions, five passes over the ten spring inputs (the two
+//      separations; the ends of the displacements of px_i, pz_i, px_{i+1},
+//      pz_{i+1}); each pass carries tangents only through what its inputs reach
+//      (the displacement of pz_{i+1}, for instance, only through the fourth prefix
+//      box) and contracts them with the adjoints;
 //   4. per-coordinate sums in a fixed order (deterministic), then the
 //      chain rule through Delta = [min(mu - sigma, 0), max(mu + sigma, 0)].
+// The FP32 tangents are those of ten one-direction passes over every term, bit
+// for bit: what is left out are products and sums with zero tangents.
 // Rows that are unbounded, and units with invalid data, contribute nothing.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "leb.h"
 #include "leb_internal.hpp"
 #include "node.hpp"
 #include "pbh_common.hpp"
+#include "pbh_node.hpp"
 
 namespace leb {
 
-constexpr int BWD_BLOCK = 128;
+constexpr int BWD_MAX_U = 128;
+constexpr int BWD_BLOCK = 256;           // lanes of the filled-chip form
+constexpr int BWD_TASKS = 5;             // tangent passes
+constexpr int BWD_SPLIT_BLOCKS = 256;    // the split form: up to one workgroup per compute unit
 
 struct BwdArgs {
     const double* z; const double* v; const double* mu; const double* sigma;
@@ -42,101 +54,110 @@ struct BwdArgs {
     double c, kL, L0;
 };
 
-struct BSpring { IV<float> L[5]; uint32_t unbounded; uint32_t pad_; };
 struct RowAdj { double xlo, xhi, zlo, zhi; };
 struct NodeGrad { double th, s, dth[2], du1[2], du2[2], dx[2], dz[2]; };
-struct SpringGrad { double d[10]; };     // dxn, dzn, Dxi lo/hi, Dzi lo/hi, Dxj lo/hi, Dzj lo/hi
 struct PieceAdj { double lo[5], hi[5]; };
+// what a lane passes to its neighbour, one after the other: spring i's pieces to
+// node i+1, node i+1's piece adjoints back to spring i, spring i's gradient of
+// node i+1's coordinates to node i+1
+union BwdPass {
+    struct { IV<float> L[5]; uint32_t unbounded; } piece;
+    PieceAdj adj;
+    double next[6];                      // dxn, dzn, Dxj lo/hi, Dzj lo/hi
+};
 
-// reverse of t_mul_z(a, p) for F = float (first-on-tie selections)
+// reverse of t_mul_z(a, p) for F = float (first-on-tie selections); both sides of a
+// selection are added (one of them 0), so that no adjoint is addressed by a branch
 __device__ __forceinline__ void bwd_mul_z(IV<float> a, IV<float> p, double tlo, double thi, double* alo,
                                           double* ahi, double* plo, double* phi) {
-    const float c1 = a.lo * p.hi, c2 = a.hi * p.lo;
-    if (c1 <= c2) { *alo += tlo * p.hi; *phi += tlo * a.lo; }
-    else { *ahi += tlo * p.lo; *plo += tlo * a.hi; }
-    const float c0 = a.lo * p.lo, c3 = a.hi * p.hi;
-    if (c0 >= c3) { *alo += thi * p.lo; *plo += thi * a.lo; }
-    else { *ahi += thi * p.hi; *phi += thi * a.hi; }
+    const bool lf = a.lo * p.hi <= a.hi * p.lo, hf = a.lo * p.lo >= a.hi * p.hi;
+    const double l1 = lf ? tlo : 0.0, l2 = lf ? 0.0 : tlo, h1 = hf ? thi : 0.0, h2 = hf ? 0.0 : thi;
+    *alo += l1 * p.hi;
+    *ahi += l2 * p.lo;
+    *phi += l1 * a.lo;
+    *plo += l2 * a.hi;
+    *alo += h1 * p.lo;
+    *ahi += h2 * p.hi;
+    *plo += h1 * a.lo;
+    *phi += h2 * a.hi;
 }
 // reverse of t_sq_z(a) = [0, max(a.lo^2, a.hi^2)]
 __device__ __forceinline__ void bwd_sq_z(IV<float> a, double thi, double* alo, double* ahi) {
-    const float l2 = a.lo * a.lo, h2 = a.hi * a.hi;
-    if (l2 >= h2) *alo += thi * 2.0 * a.lo;
-    else *ahi += thi * 2.0 * a.hi;
+    const bool f = a.lo * a.lo >= a.hi * a.hi;
+    *alo += f ? thi * 2.0 * a.lo : 0.0;
+    *ahi += f ? 0.0 : thi * 2.0 * a.hi;
 }
 
-__device__ __forceinline__ double sc_deriv(const SinCos& sc, bool is_sin, int sel, double a64, double b64, bool at_b) {
-    // derivative of the selected endpoint value; 0 when the bound is a clamped extremum
-    if (sel == 2) return 0.0;
-    if (sc.wide) {
-        const double x = sel == 0 ? a64 : b64;
-        return is_sin ? cos(x) : -sin(x);
-    }
-    const float x = sel == 0 ? sc.fa : sc.fb;
-    (void)at_b;
-    return is_sin ? (double)cos_poly(x) : -(double)sin_poly(x);
+// the two tangents of pass TASK, with the spring's inputs st
+template <int TASK>
+__device__ __forceinline__ void bwd_task(const SpringSetup& st, double K3, double K15, double K1, double K05,
+                                         AccTangent& acc) {
+    auto lohi = [](IV<float> x, float ld, float le, float hd, float he) { return iv(dfm(x.lo, ld, le), dfm(x.hi, hd, he)); };
+    // the displacement's own ends (lo: first tangent, hi: second)
+    auto ends = [&](IV<float> x) { return lohi(x, 1.0f, 0.0f, 0.0f, 1.0f); };
+    // a separation minus the displacement: its lower end moves with the displacement's upper end
+    auto minus = [&](IV<float> x) { return lohi(x, 0.0f, -1.0f, -1.0f, 0.0f); };
+    acc.g = acc.h = 0.0;
+    if constexpr (TASK == 0)             // nominal separations dxn, dzn
+        spring_core(lohi(st.dxA, 1.0f, 0.0f, 1.0f, 0.0f), lohi(st.dxB, 1.0f, 0.0f, 1.0f, 0.0f),
+                    lohi(st.dz0, 0.0f, 1.0f, 0.0f, 1.0f), lohi(st.dz1, 0.0f, 1.0f, 0.0f, 1.0f),
+                    lohi(st.dz2, 0.0f, 1.0f, 0.0f, 1.0f), st.Dxi, st.Dzi, st.Dxj, st.Dzj, 1.0, 1.0, 1.0, 1.0, K3, K15,
+                    K1, K05, acc, acc);
+    else if constexpr (TASK == 1)        // Dxi
+        spring_core(minus(st.dxA), minus(st.dxB), st.dz0, st.dz1, st.dz2, ends(st.Dxi), st.Dzi, st.Dxj, st.Dzj, 1.0, 1.0,
+                    1.0, 1.0, K3, K15, K1, K05, acc, acc);
+    else if constexpr (TASK == 2)        // Dzi
+        spring_core(st.dxA, st.dxB, st.dz0, minus(st.dz1), minus(st.dz2), st.Dxi, ends(st.Dzi), st.Dxj, st.Dzj, 1.0, 1.0,
+                    1.0, 1.0, K3, K15, K1, K05, acc, acc);
+    else if constexpr (TASK == 3)        // Dxj
+        spring_core(st.dxA, ends(st.dxB), st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, ends(st.Dxj), st.Dzj, 1.0, 1.0, 1.0, 1.0,
+                    K3, K15, K1, K05, acc, acc);
+    else                                 // Dzj
+        spring_core(st.dxA, st.dxB, st.dz0, st.dz1, ends(st.dz2), st.Dxi, st.Dzi, st.Dxj, ends(st.Dzj), 1.0, 1.0, 1.0,
+                    1.0, K3, K15, K1, K05, acc, acc);
 }
 
-__global__ void __launch_bounds__(BWD_BLOCK) pbh_chain_bwd(BwdArgs A) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int U = A.U, T = A.T;
-    const int nx = 6 * U, nu = 2 * U, n = nx + nu;
-    double* s_nom = reinterpret_cast<double*>(smem);                                 // [T][n]
-    IV<float>* s_d = reinterpret_cast<IV<float>*>(s_nom + (size_t)T * n);            // [T][n]
-    RowAdj* s_g = reinterpret_cast<RowAdj*>(s_d + (size_t)T * n);                    // [T][U]
-    unsigned char* region = reinterpret_cast<unsigned char*>(s_g + (size_t)T * U);
-    const size_t region_bytes = (size_t)T * U * (sizeof(BSpring) > sizeof(SpringGrad) ? sizeof(BSpring) : sizeof(SpringGrad));
-    BSpring* s_sp = reinterpret_cast<BSpring*>(region);                              // phases 1-2
-    SpringGrad* s_gs = reinterpret_cast<SpringGrad*>(region);                        // phases 3-4
-    PieceAdj* s_lbar = reinterpret_cast<PieceAdj*>(region + region_bytes);           // [T][U]
-    NodeGrad* s_gn = reinterpret_cast<NodeGrad*>(s_lbar + (size_t)T * U);            // [T][U]
-    uint32_t* s_unb = reinterpret_cast<uint32_t*>(s_gn + (size_t)T * U);             // [T][U] row unbounded
-    uint32_t* s_flag = s_unb + (size_t)T * U;                                        // [T]
-
-    const int tid = threadIdx.x;
+// SPLIT = false: 256 lanes, each runs its spring's five passes one after the other.
+// SPLIT = true (launches that leave the chip idle): five waves over the same up
+// to 64 lanes, each wave runs phases 1 and 2 for itself and then one pass.
+//
+// What bounds it: VALU issue (about 11,000 instructions a lane, most of them in phase
+// 3) at two waves a SIMD when the chip is full, the serial chain of one lane
+// otherwise.  28 nodes, 256 x 40 steps: 103 us (337 us with ten one-direction passes
+// over every term, whose hoisted values took 430 registers, one wave a SIMD, and
+// with adjoints addressed through scratch); 1 x 40: 15 us (55 us).
+template <bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 : 2) pbh_chain_bwd(BwdArgs A) {
+    constexpr int LANES = SPLIT ? 64 : BWD_BLOCK, COPIES = SPLIT ? BWD_TASKS : 1;
+    __shared__ BwdPass s_pass[COPIES][LANES];
+    __shared__ uint32_t s_unb[COPIES][LANES];                  // row unbounded
+    __shared__ uint32_t s_flag[COPIES][LANES];                 // per timestep
+    __shared__ double s_grad[SPLIT ? LANES : 1][2 * BWD_TASKS];
+    const int U = A.U, T = A.T, nx = 6 * U, nu = 2 * U, n = nx + nu;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int copy = SPLIT ? wave : 0, ln = SPLIT ? (threadIdx.x & 63) : threadIdx.x;
     const int64_t u0 = (int64_t)blockIdx.x * T;
     const int64_t left = A.units - u0;
     const int nloc = left < T ? (int)left : T;
-
-    for (int q = tid; q < T; q += BWD_BLOCK) s_flag[q] = 0u;
+    const int lt = ln / U, i = ln - lt * U;
+    const bool active = lt < nloc, right = active && i < U - 1;
+    s_flag[copy][ln] = 0u;
+    TileRef tr = {};
+    tr.Z = A.z + u0 * nx; tr.V = A.v + u0 * nu; tr.MU = A.mu ? A.mu + u0 * n : nullptr; tr.SG = A.sigma + u0 * n;
+    tr.nloc = nloc;
+    NodeIn d;
+    node_load(tr, U, lt, i, d);
+    RowAdj gi = {0.0, 0.0, 0.0, 0.0}, gj = {0.0, 0.0, 0.0, 0.0};
+    if (active) {
+        const double* gl = A.g_lo + (u0 + lt) * nx + 6 * i;
+        const double* gh = A.g_hi + (u0 + lt) * nx + 6 * i;
+        gi = RowAdj{gl[3], gh[3], gl[4], gh[4]};
+        if (right) gj = RowAdj{gl[9], gh[9], gl[10], gh[10]};
+    }
+    const IV<float> Dx = disp_interval(d.ms[0], d.ss[0]), Dz = disp_interval(d.ms[1], d.ss[1]);
     __syncthreads();
-    for (int idx = tid; idx < nloc * nx; idx += BWD_BLOCK) {
-        const int lt = idx / nx, c = idx - lt * nx;
-        const double x = A.z[u0 * nx + idx];
-        if (!isfinite(x)) atomicOr(&s_flag[lt], LEB_FLAG_BAD_INPUT);
-        s_nom[lt * n + c] = x;
-        const int rc = c % 6;
-        if (rc == 3 || rc == 4) {
-            RowAdj& g = s_g[lt * U + c / 6];
-            const double gl = A.g_lo[u0 * nx + idx], gh = A.g_hi[u0 * nx + idx];
-            if (rc == 3) { g.xlo = gl; g.xhi = gh; } else { g.zlo = gl; g.zhi = gh; }
-        }
-    }
-    for (int idx = tid; idx < nloc * nu; idx += BWD_BLOCK) {
-        const int lt = idx / nu, c = idx - lt * nu;
-        const double x = A.v[u0 * nu + idx];
-        if (!isfinite(x)) atomicOr(&s_flag[lt], LEB_FLAG_BAD_INPUT);
-        s_nom[lt * n + nx + c] = x;
-    }
-    for (int idx = tid; idx < nloc * n; idx += BWD_BLOCK) {
-        const int lt = idx / n;
-        const double sg = A.sigma[u0 * n + idx];
-        const double m = A.mu ? A.mu[u0 * n + idx] : 0.0;
-        if (!isfinite(sg) || !isfinite(m) || !(sg >= 0.0)) atomicOr(&s_flag[lt], LEB_FLAG_BAD_INPUT);
-        double l = m - sg, h = m + sg;
-        l = l - fabs(l) * 0x1p-52;
-        h = h + fabs(h) * 0x1p-52;
-        s_d[idx] = iv(rd32(fmin(l, 0.0)), ru32(fmax(h, 0.0)));
-    }
-    __syncthreads();
-
-    const int lt = tid / U;
-    const int i = tid - lt * U;
-    const bool active = (lt < nloc);
-    const double* nom = s_nom + lt * n;
-    const IV<float>* D = s_d + lt * n;
+    if (active && (node_flags(d) & LEB_FLAG_BAD_INPUT)) atomicOr(&s_flag[copy][lt], LEB_FLAG_BAD_INPUT);
     const double K3 = 3.0 * A.kL * A.c, K15 = 1.5 * A.kL * A.c, K1 = A.kL * A.c, K05 = 0.5 * A.kL * A.c;
-    const bool bad = active && (s_flag[lt] & LEB_FLAG_BAD_INPUT);
 
     // ---- 1. spring i primal
     IV<float> R[5];
@@ -144,46 +165,49 @@ __global__ void __launch_bounds__(BWD_BLOCK) pbh_chain_bwd(BwdArgs A) {
     for (int q = 0; q < 5; ++q) R[q] = iv(0.0f, 0.0f);
     bool spring_ok = false;
     SpringSetup st;
-    if (active && i < U - 1) {
-        spring_setup(nom, D, i, A.L0, st);
+    if (right) {
+        spring_setup_v(d.zs[0], d.zs[1], d.zj[0], d.zj[1], Dx, Dz, disp_interval(d.mj[0], d.sj[0]),
+                       disp_interval(d.mj[1], d.sj[1]), A.L0, st);
         AccPrimal acc;
-        SpringPieces<float> pc;
-        spring_ok = spring_core<float, AccPrimal>(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj,
-                                                  st.Dzj, 1.0, 1.0, 1.0, 1.0, K3, K15, K1, K05, acc, pc);
-        BSpring o;
+        SpringPieces pc;
+        spring_ok = spring_core(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj, st.Dzj, 1.0, 1.0, 1.0,
+                                1.0, K3, K15, K1, K05, acc, pc);
+        BwdPass& o = s_pass[copy][ln];
 #pragma unroll
-        for (int q = 0; q < 5; ++q) { o.L[q] = spring_ok ? pc.L[q] : iv(0.0f, 0.0f); R[q] = spring_ok ? pc.R[q] : iv(0.0f, 0.0f); }
-        o.unbounded = spring_ok ? 0u : 1u;
-        o.pad_ = 0;
-        s_sp[lt * U + i] = o;
+        for (int q = 0; q < 5; ++q) {
+            o.piece.L[q] = spring_ok ? pc.L[q] : iv(0.0f, 0.0f);
+            R[q] = spring_ok ? pc.R[q] : iv(0.0f, 0.0f);
+        }
+        o.piece.unbounded = spring_ok ? 0u : 1u;
     }
     __syncthreads();
 
     // ---- 2. node i primal + reverse
+    const bool bad = active && (s_flag[copy][lt] & LEB_FLAG_BAD_INPUT);
+    uint32_t row_unb = (right && !spring_ok) ? 1u : 0u;
     PieceAdj rbar;
 #pragma unroll
     for (int q = 0; q < 5; ++q) { rbar.lo[q] = 0.0; rbar.hi[q] = 0.0; }
+    NodeGrad ng = {};
     if (active) {
-        const int th = 6 * i + 2, pxc = 6 * i, pzc = 6 * i + 1;
-        const int u1 = nx + 2 * i, u2 = u1 + 1;
         IV<float> L[5];
 #pragma unroll
         for (int q = 0; q < 5; ++q) L[q] = iv(0.0f, 0.0f);
-        uint32_t row_unb = (i < U - 1 && !spring_ok) ? 1u : 0u;
         if (i > 0) {
-            const BSpring& o = s_sp[lt * U + i - 1];
-            row_unb |= o.unbounded;
+            const BwdPass& o = s_pass[copy][ln - 1];
+            row_unb |= o.piece.unbounded;
 #pragma unroll
-            for (int q = 0; q < 5; ++q) L[q] = o.L[q];
+            for (int q = 0; q < 5; ++q) L[q] = o.piece.L[q];
         }
-        s_unb[lt * U + i] = row_unb;
-        RowAdj g = s_g[lt * U + i];
+        s_unb[copy][ln] = row_unb;
+        RowAdj g = gi;
         if (row_unb || bad) { g.xlo = g.xhi = g.zlo = g.zhi = 0.0; }
         const bool own = U > 1 && !row_unb;
         NodeTerms nt;
-        const IV<float> Dth = D[th], Du1 = D[u1], Du2 = D[u2], Dx = D[pxc], Dz = D[pzc];
-        const double sn = nom[u1] + nom[u2];
-        node_terms(nom[th], sn, Dth, Du1, Du2, Dx, Dz, R, L, own, A.c, K15, K1, K05, 1.0, 1.0, 1.0, 1.0, 1.0, nt);
+        const IV<float> Dth = disp_interval(d.ms[2], d.ss[2]), Du1 = disp_interval(d.ms[6], d.ss[6]),
+                        Du2 = disp_interval(d.ms[7], d.ss[7]);
+        const double thn = d.zs[2], sn = d.vs[0] + d.vs[1];
+        node_terms(thn, sn, Dth, Du1, Du2, Dx, Dz, R, L, own, A.c, K15, K1, K05, 1.0, 1.0, 1.0, 1.0, 1.0, nt);
         // term adjoints
         double tlo[12], thi[12];
         double sbar = 0.0;
@@ -202,7 +226,6 @@ __global__ void __launch_bounds__(BWD_BLOCK) pbh_chain_bwd(BwdArgs A) {
                 sbar += dk * (alo * (double)a + ahi * (double)b);
             }
         }
-        NodeGrad ng = {};
         ng.s = sbar;
         double Sb_lo = 0, Sb_hi = 0, Cb_lo = 0, Cb_hi = 0;
         double Ptt_lo = 0, Ptt_hi = 0, Pu1_lo = 0, Pu1_hi = 0, Pu2_lo = 0, Pu2_hi = 0;
@@ -218,18 +241,30 @@ __global__ void __launch_bounds__(BWD_BLOCK) pbh_chain_bwd(BwdArgs A) {
         bwd_mul_z(Dth, Du1, Pu1_lo, Pu1_hi, &ng.dth[0], &ng.dth[1], &ng.du1[0], &ng.du1[1]);
         bwd_mul_z(Dth, Du2, Pu2_lo, Pu2_hi, &ng.dth[0], &ng.dth[1], &ng.du2[0], &ng.du2[1]);
         // sin / cos bounds -> Theta endpoints -> nominal theta and Dth
-        const double a64 = nom[th] + (double)Dth.lo, b64 = nom[th] + (double)Dth.hi;
+        const double a64 = thn + (double)Dth.lo, b64 = thn + (double)Dth.hi;
         double Th_lo = 0.0, Th_hi = 0.0;
         {
             const SinCos& sc = nt.sc;
-            const double dslo = sc_deriv(sc, true, sc.s_lo, a64, b64, false);
-            const double dshi = sc_deriv(sc, true, sc.s_hi, a64, b64, true);
-            const double dclo = sc_deriv(sc, false, sc.c_lo, a64, b64, false);
-            const double dchi = sc_deriv(sc, false, sc.c_hi, a64, b64, true);
-            if (sc.s_lo == 0) Th_lo += Sb_lo * dslo; else if (sc.s_lo == 1) Th_hi += Sb_lo * dslo;
-            if (sc.s_hi == 0) Th_lo += Sb_hi * dshi; else if (sc.s_hi == 1) Th_hi += Sb_hi * dshi;
-            if (sc.c_lo == 0) Th_lo += Cb_lo * dclo; else if (sc.c_lo == 1) Th_hi += Cb_lo * dclo;
-            if (sc.c_hi == 0) Th_lo += Cb_hi * dchi; else if (sc.c_hi == 1) Th_hi += Cb_hi * dchi;
+            // sine and cosine at both ends; the derivative of an end's selected value, 0
+            // when the bound is a clamped extremum (selection 2)
+            double sa, ca, sb, cb;
+            if (sc.wide) {
+                sincos(a64, &sa, &ca);
+                sincos(b64, &sb, &cb);
+            } else {
+                sa = (double)sin_poly(sc.fa); ca = (double)cos_poly(sc.fa);
+                sb = (double)sin_poly(sc.fb); cb = (double)cos_poly(sc.fb);
+            }
+            const double dslo = sc.s_lo == 0 ? ca : cb, dshi = sc.s_hi == 0 ? ca : cb;
+            const double dclo = sc.c_lo == 0 ? -sa : -sb, dchi = sc.c_hi == 0 ? -sa : -sb;
+            auto ends = [&](int sel, double x) {
+                Th_lo += sel == 0 ? x : 0.0;
+                Th_hi += sel == 1 ? x : 0.0;
+            };
+            ends(sc.s_lo, Sb_lo * dslo);
+            ends(sc.s_hi, Sb_hi * dshi);
+            ends(sc.c_lo, Cb_lo * dclo);
+            ends(sc.c_hi, Cb_hi * dchi);
         }
         ng.th = Th_lo + Th_hi;
         ng.dth[0] += Th_lo;
@@ -257,134 +292,109 @@ __global__ void __launch_bounds__(BWD_BLOCK) pbh_chain_bwd(BwdArgs A) {
                 lbar.hi[q] = -Gb_lo[q]; lbar.lo[q] = -Gb_hi[q];
             }
         }
-        if (i > 0) s_lbar[lt * U + i - 1] = lbar;
-        s_gn[lt * U + i] = ng;
+        if (i > 0) s_pass[copy][ln - 1].adj = lbar;
     }
     __syncthreads();
 
     // ---- 3. spring i tangent passes
-    if (active && spring_ok) {
-        const RowAdj gi0 = s_g[lt * U + i], gj0 = s_g[lt * U + i + 1];
-        const bool ui = bad || s_unb[lt * U + i], uj = bad || s_unb[lt * U + i + 1];
-        const double xli = ui ? 0.0 : gi0.xlo, xhi_ = ui ? 0.0 : gi0.xhi, zli = ui ? 0.0 : gi0.zlo, zhi_ = ui ? 0.0 : gi0.zhi;
-        const double xlj = uj ? 0.0 : gj0.xlo, xhj = uj ? 0.0 : gj0.xhi, zlj = uj ? 0.0 : gj0.zlo, zhj = uj ? 0.0 : gj0.zhi;
-        const PieceAdj lb = s_lbar[lt * U + i];
+    double sg[2 * BWD_TASKS];            // dxn, dzn, Dxi lo/hi, Dzi lo/hi, Dxj lo/hi, Dzj lo/hi
+#pragma unroll
+    for (int q = 0; q < 2 * BWD_TASKS; ++q) sg[q] = 0.0;
+    if (right && spring_ok) {
+        const PieceAdj lb = s_pass[copy][ln].adj;
+        if (bad || row_unb) gi = RowAdj{0.0, 0.0, 0.0, 0.0};
+        if (bad || s_unb[copy][ln + 1]) gj = RowAdj{0.0, 0.0, 0.0, 0.0};
         AccTangent acc;
         // slot adjoints: row i takes C + B, row i+1 takes -(C + A)
-        acc.alo[S_CX] = xli - xhj; acc.ahi[S_CX] = xhi_ - xlj;
-        acc.alo[S_CZ] = zli - zhj; acc.ahi[S_CZ] = zhi_ - zlj;
-        acc.alo[S_BX] = xli;       acc.ahi[S_BX] = xhi_;
-        acc.alo[S_BZ] = zli;       acc.ahi[S_BZ] = zhi_;
-        acc.alo[S_AX] = -xhj;      acc.ahi[S_AX] = -xlj;
-        acc.alo[S_AZ] = -zhj;      acc.ahi[S_AZ] = -zlj;
-        SpringGrad sgr;
-        for (int dir = 0; dir < 10; ++dir) {
-            // tangents of the spring inputs for this direction
-            const float tdx = dir == 0, tdz = dir == 1;
-            const float txil = dir == 2, txih = dir == 3, tzil = dir == 4, tzih = dir == 5;
-            const float txjl = dir == 6, txjh = dir == 7, tzjl = dir == 8, tzjh = dir == 9;
-            const IV<DF> dxA = iv(dfm(st.dxA.lo, tdx - txih), dfm(st.dxA.hi, tdx - txil));
-            const IV<DF> dxB = iv(dfm(st.dxB.lo, tdx + txjl - txih), dfm(st.dxB.hi, tdx + txjh - txil));
-            const IV<DF> dz0 = iv(dfm(st.dz0.lo, tdz), dfm(st.dz0.hi, tdz));
-            const IV<DF> dz1 = iv(dfm(st.dz1.lo, tdz - tzih), dfm(st.dz1.hi, tdz - tzil));
-            const IV<DF> dz2 = iv(dfm(st.dz2.lo, tdz + tzjl - tzih), dfm(st.dz2.hi, tdz + tzjh - tzil));
-            const IV<DF> Dxi = iv(dfm(st.Dxi.lo, txil), dfm(st.Dxi.hi, txih));
-            const IV<DF> Dzi = iv(dfm(st.Dzi.lo, tzil), dfm(st.Dzi.hi, tzih));
-            const IV<DF> Dxj = iv(dfm(st.Dxj.lo, txjl), dfm(st.Dxj.hi, txjh));
-            const IV<DF> Dzj = iv(dfm(st.Dzj.lo, tzjl), dfm(st.Dzj.hi, tzjh));
-            acc.g = 0.0;
-            SpringPieces<DF> pc;
-            spring_core<DF, AccTangent>(dxA, dxB, dz0, dz1, dz2, Dxi, Dzi, Dxj, Dzj, 1.0, 1.0, 1.0, 1.0, K3, K15, K1,
-                                        K05, acc, pc);
-            double g = acc.g;
-#pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                g += rbar.lo[q] * (double)pc.R[q].lo.d + rbar.hi[q] * (double)pc.R[q].hi.d;
-                g += lb.lo[q] * (double)pc.L[q].lo.d + lb.hi[q] * (double)pc.L[q].hi.d;
-            }
-            sgr.d[dir] = g;
-        }
-        s_gs[lt * U + i] = sgr;
-    } else if (active && i < U - 1) {
-        SpringGrad z = {};
-        s_gs[lt * U + i] = z;
+        acc.alo[S_CX] = gi.xlo - gj.xhi; acc.ahi[S_CX] = gi.xhi - gj.xlo;
+        acc.alo[S_CZ] = gi.zlo - gj.zhi; acc.ahi[S_CZ] = gi.zhi - gj.zlo;
+        acc.alo[S_BX] = gi.xlo;          acc.ahi[S_BX] = gi.xhi;
+        acc.alo[S_BZ] = gi.zlo;          acc.ahi[S_BZ] = gi.zhi;
+        acc.alo[S_AX] = -gj.xhi;         acc.ahi[S_AX] = -gj.xlo;
+        acc.alo[S_AZ] = -gj.zhi;         acc.ahi[S_AZ] = -gj.zlo;
+        acc.rlo = rbar.lo; acc.rhi = rbar.hi; acc.llo = lb.lo; acc.lhi = lb.hi;
+        auto run = [&](auto task) {
+            constexpr int Q = decltype(task)::value;
+            if (SPLIT && wave != Q) return;
+            bwd_task<Q>(st, K3, K15, K1, K05, acc);
+            if (SPLIT) { s_grad[ln][2 * Q] = acc.g; s_grad[ln][2 * Q + 1] = acc.h; }
+            else { sg[2 * Q] = acc.g; sg[2 * Q + 1] = acc.h; }
+        };
+        run(std::integral_constant<int, 0>()); run(std::integral_constant<int, 1>());
+        run(std::integral_constant<int, 2>()); run(std::integral_constant<int, 3>());
+        run(std::integral_constant<int, 4>());
+    } else if (SPLIT && active) {
+        s_grad[ln][2 * wave] = 0.0;
+        s_grad[ln][2 * wave + 1] = 0.0;
     }
-    __syncthreads();
+    if (SPLIT) {
+        __syncthreads();
+        if (wave > 0) return;            // the first wave adds up
+        if (active) {
+#pragma unroll
+            for (int q = 0; q < 2 * BWD_TASKS; ++q) sg[q] = s_grad[ln][q];
+        }
+    } else {
+        if (right) {
+            double* o = s_pass[0][ln].next;
+            o[0] = sg[0]; o[1] = sg[1];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[2 + q] = sg[6 + q];
+        }
+        __syncthreads();
+    }
+    if (!active) return;
 
     // ---- 4. per-coordinate sums (fixed order) and the box chain rule
-    for (int idx = tid; idx < nloc * n; idx += BWD_BLOCK) {
-        const int t = idx / n, c = idx - t * n;
-        const bool tbad = s_flag[t] & LEB_FLAG_BAD_INPUT;
-        double gnom = 0.0, glo = 0.0, ghi = 0.0;
-        if (!tbad) {
-            if (c < nx) {
-                const int m = c / 6, rc = c - 6 * m;
-                if (rc == 0 || rc == 1) {
-                    const NodeGrad& ng = s_gn[t * U + m];
-                    glo = rc == 0 ? ng.dx[0] : ng.dz[0];
-                    ghi = rc == 0 ? ng.dx[1] : ng.dz[1];
-                    if (m < U - 1) {        // spring m: node m is its first node
-                        const SpringGrad& sg = s_gs[t * U + m];
-                        gnom -= sg.d[rc];
-                        glo += sg.d[rc == 0 ? 2 : 4];
-                        ghi += sg.d[rc == 0 ? 3 : 5];
-                    }
-                    if (m > 0) {            // spring m-1: node m is its second node
-                        const SpringGrad& sg = s_gs[t * U + m - 1];
-                        gnom += sg.d[rc];
-                        glo += sg.d[rc == 0 ? 6 : 8];
-                        ghi += sg.d[rc == 0 ? 7 : 9];
-                    }
-                } else if (rc == 2) {
-                    const NodeGrad& ng = s_gn[t * U + m];
-                    gnom = ng.th; glo = ng.dth[0]; ghi = ng.dth[1];
-                }
-            } else {
-                const int m = (c - nx) / 2, a = (c - nx) & 1;
-                const NodeGrad& ng = s_gn[t * U + m];
-                gnom = ng.s;
-                glo = a == 0 ? ng.du1[0] : ng.du2[0];
-                ghi = a == 0 ? ng.du1[1] : ng.du2[1];
-            }
-        }
-        const int64_t o = u0 * n + idx;
-        const double sg = A.sigma[o];
-        const double mu = A.mu ? A.mu[o] : 0.0;
+    double lf[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};             // spring i-1: node i is its second node
+    if (i > 0) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+            lf[q] = SPLIT ? s_grad[ln - 1][q < 2 ? q : q + 4] : s_pass[0][ln - 1].next[q];
+    }
+    const double gnom[8] = {lf[0] - sg[0], lf[1] - sg[1], ng.th, 0.0, 0.0, 0.0, ng.s, ng.s};
+    const double glo[8] = {ng.dx[0] + sg[2] + lf[2], ng.dz[0] + sg[4] + lf[4], ng.dth[0], 0.0, 0.0, 0.0, ng.du1[0],
+                           ng.du2[0]};
+    const double ghi[8] = {ng.dx[1] + sg[3] + lf[3], ng.dz[1] + sg[5] + lf[5], ng.dth[1], 0.0, 0.0, 0.0, ng.du1[1],
+                           ng.du2[1]};
+    const int64_t u = u0 + lt;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const int64_t o = u * n + (c < 6 ? 6 * i + c : nx + 2 * i + c - 6);
+        const double sgm = d.ss[c], mu = d.ms[c];
         // Delta_lo = min(mu - sigma, 0), Delta_hi = max(mu + sigma, 0); first candidate on a tie
-        const double alo = (mu - sg <= 0.0) ? glo : 0.0;
-        const double ahi = (mu + sg >= 0.0) ? ghi : 0.0;
+        const double alo = !bad && (mu - sgm <= 0.0) ? glo[c] : 0.0;
+        const double ahi = !bad && (mu + sgm >= 0.0) ? ghi[c] : 0.0;
         A.gsigma[o] = ahi - alo;
         if (A.gmu) A.gmu[o] = alo + ahi;
-        if (c < nx) A.gz[(u0 + t) * nx + c] = gnom;
-        else A.gv[(u0 + t) * nu + (c - nx)] = gnom;
+        const double gn = bad ? 0.0 : gnom[c];
+        if (c < 6) A.gz[u * nx + 6 * i + c] = gn;
+        else A.gv[u * nu + 2 * i + c - 6] = gn;
     }
-}
-
-size_t bwd_smem_bytes(int U) {
-    const int T = BWD_BLOCK / U, n = 8 * U;
-    const size_t region = (size_t)T * U * (sizeof(BSpring) > sizeof(SpringGrad) ? sizeof(BSpring) : sizeof(SpringGrad));
-    return (size_t)T * n * (sizeof(double) + sizeof(IV<float>)) + (size_t)T * U * sizeof(RowAdj) + region +
-           (size_t)T * U * (sizeof(PieceAdj) + sizeof(NodeGrad) + sizeof(uint32_t)) + (size_t)T * sizeof(uint32_t) + 16;
 }
 
 int launch_pbh_bwd(const leb_dynamics* dyn, int64_t units, const double* z, const double* v, const double* mu,
                    const double* sigma, const double* g_lo, const double* g_hi, double* gz, double* gv,
                    double* gmu, double* gsigma, hipStream_t stream) {
-    if (dyn->n_units > BWD_BLOCK) return LEB_ENOTSUP;
+    if (dyn->n_units > BWD_MAX_U) return LEB_ENOTSUP;
     BwdArgs a;
     a.z = z; a.v = v; a.mu = mu; a.sigma = sigma; a.g_lo = g_lo; a.g_hi = g_hi;
     a.gz = gz; a.gv = gv; a.gmu = gmu; a.gsigma = gsigma;
     a.units = units;
     a.U = dyn->n_units;
-    a.T = BWD_BLOCK / a.U;
     a.c = dyn->dt / dyn->m;
     a.kL = dyn->k_spring * dyn->rest_len;
     a.L0 = dyn->rest_len;
+    // the split form while every workgroup has a compute unit of its own (28 nodes, whole
+    // call: 320 units 16.7 us, unsplit 26.0; 640 units 29.8 and 26.6); chains of more than 64
+    // nodes do not fit its lanes
+    const int ts = a.U <= 64 ? 64 / a.U : 0;
+    const bool split = ts > 0 && (units + ts - 1) / ts <= BWD_SPLIT_BLOCKS;
+    a.T = split ? ts : BWD_BLOCK / a.U;
     const int64_t blocks = (units + a.T - 1) / a.T;
     if (blocks > 0x7fffffff) return LEB_EINVAL;
-    const size_t smem = bwd_smem_bytes(a.U);
-    if (smem > 65536) return LEB_ENOTSUP;
-    hipLaunchKernelGGL(pbh_chain_bwd, dim3((unsigned)blocks), dim3(BWD_BLOCK), smem, stream, a);
+    if (split) hipLaunchKernelGGL(pbh_chain_bwd<true>, dim3((unsigned)blocks), dim3(64 * BWD_TASKS), 0, stream, a);
+    else hipLaunchKernelGGL(pbh_chain_bwd<false>, dim3((unsigned)blocks), dim3(BWD_BLOCK), 0, stream, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 

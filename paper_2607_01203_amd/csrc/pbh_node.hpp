@@ -112,8 +112,8 @@ __device__ __forceinline__ void spring_step(const NodeConsts& K, const NodeIn& d
     spring_setup_v(d.zs[0], d.zs[1], d.zj[0], d.zj[1], k.Dx, k.Dz, disp_interval(d.mj[0], d.sj[0]),
                    disp_interval(d.mj[1], d.sj[1]), K.L0, st);
     AccPrimal acc;
-    SpringPieces<float> pc;
-    const bool ok = spring_core<float, AccPrimal>(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj,
+    SpringPieces pc;
+    const bool ok = spring_core(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj,
                                                   st.Dzj, maskv(st.Dxi), maskv(st.Dzi), maskv(st.Dxj),
                                                   maskv(st.Dzj), K.K3, K.K15, K.K1, K.K05, acc, pc);
     SpringOut o = {};

@@ -20,12 +20,15 @@
 
 #include "leb.h"
 #include "leb_internal.hpp"
+#include "pbh_node.hpp"
 
 namespace leb {
 
 int launch_pbh_bwd(const leb_dynamics* dyn, int64_t units, const double* z, const double* v, const double* mu,
                    const double* sigma, const double* g_lo, const double* g_hi, double* gz, double* gv,
                    double* gmu, double* gsigma, hipStream_t stream);
+
+constexpr int PGD_MAX_ROWS = 512;        // 2 rows a node, up to 256 nodes
 
 struct PgdBufs {
     double *z, *v, *mu, *lo, *hi, *glo, *ghi, *gz, *gv, *gmu, *gsg, *best;
@@ -46,43 +49,60 @@ __global__ void pgd_init_kernel(const double* z0, const double* v0, const double
     if (i == 0) B.best[u] = INFINITY;
 }
 
-// width of every unit's bound; keep the narrowest iterate (one thread per unit)
-__global__ void pgd_width_kernel(PgdBufs B, double* zo, double* vo, double* width, double* width0, int64_t units,
-                                 int nx, int nu, int first) {
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One step of a unit, by one wave: the width of the bound at a~ (the narrowest
+// iterate is kept), then, unless it is the last one,
+//   a~ <- clamp(a~ - step sign(dW/da~), a0 +/- radius sigma); for the fixed box mu = a0 + mu0 - a~.
+// Bound by its launch and the sum's serial chain (28 nodes, 40 units: 5.6 us; one thread a unit for the width and
+// one a coordinate for the move, in two launches: 56 and 7 us).
+__global__ void __launch_bounds__(256) pgd_step_kernel(const double* z0, const double* v0, const double* mu0,
+                                                       const double* sigma, PgdBufs B, double* zo, double* vo,
+                                                       double* width, double* width0, int64_t units, int nx, int nu,
+                                                       double radius, double frac, int fixed_box, int first, int last) {
+    const int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (u >= units) return;
-    double w = 0.0;
-    for (int l = 0; l < nx; ++l) w += B.hi[u * nx + l] - B.lo[u * nx + l];
-    if (first && width0) width0[u] = w;
-    if (w < B.best[u]) {
-        B.best[u] = w;
-        for (int i = 0; i < nx; ++i) zo[u * nx + i] = B.z[u * nx + i];
-        for (int i = 0; i < nu; ++i) vo[u * nu + i] = B.v[u * nu + i];
+    const int lane = threadIdx.x & 63, n = nx + nu, rows = nx / 3;
+    // the vx and vz rows' widths, summed in row order (the affine rows are [0, 0], or
+    // [-inf, inf] together with these)
+    __shared__ double s_w[4][PGD_MAX_ROWS];
+    double* d = s_w[threadIdx.x >> 6];
+    for (int q = lane; q < rows; q += 64) {
+        const int64_t o = u * nx + 6 * (q >> 1) + 3 + (q & 1);
+        d[q] = B.hi[o] - B.lo[o];
     }
-    if (width) width[u] = B.best[u];
-}
-
-// a~ <- clamp(a~ - step sign(dW/da~), a0 +/- radius sigma); for the fixed box mu = a0 + mu0 - a~
-// (one thread per coordinate)
-__global__ void pgd_update_kernel(const double* z0, const double* v0, const double* mu0, const double* sigma,
-                                  PgdBufs B, int64_t units, int nx, int nu, double radius, double frac,
-                                  int fixed_box) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = nx + nu;
-    if (q >= units * n) return;
-    const int64_t u = q / n;
-    const int i = (int)(q - u * n);
-    const double a0 = i < nx ? z0[u * nx + i] : v0[u * nu + (i - nx)];
-    double* ap = i < nx ? &B.z[u * nx + i] : &B.v[u * nu + (i - nx)];
-    double g = i < nx ? B.gz[u * nx + i] : B.gv[u * nu + (i - nx)];
-    if (fixed_box) g -= B.gmu[q];
-    const double r = radius * sigma[q];
-    double a = *ap;
-    if (g > 0.0) a -= frac * r;
-    else if (g < 0.0) a += frac * r;
-    a = fmin(fmax(a, a0 - r), a0 + r);
-    *ap = a;
-    if (fixed_box) B.mu[q] = a0 + (mu0 ? mu0[q] : 0.0) - a;
+    wave_lds_fence();
+    double w = 0.0;
+    int q = 0;
+    for (; q + 8 <= rows; q += 8) {
+        double x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = d[q + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w += x[e];
+    }
+    for (; q < rows; ++q) w += d[q];
+    const double best = B.best[u];
+    const bool better = w < best;
+    if (lane == 0) {
+        if (first && width0) width0[u] = w;
+        if (better) B.best[u] = w;
+        if (last) width[u] = better ? w : best;
+    }
+    for (int i = lane; i < n; i += 64) {
+        const bool st = i < nx;
+        double* ap = st ? &B.z[u * nx + i] : &B.v[u * nu + (i - nx)];
+        double a = *ap;
+        if (better) { if (st) zo[u * nx + i] = a; else vo[u * nu + (i - nx)] = a; }
+        if (last) continue;
+        const double a0 = st ? z0[u * nx + i] : v0[u * nu + (i - nx)];
+        double g = st ? B.gz[u * nx + i] : B.gv[u * nu + (i - nx)];
+        if (fixed_box) g -= B.gmu[u * n + i];
+        const double r = radius * sigma[u * n + i];
+        if (g > 0.0) a -= frac * r;
+        else if (g < 0.0) a += frac * r;
+        a = fmin(fmax(a, a0 - r), a0 + r);
+        *ap = a;
+        if (fixed_box) B.mu[u * n + i] = a0 + (mu0 ? mu0[u * n + i] : 0.0) - a;
+    }
 }
 
 struct PgdWorkspace {
@@ -134,20 +154,17 @@ extern "C" int leb_pgd_nominal(const leb_dynamics* dyn, int32_t batch, int32_t N
     B.gv = take(units * nu); B.gmu = take(units * n); B.gsg = take(units * n); B.best = take(units);
     if ((rc = g_pgd.fence.enter(s))) return rc;
     WsFenceScope leave{g_pgd.fence, s};
-    const unsigned gc = (unsigned)((units * n + 255) / 256), gu = (unsigned)((units + 255) / 256);
+    const unsigned gc = (unsigned)((units * n + 255) / 256), gu = (unsigned)((units + 3) / 4);
     hipLaunchKernelGGL(pgd_init_kernel, dim3(gc), dim3(256), 0, s, z0, v0, mu0, B, z, v, units, nx, nu);
-    for (int st = 0;; ++st) {
+    for (int st = 0; st <= steps; ++st) {
         if ((rc = launch_pbh_chain(dyn, units, B.z, B.v, B.mu, sigma, B.lo, B.hi, nullptr, nullptr, 0.0, nullptr, s)))
             return rc;
-        hipLaunchKernelGGL(pgd_width_kernel, dim3(gu), dim3(256), 0, s, B, z, v, st == steps ? width : nullptr,
-                           st == 0 ? width0 : nullptr, units, nx, nu, st == 0 ? 1 : 0);
-        if (st == steps) break;
-        if ((rc = launch_pbh_bwd(dyn, units, B.z, B.v, B.mu, sigma, B.glo, B.ghi, B.gz, B.gv,
-                                 fixed_box ? B.gmu : nullptr, B.gsg, s)))
+        if (st < steps && (rc = launch_pbh_bwd(dyn, units, B.z, B.v, B.mu, sigma, B.glo, B.ghi, B.gz, B.gv,
+                                               fixed_box ? B.gmu : nullptr, B.gsg, s)))
             return rc;
-        const double frac = lr * (1.0 - (double)st / steps);
-        hipLaunchKernelGGL(pgd_update_kernel, dim3(gc), dim3(256), 0, s, z0, v0, mu0, sigma, B, units, nx, nu,
-                           radius, frac, fixed_box);
+        const double frac = st < steps ? lr * (1.0 - (double)st / steps) : 0.0;
+        hipLaunchKernelGGL(pgd_step_kernel, dim3(gu), dim3(256), 0, s, z0, v0, mu0, sigma, B, z, v, width, width0, units,
+                           nx, nu, radius, frac, fixed_box, st == 0 ? 1 : 0, st == steps ? 1 : 0);
     }
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }

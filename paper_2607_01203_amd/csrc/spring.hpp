@@ -29,40 +29,42 @@ namespace leb {
 
 enum { S_CX = 0, S_CZ = 1, S_BX = 2, S_BZ = 3, S_AX = 4, S_AZ = 5 };
 
-template <class F> struct SpringPieces {
-    IV<F> R[5];   // Txxx V1, Txxz V1, Txzz V1, Txzz V2, Tzzz V2
-    IV<F> L[5];   // Txxx V3, Txxz V3, Txzz V3, Txzz V4, Tzzz V4
-};
-
-template <class F, class Acc>
-__device__ __forceinline__ bool spring_core(IV<F> dxA, IV<F> dxB, IV<F> dz0, IV<F> dz1, IV<F> dz2,
-                                            IV<F> Dxi, IV<F> Dzi, IV<F> Dxj, IV<F> Dzj,
+// The pieces leave through out.right(q, T) / out.left(q, T), q = 0 .. 4:
+//   right: Txxx V1, Txxz V1, Txzz V1, Txzz V2, Tzzz V2
+//   left:  Txxx V3, Txxz V3, Txzz V3, Txzz V4, Tzzz V4
+template <class XA, class XB, class Z0, class Z1, class Z2, class PXI, class PZI, class PXJ, class PZJ, class Acc,
+          class Out>
+__device__ __forceinline__ bool spring_core(IV<XA> dxA, IV<XB> dxB, IV<Z0> dz0, IV<Z1> dz1, IV<Z2> dz2,
+                                            IV<PXI> Dxi, IV<PZI> Dzi, IV<PXJ> Dxj, IV<PZJ> Dzj,
                                             double mxi, double mzi, double mxj, double mzj,
                                             double K3, double K15, double K1, double K05,
-                                            Acc& acc, SpringPieces<F>& out) {
-    const IV<F> aA = t_sq(dxA), aB = t_sq(dxB), b0 = t_sq(dz0), b1 = t_sq(dz1), b2 = t_sq(dz2);
-    const IV<F> s1 = t_add(aA, b0), s2 = t_add(aA, b1), s3 = t_add(aB, b1), s4 = t_add(aB, b2);
+                                            Acc& acc, Out& out) {
+    const auto aA = t_sq(dxA); const auto aB = t_sq(dxB);
+    const auto b0 = t_sq(dz0); const auto b1 = t_sq(dz1); const auto b2 = t_sq(dz2);
+    const auto s1 = t_add(aA, b0); const auto s2 = t_add(aA, b1);
+    const auto s3 = t_add(aB, b1); const auto s4 = t_add(aB, b2);
     const float smin = fminf(fminf(val(s1.lo), val(s2.lo)), fminf(val(s3.lo), val(s4.lo)));
     if (!(smin >= 0x1p-40f)) return false;
-    const IV<F> q1 = t_rcp_pos(t_mul_nn(t_mul_nn(s1, s1), t_sqrt_pos(s1)));
-    const IV<F> q2 = t_rcp_pos(t_mul_nn(t_mul_nn(s2, s2), t_sqrt_pos(s2)));
-    const IV<F> q3 = t_rcp_pos(t_mul_nn(t_mul_nn(s3, s3), t_sqrt_pos(s3)));
-    const IV<F> q4 = t_rcp_pos(t_mul_nn(t_mul_nn(s4, s4), t_sqrt_pos(s4)));
-    const IV<F> Txxx1 = t_mul_nonneg(dxA, t_mul_nn(b0, q1));
-    const IV<F> Txxz1 = t_mul(dz0, t_mul_nonneg(t_twoa_minus_b(aA, b0), q1));
-    const IV<F> Txzz1 = t_mul(dxA, t_mul_nonneg(t_a_minus_twob(aA, b0), q1));
-    const IV<F> Txxz2 = t_mul(dz1, t_mul_nonneg(t_twoa_minus_b(aA, b1), q2));
-    const IV<F> Txzz2 = t_mul(dxA, t_mul_nonneg(t_a_minus_twob(aA, b1), q2));
-    const IV<F> Tzzz2 = t_mul_nonneg(dz1, t_mul_nn(aA, q2));
-    const IV<F> Txxx3 = t_mul_nonneg(dxB, t_mul_nn(b1, q3));
-    const IV<F> Txxz3 = t_mul(dz1, t_mul_nonneg(t_twoa_minus_b(aB, b1), q3));
-    const IV<F> Txzz3 = t_mul(dxB, t_mul_nonneg(t_a_minus_twob(aB, b1), q3));
-    const IV<F> Txzz4 = t_mul(dxB, t_mul_nonneg(t_a_minus_twob(aB, b2), q4));
-    const IV<F> Tzzz4 = t_mul_nonneg(dz2, t_mul_nn(aB, q4));
+    const auto q1 = t_rcp_pos(t_mul_nn(t_mul_nn(s1, s1), t_sqrt_pos(s1)));
+    const auto q2 = t_rcp_pos(t_mul_nn(t_mul_nn(s2, s2), t_sqrt_pos(s2)));
+    const auto q3 = t_rcp_pos(t_mul_nn(t_mul_nn(s3, s3), t_sqrt_pos(s3)));
+    const auto q4 = t_rcp_pos(t_mul_nn(t_mul_nn(s4, s4), t_sqrt_pos(s4)));
+    const auto Txxx1 = t_mul_nonneg(dxA, t_mul_nn(b0, q1));
+    const auto Txxz1 = t_mul(dz0, t_mul_nonneg(t_twoa_minus_b(aA, b0), q1));
+    const auto Txzz1 = t_mul(dxA, t_mul_nonneg(t_a_minus_twob(aA, b0), q1));
+    const auto Txxz2 = t_mul(dz1, t_mul_nonneg(t_twoa_minus_b(aA, b1), q2));
+    const auto Txzz2 = t_mul(dxA, t_mul_nonneg(t_a_minus_twob(aA, b1), q2));
+    const auto Tzzz2 = t_mul_nonneg(dz1, t_mul_nn(aA, q2));
+    const auto Txxx3 = t_mul_nonneg(dxB, t_mul_nn(b1, q3));
+    const auto Txxz3 = t_mul(dz1, t_mul_nonneg(t_twoa_minus_b(aB, b1), q3));
+    const auto Txzz3 = t_mul(dxB, t_mul_nonneg(t_a_minus_twob(aB, b1), q3));
+    const auto Txzz4 = t_mul(dxB, t_mul_nonneg(t_a_minus_twob(aB, b2), q4));
+    const auto Tzzz4 = t_mul_nonneg(dz2, t_mul_nn(aB, q4));
     // displacement products (every factor contains 0)
-    const IV<F> C1 = t_mul_z(Dxi, Dxj), C2 = t_mul_z(Dxi, Dzj), C3 = t_mul_z(Dzi, Dxj), C4 = t_mul_z(Dzi, Dzj);
-    const IV<F> Pxxi = t_sq_z(Dxi), Pxzi = t_mul_z(Dxi, Dzi), Pzzi = t_sq_z(Dzi);
-    const IV<F> Pxxj = t_sq_z(Dxj), Pxzj = t_mul_z(Dxj, Dzj), Pzzj = t_sq_z(Dzj);
+    const auto C1 = t_mul_z(Dxi, Dxj); const auto C2 = t_mul_z(Dxi, Dzj);
+    const auto C3 = t_mul_z(Dzi, Dxj); const auto C4 = t_mul_z(Dzi, Dzj);
+    const auto Pxxi = t_sq_z(Dxi); const auto Pxzi = t_mul_z(Dxi, Dzi); const auto Pzzi = t_sq_z(Dzi);
+    const auto Pxxj = t_sq_z(Dxj); const auto Pxzj = t_mul_z(Dxj, Dzj); const auto Pzzj = t_sq_z(Dzj);
     // cross entries: +row i, -row i+1
     acc.neg(S_CX, -K3 * mxi * mxj, t_mul_z(Txxx1, C1));
     acc.pos(S_CX, K1 * mxi * mzj, t_mul_z(Txxz1, C2));
@@ -86,10 +88,16 @@ __device__ __forceinline__ bool spring_core(IV<F> dxA, IV<F> dxB, IV<F> dz0, IV<
     acc.neg(S_AZ, -K05 * mxi, t_mul_z(Txxz1, Pxxi));
     acc.pos(S_AZ, K1 * mxi * mzi, t_mul_z(Txzz1, Pxzi));
     acc.pos(S_AZ, K15 * mzi, t_mul_z(Tzzz2, Pzzi));
-    out.R[0] = Txxx1; out.R[1] = Txxz1; out.R[2] = Txzz1; out.R[3] = Txzz2; out.R[4] = Tzzz2;
-    out.L[0] = Txxx3; out.L[1] = Txxz3; out.L[2] = Txzz3; out.L[3] = Txzz4; out.L[4] = Tzzz4;
+    out.right(0, Txxx1); out.right(1, Txxz1); out.right(2, Txzz1); out.right(3, Txzz2); out.right(4, Tzzz2);
+    out.left(0, Txxx3); out.left(1, Txxz3); out.left(2, Txzz3); out.left(3, Txzz4); out.left(4, Tzzz4);
     return true;
 }
+
+struct SpringPieces {
+    IV<float> R[5], L[5];
+    __device__ __forceinline__ void right(int q, IV<float> t) { R[q] = t; }
+    __device__ __forceinline__ void left(int q, IV<float> t) { L[q] = t; }
+};
 
 // FP64 accumulation of the primal bound (kappa * T into [lo, hi])
 struct AccPrimal {
@@ -108,16 +116,25 @@ struct AccPrimal {
     }
 };
 
-// Tangent pass: d L = sum over terms of adj(slot) . kappa d T
+// Tangent pass in two directions: d L = sum over terms of adj(slot) . kappa d T,
+// and over the shared pieces of their adjoints; terms that the pass's inputs do
+// not reach have no tangents.
 struct AccTangent {
-    double alo[6], ahi[6];
-    double g;
-    __device__ __forceinline__ void pos(int s, double k, IV<DF> t) {
-        g += alo[s] * k * (double)t.lo.d + ahi[s] * k * (double)t.hi.d;
+    double alo[6], ahi[6];               // slot adjoints
+    const double *rlo, *rhi, *llo, *lhi; // piece adjoints, right and left [5]
+    double g, h;
+    __device__ __forceinline__ void pos(int, double, IV<float>) {}
+    __device__ __forceinline__ void neg(int, double, IV<float>) {}
+    __device__ __forceinline__ void right(int, IV<float>) {}
+    __device__ __forceinline__ void left(int, IV<float>) {}
+    __device__ __forceinline__ void add(double lo, double hi, DF tlo, DF thi) {
+        g += lo * (double)tlo.d + hi * (double)thi.d;
+        h += lo * (double)tlo.e + hi * (double)thi.e;
     }
-    __device__ __forceinline__ void neg(int s, double k, IV<DF> t) {
-        g += alo[s] * k * (double)t.hi.d + ahi[s] * k * (double)t.lo.d;
-    }
+    __device__ __forceinline__ void pos(int s, double k, IV<DF> t) { add(alo[s] * k, ahi[s] * k, t.lo, t.hi); }
+    __device__ __forceinline__ void neg(int s, double k, IV<DF> t) { add(alo[s] * k, ahi[s] * k, t.hi, t.lo); }
+    __device__ __forceinline__ void right(int q, IV<DF> t) { add(rlo[q], rhi[q], t.lo, t.hi); }
+    __device__ __forceinline__ void left(int q, IV<DF> t) { add(llo[q], lhi[q], t.lo, t.hi); }
 };
 
 }  // namespace leb

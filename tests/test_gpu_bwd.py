@@ -141,3 +141,31 @@ def test_backward_rejects_mu_gradient_without_mu(gpu):
                                     leb._dev_ptr(torch.empty_like(z), "a"), leb._dev_ptr(torch.empty_like(v), "b"),
                                     leb._dev_ptr(out, "c"), leb._dev_ptr(torch.empty_like(s), "d"), None)
         leb._check(rc)
+
+
+@pytest.mark.parametrize("n_units,mu", [(1, False), (2, True), (3, False), (28, True), (33, False), (64, True), (65, False),
+                                        (128, True)])
+def test_split_and_whole_forms_agree(gpu, n_units, mu):
+    """A few units (five waves share each spring's tangent passes up to 64 nodes)
+    give bit for bit what the same units give in a launch that fills the chip;
+    one unit has invalid data and, with springs, one an unbounded row."""
+    import torch
+    import paper_2607_01203_amd as leb
+    b = W.chain_batch(40 + n_units, 1, 5, n_units)
+    dyn = leb.dynamics_like(b.dyn)
+    rng = np.random.default_rng(n_units)
+    b.sigma[0, 1, 2] = -1.0
+    if n_units > 1:
+        b.z[0, 2, 6:8] = b.z[0, 2, 0:2] - [1.0, 0.0]              # spring 0 has length 0
+    off = b.sigma * rng.uniform(-0.5, 0.5, b.sigma.shape)
+    few = [b.z, b.v, b.sigma, rng.normal(size=b.z.shape), rng.normal(size=b.z.shape)] + ([off] if mu else [])
+    reps = 1200
+    call = lambda a: leb.backward(dyn, a[0], a[1], a[2], a[3], a[4], mu=a[5] if mu else None)
+    print("case: adjoint forms U=%d mu=%s" % (n_units, mu), flush=True)
+    one = call([torch.from_numpy(np.ascontiguousarray(x)).to(gpu) for x in few])
+    many = call([torch.from_numpy(np.repeat(x, reps, 0)).to(gpu) for x in few])
+    torch.cuda.synchronize()
+    for a, m in zip(one, many):
+        if a is not None:
+            assert torch.equal(a.expand_as(m), m)
+            assert (a[0, 1] == 0).all() and torch.isfinite(a).all()
