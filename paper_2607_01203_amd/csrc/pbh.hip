@@ -65,6 +65,14 @@ struct ChainArgs {
 };
 
 
+__device__ __forceinline__ TileRef tile_ref(const PbhTile& p) {
+    return TileRef{global_ptr(p.z),     global_ptr(p.v),       global_ptr(p.mu),      global_ptr(p.sigma), global_ptr(p.r_lo),
+                   global_ptr(p.r_hi), global_ptr(p.c_bar), global_ptr(p.rho_bar), global_ptr(p.flags), p.n};
+}
+
+// TILES: every workgroup has its own pointers (A.tiles); a form of its own, so that the
+// other form's loads and stores are known to be global ones.
+template <bool TILES>
 __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int U = A.U, T = A.T;
@@ -75,9 +83,8 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
     const int tid = threadIdx.x;
     TileRef t0;
     int64_t u0 = 0;
-    if (A.tiles) {
-        const PbhTile& pt = A.tiles[blockIdx.x];
-        t0 = TileRef{pt.z, pt.v, pt.mu, pt.sigma, pt.r_lo, pt.r_hi, pt.c_bar, pt.rho_bar, pt.flags, pt.n};
+    if (TILES) {
+        t0 = tile_ref(A.tiles[blockIdx.x]);
     } else {
         u0 = (int64_t)blockIdx.x * T;
         const int64_t left = A.units - u0;
@@ -94,7 +101,7 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
     // span at most T <= PBH_BLOCK trajectories.)  A certified trajectory's tube is
     // frozen, so its residuals are not needed again.
     __shared__ uint32_t s_wopen[PBH_BLOCK / 64];
-    const bool fold = A.fold.prev != nullptr;
+    const bool fold = !TILES && A.fold.prev != nullptr;
     if (fold) {
         uint32_t my = 1u;
         if (A.fold.sweep > 0) {
@@ -178,10 +185,10 @@ int launch_pbh_chain(const leb_dynamics* dyn, int64_t units, const double* z, co
     int64_t blocks = (units + a.T - 1) / a.T;
     if (blocks > 0x7fffffff) return LEB_EINVAL;
     if (ev0)        // timed: events at the kernel's start and end
-        hipExtLaunchKernelGGL(pbh_chain_fwd, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, ev0,
+        hipExtLaunchKernelGGL(pbh_chain_fwd<false>, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, ev0,
                               ev1, 0, a);
     else
-        hipLaunchKernelGGL(pbh_chain_fwd, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, a);
+        hipLaunchKernelGGL(pbh_chain_fwd<false>, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 
@@ -196,7 +203,7 @@ int launch_pbh_tiles(const leb_dynamics* dyn, const PbhTile* tiles, int n_tiles,
     a.kL = dyn->k_spring * dyn->rest_len;
     a.L0 = dyn->rest_len;
     a.pad = 0.0;
-    hipLaunchKernelGGL(pbh_chain_fwd, dim3((unsigned)n_tiles), dim3(PBH_BLOCK), pbh_smem_bytes_T(a.U, T), stream, a);
+    hipLaunchKernelGGL(pbh_chain_fwd<true>, dim3((unsigned)n_tiles), dim3(PBH_BLOCK), pbh_smem_bytes_T(a.U, T), stream, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 
@@ -229,7 +236,7 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_queue_kernel(PbhQueueArgs Q) {
         SpringOut* s_sp = reinterpret_cast<SpringOut*>(smem);                  // [T][U]
         uint32_t* s_flag = reinterpret_cast<uint32_t*>(s_sp + (size_t)T * U);   // [T]
         const PbhTile& pt = G.tiles[item - G.first];
-        const TileRef t0{pt.z, pt.v, pt.mu, pt.sigma, pt.r_lo, pt.r_hi, pt.c_bar, pt.rho_bar, pt.flags, pt.n};
+        const TileRef t0 = tile_ref(pt);
         for (int q = tid; q < T; q += PBH_BLOCK) s_flag[q] = 0u;
         const int lt = tid / U;
         const int i = tid - lt * U;

@@ -30,35 +30,49 @@ struct TileRef {
     int nloc;
 };
 
+// A pointer known to address global memory (loads and stores through it need not be
+// flat, which would tie their waits to those of LDS).
+template <class T> __device__ __forceinline__ T* global_ptr(T* p) {
+    return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
+typedef double node_d2 __attribute__((ext_vector_type(2), aligned(8)));
+
 // Coordinates of node i at one timestep (state rows 6i.., inputs 2i..) and
 // the positions of node i+1 that spring i needs.
 struct NodeIn { double zs[6], vs[2], ms[8], ss[8], zj[2], mj[2], sj[2]; };
 
+// Every load is unconditional, two doubles at a time, from a clamped place: a lane
+// past the last timestep reads the first one's, the last node its own position again.
 __device__ __forceinline__ void node_load(const TileRef& t, int U, int lt, int i, NodeIn& d) {
     const int nx = 6 * U, nu = 2 * U, n = nx + nu;
+    const bool active = lt < t.nloc;
+    const int l = active ? lt : 0, c = active ? i : 0, cj = c < U - 1 ? c + 1 : c;
+    const double* zp = t.Z + (int64_t)l * nx;
+    const double* vp = t.V + (int64_t)l * nu;
+    const double* sp = t.SG + (int64_t)l * n;
+    auto pair = [](const double* p, double* o) {
+        const node_d2 x = *reinterpret_cast<const node_d2*>(p);
+        o[0] = x[0];
+        o[1] = x[1];
+    };
 #pragma unroll
-    for (int c = 0; c < 6; ++c) d.zs[c] = 0.0;
-    d.vs[0] = d.vs[1] = 0.0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) { d.ms[c] = 0.0; d.ss[c] = 0.0; }
-    d.zj[0] = d.zj[1] = d.mj[0] = d.mj[1] = d.sj[0] = d.sj[1] = 0.0;
-    if (lt >= t.nloc) return;
-    const bool right = i < U - 1;
-    const double* zp = t.Z + (int64_t)lt * nx + 6 * i;
-    const double* vp = t.V + (int64_t)lt * nu + 2 * i;
-    const double* sp = t.SG + (int64_t)lt * n;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) { d.zs[c] = zp[c]; d.ss[c] = sp[6 * i + c]; }
-    d.vs[0] = vp[0]; d.vs[1] = vp[1];
-    d.ss[6] = sp[nx + 2 * i]; d.ss[7] = sp[nx + 2 * i + 1];
+    for (int q = 0; q < 6; q += 2) { pair(zp + 6 * c + q, d.zs + q); pair(sp + 6 * c + q, d.ss + q); }
+    pair(vp + 2 * c, d.vs);
+    pair(sp + nx + 2 * c, d.ss + 6);
+    pair(zp + 6 * cj, d.zj);
+    pair(sp + 6 * cj, d.sj);
     if (t.MU) {
-        const double* mp = t.MU + (int64_t)lt * n;
+        const double* mp = t.MU + (int64_t)l * n;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) d.ms[c] = mp[6 * i + c];
-        d.ms[6] = mp[nx + 2 * i]; d.ms[7] = mp[nx + 2 * i + 1];
-        if (right) { d.mj[0] = mp[6 * i + 6]; d.mj[1] = mp[6 * i + 7]; }
+        for (int q = 0; q < 6; q += 2) pair(mp + 6 * c + q, d.ms + q);
+        pair(mp + nx + 2 * c, d.ms + 6);
+        pair(mp + 6 * cj, d.mj);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) d.ms[q] = 0.0;
+        d.mj[0] = d.mj[1] = 0.0;
     }
-    if (right) { d.zj[0] = zp[6]; d.zj[1] = zp[7]; d.sj[0] = sp[6 * i + 6]; d.sj[1] = sp[6 * i + 7]; }
 }
 
 // input flags of the node's coordinates (bad input, hull extended)
@@ -225,19 +239,27 @@ __device__ __forceinline__ void node_pass(const Args& A, const TileRef& t, const
     }
     lo[3] = lo34[0]; hi[3] = hi34[0]; lo[4] = lo34[1]; hi[4] = hi34[1];
     const int64_t o = (int64_t)lt * nx + 6 * i;
+    auto put = [](double* p, double x, double y) { *reinterpret_cast<node_d2*>(p) = node_d2{x, y}; };
     if (t.RLO) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) { t.RLO[o + c] = lo[c]; t.RHI[o + c] = hi[c]; }
+        for (int c = 0; c < 6; c += 2) { put(t.RLO + o + c, lo[c], lo[c + 1]); put(t.RHI + o + c, hi[c], hi[c + 1]); }
     }
-    if (t.CB && A.compact) {
-        // the four affine rows are exactly (0, pad) unless the unit is bad, and then
-        // rows 3 and 4 are not finite either
-        const int64_t o2 = 2 * ((int64_t)lt * U + i);
-        row_zono(lo[3], hi[3], A.pad, &t.CB[o2], &t.RB[o2]);
-        row_zono(lo[4], hi[4], A.pad, &t.CB[o2 + 1], &t.RB[o2 + 1]);
-    } else if (t.CB) {
+    if (t.CB) {
+        double cb[6], rb[6];
+        // compact: the four affine rows are exactly (0, pad) unless the unit is bad, and
+        // then rows 3 and 4 are not finite either
+        if (A.compact) {
+            const int64_t o2 = 2 * ((int64_t)lt * U + i);
+            row_zono(lo[3], hi[3], A.pad, &cb[3], &rb[3]);
+            row_zono(lo[4], hi[4], A.pad, &cb[4], &rb[4]);
+            put(t.CB + o2, cb[3], cb[4]);
+            put(t.RB + o2, rb[3], rb[4]);
+        } else {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) row_zono(lo[c], hi[c], A.pad, &t.CB[o + c], &t.RB[o + c]);
+            for (int c = 0; c < 6; ++c) row_zono(lo[c], hi[c], A.pad, &cb[c], &rb[c]);
+#pragma unroll
+            for (int c = 0; c < 6; c += 2) { put(t.CB + o + c, cb[c], cb[c + 1]); put(t.RB + o + c, rb[c], rb[c + 1]); }
+        }
     }
     if (t.FL && i == 0) t.FL[lt] = (ft & LEB_FLAG_BAD_INPUT) ? (ft & ~LEB_FLAG_UNBOUNDED) : ft;
 }
