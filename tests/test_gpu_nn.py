@@ -131,3 +131,37 @@ def test_nn_bound_two_chunks(gpu):
     idx = np.array([0, 1, 4095, 4096, 4097, 4299])
     o = _oracle(net, a[0, idx, :12], a[0, idx, 12:], sg[0, idx])
     check_bounds(g["r_lo"][0, idx], g["r_hi"][0, idx], o["r_lo"], o["r_hi"], "two chunks")
+
+
+@pytest.mark.parametrize("widths", [[16, 16, 16, 16, 4], [16, 48, 80, 112, 12], [16, 256, 240, 32, 12],
+                                    [16, 64, 256, 256, 16, 8]])
+@pytest.mark.parametrize("shift", [0.0, 50.0, -50.0])
+def test_nn_hidden_targets_tiles(gpu, widths, shift):
+    """The 16-input hidden-layer passes: fewer tiles than waves, a ragged last
+    row block, the widest layers, a fourth hidden layer above them, and layers
+    whose neurons are mixed, all stably active or all stably inactive."""
+    rng = W.rng_for(910 + widths[1] + len(widths))
+    Wl, bl = W.mlp_weights(rng, widths)
+    bl = [x + np.float32(shift) if 0 < i < len(bl) - 1 else x for i, x in enumerate(bl)]
+    net = W.MLPNet(Wl, bl, 12, 4, False)
+    import paper_2607_01203_amd as leb
+    a = rng.uniform(-1, 1, (2, 4, 16))
+    sg = rng.uniform(0.005, 0.3, (2, 4, 16))
+    print("case: nn hidden targets %s shift %g" % (widths, shift), flush=True)
+    import torch
+    mlp = leb.MLP(net.W, net.b, 12, False)
+    out = leb.nn_bound(mlp, _t(a[..., :12], gpu), _t(a[..., 12:], gpu), _t(sg, gpu))
+    torch.cuda.synchronize()
+    o = _oracle(net, a[..., :12], a[..., 12:], sg)
+    lo, hi = out["r_lo"].cpu().numpy(), out["r_hi"].cpu().numpy()
+    # a constant network over a box that crosses layer-1 kinks: the oracle's bound is
+    # exactly 0, the kernel's is its rounding allowance, 2^-40 times a few sums of
+    # magnitudes, each at most the chain |b| + |W| m
+    zero = (o["r_lo"] == 0.0) & (o["r_hi"] == 0.0)
+    m = np.abs(a) + 2.0 * sg
+    for w, x in zip(net.W, net.b):
+        m = m @ np.abs(np.asarray(w, np.float64)).T + np.abs(np.asarray(x, np.float64))
+    assert (lo[zero] <= 0.0).all() and (hi[zero] >= 0.0).all()
+    assert (np.maximum(-lo, hi)[zero] <= 8.0 * 2.0 ** -40 * m[zero]).all()
+    check_bounds(lo[~zero], hi[~zero], o["r_lo"][~zero], o["r_hi"][~zero], "hidden targets")
+    mlp.close()
