@@ -178,3 +178,17 @@ def test_nn_backward_edge_boxes(gpu, case):
     if case != "wide_box":
         for key in g:
             assert np.abs(g[key]).max() <= 1e-12, key
+
+
+@pytest.mark.parametrize("widths", [[16, 48, 112, 64, 12], [16, 32, 16, 12], [16, 16, 32, 32, 8]])
+@pytest.mark.parametrize("scale", [1e-9, 0.02, 0.3, 8.0])
+def test_nn_backward_unstable_rows(gpu, widths, scale):
+    """Hidden-layer passes run over the unstable target rows: none, a few (less
+    than a block), several blocks and all of them."""
+    import paper_2607_01203_amd as leb
+    rng = W.rng_for(4100 + widths[1] + len(widths))
+    net, z, v, sg, mu, g_lo, g_hi = _case(rng, widths, widths[-1], 1, 3, scale, 1.5 * scale, True)
+    print("case: nn backward rows %s scale %g" % (widths, scale), flush=True)
+    g = _gpu_grad(leb, net, z, v, sg, mu, g_lo, g_hi, gpu)
+    for k in range(3):
+        _check_box(net, g, 0, k, z, v, sg, mu, g_lo, g_hi, "rows %s %g" % (widths, scale))
