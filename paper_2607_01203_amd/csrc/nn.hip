@@ -39,12 +39,10 @@
 #include "leb_internal.hpp"
 
 #include "nn_net.hpp"
+#include "nn_hid.hpp"
 
 namespace leb {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-
-constexpr double RT = 0x1p-40;   // rounding allowance factor
 constexpr int NN_CHUNK = 4096;   // boxes per pass
 constexpr uint32_t NN_UNSTABLE = 1u << 31;   // private per-box bit: some neuron is unstable
 
@@ -528,369 +526,6 @@ __global__ void __launch_bounds__(256) nn_chain1_kernel(ChainArgs A) {
     }
 }
 
-// ------------------------------------------- hidden targets, 16-wide input
-//
-// The passes for the bounds of hidden layers 2 and 3 (one and two steps) of networks
-// with 16 inputs, both modes in one workgroup.  In the first step Lambda is rows
-// of W_k, the same for both modes, and on a neuron that is stably active (l >= 0)
-// both modes multiply it by 1: those neurons' products are formed once and start
-// both modes' accumulators; only the unstable neurons are multiplied per mode.
-// Lists of the two classes (stably inactive neurons are in neither) are built per
-// box.  The bounds are formed from the accumulators at the end (concretisation),
-// so neither Lambda_0 nor its sums reach memory.
-struct HidArgs {
-    const double* WTt;             // target layer k, transposed: [w_{k-1}][M]
-    const double* bt;              // [M]
-    const double* W1; const double* W2;      // [w_1][16], [w_2][w_1]
-    const double* b1; const double* b2;
-    int w1, w2, M;
-    // per-box vectors of hidden layer 1 (layer 2 at + lstride), [box][NN_MAXW]
-    const double* s; const double* t; const double* a; const double* e; const double* lo; const double* hi;
-    size_t lstride;
-    const double* c; const double* rho;      // [box][16]
-    double* lo_out; double* hi_out;          // the target layer's bounds, [box][NN_MAXW]
-};
-
-constexpr int HID_PAD = NN_MAXW + 8;         // listed neurons, padded past the last k-step read
-
-// The two lists of one layer and the vectors their k-steps need, in list order.
-struct HidLists {
-    int na, nu;                              // active, unstable
-    int ka[HID_PAD], ku[HID_PAD];
-    double ab[HID_PAD], ae[HID_PAD];         // active: bias, rounding weight
-    double us[HID_PAD], ua[HID_PAD], ut[HID_PAD], ub[HID_PAD], ue[HID_PAD];
-};
-
-// Built by 256 lanes (neuron `tid` of K <= 256); contains barriers.
-__device__ __forceinline__ void hid_lists(HidLists& L, int K, const double* s, const double* t, const double* a,
-                                          const double* e, const double* lo, const double* hi, const double* b,
-                                          int (*cnt)[4]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool in = tid < K;
-    const double h = in ? hi[tid] : 0.0;
-    const bool keep = in && h > 0.0, act = keep && lo[tid] >= 0.0, uns = keep && !act;
-    const uint64_t ba = __ballot(act), bu = __ballot(uns), below = (1ull << lane) - 1ull;
-    if (lane == 0) { cnt[0][wave] = __popcll(ba); cnt[1][wave] = __popcll(bu); }
-    __syncthreads();
-    int oa = 0, ou = 0, na = 0, nu = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        oa += q < wave ? cnt[0][q] : 0;
-        ou += q < wave ? cnt[1][q] : 0;
-        na += cnt[0][q];
-        nu += cnt[1][q];
-    }
-    if (act) {
-        const int p = oa + __popcll(ba & below);
-        L.ka[p] = tid;
-        L.ab[p] = b[tid];
-        L.ae[p] = e[tid];
-    }
-    if (uns) {
-        const int p = ou + __popcll(bu & below);
-        L.ku[p] = tid;
-        L.us[p] = s[tid]; L.ua[p] = a[tid]; L.ut[p] = t[tid]; L.ub[p] = b[tid]; L.ue[p] = e[tid];
-    }
-    // eight padding entries past each list (neuron 0, x forced to 0 by its readers)
-    if (tid < 8) {
-        L.ka[na + tid] = 0; L.ab[na + tid] = 0.0; L.ae[na + tid] = 0.0;
-        L.ku[nu + tid] = 0;
-        L.us[nu + tid] = L.ua[nu + tid] = L.ut[nu + tid] = L.ub[nu + tid] = L.ue[nu + tid] = 0.0;
-    }
-    if (tid == 0) { L.na = na; L.nu = nu; }
-    __syncthreads();
-}
-
-// sum over the four lane groups of a 16 x 16 tile's columns
-__device__ __forceinline__ double sum_groups(double x) {
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
-}
-
-// The bound of target row `row` (lane column) in one mode from its Lambda_0^T tile
-// (element i of lane group g: input 4 i + g) and its partial sums.
-__device__ __forceinline__ void hid_concretize(const HidArgs& A, int box, int row, int mode, const d4& L0, double pb,
-                                               double pe, int g) {
-    const double* c = A.c + (size_t)box * 16;
-    const double* rho = A.rho + (size_t)box * 16;
-    double lin = 0.0, mag = 0.0, ab = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const double cn = c[4 * i + g], rn = rho[4 * i + g];
-        lin = __builtin_fma(L0[i], cn, lin);
-        mag = __builtin_fma(fabs(L0[i]), rn, mag);
-        ab = __builtin_fma(fabs(L0[i]), fabs(cn), ab);
-    }
-    lin = sum_groups(lin); mag = sum_groups(mag); ab = sum_groups(ab);
-    pb = sum_groups(pb); pe = sum_groups(pe);
-    if (g == 0 && row < A.M) {
-        const double bt = A.bt[row], beta = bt + pb;
-        const double err = RT * (pe + fabs(bt) + ab + mag + fabs(beta) + fabs(lin));
-        if (mode == 0) A.hi_out[(size_t)box * NN_MAXW + row] = lin + mag + beta + err;
-        else A.lo_out[(size_t)box * NN_MAXW + row] = lin - mag + beta - err;
-    }
-}
-
-// Target layer 2: Lambda_0 = (W_2 (.) S_1) W_1, one workgroup per box; wave w owns the
-// row tiles w, w + 4, ... (up to four) and runs all k-steps, so nothing is summed
-// over waves.  A: W_1 rows of the listed neurons, B: the same rows of W_2^T.
-//
-// What bounds it: the operands' path from L2 (five reads a k-step for 4 or 8 MFMA).
-// 3,200 boxes of the 16-256-256-256-12 network: 173 us with the concretisation
-// (one workgroup per mode with its k-steps split over the waves: 690 us, and 42 us).
-__global__ void __launch_bounds__(256) nn_hid1_kernel(HidArgs A) {
-    __shared__ HidLists L;
-    __shared__ int cnt[2][4];
-    const int box = blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t o = (size_t)box * NN_MAXW;
-    hid_lists(L, A.w1, A.s + o, A.t + o, A.a + o, A.e + o, A.lo + o, A.hi + o, A.b1, cnt);
-    const int na = L.na, nu = L.nu, M = A.M, nrt = (M + 15) >> 4;
-    const int nmine = (nrt - wave + 3) >> 2;              // row tiles of this wave
-    d4 U[4], D[4];
-    double pb[4], pbu[4], pbl[4], pe[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        U[q] = D[q] = d4{0.0, 0.0, 0.0, 0.0};
-        pb[q] = pbu[q] = pbl[q] = pe[q] = 0.0;
-    }
-    double wn, xn[4];
-    auto fetch = [&](int k, bool ok) {                    // neuron k of this lane group
-        wn = A.W1[k * 16 + r];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int row = 16 * (wave + 4 * q) + r;
-            const bool in = ok && row < M;
-            const double x = A.WTt[in ? (size_t)k * M + row : 0];
-            xn[q] = in ? x : 0.0;
-        }
-    };
-    if (nmine > 0) {
-        fetch(L.ka[g], g < na);
-        for (int c0 = 0; c0 < na; c0 += 4) {
-            const int c = c0 + g;
-            const double w = wn, b = L.ab[c], e = L.ae[c];
-            double x[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = xn[q];
-            const int cn = c + 4;
-            if (c0 + 4 < na) fetch(L.ka[cn], cn < na);
-            else fetch(L.ku[g], g < nu);                  // the first unstable k-step
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (q >= nmine) break;
-                U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, x[q], U[q], 0, 0, 0);
-                pb[q] = __builtin_fma(x[q], b, pb[q]);
-                pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
-            }
-        }
-        if (na == 0) fetch(L.ku[g], g < nu);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) D[q] = U[q];
-        for (int c0 = 0; c0 < nu; c0 += 4) {
-            const int c = c0 + g;
-            const double w = wn, s = L.us[c], a = L.ua[c], t = L.ut[c], b = L.ub[c], e = L.ue[c];
-            double x[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = xn[q];
-            const int cn = c + 4;
-            fetch(L.ku[cn], cn < nu);                     // past the end: padding
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (q >= nmine) break;
-                const bool pos = x[q] >= 0.0;
-                const double xs = x[q] * s, xa = x[q] * a, xt = x[q] * t;
-                const double ou = pos ? xs : xa, ol = pos ? xa : xs;
-                U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ou, U[q], 0, 0, 0);
-                D[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ol, D[q], 0, 0, 0);
-                pbu[q] = __builtin_fma(ou, b, pbu[q] + (pos ? xt : 0.0));
-                pbl[q] = __builtin_fma(ol, b, pbl[q] + (pos ? 0.0 : xt));
-                pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (q >= nmine) break;
-            const int row = 16 * (wave + 4 * q) + r;
-            hid_concretize(A, box, row, 0, U[q], pb[q] + pbu[q], pe[q], g);
-            hid_concretize(A, box, row, 1, D[q], pb[q] + pbl[q], pe[q], g);
-        }
-    }
-}
-
-// Target layer 3, 32 of its rows and one box per workgroup: Lambda_1 = (W_3 (.) S_2) W_2
-// with wave w owning the layer-1 tiles w, w + 4, ..., then Lambda_0 = (Lambda_1 (.)
-// S_1) W_1.  The transposed accumulator of the first step (lane l holds neuron
-// [4 i + l/16] of row [l%16]) is the B operand of the second, so each wave
-// multiplies its own tiles' neurons straight from its registers and only the four
-// waves' 16 x 16 partial tiles meet in LDS.  Row sums of the first step are taken
-// by the waves in turn (k-step modulo 4).
-//
-// What bounds it: FP64 MFMA (about 1,760 a workgroup of the 16-256-256-256-12
-// network where both modes over all kept neurons took 2,416) with six operand reads
-// from L2 for 8 or 16 of them.  3,200 boxes: 2.1 ms (one workgroup per mode and
-// 16 rows with Lambda in LDS between the steps: 4.2 ms, and 42 us to concretise).
-__global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
-    __shared__ HidLists L;
-    __shared__ double v1[5][NN_MAXW];                     // layer 1: s, a, t, bias, e (0 where inactive)
-    __shared__ double part[4][4][4][64];                  // waves: partial tiles (row tile, mode)
-    __shared__ double psum[4][4][2][64];                  // waves: bias and rounding sums (row tile, mode)
-    __shared__ int cnt[2][4];
-    const int box = blockIdx.y, row0 = 32 * blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t o1 = (size_t)box * NN_MAXW, o2 = A.lstride + o1;
-    {
-        const bool on = tid < A.w1 && A.hi[o1 + tid] > 0.0;
-        v1[0][tid] = on ? A.s[o1 + tid] : 0.0;
-        v1[1][tid] = on ? A.a[o1 + tid] : 0.0;
-        v1[2][tid] = on ? A.t[o1 + tid] : 0.0;
-        v1[3][tid] = on ? A.b1[tid] : 0.0;
-        v1[4][tid] = on ? A.e[o1 + tid] : 0.0;
-    }
-    hid_lists(L, A.w2, A.s + o2, A.t + o2, A.a + o2, A.e + o2, A.lo + o2, A.hi + o2, A.b2, cnt);
-    const int na = L.na, nu = L.nu, M = A.M, N = A.w1, nt = N >> 4;
-    const int nmine = (nt - wave + 3) >> 2;               // layer-1 tiles of this wave
-    d4 U[4][2], D[4][2];
-    double pb[2] = {0.0, 0.0}, pbu[2] = {0.0, 0.0}, pbl[2] = {0.0, 0.0}, pe[2] = {0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) U[i][q] = d4{0.0, 0.0, 0.0, 0.0};
-    double wn[4], xn[2];
-    auto fetch = [&](int k, bool ok) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int tt = i < nmine ? wave + 4 * i : 0;
-            wn[i] = A.W2[(size_t)k * N + 16 * tt + r];
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int row = row0 + 16 * q + r;
-            const bool in = ok && row < M;
-            const double x = A.WTt[in ? (size_t)k * M + row : 0];
-            xn[q] = in ? x : 0.0;
-        }
-    };
-    fetch(L.ka[g], g < na);
-    for (int c0 = 0; c0 < na; c0 += 4) {
-        const int c = c0 + g;
-        double w[4], x[2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = wn[i];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) x[q] = xn[q];
-        const int cn = c + 4;
-        if (c0 + 4 < na) fetch(L.ka[cn], cn < na);
-        else fetch(L.ku[g], g < nu);                      // the first unstable k-step
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i >= nmine) break;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], x[q], U[i][q], 0, 0, 0);
-        }
-        if (((c0 >> 2) & 3) == wave) {
-            const double b = L.ab[c], e = L.ae[c];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                pb[q] = __builtin_fma(x[q], b, pb[q]);
-                pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
-            }
-        }
-    }
-    if (na == 0) fetch(L.ku[g], g < nu);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) D[i][q] = U[i][q];
-    for (int c0 = 0; c0 < nu; c0 += 4) {
-        const int c = c0 + g;
-        double w[4], ou[2], ol[2];
-        const double s = L.us[c], a = L.ua[c];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = wn[i];
-        if (((c0 >> 2) & 3) == wave) {
-            const double t = L.ut[c], b = L.ub[c], e = L.ue[c];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const double x = xn[q], xt = x * t;
-                const bool pos = x >= 0.0;
-                pbu[q] = __builtin_fma(x * (pos ? s : a), b, pbu[q] + (pos ? xt : 0.0));
-                pbl[q] = __builtin_fma(x * (pos ? a : s), b, pbl[q] + (pos ? 0.0 : xt));
-                pe[q] = __builtin_fma(fabs(x), e, pe[q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const double x = xn[q];
-            const bool pos = x >= 0.0;
-            ou[q] = x * (pos ? s : a);
-            ol[q] = x * (pos ? a : s);
-        }
-        const int cn = c + 4;
-        fetch(L.ku[cn], cn < nu);                         // past the end: padding
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i >= nmine) break;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ou[q], U[i][q], 0, 0, 0);
-                D[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ol[q], D[i][q], 0, 0, 0);
-            }
-        }
-    }
-    // second step: this wave's neurons 16 tt + 4 j + g of layer 1
-    d4 Z[2][2];                                           // (row tile, mode): Lambda_0^T
-    double sb[2][2], se[2][2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        sb[q][0] = pb[q] + pbu[q]; sb[q][1] = pb[q] + pbl[q];
-        se[q][0] = se[q][1] = pe[q];
-        Z[q][0] = Z[q][1] = d4{0.0, 0.0, 0.0, 0.0};
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (i >= nmine) break;
-        const int n0 = 16 * (wave + 4 * i) + g;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + 4 * j;
-            const double w = A.W1[n * 16 + r];
-            const double s = v1[0][n], a = v1[1][n], t = v1[2][n], b = v1[3][n], e = v1[4][n];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const double xu = U[i][q][j], xl = D[i][q][j];
-                const bool pu = xu >= 0.0, pl = xl >= 0.0;
-                const double ou = xu * (pu ? s : a), ol = xl * (pl ? a : s);
-                Z[q][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ou, Z[q][0], 0, 0, 0);
-                Z[q][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ol, Z[q][1], 0, 0, 0);
-                sb[q][0] = __builtin_fma(ou, b, sb[q][0] + (pu ? xu * t : 0.0));
-                sb[q][1] = __builtin_fma(ol, b, sb[q][1] + (pl ? 0.0 : xl * t));
-                se[q][0] = __builtin_fma(fabs(xu), e, se[q][0]);
-                se[q][1] = __builtin_fma(fabs(xl), e, se[q][1]);
-            }
-        }
-    }
-    // the waves' partial tiles and sums; wave w finishes (row tile w / 2, mode w % 2)
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part[wave][m][i][lane] = Z[m >> 1][m & 1][i];
-        psum[wave][m][0][lane] = sb[m >> 1][m & 1];
-        psum[wave][m][1][lane] = se[m >> 1][m & 1];
-    }
-    __syncthreads();
-    d4 z = d4{0.0, 0.0, 0.0, 0.0};
-    double b = 0.0, e = 0.0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) z[i] += part[w][wave][i][lane];
-        b += psum[w][wave][0][lane];
-        e += psum[w][wave][1][lane];
-    }
-    hid_concretize(A, box, row0 + 16 * (wave >> 1) + r, wave & 1, z, b, e, g);
-}
-
 // ----------------------------------------------------------- concretize
 
 struct ConcArgs {
@@ -1198,16 +833,16 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
                 // one or two steps down to a 16-wide input (one MFMA tile): both modes and the
                 // concretisation in one launch (3,200 boxes of 16-256-256-256-12: 2.3 ms for the
                 // two targets, 5.0 ms by the general chain); deeper targets and other inputs below
-                HidArgs ha;
+                HidArgs ha = {};
                 ha.WTt = net->WT[k - 1]; ha.bt = net->b[k - 1];
                 ha.W1 = net->W[0]; ha.b1 = net->b[0]; ha.W2 = net->W[1]; ha.b2 = net->b[1];
                 ha.w1 = net->w[1]; ha.w2 = net->w[2]; ha.M = net->w[k];
                 ha.s = s; ha.t = t; ha.a = a; ha.e = e; ha.lo = lo; ha.hi = hi;
-                ha.lstride = (size_t)CB * NN_MAXW;
-                ha.c = c; ha.rho = rho;
+                ha.bstride = NN_MAXW; ha.lstride = (size_t)CB * NN_MAXW;
+                ha.c = c; ha.rho = rho; ha.cstride = 16;
                 ha.lo_out = layer(lo, k - 1); ha.hi_out = layer(hi, k - 1);
-                if (k == 2) hipLaunchKernelGGL(nn_hid1_kernel, dim3(nb), dim3(256), 0, st, ha);
-                else hipLaunchKernelGGL(nn_hid2_kernel, dim3((ha.M + 31) / 32, nb), dim3(256), 0, st, ha);
+                if (k == 2) hipLaunchKernelGGL(nn_hid1_kernel<false>, dim3(nb), dim3(256), 0, st, ha);
+                else hipLaunchKernelGGL(nn_hid2_kernel<false>, dim3((ha.M + 31) / 32, nb), dim3(256), 0, st, ha);
                 if (hipGetLastError() != hipSuccess) return LEB_EDEVICE;
                 if ((rc = relax(k - 1))) return rc;
                 continue;

@@ -45,6 +45,8 @@
 //    FP64 MFMA; every pass has a forward launch that stores its levels and the
 //    reverse launch reads them back; the k range of each product runs over
 //    the neurons that are not stably inactive (see the MFMA section below).
+//    Hidden targets of 16-input networks: the forward kernels of the bound
+//    (nn_hid.hpp), storing the levels of unstable rows, the only ones read back.
 //  * VALU (deeper networks): 8-row blocks, Lambda^(j) of the lane's column
 //    kept in registers for the reverse sweep; hidden-layer passes store their
 //    levels, the output pass recomputes its chain; narrow outputs (the input
@@ -60,6 +62,7 @@
 
 #include "leb.h"
 #include "leb_internal.hpp"
+#include "nn_hid.hpp"
 #include "nn_net.hpp"
 
 namespace leb {
@@ -108,14 +111,6 @@ __device__ __forceinline__ size_t ix_ub(int box, int j, int which) {
 }
 __device__ __forceinline__ size_t ix_cg(int box, int mode, int which) {
     return (((size_t)box * 2 + mode) * 2 + which) * NN_MAXW;
-}
-
-// ReLU relaxation of a neuron with pre-activation bounds [lo, hi]: upper
-// line s z + t, lower line a z
-__device__ __forceinline__ void nb_relax(double lo, double hi, double& s, double& t, double& a) {
-    if (lo >= 0.0) { s = 1.0; t = 0.0; a = 1.0; }
-    else if (hi > 0.0) { s = hi / (hi - lo); t = -s * lo; a = hi >= -lo ? 1.0 : 0.0; }
-    else { s = 0.0; t = 0.0; a = 0.0; }
 }
 
 // out[r][i] = sum_{p < len} X[p][r] M[p nc + i] for i < nc, X in LDS as [p][NB_R];
@@ -932,6 +927,24 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
             const dim3 grid((unsigned)nb, 2u);
             for (int k = 2; k <= L; ++k) {
                 a.k = k;
+                if (k < L && k <= 3 && net->w[0] == 16) {
+                    // one or two steps down to a 16-wide input: both directions together, levels of
+                    // unstable rows only (3,200 boxes of 16-256-256-256-12: 1.95 ms for the
+                    // two targets, 8.5 ms by the general pass); the rest below
+                    HidArgs ha = {};
+                    ha.WTt = net->WT[k - 1]; ha.bt = net->b[k - 1];
+                    ha.W1 = net->W[0]; ha.b1 = net->b[0]; ha.W2 = net->W[1]; ha.b2 = net->b[1];
+                    ha.w1 = net->w[1]; ha.w2 = net->w[2]; ha.M = net->w[k];
+                    ha.lo = a.bd; ha.hi = a.bd + NN_MAXW;
+                    ha.bstride = (size_t)NN_MAXL * 2 * NN_MAXW; ha.lstride = 2 * NN_MAXW;
+                    ha.c = a.cr; ha.rho = a.cr + NN_MAXW; ha.cstride = 2 * NN_MAXW;
+                    ha.lo_out = a.bd + (k - 1) * ha.lstride; ha.hi_out = ha.lo_out + NN_MAXW;
+                    ha.lv = a.lv; ha.lv_bm = lv_bm; ha.off0 = a.lv_off[k][0]; ha.off1 = a.lv_off[k][1];
+                    ha.ok = a.ok;
+                    if (k == 2) hipLaunchKernelGGL(nn_hid1_kernel<true>, dim3(nb), dim3(256), 0, st, ha);
+                    else hipLaunchKernelGGL(nn_hid2_kernel<true>, dim3((ha.M + 31) / 32, nb), dim3(256), 0, st, ha);
+                    continue;
+                }
                 hipLaunchKernelGGL(nbm_pass_kernel<false>, grid, dim3(NB_T), 0, st, a);
             }
             a.k = L;

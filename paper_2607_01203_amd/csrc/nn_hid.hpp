@@ -1,0 +1,481 @@
+// nn_hid.hpp -- CROWN passes for the bounds of hidden layers 2 and 3 of a ReLU MLP
+// with 16 inputs, shared by the bound (nn.hip) and its adjoint (nn_bwd.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "nn_net.hpp"
+
+namespace leb {
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+constexpr double RT = 0x1p-40;   // rounding allowance factor of the bound
+
+// ------------------------------------------- hidden targets, 16-wide input
+//
+// Both modes of one or two steps run in one workgroup.  In the first step Lambda is rows
+// of W_k, the same for both modes, and on a neuron that is stably active (l >= 0)
+// both modes multiply it by 1: those neurons' products are formed once and start
+// both modes' accumulators; only the unstable neurons are multiplied per mode.
+// Lists of the two classes (stably inactive neurons are in neither) are built per
+// box.  The bounds are formed from the accumulators at the end (concretisation),
+// so neither Lambda_0 nor its sums reach memory.
+struct HidArgs {
+    const double* WTt;             // target layer k, transposed: [w_{k-1}][M]
+    const double* bt;              // [M]
+    const double* W1; const double* W2;      // [w_1][16], [w_2][w_1]
+    const double* b1; const double* b2;
+    int w1, w2, M;
+    // bounds of hidden layer 1 at lo, hi + box * bstride, of layer 2 at + lstride;
+    // bound: slopes s, a, intercepts t, rounding weights e at the same offsets
+    const double* lo; const double* hi;
+    const double* s; const double* t; const double* a; const double* e;
+    size_t bstride, lstride;
+    const double* c; const double* rho;      // + box * cstride: [16]
+    size_t cstride;
+    double* lo_out; double* hi_out;          // + box * bstride: the target layer's bounds
+    // adjoint: levels Lambda^(0) ([M][16] at off0) and Lambda^(1) ([M][w_1] at off1) of
+    // direction d at lv + (2 box + d) lv_bm; validity of each box
+    double* lv; size_t lv_bm; int off0, off1;
+    const uint32_t* ok;
+};
+
+// ReLU relaxation of a neuron with pre-activation bounds [lo, hi] in exact
+// arithmetic: upper line s z + t, lower line a z
+__device__ __forceinline__ void nb_relax(double lo, double hi, double& s, double& t, double& a) {
+    if (lo >= 0.0) { s = 1.0; t = 0.0; a = 1.0; }
+    else if (hi > 0.0) { s = hi / (hi - lo); t = -s * lo; a = hi >= -lo ? 1.0 : 0.0; }
+    else { s = 0.0; t = 0.0; a = 0.0; }
+}
+
+// neuron's relaxation and rounding weight at offset o (ADJ: none)
+template <bool ADJ>
+__device__ __forceinline__ void hid_relax(const HidArgs& A, size_t o, double l, double h, double& s, double& t,
+                                          double& a, double& e) {
+    if constexpr (ADJ) {
+        nb_relax(l, h, s, t, a);
+        e = 0.0;
+    } else {
+        s = A.s[o]; t = A.t[o]; a = A.a[o]; e = A.e[o];
+    }
+}
+
+constexpr int HID_PAD = NN_MAXW + 8;         // listed neurons, padded past the last k-step read
+
+// The two lists of one layer and the vectors their k-steps need, in list order.
+struct HidLists {
+    int na, nu;                              // active, unstable
+    int ka[HID_PAD], ku[HID_PAD];
+    double ab[HID_PAD], ae[HID_PAD];         // active: bias, rounding weight
+    double us[HID_PAD], ua[HID_PAD], ut[HID_PAD], ub[HID_PAD], ue[HID_PAD];
+};
+
+// Built by 256 lanes (neuron `tid` of K <= 256) from the vectors at offset o; contains
+// barriers.  A neuron with l >= 0 and u <= 0 has input 0 on the whole box: the bound
+// drops it, the adjoint keeps it (its derivative is that of an active one).
+template <bool ADJ>
+__device__ __forceinline__ void hid_lists(HidLists& L, const HidArgs& A, size_t o, int K, const double* b,
+                                          int (*cnt)[4]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool in = tid < K;
+    const double l = in ? A.lo[o + tid] : -1.0, h = in ? A.hi[o + tid] : -1.0;
+    const bool keep = h > 0.0 || (ADJ && l >= 0.0), act = keep && l >= 0.0, uns = keep && !act;
+    const uint64_t ba = __ballot(act), bu = __ballot(uns), below = (1ull << lane) - 1ull;
+    if (lane == 0) { cnt[0][wave] = __popcll(ba); cnt[1][wave] = __popcll(bu); }
+    __syncthreads();
+    int oa = 0, ou = 0, na = 0, nu = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        oa += q < wave ? cnt[0][q] : 0;
+        ou += q < wave ? cnt[1][q] : 0;
+        na += cnt[0][q];
+        nu += cnt[1][q];
+    }
+    double s = 0.0, t = 0.0, a = 0.0, e = 0.0;
+    if (keep) hid_relax<ADJ>(A, o + tid, l, h, s, t, a, e);
+    if (act) {
+        const int p = oa + __popcll(ba & below);
+        L.ka[p] = tid;
+        L.ab[p] = b[tid];
+        L.ae[p] = e;
+    }
+    if (uns) {
+        const int p = ou + __popcll(bu & below);
+        L.ku[p] = tid;
+        L.us[p] = s; L.ua[p] = a; L.ut[p] = t; L.ub[p] = b[tid]; L.ue[p] = e;
+    }
+    // eight padding entries past each list (neuron 0, x forced to 0 by its readers)
+    if (tid < 8) {
+        L.ka[na + tid] = 0; L.ab[na + tid] = 0.0; L.ae[na + tid] = 0.0;
+        L.ku[nu + tid] = 0;
+        L.us[nu + tid] = L.ua[nu + tid] = L.ut[nu + tid] = L.ub[nu + tid] = L.ue[nu + tid] = 0.0;
+    }
+    if (tid == 0) { L.na = na; L.nu = nu; }
+    __syncthreads();
+}
+
+// sum over the four lane groups of a 16 x 16 tile's columns
+__device__ __forceinline__ double sum_groups(double x) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// The bound of target row `row` (lane column) in one mode from its Lambda_0^T tile
+// (element i of lane group g: input 4 i + g) and its partial sums; the same in
+// every lane group.
+template <bool ADJ>
+__device__ __forceinline__ double hid_concretize(const HidArgs& A, int box, int row, int mode, const d4& L0, double pb,
+                                                 double pe, int g) {
+    const double* c = A.c + (size_t)box * A.cstride;
+    const double* rho = A.rho + (size_t)box * A.cstride;
+    double lin = 0.0, mag = 0.0, ab = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double cn = c[4 * i + g], rn = rho[4 * i + g];
+        lin = __builtin_fma(L0[i], cn, lin);
+        mag = __builtin_fma(fabs(L0[i]), rn, mag);
+        if (!ADJ) ab = __builtin_fma(fabs(L0[i]), fabs(cn), ab);
+    }
+    lin = sum_groups(lin); mag = sum_groups(mag); pb = sum_groups(pb);
+    const double bt = row < A.M ? A.bt[row] : 0.0, beta = bt + pb;
+    double err = 0.0;
+    if (!ADJ) {
+        ab = sum_groups(ab); pe = sum_groups(pe);
+        err = RT * (pe + fabs(bt) + ab + mag + fabs(beta) + fabs(lin));
+    }
+    const double out = mode == 0 ? lin + mag + beta + err : lin - mag + beta - err;
+    if (g == 0 && row < A.M) (mode == 0 ? A.hi_out : A.lo_out)[(size_t)box * A.bstride + row] = out;
+    return out;
+}
+
+// adjoint: store row `row` of Lambda_0 of one direction
+__device__ __forceinline__ void hid_store0(const HidArgs& A, int box, int row, int mode, const d4& L0, int g) {
+    double* dst = A.lv + ((size_t)box * 2 + mode) * A.lv_bm + A.off0 + (size_t)row * 16 + g;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dst[4 * i] = L0[i];
+}
+
+// Target layer 2: Lambda_0 = (W_2 (.) S_1) W_1, one workgroup per box; wave w owns the
+// row tiles w, w + 4, ... (up to four) and runs all k-steps, so nothing is summed
+// over waves.  A: W_1 rows of the listed neurons, B: the same rows of W_2^T.
+//
+// What bounds it: the operands' path from L2 (five reads a k-step for 4 or 8 MFMA).
+// 3,200 boxes of the 16-256-256-256-12 network: 173 us with the concretisation
+// (one workgroup per mode with its k-steps split over the waves: 690 us, and 42 us).
+template <bool ADJ>
+__global__ void __launch_bounds__(256) nn_hid1_kernel(HidArgs A) {
+    __shared__ HidLists L;
+    __shared__ int cnt[2][4];
+    const int box = blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (ADJ && !A.ok[box]) return;
+    hid_lists<ADJ>(L, A, (size_t)box * A.bstride, A.w1, A.b1, cnt);
+    const int na = L.na, nu = L.nu, M = A.M, nrt = (M + 15) >> 4;
+    const int nmine = (nrt - wave + 3) >> 2;              // row tiles of this wave
+    d4 U[4], D[4];
+    double pb[4], pbu[4], pbl[4], pe[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        U[q] = D[q] = d4{0.0, 0.0, 0.0, 0.0};
+        pb[q] = pbu[q] = pbl[q] = pe[q] = 0.0;
+    }
+    double wn, xn[4];
+    auto fetch = [&](int k, bool ok) {                    // neuron k of this lane group
+        wn = A.W1[k * 16 + r];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = 16 * (wave + 4 * q) + r;
+            const bool in = ok && row < M;
+            const double x = A.WTt[in ? (size_t)k * M + row : 0];
+            xn[q] = in ? x : 0.0;
+        }
+    };
+    if (nmine > 0) {
+        fetch(L.ka[g], g < na);
+        for (int c0 = 0; c0 < na; c0 += 4) {
+            const int c = c0 + g;
+            const double w = wn, b = L.ab[c], e = L.ae[c];
+            double x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = xn[q];
+            const int cn = c + 4;
+            if (c0 + 4 < na) fetch(L.ka[cn], cn < na);
+            else fetch(L.ku[g], g < nu);                  // the first unstable k-step
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q >= nmine) break;
+                U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, x[q], U[q], 0, 0, 0);
+                pb[q] = __builtin_fma(x[q], b, pb[q]);
+                if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
+            }
+        }
+        if (na == 0) fetch(L.ku[g], g < nu);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) D[q] = U[q];
+        for (int c0 = 0; c0 < nu; c0 += 4) {
+            const int c = c0 + g;
+            const double w = wn, s = L.us[c], a = L.ua[c], t = L.ut[c], b = L.ub[c], e = L.ue[c];
+            double x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = xn[q];
+            const int cn = c + 4;
+            fetch(L.ku[cn], cn < nu);                     // past the end: padding
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q >= nmine) break;
+                const bool pos = x[q] >= 0.0;
+                const double xs = x[q] * s, xa = x[q] * a, xt = x[q] * t;
+                const double ou = pos ? xs : xa, ol = pos ? xa : xs;
+                U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ou, U[q], 0, 0, 0);
+                D[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ol, D[q], 0, 0, 0);
+                pbu[q] = __builtin_fma(ou, b, pbu[q] + (pos ? xt : 0.0));
+                pbl[q] = __builtin_fma(ol, b, pbl[q] + (pos ? 0.0 : xt));
+                if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= nmine) break;
+            const int row = 16 * (wave + 4 * q) + r;
+            const double h = hid_concretize<ADJ>(A, box, row, 0, U[q], pb[q] + pbu[q], pe[q], g);
+            const double l = hid_concretize<ADJ>(A, box, row, 1, D[q], pb[q] + pbl[q], pe[q], g);
+            // only an unstable neuron's rows are read back
+            if (ADJ && row < M && l < 0.0 && h > 0.0) {
+                hid_store0(A, box, row, 0, U[q], g);
+                hid_store0(A, box, row, 1, D[q], g);
+            }
+        }
+    }
+}
+
+// Target layer 3, 32 of its rows and one box per workgroup: Lambda_1 = (W_3 (.) S_2) W_2
+// in the columns of layer 1's neurons that are not stably inactive (the others are
+// multiplied by 0 below), wave w owning every fourth tile of them, then Lambda_0 =
+// (Lambda_1 (.) S_1) W_1.  The transposed accumulator of the first step (lane l holds
+// neuron [4 i + l/16] of row [l%16]) is the B operand of the second, so each wave
+// multiplies its own tiles' neurons straight from its registers and only the four
+// waves' 16 x 16 partial tiles meet in LDS.  Row sums of the first step are taken
+// by the waves in turn (k-step modulo 4).
+//
+// What bounds it: FP64 MFMA (about 1,000 a workgroup of the 16-256-256-256-12
+// network where both modes over all kept neurons and every column took 2,416: 0.7 ms
+// at the peak rate) and the latency of the operand reads from L2, two waves a SIMD.
+// 3,200 boxes: 1.76 ms, the adjoint's 1.78 ms (every column of Lambda_1: 2.12 ms;
+// one workgroup per mode and 16 rows with Lambda in LDS between the steps: 4.2 ms,
+// and 42 us to concretise; the adjoint's general pass 6.4 ms).
+template <bool ADJ>
+__global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
+    __shared__ HidLists L;
+    // layer 1: the neurons that are not stably inactive (the columns of Lambda_1 that
+    // are formed), padded to whole tiles, and their s, a, t, bias, e (0 in the padding)
+    __shared__ int col1[NN_MAXW];
+    __shared__ double v1[5][NN_MAXW];
+    __shared__ double part[4][4][4][64];                  // waves: partial tiles (row tile, mode)
+    __shared__ double psum[4][4][2][64];                  // waves: bias and rounding sums (row tile, mode)
+    __shared__ int cnt[2][4], cnt1[4];
+    const int box = blockIdx.y, row0 = 32 * blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (ADJ && !A.ok[box]) return;
+    const size_t o1 = (size_t)box * A.bstride, o2 = A.lstride + o1;
+    const int M = A.M, N = A.w1;
+    int n1 = 0;
+    {
+        const double l = tid < N ? A.lo[o1 + tid] : -1.0, h = tid < N ? A.hi[o1 + tid] : -1.0;
+        const bool keep = h > 0.0 || (ADJ && l >= 0.0);
+        const uint64_t bal = __ballot(keep);
+        if (lane == 0) cnt1[wave] = __popcll(bal);
+        double s = 0.0, t = 0.0, a = 0.0, e = 0.0;
+        if (keep) hid_relax<ADJ>(A, o1 + tid, l, h, s, t, a, e);
+        col1[tid] = 0;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) v1[q][tid] = 0.0;
+        __syncthreads();
+        int off = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            off += q < wave ? cnt1[q] : 0;
+            n1 += cnt1[q];
+        }
+        if (keep) {
+            const int p = off + __popcll(bal & ((1ull << lane) - 1ull));
+            col1[p] = tid;
+            v1[0][p] = s; v1[1][p] = a; v1[2][p] = t; v1[3][p] = A.b1[tid]; v1[4][p] = e;
+        }
+    }
+    hid_lists<ADJ>(L, A, o2, A.w2, A.b2, cnt);
+    // this wave's tiles of the listed columns: first, first + 4, ... (first rotates over
+    // the workgroups, so that the waves with a tile more spread over the SIMDs)
+    const int na = L.na, nu = L.nu, nt = (n1 + 15) >> 4;
+    const int first = (wave + blockIdx.x + blockIdx.y) & 3, nmine = (nt - first + 3) >> 2;
+    int wcol[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) wcol[i] = col1[i < nmine ? 16 * (first + 4 * i) + r : 0];
+    d4 U[4][2], D[4][2];
+    double pb[2] = {0.0, 0.0}, pbu[2] = {0.0, 0.0}, pbl[2] = {0.0, 0.0}, pe[2] = {0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) U[i][q] = d4{0.0, 0.0, 0.0, 0.0};
+    double wn[4], xn[2];
+    auto fetch = [&](int k, bool ok) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wn[i] = A.W2[(size_t)k * N + wcol[i]];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int row = row0 + 16 * q + r;
+            const bool in = ok && row < M;
+            const double x = A.WTt[in ? (size_t)k * M + row : 0];
+            xn[q] = in ? x : 0.0;
+        }
+    };
+    fetch(L.ka[g], g < na);
+    for (int c0 = 0; c0 < na; c0 += 4) {
+        const int c = c0 + g;
+        double w[4], x[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = wn[i];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) x[q] = xn[q];
+        const int cn = c + 4;
+        if (c0 + 4 < na) fetch(L.ka[cn], cn < na);
+        else fetch(L.ku[g], g < nu);                      // the first unstable k-step
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i >= nmine) break;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], x[q], U[i][q], 0, 0, 0);
+        }
+        if (((c0 >> 2) & 3) == wave) {
+            const double b = L.ab[c], e = L.ae[c];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                pb[q] = __builtin_fma(x[q], b, pb[q]);
+                if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
+            }
+        }
+    }
+    if (na == 0) fetch(L.ku[g], g < nu);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) D[i][q] = U[i][q];
+    for (int c0 = 0; c0 < nu; c0 += 4) {
+        const int c = c0 + g;
+        double w[4], ou[2], ol[2];
+        const double s = L.us[c], a = L.ua[c];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = wn[i];
+        if (((c0 >> 2) & 3) == wave) {
+            const double t = L.ut[c], b = L.ub[c], e = L.ue[c];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const double x = xn[q], xt = x * t;
+                const bool pos = x >= 0.0;
+                pbu[q] = __builtin_fma(x * (pos ? s : a), b, pbu[q] + (pos ? xt : 0.0));
+                pbl[q] = __builtin_fma(x * (pos ? a : s), b, pbl[q] + (pos ? 0.0 : xt));
+                if (!ADJ) pe[q] = __builtin_fma(fabs(x), e, pe[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const double x = xn[q];
+            const bool pos = x >= 0.0;
+            ou[q] = x * (pos ? s : a);
+            ol[q] = x * (pos ? a : s);
+        }
+        const int cn = c + 4;
+        fetch(L.ku[cn], cn < nu);                         // past the end: padding
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i >= nmine) break;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ou[q], U[i][q], 0, 0, 0);
+                D[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ol[q], D[i][q], 0, 0, 0);
+            }
+        }
+    }
+    // second step: this wave's listed neurons 16 tt + 4 j + g of layer 1
+    d4 Z[2][2];                                           // (row tile, mode): Lambda_0^T
+    double sb[2][2], se[2][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        sb[q][0] = pb[q] + pbu[q]; sb[q][1] = pb[q] + pbl[q];
+        se[q][0] = se[q][1] = pe[q];
+        Z[q][0] = Z[q][1] = d4{0.0, 0.0, 0.0, 0.0};
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (i >= nmine) break;
+        const int n0 = 16 * (first + 4 * i) + g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int n = n0 + 4 * j;
+            const double w = A.W1[col1[n] * 16 + r];
+            const double s = v1[0][n], a = v1[1][n], t = v1[2][n], b = v1[3][n], e = v1[4][n];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const double xu = U[i][q][j], xl = D[i][q][j];
+                const bool pu = xu >= 0.0, pl = xl >= 0.0;
+                const double ou = xu * (pu ? s : a), ol = xl * (pl ? a : s);
+                Z[q][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ou, Z[q][0], 0, 0, 0);
+                Z[q][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ol, Z[q][1], 0, 0, 0);
+                sb[q][0] = __builtin_fma(ou, b, sb[q][0] + (pu ? xu * t : 0.0));
+                sb[q][1] = __builtin_fma(ol, b, sb[q][1] + (pl ? 0.0 : xl * t));
+                if (!ADJ) {
+                    se[q][0] = __builtin_fma(fabs(xu), e, se[q][0]);
+                    se[q][1] = __builtin_fma(fabs(xl), e, se[q][1]);
+                }
+            }
+        }
+    }
+    // the waves' partial tiles and sums; wave w finishes (row tile w / 2, mode w % 2)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[wave][m][i][lane] = Z[m >> 1][m & 1][i];
+        psum[wave][m][0][lane] = sb[m >> 1][m & 1];
+        psum[wave][m][1][lane] = se[m >> 1][m & 1];
+    }
+    __syncthreads();
+    d4 z = d4{0.0, 0.0, 0.0, 0.0};
+    double b = 0.0, e = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z[i] += part[w][wave][i][lane];
+        b += psum[w][wave][0][lane];
+        e += psum[w][wave][1][lane];
+    }
+    const int row = row0 + 16 * (wave >> 1) + r;
+    const double v = hid_concretize<ADJ>(A, box, row, wave & 1, z, b, e, g);
+    if constexpr (ADJ) {
+        // only an unstable neuron's rows are read back: both directions' bounds meet in LDS
+        __syncthreads();                                  // part and psum read
+        if (g == 0) psum[0][wave & 1][0][16 * (wave >> 1) + r] = row < M ? v : 0.0;
+        __syncthreads();
+        bool uns[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) uns[q] = psum[0][1][0][16 * q + r] < 0.0 && psum[0][0][0][16 * q + r] > 0.0;
+        if (uns[wave >> 1]) hid_store0(A, box, row, wave & 1, z, g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i >= nmine) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int n = 16 * (first + 4 * i) + 4 * j + g;
+                if (n >= n1) continue;
+                double* dst = A.lv + (size_t)box * 2 * A.lv_bm + A.off1 + (size_t)(row0 + r) * N + col1[n];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (uns[q]) {
+                        dst[(size_t)16 * q * N] = U[i][q][j];
+                        dst[A.lv_bm + (size_t)16 * q * N] = D[i][q][j];
+                    }
+            }
+        }
+    }
+}
+
+}  // namespace leb
