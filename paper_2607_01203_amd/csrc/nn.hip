@@ -831,7 +831,7 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
         for (int k = 2; k <= L - 1; ++k) {
             if (n0 == 16 && k <= 3) {
                 // one or two steps down to a 16-wide input (one MFMA tile): both modes and the
-                // concretisation in one launch (3,200 boxes of 16-256-256-256-12: 2.3 ms for the
+                // concretisation in one launch (3,200 boxes of 16-256-256-256-12: 1.5 ms for the
                 // two targets, 5.0 ms by the general chain); deeper targets and other inputs below
                 HidArgs ha = {};
                 ha.WTt = net->WT[k - 1]; ha.bt = net->b[k - 1];

@@ -929,7 +929,7 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
                 a.k = k;
                 if (k < L && k <= 3 && net->w[0] == 16) {
                     // one or two steps down to a 16-wide input: both directions together, levels of
-                    // unstable rows only (3,200 boxes of 16-256-256-256-12: 1.95 ms for the
+                    // unstable rows only (3,200 boxes of 16-256-256-256-12: 1.65 ms for the
                     // two targets, 8.5 ms by the general pass); the rest below
                     HidArgs ha = {};
                     ha.WTt = net->WT[k - 1]; ha.bt = net->b[k - 1];

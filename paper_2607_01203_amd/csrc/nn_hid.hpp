@@ -61,7 +61,7 @@ __device__ __forceinline__ void hid_relax(const HidArgs& A, size_t o, double l, 
     }
 }
 
-constexpr int HID_PAD = NN_MAXW + 8;         // listed neurons, padded past the last k-step read
+constexpr int HID_PAD = NN_MAXW + 12;        // listed neurons, padded past the last k-step read
 
 // The two lists of one layer and the vectors their k-steps need, in list order.
 struct HidLists {
@@ -105,8 +105,8 @@ __device__ __forceinline__ void hid_lists(HidLists& L, const HidArgs& A, size_t 
         L.ku[p] = tid;
         L.us[p] = s; L.ua[p] = a; L.ut[p] = t; L.ub[p] = b[tid]; L.ue[p] = e;
     }
-    // eight padding entries past each list (neuron 0, x forced to 0 by its readers)
-    if (tid < 8) {
+    // twelve padding entries past each list (neuron 0, x forced to 0 by its readers)
+    if (tid < 12) {
         L.ka[na + tid] = 0; L.ab[na + tid] = 0.0; L.ae[na + tid] = 0.0;
         L.ku[nu + tid] = 0;
         L.us[nu + tid] = L.ua[nu + tid] = L.ut[nu + tid] = L.ub[nu + tid] = L.ue[nu + tid] = 0.0;
@@ -156,97 +156,212 @@ __device__ __forceinline__ void hid_store0(const HidArgs& A, int box, int row, i
     for (int i = 0; i < 4; ++i) dst[4 * i] = L0[i];
 }
 
+// NT row tiles (wave, wave + 4, ...) of one wave: the products, then the bounds.
+template <bool ADJ, int NT>
+__device__ __forceinline__ void hid1_tiles(const HidArgs& A, const HidLists& L, int box, int wave, int r, int g) {
+    const int na = L.na, nu = L.nu;
+    const unsigned M8 = 8u * A.M;
+    d4 U[NT], D[NT];
+    double pb[NT], pbu[NT], pbl[NT], pe[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        U[q] = d4{0.0, 0.0, 0.0, 0.0};
+        pb[q] = pbu[q] = pbl[q] = pe[q] = 0.0;
+    }
+    double wn[2], xn[2][NT];                              // operands of two k-steps in flight
+    auto fetch = [&](int p, int k, bool ok) {             // neuron k of this lane group
+        const unsigned kx = __umul24(k, M8) + 8u * (16 * wave + r);
+        wn[p] = A.W1[k * 16 + r];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const double x = *(const double*)((const char*)A.WTt + (kx + 512u * q));
+            xn[p][q] = ok ? x : 0.0;
+        }
+    };
+    auto active = [&](int p, int c0) {
+        const int c = c0 + g;
+        const double w = wn[p], b = L.ab[c], e = L.ae[c];
+        double x[NT];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) x[q] = xn[p][q];
+        fetch(p, L.ka[c + 8], c + 8 < na);                // past the end: padding
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, x[q], U[q], 0, 0, 0);
+            pb[q] = __builtin_fma(x[q], b, pb[q]);
+            if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
+        }
+    };
+    auto unstable = [&](int p, int c0) {
+        const int c = c0 + g;
+        const double w = wn[p], s = L.us[c], a = L.ua[c], t = L.ut[c], b = L.ub[c], e = L.ue[c];
+        double x[NT];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) x[q] = xn[p][q];
+        fetch(p, L.ku[c + 8], c + 8 < nu);                // past the end: padding
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const bool pos = x[q] >= 0.0;
+            const double xs = x[q] * s, xa = x[q] * a, xt = x[q] * t;
+            const double ou = pos ? xs : xa, ol = pos ? xa : xs;
+            U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ou, U[q], 0, 0, 0);
+            D[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ol, D[q], 0, 0, 0);
+            pbu[q] = __builtin_fma(ou, b, pbu[q] + (pos ? xt : 0.0));
+            pbl[q] = __builtin_fma(ol, b, pbl[q] + (pos ? 0.0 : xt));
+            if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
+        }
+    };
+    fetch(0, L.ka[g], g < na);
+    fetch(1, L.ka[g + 4], g + 4 < na);
+    int c0 = 0;
+    for (; c0 + 4 < na; c0 += 8) {
+        active(0, c0);
+        active(1, c0 + 4);
+    }
+    if (c0 < na) active(0, c0);
+    fetch(0, L.ku[g], g < nu);
+    fetch(1, L.ku[g + 4], g + 4 < nu);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) D[q] = U[q];
+    c0 = 0;
+    for (; c0 + 4 < nu; c0 += 8) {
+        unstable(0, c0);
+        unstable(1, c0 + 4);
+    }
+    if (c0 < nu) unstable(0, c0);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const int row = 16 * (wave + 4 * q) + r;
+        const double h = hid_concretize<ADJ>(A, box, row, 0, U[q], pb[q] + pbu[q], pe[q], g);
+        const double l = hid_concretize<ADJ>(A, box, row, 1, D[q], pb[q] + pbl[q], pe[q], g);
+        // only an unstable neuron's rows are read back
+        if (ADJ && l < 0.0 && h > 0.0) {
+            hid_store0(A, box, row, 0, U[q], g);
+            hid_store0(A, box, row, 1, D[q], g);
+        }
+    }
+}
+
 // Target layer 2: Lambda_0 = (W_2 (.) S_1) W_1, one workgroup per box; wave w owns the
 // row tiles w, w + 4, ... (up to four) and runs all k-steps, so nothing is summed
 // over waves.  A: W_1 rows of the listed neurons, B: the same rows of W_2^T.
 //
 // What bounds it: the operands' path from L2 (five reads a k-step for 4 or 8 MFMA).
-// 3,200 boxes of the 16-256-256-256-12 network: 173 us with the concretisation
-// (one workgroup per mode with its k-steps split over the waves: 690 us, and 42 us).
+// 3,200 boxes of the 16-256-256-256-12 network: 158 us with the concretisation
+// (173 us with one k-step in flight and a branch per row tile; one workgroup per mode
+// with its k-steps split over the waves: 690 us, and 42 us).
 template <bool ADJ>
 __global__ void __launch_bounds__(256) nn_hid1_kernel(HidArgs A) {
     __shared__ HidLists L;
     __shared__ int cnt[2][4];
-    const int box = blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int box = blockIdx.x, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (ADJ && !A.ok[box]) return;
     hid_lists<ADJ>(L, A, (size_t)box * A.bstride, A.w1, A.b1, cnt);
-    const int na = L.na, nu = L.nu, M = A.M, nrt = (M + 15) >> 4;
-    const int nmine = (nrt - wave + 3) >> 2;              // row tiles of this wave
-    d4 U[4], D[4];
-    double pb[4], pbu[4], pbl[4], pe[4];
+    // the loops for this wave's number of row tiles (no branch inside a k-step, so that
+    // the waits on loads in flight are exact)
+    const int nmine = ((A.M >> 4) - wave + 3) >> 2;
+    if (nmine == 4) hid1_tiles<ADJ, 4>(A, L, box, wave, r, g);
+    else if (nmine == 3) hid1_tiles<ADJ, 3>(A, L, box, wave, r, g);
+    else if (nmine == 2) hid1_tiles<ADJ, 2>(A, L, box, wave, r, g);
+    else if (nmine == 1) hid1_tiles<ADJ, 1>(A, L, box, wave, r, g);
+}
+
+// The first step of target layer 3 for one wave: NT tiles of 16 listed columns of W_2
+// (byte offsets wcol8 of the lane's columns), two tiles of target rows (row8).  Two
+// k-steps of operands are in flight.
+template <bool ADJ, int NT>
+__device__ __forceinline__ void hid2_first(const HidArgs& A, const HidLists& L, const unsigned (&wcol8)[4],
+                                           const unsigned (&row8)[2], int wave, int g, d4 (&U)[4][2], d4 (&D)[4][2],
+                                           double (&pb)[2], double (&pbu)[2], double (&pbl)[2], double (&pe)[2]) {
+    const int na = L.na, nu = L.nu;
+    const unsigned N8 = 8u * A.w1, M8 = 8u * A.M;
+    double wn[2][4], xn[2][2];
+    auto fetch = [&](int p, int k, bool ok) {
+        const unsigned kw = __umul24(k, N8), kx = __umul24(k, M8);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        U[q] = D[q] = d4{0.0, 0.0, 0.0, 0.0};
-        pb[q] = pbu[q] = pbl[q] = pe[q] = 0.0;
-    }
-    double wn, xn[4];
-    auto fetch = [&](int k, bool ok) {                    // neuron k of this lane group
-        wn = A.W1[k * 16 + r];
+        for (int i = 0; i < NT; ++i) wn[p][i] = *(const double*)((const char*)A.W2 + (kw + wcol8[i]));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int row = 16 * (wave + 4 * q) + r;
-            const bool in = ok && row < M;
-            const double x = A.WTt[in ? (size_t)k * M + row : 0];
-            xn[q] = in ? x : 0.0;
+        for (int q = 0; q < 2; ++q) {
+            const double x = *(const double*)((const char*)A.WTt + (kx + row8[q]));
+            xn[p][q] = ok ? x : 0.0;
         }
     };
-    if (nmine > 0) {
-        fetch(L.ka[g], g < na);
-        for (int c0 = 0; c0 < na; c0 += 4) {
-            const int c = c0 + g;
-            const double w = wn, b = L.ab[c], e = L.ae[c];
-            double x[4];
+    auto active = [&](int p, int c0) {
+        const int c = c0 + g;
+        double w[4], x[2];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = xn[q];
-            const int cn = c + 4;
-            if (c0 + 4 < na) fetch(L.ka[cn], cn < na);
-            else fetch(L.ku[g], g < nu);                  // the first unstable k-step
+        for (int i = 0; i < NT; ++i) w[i] = wn[p][i];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (q >= nmine) break;
-                U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, x[q], U[q], 0, 0, 0);
+        for (int q = 0; q < 2; ++q) x[q] = xn[p][q];
+        fetch(p, L.ka[c + 8], c + 8 < na);                // past the end: padding
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], x[q], U[i][q], 0, 0, 0);
+        if (((c0 >> 2) & 3) == wave) {
+            const double b = L.ab[c], e = L.ae[c];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
                 pb[q] = __builtin_fma(x[q], b, pb[q]);
                 if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
             }
         }
-        if (na == 0) fetch(L.ku[g], g < nu);
+    };
+    auto unstable = [&](int p, int c0) {
+        const int c = c0 + g;
+        double w[4], x[2], ou[2], ol[2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) D[q] = U[q];
-        for (int c0 = 0; c0 < nu; c0 += 4) {
-            const int c = c0 + g;
-            const double w = wn, s = L.us[c], a = L.ua[c], t = L.ut[c], b = L.ub[c], e = L.ue[c];
-            double x[4];
+        for (int i = 0; i < NT; ++i) w[i] = wn[p][i];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = xn[q];
-            const int cn = c + 4;
-            fetch(L.ku[cn], cn < nu);                     // past the end: padding
+        for (int q = 0; q < 2; ++q) x[q] = xn[p][q];
+        fetch(p, L.ku[c + 8], c + 8 < nu);                // past the end: padding
+        const double s = L.us[c], a = L.ua[c];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (q >= nmine) break;
+        for (int q = 0; q < 2; ++q) {
+            const bool pos = x[q] >= 0.0;
+            ou[q] = x[q] * (pos ? s : a);
+            ol[q] = x[q] * (pos ? a : s);
+        }
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ou[q], U[i][q], 0, 0, 0);
+                D[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ol[q], D[i][q], 0, 0, 0);
+            }
+        if (((c0 >> 2) & 3) == wave) {
+            const double t = L.ut[c], b = L.ub[c], e = L.ue[c];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const double xt = x[q] * t;
                 const bool pos = x[q] >= 0.0;
-                const double xs = x[q] * s, xa = x[q] * a, xt = x[q] * t;
-                const double ou = pos ? xs : xa, ol = pos ? xa : xs;
-                U[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ou, U[q], 0, 0, 0);
-                D[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, ol, D[q], 0, 0, 0);
-                pbu[q] = __builtin_fma(ou, b, pbu[q] + (pos ? xt : 0.0));
-                pbl[q] = __builtin_fma(ol, b, pbl[q] + (pos ? 0.0 : xt));
+                pbu[q] = __builtin_fma(ou[q], b, pbu[q] + (pos ? xt : 0.0));
+                pbl[q] = __builtin_fma(ol[q], b, pbl[q] + (pos ? 0.0 : xt));
                 if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
             }
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (q >= nmine) break;
-            const int row = 16 * (wave + 4 * q) + r;
-            const double h = hid_concretize<ADJ>(A, box, row, 0, U[q], pb[q] + pbu[q], pe[q], g);
-            const double l = hid_concretize<ADJ>(A, box, row, 1, D[q], pb[q] + pbl[q], pe[q], g);
-            // only an unstable neuron's rows are read back
-            if (ADJ && row < M && l < 0.0 && h > 0.0) {
-                hid_store0(A, box, row, 0, U[q], g);
-                hid_store0(A, box, row, 1, D[q], g);
-            }
-        }
+    };
+    fetch(0, L.ka[g], g < na);
+    fetch(1, L.ka[g + 4], g + 4 < na);
+    int c0 = 0;
+    for (; c0 + 4 < na; c0 += 8) {
+        active(0, c0);
+        active(1, c0 + 4);
     }
+    if (c0 < na) active(0, c0);
+    fetch(0, L.ku[g], g < nu);
+    fetch(1, L.ku[g + 4], g + 4 < nu);
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) D[i][q] = U[i][q];
+    c0 = 0;
+    for (; c0 + 4 < nu; c0 += 8) {
+        unstable(0, c0);
+        unstable(1, c0 + 4);
+    }
+    if (c0 < nu) unstable(0, c0);
 }
 
 // Target layer 3, 32 of its rows and one box per workgroup: Lambda_1 = (W_3 (.) S_2) W_2
@@ -261,8 +376,9 @@ __global__ void __launch_bounds__(256) nn_hid1_kernel(HidArgs A) {
 // What bounds it: FP64 MFMA (about 1,000 a workgroup of the 16-256-256-256-12
 // network where both modes over all kept neurons and every column took 2,416: 0.7 ms
 // at the peak rate) and the latency of the operand reads from L2, two waves a SIMD.
-// 3,200 boxes: 1.76 ms, the adjoint's 1.78 ms (every column of Lambda_1: 2.12 ms;
-// one workgroup per mode and 16 rows with Lambda in LDS between the steps: 4.2 ms,
+// 3,200 boxes: 1.37 ms, the adjoint's 1.50 ms (one k-step in flight, and branches on
+// the tiles in each: 1.76 ms; eight waves of half the tiles each, four a SIMD: the
+// same 1.77; every column of Lambda_1: 2.12 ms; one workgroup per mode and 16 rows with Lambda in LDS between the steps: 4.2 ms,
 // and 42 us to concretise; the adjoint's general pass 6.4 ms).
 template <bool ADJ>
 __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
@@ -308,94 +424,24 @@ __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
     // the workgroups, so that the waves with a tile more spread over the SIMDs)
     const int na = L.na, nu = L.nu, nt = (n1 + 15) >> 4;
     const int first = (wave + blockIdx.x + blockIdx.y) & 3, nmine = (nt - first + 3) >> 2;
-    int wcol[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) wcol[i] = col1[i < nmine ? 16 * (first + 4 * i) + r : 0];
     d4 U[4][2], D[4][2];
     double pb[2] = {0.0, 0.0}, pbu[2] = {0.0, 0.0}, pbl[2] = {0.0, 0.0}, pe[2] = {0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int q = 0; q < 2; ++q) U[i][q] = d4{0.0, 0.0, 0.0, 0.0};
-    double wn[4], xn[2];
-    auto fetch = [&](int k, bool ok) {
+    // first step, the loops for this wave's number of tiles (no branch inside a k-step,
+    // so that the waits on loads in flight are exact)
+    unsigned wcol8[4], row8[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) wn[i] = A.W2[(size_t)k * N + wcol[i]];
+    for (int i = 0; i < 4; ++i) wcol8[i] = 8u * col1[i < nmine ? 16 * (first + 4 * i) + r : 0];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int row = row0 + 16 * q + r;
-            const bool in = ok && row < M;
-            const double x = A.WTt[in ? (size_t)k * M + row : 0];
-            xn[q] = in ? x : 0.0;
-        }
-    };
-    fetch(L.ka[g], g < na);
-    for (int c0 = 0; c0 < na; c0 += 4) {
-        const int c = c0 + g;
-        double w[4], x[2];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = wn[i];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) x[q] = xn[q];
-        const int cn = c + 4;
-        if (c0 + 4 < na) fetch(L.ka[cn], cn < na);
-        else fetch(L.ku[g], g < nu);                      // the first unstable k-step
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i >= nmine) break;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], x[q], U[i][q], 0, 0, 0);
-        }
-        if (((c0 >> 2) & 3) == wave) {
-            const double b = L.ab[c], e = L.ae[c];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                pb[q] = __builtin_fma(x[q], b, pb[q]);
-                if (!ADJ) pe[q] = __builtin_fma(fabs(x[q]), e, pe[q]);
-            }
-        }
-    }
-    if (na == 0) fetch(L.ku[g], g < nu);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) D[i][q] = U[i][q];
-    for (int c0 = 0; c0 < nu; c0 += 4) {
-        const int c = c0 + g;
-        double w[4], ou[2], ol[2];
-        const double s = L.us[c], a = L.ua[c];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = wn[i];
-        if (((c0 >> 2) & 3) == wave) {
-            const double t = L.ut[c], b = L.ub[c], e = L.ue[c];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const double x = xn[q], xt = x * t;
-                const bool pos = x >= 0.0;
-                pbu[q] = __builtin_fma(x * (pos ? s : a), b, pbu[q] + (pos ? xt : 0.0));
-                pbl[q] = __builtin_fma(x * (pos ? a : s), b, pbl[q] + (pos ? 0.0 : xt));
-                if (!ADJ) pe[q] = __builtin_fma(fabs(x), e, pe[q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const double x = xn[q];
-            const bool pos = x >= 0.0;
-            ou[q] = x * (pos ? s : a);
-            ol[q] = x * (pos ? a : s);
-        }
-        const int cn = c + 4;
-        fetch(L.ku[cn], cn < nu);                         // past the end: padding
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i >= nmine) break;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ou[q], U[i][q], 0, 0, 0);
-                D[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ol[q], D[i][q], 0, 0, 0);
-            }
-        }
-    }
+    for (int q = 0; q < 2; ++q) row8[q] = 8u * (row0 + 16 * q < M ? row0 + 16 * q + r : row0 + r);
+    if (nmine == 4) hid2_first<ADJ, 4>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
+    else if (nmine == 3) hid2_first<ADJ, 3>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
+    else if (nmine == 2) hid2_first<ADJ, 2>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
+    else if (nmine == 1) hid2_first<ADJ, 1>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
+    else hid2_first<ADJ, 0>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
     // second step: this wave's listed neurons 16 tt + 4 j + g of layer 1
     d4 Z[2][2];                                           // (row tile, mode): Lambda_0^T
     double sb[2][2], se[2][2];
