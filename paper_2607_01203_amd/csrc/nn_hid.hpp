@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(256) nn_hid1_kernel(HidArgs A) {
 // k-steps of operands are in flight.
 template <bool ADJ, int NT>
 __device__ __forceinline__ void hid2_first(const HidArgs& A, const HidLists& L, const unsigned (&wcol8)[4],
-                                           const unsigned (&row8)[2], int wave, int g, d4 (&U)[4][2], d4 (&D)[4][2],
+                                           const unsigned (&row8)[2], int first, int g, d4 (&U)[4][2], d4 (&D)[4][2],
                                            double (&pb)[2], double (&pbu)[2], double (&pbl)[2], double (&pe)[2]) {
     const int na = L.na, nu = L.nu;
     const unsigned N8 = 8u * A.w1, M8 = 8u * A.M;
@@ -299,7 +299,7 @@ __device__ __forceinline__ void hid2_first(const HidArgs& A, const HidLists& L, 
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int q = 0; q < 2; ++q) U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], x[q], U[i][q], 0, 0, 0);
-        if (((c0 >> 2) & 3) == wave) {
+        if (((c0 >> 2) & 3) == first) {
             const double b = L.ab[c], e = L.ae[c];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -330,7 +330,7 @@ __device__ __forceinline__ void hid2_first(const HidArgs& A, const HidLists& L, 
                 U[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ou[q], U[i][q], 0, 0, 0);
                 D[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], ol[q], D[i][q], 0, 0, 0);
             }
-        if (((c0 >> 2) & 3) == wave) {
+        if (((c0 >> 2) & 3) == first) {
             const double t = L.ut[c], b = L.ub[c], e = L.ue[c];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -421,7 +421,8 @@ __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
     }
     hid_lists<ADJ>(L, A, o2, A.w2, A.b2, cnt);
     // this wave's tiles of the listed columns: first, first + 4, ... (first rotates over
-    // the workgroups, so that the waves with a tile more spread over the SIMDs)
+    // the workgroups, so that the waves with a tile more spread over the SIMDs; every sum
+    // below is split and added by `first`, so that a box's result does not depend on its place)
     const int na = L.na, nu = L.nu, nt = (n1 + 15) >> 4;
     const int first = (wave + blockIdx.x + blockIdx.y) & 3, nmine = (nt - first + 3) >> 2;
     d4 U[4][2], D[4][2];
@@ -437,11 +438,11 @@ __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
     for (int i = 0; i < 4; ++i) wcol8[i] = 8u * col1[i < nmine ? 16 * (first + 4 * i) + r : 0];
 #pragma unroll
     for (int q = 0; q < 2; ++q) row8[q] = 8u * (row0 + 16 * q < M ? row0 + 16 * q + r : row0 + r);
-    if (nmine == 4) hid2_first<ADJ, 4>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
-    else if (nmine == 3) hid2_first<ADJ, 3>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
-    else if (nmine == 2) hid2_first<ADJ, 2>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
-    else if (nmine == 1) hid2_first<ADJ, 1>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
-    else hid2_first<ADJ, 0>(A, L, wcol8, row8, wave, g, U, D, pb, pbu, pbl, pe);
+    if (nmine == 4) hid2_first<ADJ, 4>(A, L, wcol8, row8, first, g, U, D, pb, pbu, pbl, pe);
+    else if (nmine == 3) hid2_first<ADJ, 3>(A, L, wcol8, row8, first, g, U, D, pb, pbu, pbl, pe);
+    else if (nmine == 2) hid2_first<ADJ, 2>(A, L, wcol8, row8, first, g, U, D, pb, pbu, pbl, pe);
+    else if (nmine == 1) hid2_first<ADJ, 1>(A, L, wcol8, row8, first, g, U, D, pb, pbu, pbl, pe);
+    else hid2_first<ADJ, 0>(A, L, wcol8, row8, first, g, U, D, pb, pbu, pbl, pe);
     // second step: this wave's listed neurons 16 tt + 4 j + g of layer 1
     d4 Z[2][2];                                           // (row tile, mode): Lambda_0^T
     double sb[2][2], se[2][2];
@@ -480,9 +481,9 @@ __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) part[wave][m][i][lane] = Z[m >> 1][m & 1][i];
-        psum[wave][m][0][lane] = sb[m >> 1][m & 1];
-        psum[wave][m][1][lane] = se[m >> 1][m & 1];
+        for (int i = 0; i < 4; ++i) part[first][m][i][lane] = Z[m >> 1][m & 1][i];
+        psum[first][m][0][lane] = sb[m >> 1][m & 1];
+        psum[first][m][1][lane] = se[m >> 1][m & 1];
     }
     __syncthreads();
     d4 z = d4{0.0, 0.0, 0.0, 0.0};
