@@ -48,6 +48,7 @@ struct TubeFP {
     uint32_t* cert;       // NULL, or [B]: written (state & FP_CERT) by a launch that finds every
                           // trajectory certified (the sweep enqueued after the last one)
     double conv;          // acceptance also needs |C_t - C_{t-1}| within conv (relative to sigma)
+    int sweep;            // t
 };
 
 struct TubeArgs {
@@ -64,6 +65,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double se_row(const double (&e)[6], int q) { return q == 3 ? e[3] : e[4]; }
 constexpr int TM_RT = 5;        // 16-row tiles per wave and row group
+typedef double node_d2 __attribute__((ext_vector_type(2), aligned(8)));    // two neighbouring rows of a tube
 
 // The tube map as a contraction on FP64 MFMA (v_mfma_f64_16x16x4f64):
 //   [mu; sigma][row (k, r)][col] = sum_{kk = (j, q)} T[row][kk] [c; w][kk][col],
@@ -78,8 +80,9 @@ constexpr int TM_RT = 5;        // 16-row tiles per wave and row group
 //
 // row tile of slot s of a wave: tiles are dealt so that each wave gets a
 // mix of short (early steps) and long (late steps) K ranges
+template <int RT = TM_RT>
 __device__ __forceinline__ int tm_tile(int wave, int s, int group) {
-    const int base = group * 4 * TM_RT + 4 * s;
+    const int base = group * 4 * RT + 4 * s;
     return base + ((s & 1) ? 3 - wave : wave);
 }
 
@@ -209,7 +212,7 @@ __global__ void __launch_bounds__(256) tube_map_kernel(const double* __restrict_
     // kk = k0 + lq = 6 j + q, and the A offset of kk is abase - (48 j - q).
 #pragma unroll
     for (int s = 0; s < TM_RT; ++s) {
-        const int rt = tm_tile(wave, s, blockIdx.y);
+        const int rt = tm_tile<>(wave, s, blockIdx.y);
         const int kmax = rt < nrt ? 6 * min(N - 1, 2 * rt + 1) : 0;
         // A[(k, rr)][(j, q)] = Phi_{k-j-1}[rr][q] at sp[(k - j + 3) * 48 + rr * 6 + q]
         const int abase = (((16 * rt + lr) >> 3) + 3) * 48 + ((16 * rt + lr) & 7) * 6;
@@ -291,12 +294,18 @@ struct Tube2Args {
 
 __device__ double kZero8[8];          // zero-initialised; stands in for Phi at a single step
 
+// What bounds it: the tube's traffic (73 MB a sweep at 28 nodes x 256 x 40, 11 us at the
+// rate of a copy that size) and, before and after it, the latency of the staging and of
+// the last slots' stores.  Rows are loaded and stored in pairs at 32-bit offsets from the
+// workgroup's first trajectory: 20 us a sweep (single rows at 64-bit addresses, settled
+// steps moved too: 24 us).
+//
 // Loads are issued unconditionally (clamped to a valid address, the value
 // then selected) so that no load sits in a branch: the wait counters stay
 // exact and a wait for one batch of loads never also waits for a later batch.
 // LONG (more than 65 steps) stages Phi and the residuals in passes, before
 // and after the tube loads; the short form has no loop around a load.
-template <bool FP, bool LONG>
+template <bool FP, bool LONG, int RT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) tube_map2_kernel(const double* __restrict__ phi, Tube2Args A, TubeFP P) {
     // LDS: the affine table [N][8] and per-lag affine sums [N-1][8] (FP64), a
     // spare [4]; then FP32: Phi rows' columns 3, 4 for lags -4..N-1 [(N+4)*16],
@@ -304,15 +313,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     extern __shared__ double lds2[];
     __shared__ uint32_t sbad[16];
     __shared__ int sjinf[16];
-    if (FP && P.state[A.B] == 0u) {           // every trajectory certified by an earlier sweep
-        if (P.cert) {
-            const int64_t stride = (int64_t)gridDim.x * gridDim.y * blockDim.x;
-            for (int64_t b = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; b < A.B;
-                 b += stride)
-                P.cert[b] = P.state[b] & FP_CERT;
-        }
-        return;
-    }
+    const uint32_t n_open = FP ? P.state[A.B] : 1u;      // looked at after the loads are issued
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = A.N, U = A.U, nx = 6 * U, n = 8 * U;
@@ -332,16 +333,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     // this lane's accumulator column (lr) and its trajectory's state word
     const int lr = lane & 15, lq = lane >> 4;
     const bool cin = lr < ncol;
-    int64_t ob_s, ob_i;
-    uint32_t stw = 0u;
+    // Its accumulators are rows rr0 .. rr0 + 3 (two pairs) of step 2 rt + kh: the byte
+    // offsets of the pairs within the trajectories of this workgroup (at most 16, of U
+    // nodes in all or one more trajectory than that: below 2^32)
+    const int kh = lq >> 1;
+    uint32_t ofs[2], stw = 0u;
+    int bsel;
     {
         const int col = min(c0 + lr, cols - 1);
         const int bb = col / U, nd = col - bb * U;
-        const int64_t tub = (int64_t)bb * N * n;
-        ob_s = tub + 6 * nd;
-        ob_i = tub + nx + 2 * nd - 6;
+        bsel = bb - bfirst;
+        const uint32_t tub = (uint32_t)bsel * (uint32_t)N * (uint32_t)n;
+        ofs[0] = 8u * (tub + 6 * nd + ((lq & 1) ? 4 : 0));
+        ofs[1] = 8u * (tub + ((lq & 1) ? nx + 2 * nd : 6 * nd + 2));
         if (FP) stw = P.state[bb];
     }
+    const int64_t tub0 = (int64_t)bfirst * N * n;
     if (tid < 16) { sbad[tid] = 0u; sjinf[tid] = 0x7fffffff; }
     // Every load of the first pass is issued before any of it is used, in the
     // order it is needed: Phi (columns 3, 4 and the per-lag affine sums), the
@@ -426,8 +433,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     };
     const int nrt = (N + 1) >> 1;
     const bool frozen = FP && (stw & FP_CERT) != 0u;
-    const int64_t ob_d = ob_i - ob_s;       // (an arithmetic select keeps both offsets in registers)
-    auto tube_off = [&](int rr, int k) -> int64_t { return ob_s + (rr < 6 ? 0 : ob_d) + rr + (int64_t)k * n; };
     // The slots of a wave run from the longest K range down or the other way
     // round, alternating between blocks 256 apart (the two blocks that share
     // a compute unit when the grid holds more than one block per unit), so that
@@ -435,17 +440,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     // C_{t-1} under this lane's accumulators is read two slots ahead of its use;
     // mi[p], si[p] belong to the p-th slot processed.
     const bool down = ((blockIdx.x >> 8) & 1) == 0;
-    auto ord = [&](int p) { return down ? TM_RT - 1 - p : p; };
-    double mi[TM_RT][4], si[TM_RT][4];
+    auto ord = [&](int p) { return down ? RT - 1 - p : p; };
+    // Steps at which C_t = C_{t-1} = C_{t-2} whatever the start (the tube at k uses steps
+    // j < k): tiles of such steps are neither read nor written (the buffer holds C_{t-2}).
+    const int settled = FP ? P.sweep - 3 : -1;
+    node_d2 mi[RT][2], si[RT][2];
     auto tube_load = [&](int p) {
-        const int rt = tm_tile(wave, ord(p), blockIdx.y);
+        // (a tile past the end, a settled one: the first step, unused; a step past the end: the one before)
+        const int rt = tm_tile<RT>(wave, ord(p), blockIdx.y);
+        const bool use = rt < nrt && 2 * rt + 1 > settled;
+        const char* m = reinterpret_cast<const char*>(P.mu_in + tub0 + (use ? (int64_t)2 * rt * n : 0));
+        const char* g_ = reinterpret_cast<const char*>(P.sg_in + tub0 + (use ? (int64_t)2 * rt * n : 0));
+        const uint32_t ko = use && 2 * rt + 1 < N ? 8u * n * kh : 0u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = 16 * rt + 4 * lq + i, k = r >> 3;
-            const bool ok = cin && rt < nrt && k < N;     // (a frozen column's values go unused)
-            const int64_t o = ok ? tube_off(r & 7, k) : ob_s;
-            mi[p][i] = P.mu_in[o];
-            si[p][i] = P.sg_in[o];
+        for (int i = 0; i < 2; ++i) {
+            mi[p][i] = *reinterpret_cast<const node_d2*>(m + (ofs[i] + ko));
+            si[p][i] = *reinterpret_cast<const node_d2*>(g_ + (ofs[i] + ko));
         }
     };
     phi_load(0);
@@ -460,7 +470,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     if (!LONG) phi_store(0);
     if (FP) {
         tube_load(0);
-        tube_load(1);
+        if (RT > 1) tube_load(1);
+    }
+    if (FP && n_open == 0u) {                 // every trajectory certified by an earlier sweep
+        if (P.cert) {
+            const int64_t stride = (int64_t)gridDim.x * gridDim.y * blockDim.x;
+            for (int64_t b = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; b < A.B;
+                 b += stride)
+                P.cert[b] = P.state[b] & FP_CERT;
+        }
+        return;
     }
     // zero lags -4..-1 and N-1 of sp (the rows past a tile's causal range)
     if (tid < 64) sp[tid] = 0.0f;
@@ -492,9 +511,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     // next iteration's fragments read before this one's MFMAs;
     // kk = k4 + lq = 2 j + q', the A entry of kk is sp[(k - j + 3) * 16 + rr * 2 + q']
 #pragma unroll
-    for (int p = 0; p < TM_RT; ++p) {
-        if (FP && p + 2 < TM_RT) tube_load(p + 2);
-        const int rt = tm_tile(wave, ord(p), blockIdx.y);
+    for (int p = 0; p < RT; ++p) {
+        if (FP && p + 2 < RT) tube_load(p + 2);
+        const int rt = tm_tile<RT>(wave, ord(p), blockIdx.y);
         if (rt >= nrt) continue;
         const int r = 16 * rt + lr, kr = r >> 3, rrr = r & 7;
         const int kmax = 2 * min(nst, 2 * rt + 1);
@@ -535,33 +554,44 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
                 vd[i] += (double)v0[i] + (double)v1[i];
             }
         }
-        if (!cin) continue;
+        const int k = 2 * rt + kh;
+        if (!cin || k >= N) continue;
+        const bool fixed = FP && 2 * rt + 1 <= settled;
+        bool bad = false;
+        node_d2 mo[2], so[2];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int rr4 = 16 * rt + 4 * lq + i, k = rr4 >> 3, rr = rr4 & 7;
-            if (k >= N) continue;
             const double mF = md[i];
             // both sums have nonnegative terms; rounded upward as a whole (FP32
             // chunks and FP64 sums), 2^-90 for products lost to underflow
             const double tot = vd[i] + dt[i];
             const double sF = k > sjl ? INFINITY : tot + tot * (A.wid + A.wid32) + 0x1p-90;
-            double so = sF * A.scale + A.shift;
+            double s_ = sF * A.scale + A.shift;
             if (FP) {
                 // [mF - sF, mF + sF] inside [mi - si, mi + si], with the rounding of the
                 // test covered; a tube that is not finite is never accepted
-                so = sF + sF * P.tol + P.abs_;
-                const double dm = fabs(mF - mi[p][i]);
-                const bool contained = sF <= DBL_MAX && (dm + sF) * (1.0 + 0x1p-50) <= si[p][i];
+                s_ = sF + sF * P.tol + P.abs_;
+                const double m0_ = fixed ? mF : mi[p][i >> 1][i & 1], s0_ = fixed ? s_ : si[p][i >> 1][i & 1];
+                const double dm = fabs(mF - m0_);
+                const bool contained = sF <= DBL_MAX && (dm + sF) * (1.0 + 0x1p-50) <= s0_;
                 // converged: the next iterate within conv of this one (the slack 2^-44 si
                 // absorbs the rounding of the sums, far below any conv in use)
-                const double slack = P.conv * si[p][i] + 0x1p-44 * si[p][i];
-                const bool conv = fabs(so - si[p][i]) <= slack + 2.0 * P.abs_ && dm <= slack + P.abs_;
-                if (!frozen && !(contained && conv)) sbad[(c0 + lr) / U - bfirst] = 1u;
+                const double slack = P.conv * s0_ + 0x1p-44 * s0_;
+                const bool conv = fabs(s_ - s0_) <= slack + 2.0 * P.abs_ && dm <= slack + P.abs_;
+                bad |= !(contained && conv);
             }
-            if (!frozen) {
-                const int64_t o = tube_off(rr, k);
-                A.mu[o] = mF;
-                A.sigma[o] = so;
+            mo[i >> 1][i & 1] = mF;
+            so[i >> 1][i & 1] = s_;
+        }
+        if (FP && frozen) continue;
+        if (FP && bad) sbad[bsel] = 1u;
+        if (!fixed) {
+            char* m = reinterpret_cast<char*>(A.mu + tub0 + (int64_t)2 * rt * n);
+            char* g_ = reinterpret_cast<char*>(A.sigma + tub0 + (int64_t)2 * rt * n);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                *reinterpret_cast<node_d2*>(m + (ofs[i] + 8u * n * kh)) = mo[i];
+                *reinterpret_cast<node_d2*>(g_ + (ofs[i] + 8u * n * kh)) = so[i];
             }
         }
     }
@@ -707,6 +737,17 @@ static int launch_tube(int B, int N, int U, const double* phi, const double* e, 
 
 // Tube map of compact residuals (rows 3 and 4 of each node, the affine rows
 // (0, pad)); fp as launch_tube's
+// Row tiles a wave takes (RT): with one workgroup for all rows of 16 node columns a
+// small grid leaves compute units idle, with more every workgroup stages Phi and the
+// residuals again.  28 nodes, 40 steps, the whole fixed point (11 sweeps):
+//   batch        1    32    64   128   200   256   512
+//   RT = 1     183   228   278   387   500   564   972 us
+//   RT = 3     195   235   267   348   435   519   856
+//   RT = 5     224   269   300   352   443   488   793
+// One tile a wave up to about one workgroup per compute unit, three up to 384 column
+// groups (219 trajectories of 28 nodes).
+constexpr int TM2_GRID_1 = 320, TM2_GRID_3 = 384;
+
 static int launch_tube2(int B, int N, int U, const double* phi, const double* e, double pad, const double* c2,
                         const double* r2, double* mu, double* sigma, const TubeFP& fp, hipStream_t s,
                         double scale = 1.0, double shift = 0.0, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
@@ -722,17 +763,22 @@ static int launch_tube2(int B, int N, int U, const double* phi, const double* e,
     if (cols == 0 || N == 0) return LEB_OK;
     const int64_t gx = (cols + 15) / 16;
     const int nrt = (N + 1) / 2;
-    const int gy = (nrt + 4 * TM_RT - 1) / (4 * TM_RT);
+    const int rti = gx * ((nrt + 3) / 4) <= TM2_GRID_1 ? 0 : (gx <= TM2_GRID_3 ? 1 : 2);
+    const int rt = rti == 0 ? 1 : (rti == 1 ? 3 : TM_RT);
+    const int gy = (nrt + 4 * rt - 1) / (4 * rt);
     if (gx > 0x7fffffff || cols > 0x7fffffff) return LEB_EINVAL;
     const size_t nst = N > 1 ? N - 1 : 0;
     const size_t smem = ((size_t)N * 8 + nst * 8 + 4) * sizeof(double) +
                         ((size_t)(N + 4) * 16 + 2 * (2 * nst + 8) * 16) * sizeof(float);
     const bool isfp = fp.state != nullptr, lng = N > 65;
-    const int which = (isfp ? 2 : 0) + (lng ? 1 : 0);
+    const int which = (isfp ? 6 : 0) + (lng ? 3 : 0) + rti;
     using K2 = void (*)(const double*, Tube2Args, TubeFP);
-    static const K2 kern[4] = {tube_map2_kernel<false, false>, tube_map2_kernel<false, true>,
-                               tube_map2_kernel<true, false>, tube_map2_kernel<true, true>};
-    static size_t dyn_max[4] = {0, 0, 0, 0};
+    static const K2 kern[12] = {
+        tube_map2_kernel<false, false, 1>, tube_map2_kernel<false, false, 3>, tube_map2_kernel<false, false, TM_RT>,
+        tube_map2_kernel<false, true, 1>,  tube_map2_kernel<false, true, 3>,  tube_map2_kernel<false, true, TM_RT>,
+        tube_map2_kernel<true, false, 1>,  tube_map2_kernel<true, false, 3>,  tube_map2_kernel<true, false, TM_RT>,
+        tube_map2_kernel<true, true, 1>,   tube_map2_kernel<true, true, 3>,   tube_map2_kernel<true, true, TM_RT>};
+    static size_t dyn_max[12] = {};
     if (dyn_max[which] == 0) {
         hipFuncAttributes fa;
         if (hipFuncGetAttributes(&fa, (const void*)kern[which]) != hipSuccess) return LEB_EDEVICE;
@@ -752,7 +798,7 @@ static int launch_tube2(int B, int N, int U, const double* phi, const double* e,
 
 int launch_tube_map_compact(int B, int N, int U, const double* phi, const double* e, double pad, const double* c2,
                             const double* r2, double* mu, double* sigma, hipStream_t s, double scale, double shift) {
-    TubeFP none{nullptr, nullptr, nullptr, 0.0, 0.0, nullptr};
+    TubeFP none = {};
     return launch_tube2(B, N, U, phi, e, pad, c2, r2, mu, sigma, none, s, scale, shift);
 }
 
@@ -953,7 +999,7 @@ extern "C" int leb_fixed_point_solve(const leb_dynamics* dyn, int32_t batch, int
         int r = launch_pbh_chain(dyn, units, z, v, xm[a], xs[a], nullptr, nullptr, cb, rb, opt->pad, nullptr, s,
                                  &fold, b0, b1, true);
         if (r) return r;
-        const TubeFP fp{xm[a], xs[a], st[w], opt->tol, opt->inflate_abs, certified, opt->conv_tol};
+        const TubeFP fp{xm[a], xs[a], st[w], opt->tol, opt->inflate_abs, certified, opt->conv_tol, t};
         return launch_tube2(batch, N, U, phi, e, opt->pad, cb, rb, xm[w], xs[w], fp, s, 1.0, 0.0, t0, t1);
     };
     // Wait until the open count of sweep t is published: the bound launch of
@@ -1086,7 +1132,7 @@ extern "C" int leb_fixed_point_solve_noalloc(const leb_dynamics* dyn, int32_t ba
         if ((rc = launch_pbh_chain(dyn, units, z, v, xm[a], xs[a], nullptr, nullptr, cb, rb, opt->pad, nullptr, s,
                                    &fold, nullptr, nullptr, true)))
             return rc;
-        const TubeFP fp{xm[a], xs[a], st[w], opt->tol, opt->inflate_abs, certified, opt->conv_tol};
+        const TubeFP fp{xm[a], xs[a], st[w], opt->tol, opt->inflate_abs, certified, opt->conv_tol, t};
         if ((rc = launch_tube2(batch, N, U, phi, e, opt->pad, cb, rb, xm[w], xs[w], fp, s, 1.0, 0.0, nullptr,
                                nullptr)))
             return rc;

@@ -265,3 +265,25 @@ def test_fixed_point_boxes_sound_1e6(gpu, orc):
         eps = eps.reshape(e - s, per, 168)
         viol += int(((r > hi[s:e, None] + eps) | (r < lo[s:e, None] - eps)).sum())
     assert viol == 0
+
+
+@pytest.mark.parametrize("N", [2, 9, 40, 41, 67])
+def test_fixed_point_row_splits_agree(gpu, orc, N):
+    """A trajectory's certified tube does not depend on the batch around it: one,
+    three and five row tiles a wave of the tube map (by the grid's size), odd and
+    even horizons, settled steps left in place; the small batch against the oracle."""
+    import torch
+    import paper_2607_01203_amd as leb
+    tp = W.fixed_point_cfg(seed=60, batch=4, N=N, n_units=2)
+    print("case: fixed point row splits N=%d" % N, flush=True)
+    mu, sg, cert, sweeps = _solve(leb, tp, gpu)
+    _check_against_oracle(orc, tp, mu, sg, np.arange(4))
+    dyn = leb.dynamics_like(tp.batch.dyn)
+    for rep in (500, 800):
+        mu2, sg2, cert2, sweeps2 = leb.fixed_point_solve(dyn, _t(np.tile(tp.batch.z, (rep, 1, 1)), gpu),
+                                                         _t(np.tile(tp.batch.v, (rep, 1, 1)), gpu),
+                                                         _t(tp.phi, gpu), tp.e)
+        torch.cuda.synchronize()
+        assert sweeps2 == sweeps and (cert2.cpu().numpy().reshape(rep, 4) == cert).all()
+        assert (mu2.cpu().numpy().reshape(rep, *mu.shape) == mu).all()
+        assert (sg2.cpu().numpy().reshape(rep, *sg.shape) == sg).all()
