@@ -62,6 +62,8 @@ struct ChainArgs {
     double L0;
     double pad;
     int compact;     // 1: c_bar, rho_bar hold rows 3 and 4 of each node only, [unit][U][2]
+    // sweeps: the units are steps step0 .. step0 + steps - 1 of each trajectory of N steps
+    int N, step0, steps;
 };
 
 
@@ -70,9 +72,16 @@ __device__ __forceinline__ TileRef tile_ref(const PbhTile& p) {
                    global_ptr(p.r_hi), global_ptr(p.c_bar), global_ptr(p.rho_bar), global_ptr(p.flags), p.n};
 }
 
-// TILES: every workgroup has its own pointers (A.tiles); a form of its own, so that the
-// other form's loads and stores are known to be global ones.
-template <bool TILES>
+// PBH_TILES: every workgroup has its own pointers (A.tiles); a form of its own, so that
+// the other forms' loads and stores are known to be global ones.
+// PBH_SWEEP: a fixed-point sweep.  The bounds at step j do not change any more once the
+// tube there does not (C_{t-1} = C_{t-2} up to step t - 3, as the tube at a step uses
+// earlier steps only), and those of the last step are never used: sweep t bounds the steps
+// t - 2 .. N - 2 and leaves the other residuals as they are.  28 nodes x 256 x 40: 21.8 us
+// in the first sweeps, 18.2 from 1,024 workgroups (four a compute unit) down, the fixed
+// point 440 us (every step in every sweep: 22.6 and 474 us).
+enum { PBH_UNITS = 0, PBH_TILES = 1, PBH_SWEEP = 2 };
+template <int FORM>
 __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int U = A.U, T = A.T;
@@ -83,12 +92,24 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
     const int tid = threadIdx.x;
     TileRef t0;
     int64_t u0 = 0;
-    if (TILES) {
+    if (FORM == PBH_TILES) {
         t0 = tile_ref(A.tiles[blockIdx.x]);
     } else {
         u0 = (int64_t)blockIdx.x * T;
         const int64_t left = A.units - u0;
         t0.nloc = left < T ? (int)left : T;
+    }
+    const int lt = tid / U;
+    const int i = tid - lt * U;
+    if (FORM == PBH_SWEEP) {
+        // lane's row of the arrays, minus the lt that the accesses add
+        const uint32_t l = lt < t0.nloc ? lt : 0, un = (uint32_t)u0 + l, b = un / (uint32_t)A.steps;
+        const int64_t row = (int64_t)b * A.N + A.step0 + (int)(un - b * A.steps) - (int)l;
+        t0.Z = A.z + row * nx; t0.V = A.v + row * nu; t0.MU = A.mu + row * n; t0.SG = A.sigma + row * n;
+        t0.CB = A.c_bar + row * (2 * U); t0.RB = A.rho_bar + row * (2 * U);
+        t0.RLO = t0.RHI = nullptr; t0.FL = nullptr;
+    }
+    if (FORM == PBH_UNITS) {
         t0.Z = A.z + u0 * nx; t0.V = A.v + u0 * nu; t0.MU = A.mu ? A.mu + u0 * n : nullptr;
         t0.SG = A.sigma + u0 * n;
         t0.RLO = A.r_lo ? A.r_lo + u0 * nx : nullptr; t0.RHI = A.r_hi ? A.r_hi + u0 * nx : nullptr;
@@ -101,12 +122,12 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
     // span at most T <= PBH_BLOCK trajectories.)  A certified trajectory's tube is
     // frozen, so its residuals are not needed again.
     __shared__ uint32_t s_wopen[PBH_BLOCK / 64];
-    const bool fold = !TILES && A.fold.prev != nullptr;
+    constexpr bool fold = FORM == PBH_SWEEP;
     if (fold) {
         uint32_t my = 1u;
         if (A.fold.sweep > 0) {
-            const int64_t N = A.units / A.fold.B;
-            const int64_t b0 = u0 / N, nb = (u0 + t0.nloc - 1) / N - b0 + 1;
+            const uint32_t b0 = (uint32_t)u0 / (uint32_t)A.steps;
+            const int nb = t0.nloc > 0 ? (int)(((uint32_t)u0 + t0.nloc - 1) / (uint32_t)A.steps - b0) + 1 : 0;
             my = tid < nb ? fp_is_open(A.fold.prev[b0 + tid]) : 0u;
         }
 #pragma unroll
@@ -114,10 +135,8 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
         if ((tid & 63) == 0) s_wopen[tid >> 6] = my;
     }
     for (int q = tid; q < T; q += PBH_BLOCK) s_flag[q] = 0u;
-    const int lt = tid / U;
-    const int i = tid - lt * U;
     NodeIn d0;
-    node_load(t0, U, lt, i, d0);
+    if (FORM != PBH_SWEEP || t0.nloc > 0) node_load(t0, U, lt, i, d0);
     __syncthreads();      // s_flag cleared, s_wopen written
     if (fold) {
         uint32_t mine = 0u;
@@ -154,7 +173,7 @@ __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {
                                        __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
-        if (mine == 0u) return;       // every trajectory of this workgroup is certified
+        if (mine == 0u || t0.nloc <= 0) return;       // every trajectory of this workgroup is certified
     }
     node_pass(A, t0, d0, lt, i, s_sp, s_flag);
 }
@@ -175,6 +194,7 @@ int launch_pbh_chain(const leb_dynamics* dyn, int64_t units, const double* z, co
     a.fold = fold ? *fold : SweepFold{nullptr, nullptr, nullptr, 0, 0};
     a.tiles = nullptr;
     a.units = units;
+    a.N = a.step0 = a.steps = 0;
     a.U = dyn->n_units;
     a.T = PBH_BLOCK / a.U;
     a.c = dyn->dt / dyn->m;
@@ -182,13 +202,23 @@ int launch_pbh_chain(const leb_dynamics* dyn, int64_t units, const double* z, co
     a.L0 = dyn->rest_len;
     a.pad = pad;
     a.compact = compact ? 1 : 0;
-    int64_t blocks = (units + a.T - 1) / a.T;
+    if (fold) {
+        if (units > 0x7fffffff) return LEB_EINVAL;       // 32-bit unit indices (a tube of 137 GB and more)
+        a.N = (int)(units / fold->B);
+        a.step0 = std::max(fold->sweep - 1, 0);          // sweep t = fold->sweep + 1
+        a.steps = std::max(a.N - 1 - a.step0, 0);
+        a.units = (int64_t)fold->B * a.steps;
+        a.steps = std::max(a.steps, 1);                  // (a divisor; no units then)
+    }
+    int64_t blocks = (a.units + a.T - 1) / a.T;
+    if (fold) blocks = std::max<int64_t>(blocks, 1);     // the fold itself
     if (blocks > 0x7fffffff) return LEB_EINVAL;
+    const auto kern = fold ? pbh_chain_fwd<PBH_SWEEP> : pbh_chain_fwd<PBH_UNITS>;
     if (ev0)        // timed: events at the kernel's start and end
-        hipExtLaunchKernelGGL(pbh_chain_fwd<false>, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, ev0,
+        hipExtLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, ev0,
                               ev1, 0, a);
     else
-        hipLaunchKernelGGL(pbh_chain_fwd<false>, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, a);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PBH_BLOCK), pbh_smem_bytes(a.U), stream, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 
@@ -203,7 +233,7 @@ int launch_pbh_tiles(const leb_dynamics* dyn, const PbhTile* tiles, int n_tiles,
     a.kL = dyn->k_spring * dyn->rest_len;
     a.L0 = dyn->rest_len;
     a.pad = 0.0;
-    hipLaunchKernelGGL(pbh_chain_fwd<true>, dim3((unsigned)n_tiles), dim3(PBH_BLOCK), pbh_smem_bytes_T(a.U, T), stream, a);
+    hipLaunchKernelGGL(pbh_chain_fwd<PBH_TILES>, dim3((unsigned)n_tiles), dim3(PBH_BLOCK), pbh_smem_bytes_T(a.U, T), stream, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 

@@ -287,3 +287,24 @@ def test_fixed_point_row_splits_agree(gpu, orc, N):
         assert sweeps2 == sweeps and (cert2.cpu().numpy().reshape(rep, 4) == cert).all()
         assert (mu2.cpu().numpy().reshape(rep, *mu.shape) == mu).all()
         assert (sg2.cpu().numpy().reshape(rep, *sg.shape) == sg).all()
+
+
+@pytest.mark.parametrize("batch,N,U", [(1, 1, 3), (3, 2, 2), (5, 3, 100), (40, 5, 1)])
+def test_fixed_point_sweeps_past_the_horizon(gpu, orc, batch, N, U):
+    """More sweeps than steps: the last sweeps have no step left to bound (and a
+    single step none at all), and only fold the state words."""
+    import torch
+    import paper_2607_01203_amd as leb
+    tp = W.fixed_point_cfg(seed=70 + N, batch=batch, N=N, n_units=U)
+    print("case: fixed point past the horizon %d x %d x %d" % (batch, N, U), flush=True)
+    mu, sg, cert, sweeps = _solve(leb, tp, gpu)
+    assert (cert == 1).all() and sweeps <= N + 2
+    _check_against_oracle(orc, tp, mu, sg, np.arange(batch))
+    n = mu.shape[-1]
+    m2, s2 = (torch.zeros((batch, N, n), dtype=torch.float64, device=gpu) for _ in range(2))
+    c2 = torch.zeros(batch, dtype=torch.int32, device=gpu)
+    leb.fixed_point_solve_noalloc(leb.dynamics_like(tp.batch.dyn), _t(tp.batch.z, gpu), _t(tp.batch.v, gpu),
+                                  _t(tp.phi, gpu), tp.e, m2, s2, c2, max_sweeps=N + 6)
+    torch.cuda.synchronize()
+    assert (c2.cpu().numpy() == cert).all()
+    assert (m2.cpu().numpy() == mu).all() and (s2.cpu().numpy() == sg).all()
