@@ -78,7 +78,7 @@ def quadratic_dynamics(Q, nu=0) -> Dynamics:
     Q = Q.contiguous()
     nx, n = int(Q.shape[0]), int(Q.shape[1])
     d = Dynamics(DYN_QUADRATIC, nx, n - nx if nu is None else int(nu), 0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0,
-                 _dev_ptr(Q, "Q", torch.float64).value)
+                 _dev_ptr(Q, "Q", torch.float64))
     d._Q = Q
     return d
 
@@ -235,22 +235,25 @@ def _check(rc):
 
 
 def _dev_ptr(t, name, dtype=None):
+    # an int (ctypes converts it by argtypes): a c_void_p object costs as much as all the checks
     if t is None:
         return None
-    import torch
     if not t.is_cuda:
         raise LebError("%s must be a GPU tensor" % name)
     if dtype is not None and t.dtype != dtype:
         raise LebError("%s must be %s" % (name, dtype))
     if not t.is_contiguous():
         raise LebError("%s must be contiguous" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
+    """The raw handle of a stream, or of the current device's current stream
+    (0.3 us by the raw query; torch.cuda.current_stream() builds an object, 3 us)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def analytic_bound(dyn: Dynamics, z, v, sigma, mu=None, pad: float = 0.0, zonotope: bool = False,
@@ -265,15 +268,15 @@ def analytic_bound(dyn: Dynamics, z, v, sigma, mu=None, pad: float = 0.0, zonoto
     B, N = int(z.shape[0]), int(z.shape[1])
     f64 = torch.float64
     if out is None:
-        out = {"r_lo": torch.empty((B, N, dyn.nx), dtype=f64, device=z.device),
-               "r_hi": torch.empty((B, N, dyn.nx), dtype=f64, device=z.device),
-               "flags": torch.empty((B, N), dtype=torch.int32, device=z.device)}
+        out = {"r_lo": z.new_empty((B, N, dyn.nx), dtype=f64),
+               "r_hi": z.new_empty((B, N, dyn.nx), dtype=f64),
+               "flags": z.new_empty((B, N), dtype=torch.int32)}
         if zonotope:
-            out["c_bar"] = torch.empty((B, N, dyn.nx), dtype=f64, device=z.device)
-            out["rho_bar"] = torch.empty((B, N, dyn.nx), dtype=f64, device=z.device)
+            out["c_bar"] = z.new_empty((B, N, dyn.nx), dtype=f64)
+            out["rho_bar"] = z.new_empty((B, N, dyn.nx), dtype=f64)
         if jacobians:
-            out["A"] = torch.empty((B, N, dyn.nx, dyn.nx), dtype=f64, device=z.device)
-            out["B"] = torch.empty((B, N, dyn.nx, dyn.nu), dtype=f64, device=z.device)
+            out["A"] = z.new_empty((B, N, dyn.nx, dyn.nx), dtype=f64)
+            out["B"] = z.new_empty((B, N, dyn.nx, dyn.nu), dtype=f64)
     rc = lib().leb_analytic_bound(
         ctypes.byref(dyn), B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64), _dev_ptr(mu, "mu", f64),
         _dev_ptr(sigma, "sigma", f64), _dev_ptr(out.get("r_lo"), "r_lo", f64), _dev_ptr(out.get("r_hi"), "r_hi", f64),
@@ -293,8 +296,8 @@ def pgd_nominal(dyn: Dynamics, z0, v0, sigma, mu0=None, radius=0.5, steps=20, lr
     B, N = int(z0.shape[0]), int(z0.shape[1])
     z = torch.empty_like(z0)
     v = torch.empty_like(v0)
-    w = torch.empty((B, N), dtype=f64, device=z0.device)
-    w0 = torch.empty((B, N), dtype=f64, device=z0.device)
+    w = z0.new_empty((B, N), dtype=f64)
+    w0 = z0.new_empty((B, N), dtype=f64)
     _check(lib().leb_pgd_nominal(ctypes.byref(dyn), B, N, _dev_ptr(z0, "z0", f64), _dev_ptr(v0, "v0", f64),
                                  _dev_ptr(mu0, "mu0", f64), _dev_ptr(sigma, "sigma", f64), int(bool(fixed_box)),
                                  float(radius), int(steps), float(lr),
@@ -310,9 +313,9 @@ def interval_hessian_bound(dyn: Dynamics, z, v, sigma, mu=None, mode="path", str
     import torch
     f64 = torch.float64
     B, N = int(z.shape[0]), int(z.shape[1])
-    lo = torch.empty((B, N, dyn.nx), dtype=f64, device=z.device)
+    lo = z.new_empty((B, N, dyn.nx), dtype=f64)
     hi = torch.empty_like(lo)
-    fl = torch.empty((B, N), dtype=torch.int32, device=z.device)
+    fl = z.new_empty((B, N), dtype=torch.int32)
     _check(lib().leb_interval_hessian_bound(ctypes.byref(dyn), IH_MODES[mode], B, N, _dev_ptr(z, "z", f64),
                                             _dev_ptr(v, "v", f64), _dev_ptr(mu, "mu", f64),
                                             _dev_ptr(sigma, "sigma", f64), _dev_ptr(lo, "r_lo", f64),
@@ -327,7 +330,7 @@ def sample_remainder(dyn: Dynamics, z, v, sigma, t, mu=None, stream=None):
     import torch
     f64 = torch.float64
     B, N = int(z.shape[0]), int(z.shape[1])
-    lo = torch.empty((B, N, dyn.nx), dtype=f64, device=z.device)
+    lo = z.new_empty((B, N, dyn.nx), dtype=f64)
     hi = torch.empty_like(lo)
     _check(lib().leb_sample_remainder(ctypes.byref(dyn), B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64),
                                       _dev_ptr(mu, "mu", f64), _dev_ptr(sigma, "sigma", f64), int(t.shape[0]),
@@ -344,12 +347,12 @@ def linearize(dyn: Dynamics, z, v, e=None, thrust=0.0, stream=None):
     f64 = torch.float64
     B_, N = int(z.shape[0]), int(z.shape[1])
     nx, nu = dyn.nx, dyn.nu
-    A = torch.empty((B_, N, nx, nx), dtype=f64, device=z.device)
-    Bm = torch.empty((B_, N, nx, nu), dtype=f64, device=z.device)
+    A = z.new_empty((B_, N, nx, nx), dtype=f64)
+    Bm = z.new_empty((B_, N, nx, nu), dtype=f64)
     E = None
     eh = None
     if e is not None:
-        E = torch.empty((B_, N, nx, nx + dyn.n_units), dtype=f64, device=z.device)
+        E = z.new_empty((B_, N, nx, nx + dyn.n_units), dtype=f64)
         eh = (ctypes.c_double * nx)(*[float(x) for x in e])
     _check(lib().leb_linearize(ctypes.byref(dyn), B_, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64),
                                None if eh is None else ctypes.cast(eh, ctypes.c_void_p), float(thrust),
@@ -366,8 +369,8 @@ def sls_responses(A, B, qx, qu, stream=None):
     import torch
     f64 = torch.float64
     b, N, nx, nu = (int(x) for x in B.shape)
-    K = torch.empty((b, N, N, nu, nx), dtype=f64, device=A.device)
-    phi = torch.empty((b, N, N, nx + nu, nx), dtype=f64, device=A.device)
+    K = A.new_empty((b, N, N, nu, nx), dtype=f64)
+    phi = A.new_empty((b, N, N, nx + nu, nx), dtype=f64)
     _check(lib().leb_sls_responses_full(nx, nu, b, N, _dev_ptr(A, "A", f64), _dev_ptr(B, "B", f64),
                                         _dev_ptr(qx, "qx", f64), _dev_ptr(qu, "qu", f64), _dev_ptr(K, "K", f64),
                                         _dev_ptr(phi, "phi", f64), _stream(stream)))
@@ -382,7 +385,7 @@ def sls_tube_map(phi, E, c_bar, rho_bar, stream=None):
     f64 = torch.float64
     b, N, _, n, nx = (int(x) for x in phi.shape)
     nw = int(E.shape[3]) if E is not None else 0
-    mu = torch.empty((b, N, n), dtype=f64, device=phi.device)
+    mu = phi.new_empty((b, N, n), dtype=f64)
     sg = torch.empty_like(mu)
     _check(lib().leb_sls_tube_map(nx, n - nx, nw, b, N, _dev_ptr(phi, "phi", f64), _dev_ptr(E, "E", f64),
                                   _dev_ptr(c_bar, "c_bar", f64), _dev_ptr(rho_bar, "rho_bar", f64),
@@ -398,11 +401,11 @@ def sls_fixed_point(dyn: Dynamics, z, v, phi, E, thrust=0.0, pad=0.0, stream=Non
     b, N = int(z.shape[0]), int(z.shape[1])
     n = dyn.nx + dyn.nu
     nw = int(E.shape[3]) if E is not None else 0
-    mu = torch.empty((b, N, n), dtype=f64, device=z.device)
+    mu = z.new_empty((b, N, n), dtype=f64)
     sg = torch.empty_like(mu)
-    lo = torch.empty((b, N, dyn.nx), dtype=f64, device=z.device)
+    lo = z.new_empty((b, N, dyn.nx), dtype=f64)
     hi = torch.empty_like(lo)
-    cert = torch.empty((b,), dtype=torch.int32, device=z.device)
+    cert = z.new_empty((b,), dtype=torch.int32)
     _check(lib().leb_sls_fixed_point(ctypes.byref(dyn), b, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64),
                                      _dev_ptr(phi, "phi", f64), nw, _dev_ptr(E, "E", f64), float(thrust),
                                      float(pad), _dev_ptr(mu, "mu", f64), _dev_ptr(sg, "sigma", f64),
@@ -427,8 +430,8 @@ def zonotope_hull(G, c=None, stream=None):
     import torch
     f64 = torch.float64
     rows, ng = int(G.shape[0]), int(G.shape[1])
-    mu = torch.empty((rows,), dtype=f64, device=G.device)
-    sg = torch.empty((rows,), dtype=f64, device=G.device)
+    mu = G.new_empty((rows,), dtype=f64)
+    sg = G.new_empty((rows,), dtype=f64)
     _check(lib().leb_zonotope_hull(rows, ng, _dev_ptr(G, "G", f64), _dev_ptr(c, "c", f64), _dev_ptr(mu, "mu", f64),
                                    _dev_ptr(sg, "sigma", f64), _stream(stream)))
     return mu, sg
@@ -559,8 +562,8 @@ def tube_map(n_units, phi, e, c_bar, rho_bar, stream=None, out=None):
     B, N = int(c_bar.shape[0]), int(c_bar.shape[1])
     f64 = torch.float64
     if out is None:
-        out = (torch.empty((B, N, 8 * n_units), dtype=f64, device=c_bar.device),
-               torch.empty((B, N, 8 * n_units), dtype=f64, device=c_bar.device))
+        out = (c_bar.new_empty((B, N, 8 * n_units), dtype=f64),
+               c_bar.new_empty((B, N, 8 * n_units), dtype=f64))
     rc = lib().leb_tube_map(B, N, int(n_units), _dev_ptr(phi, "phi", f64), _host6(e),
                             _dev_ptr(c_bar, "c_bar", f64), _dev_ptr(rho_bar, "rho_bar", f64),
                             _dev_ptr(out[0], "mu", f64), _dev_ptr(out[1], "sigma", f64), _stream(stream))
@@ -588,8 +591,8 @@ def fixed_point_solve(dyn: Dynamics, z, v, phi, e, tol=1e-6, max_sweeps=200, pad
     n = dyn.nx + dyn.nu
     warm = mu is not None
     if not warm:        # the cold start writes every entry
-        mu = torch.empty((B, N, n), dtype=torch.float64, device=z.device)
-        sigma = torch.empty((B, N, n), dtype=torch.float64, device=z.device)
+        mu = z.new_empty((B, N, n), dtype=torch.float64)
+        sigma = z.new_empty((B, N, n), dtype=torch.float64)
     cert = _cert_out(B, N, z.device)
     opt = FPOptions(tol, max_sweeps, pad, inflate_abs, 1 if warm else 0, tol if conv_tol is None else conv_tol)
     sweeps = ctypes.c_int32(0)
@@ -627,8 +630,8 @@ def fixed_point_learned(dyn: Dynamics, z, v, phi, e, net, sweeps=1, margin=5e-2,
     import torch
     B, N = int(z.shape[0]), int(z.shape[1])
     n = dyn.nx + dyn.nu
-    mu = torch.empty((B, N, n), dtype=torch.float64, device=z.device)
-    sigma = torch.empty((B, N, n), dtype=torch.float64, device=z.device)
+    mu = z.new_empty((B, N, n), dtype=torch.float64)
+    sigma = z.new_empty((B, N, n), dtype=torch.float64)
     cert = _cert_out(B, N, z.device)
     opt = FPOptions(tol, max_sweeps, pad, inflate_abs, 1, tol if conv_tol is None else conv_tol)
     ws = WarmStart(net.handle, int(sweeps), float(margin))
@@ -646,7 +649,7 @@ def chain_features(dyn: Dynamics, z, v, sigma, mu=None, stream=None):
     """Surrogate inputs [B][N][n_units][32] (float32) of a chain tube."""
     import torch
     B, N = int(z.shape[0]), int(z.shape[1])
-    x = torch.empty((B, N, dyn.n_units, CHAIN_FEATURES), dtype=torch.float32, device=z.device)
+    x = z.new_empty((B, N, dyn.n_units, CHAIN_FEATURES), dtype=torch.float32)
     f64 = torch.float64
     _check(lib().leb_chain_features(ctypes.byref(dyn), B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64),
                                     _dev_ptr(mu, "mu", f64), _dev_ptr(sigma, "sigma", f64),
@@ -660,7 +663,7 @@ def chain_surrogate_bound(dyn: Dynamics, z, v, sigma, net, mu=None, pad=0.0, str
     import torch
     B, N = int(z.shape[0]), int(z.shape[1])
     f64 = torch.float64
-    cb = torch.empty((B, N, dyn.nx), dtype=f64, device=z.device)
+    cb = z.new_empty((B, N, dyn.nx), dtype=f64)
     rb = torch.empty_like(cb)
     _check(lib().leb_chain_surrogate_bound(ctypes.byref(dyn), B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64),
                                            _dev_ptr(mu, "mu", f64), _dev_ptr(sigma, "sigma", f64), net.handle,
@@ -673,7 +676,7 @@ def chain_targets(dyn: Dynamics, r_lo, r_hi, stream=None):
     """Surrogate targets [B][N][n_units][4] (float32) from a chain bound."""
     import torch
     B, N = int(r_lo.shape[0]), int(r_lo.shape[1])
-    t = torch.empty((B, N, dyn.n_units, CHAIN_OUTPUTS), dtype=torch.float32, device=r_lo.device)
+    t = r_lo.new_empty((B, N, dyn.n_units, CHAIN_OUTPUTS), dtype=torch.float32)
     f64 = torch.float64
     _check(lib().leb_chain_targets(ctypes.byref(dyn), B, N, _dev_ptr(r_lo, "r_lo", f64),
                                    _dev_ptr(r_hi, "r_hi", f64), _dev_ptr(t, "t", torch.float32), _stream(stream)))
@@ -685,7 +688,7 @@ def nn_features(z, v, sigma, mu=None, stream=None):
     ReLU-MLP dynamics (see leb.h: leb_nn_features)."""
     import torch
     B, N, nx, nu = int(z.shape[0]), int(z.shape[1]), int(z.shape[2]), int(v.shape[2])
-    x = torch.empty((B, N, 2 * (nx + nu)), dtype=torch.float32, device=z.device)
+    x = z.new_empty((B, N, 2 * (nx + nu)), dtype=torch.float32)
     f64 = torch.float64
     _check(lib().leb_nn_features(nx, nu, B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64), _dev_ptr(mu, "mu", f64),
                                  _dev_ptr(sigma, "sigma", f64), _dev_ptr(x, "x", torch.float32), _stream(stream)))
@@ -696,7 +699,7 @@ def nn_targets(r_lo, r_hi, stream=None):
     """NN-surrogate targets [B][N][2m] (float32) from a bound [B][N][m]."""
     import torch
     B, N, m = int(r_lo.shape[0]), int(r_lo.shape[1]), int(r_lo.shape[2])
-    t = torch.empty((B, N, 2 * m), dtype=torch.float32, device=r_lo.device)
+    t = r_lo.new_empty((B, N, 2 * m), dtype=torch.float32)
     f64 = torch.float64
     _check(lib().leb_nn_targets(m, B, N, _dev_ptr(r_lo, "r_lo", f64), _dev_ptr(r_hi, "r_hi", f64),
                                 _dev_ptr(t, "t", torch.float32), _stream(stream)))
@@ -710,7 +713,7 @@ def nn_surrogate_bound(net, z, v, sigma, mu=None, stream=None):
     B, N, nx, nu = int(z.shape[0]), int(z.shape[1]), int(z.shape[2]), int(v.shape[2])
     m = net.widths[-1] // 2
     f64 = torch.float64
-    lo = torch.empty((B, N, m), dtype=f64, device=z.device)
+    lo = z.new_empty((B, N, m), dtype=f64)
     hi = torch.empty_like(lo)
     _check(lib().leb_nn_surrogate_bound(net.handle, nx, nu, B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64),
                                         _dev_ptr(mu, "mu", f64), _dev_ptr(sigma, "sigma", f64),
@@ -760,12 +763,12 @@ def nn_bound(mlp: MLP, z, v, sigma, mu=None, pad: float = 0.0, zonotope: bool = 
     import torch
     B, N = int(z.shape[0]), int(z.shape[1])
     f64 = torch.float64
-    out = {"r_lo": torch.empty((B, N, mlp.m), dtype=f64, device=z.device),
-           "r_hi": torch.empty((B, N, mlp.m), dtype=f64, device=z.device),
-           "flags": torch.empty((B, N), dtype=torch.int32, device=z.device)}
+    out = {"r_lo": z.new_empty((B, N, mlp.m), dtype=f64),
+           "r_hi": z.new_empty((B, N, mlp.m), dtype=f64),
+           "flags": z.new_empty((B, N), dtype=torch.int32)}
     if zonotope:
-        out["c_bar"] = torch.empty((B, N, mlp.m), dtype=f64, device=z.device)
-        out["rho_bar"] = torch.empty((B, N, mlp.m), dtype=f64, device=z.device)
+        out["c_bar"] = z.new_empty((B, N, mlp.m), dtype=f64)
+        out["rho_bar"] = z.new_empty((B, N, mlp.m), dtype=f64)
     rc = lib().leb_nn_bound(mlp.handle, B, N, _dev_ptr(z, "z", f64), _dev_ptr(v, "v", f64), _dev_ptr(mu, "mu", f64),
                             _dev_ptr(sigma, "sigma", f64), _dev_ptr(J, "J", f64), _dev_ptr(out["r_lo"], "r_lo", f64),
                             _dev_ptr(out["r_hi"], "r_hi", f64), _dev_ptr(out.get("c_bar"), "c_bar", f64),
@@ -822,7 +825,7 @@ class Surrogate:
         """x [B][d_0] float32 GPU tensor -> y [B][d_L]."""
         import torch
         B = int(x.shape[0])
-        y = out if out is not None else torch.empty((B, self.widths[-1]), dtype=torch.float32, device=x.device)
+        y = out if out is not None else x.new_empty((B, self.widths[-1]), dtype=torch.float32)
         _check(lib().leb_mlp_fwd_bf16(self.handle, B, _dev_ptr(x, "x", torch.float32),
                                       _dev_ptr(y, "y", torch.float32), _stream(stream)))
         return y
@@ -830,7 +833,7 @@ class Surrogate:
     def backward(self, x, dy, stream=None):
         """Parameter gradient of sum(dy * forward(x)) (flat float32 GPU tensor)."""
         import torch
-        g = torch.empty(self.n_params, dtype=torch.float32, device=x.device)
+        g = x.new_empty(self.n_params, dtype=torch.float32)
         _check(lib().leb_mlp_bwd_bf16(self.handle, int(x.shape[0]), _dev_ptr(x, "x", torch.float32),
                                       _dev_ptr(dy, "dy", torch.float32), _dev_ptr(g, "grads", torch.float32),
                                       _stream(stream)))
