@@ -93,6 +93,7 @@ struct NbArgs {
     double* ub;                    // [box][NN_MAXL][2][NN_MAXW] u-bar, l-bar of hidden layer j
     double* cg;                    // [box][2][2][NN_MAXW]       c-bar, rho-bar per pass direction
     uint32_t* ok;                  // [box] 1: valid input
+    double* jac;                   // NULL, or [box][w[L]][w[0]] the Jacobian's rows (chain form of the output pass)
     double* lv;                    // [box][2][lv_bm] levels Lambda^(j) of the hidden-layer passes
     size_t lv_bm;                  // doubles per (box, direction)
     int lv_off[NN_MAXL][NN_MAXL];  // offset of level j of pass k: [row][column], w[k] x w[j]
@@ -699,7 +700,13 @@ __global__ void __launch_bounds__(NB_T) __attribute__((amdgpu_waves_per_eu(2))) 
         double jv[NBM_R];
 #pragma unroll
         for (int r = 0; r < NBM_R; ++r) jv[r] = 0.0;
-        if (k == L) {
+        if (k == L && A.jac) {
+            if (q < n0) {
+#pragma unroll
+                for (int r = 0; r < NBM_R; ++r)
+                    jv[r] = r < nr ? A.jac[((size_t)box * rows_k + sRow[r0 + r]) * n0 + q] : 0.0;
+            }
+        } else if (k == L) {
             // rows of J = W_L D_{L-1} W_{L-1} ... D_1 W_1 (D = [z^ > 0]) for this block
             for (int j = L - 1; j >= 1; --j) {
                 const int nj = A.w[j];
@@ -892,7 +899,10 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
         }
     a.lv_bm = lv_bm;
     // per box: cr 2, zn L, bd 2L, st 4L, ub 2L, cg 4 rows of NN_MAXW doubles, the levels, the flag
-    const size_t per_box = (size_t)NN_MAXW * (2 + 9 * NN_MAXL + 4) + 2 * lv_bm;
+    // (networks with 16 inputs: also the Jacobian's rows)
+    const bool chain = use_mfma && net->w[0] == 16;
+    const size_t jrows = chain ? (size_t)net->w[L] * net->w[0] : 0;
+    const size_t per_box = (size_t)NN_MAXW * (2 + 9 * NN_MAXL + 4) + 2 * lv_bm + jrows;
     int64_t cb = (int64_t)(NB_LV_BUDGET / (per_box * sizeof(double)));
     cb = cb < NB_CHUNK_MIN ? NB_CHUNK_MIN : (cb > NB_CHUNK ? NB_CHUNK : cb);
     const int CB = (int)(units < cb ? units : cb);
@@ -922,6 +932,7 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
     a.ub = p; p += (size_t)CB * NN_MAXL * 2 * NN_MAXW;
     a.cg = p; p += (size_t)CB * 2 * 2 * NN_MAXW;
     a.lv = p; p += (size_t)CB * 2 * lv_bm;
+    a.jac = chain ? p : nullptr; p += (size_t)CB * jrows;
     a.ok = (uint32_t*)p;
     for (int64_t u0 = 0; u0 < units; u0 += CB) {
         const int nb = (int)((units - u0) < CB ? (units - u0) : CB);
@@ -931,7 +942,7 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
             const dim3 grid((unsigned)nb, 2u);
             for (int k = 2; k <= L; ++k) {
                 a.k = k;
-                if (k < L && k <= 3 && net->w[0] == 16) {
+                if (chain && k < L) {
                     // one or two steps down to a 16-wide input: both directions together, levels of
                     // unstable rows only (3,200 boxes of 16-256-256-256-12: 1.65 ms for the
                     // two targets, 8.5 ms by the general pass); the rest below
@@ -947,6 +958,23 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
                     ha.ok = a.ok;
                     if (k == 2) hipLaunchKernelGGL(nn_hid1_kernel<true>, dim3(nb), dim3(256), 0, st, ha);
                     else hipLaunchKernelGGL(nn_hid2_kernel<true>, dim3((ha.M + 31) / 32, nb), dim3(256), 0, st, ha);
+                    continue;
+                }
+                if (chain) {
+                    // the output pass: both directions and the Jacobian's rows
+                    ChainArgs ca = {};
+                    ca.WTt = net->WT[L - 1]; ca.bt = net->b[L - 1];
+                    for (int l = 0; l < L; ++l) { ca.W[l] = net->W[l]; ca.b[l] = net->b[l]; }
+                    for (int l = 0; l <= L; ++l) ca.w[l] = net->w[l];
+                    ca.k = L; ca.M = net->w[L]; ca.nbox = CB;
+                    ca.lo = a.bd; ca.hi = a.bd + NN_MAXW;
+                    ca.bstride = (size_t)NN_MAXL * 2 * NN_MAXW; ca.lstride = 2 * NN_MAXW;
+                    ca.D = a.zn; ca.dbstride = (size_t)NN_MAXL * NN_MAXW; ca.dlstride = NN_MAXW;
+                    ca.lv = a.lv; ca.lv_bm = lv_bm;
+                    for (int l = 0; l + 2 <= L; ++l) ca.off[l] = a.lv_off[L][l];
+                    ca.jac = a.jac; ca.jstride = jrows;
+                    ca.ok = a.ok;
+                    if ((rc = launch_nn_chain<true>(ca, 3, nb, st))) return rc;
                     continue;
                 }
                 hipLaunchKernelGGL(nbm_pass_kernel<false>, grid, dim3(NB_T), 0, st, a);

@@ -1,9 +1,13 @@
-// nn_hid.hpp -- CROWN passes for the bounds of hidden layers 2 and 3 of a ReLU MLP
-// with 16 inputs, shared by the bound (nn.hip) and its adjoint (nn_bwd.hip).
+// nn_hid.hpp -- CROWN passes of a ReLU MLP, shared by the bound (nn.hip) and its
+// adjoint (nn_bwd.hip): the bounds of hidden layers 2 and 3 of networks with 16
+// inputs, and the chain of any target layer.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
+#include "leb.h"
 #include "nn_net.hpp"
 
 namespace leb {
@@ -523,6 +527,299 @@ __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
             }
         }
     }
+}
+
+// ---------------------------------------------------------- fused chain
+//
+// The whole backward substitution of one target layer k, for one box, one
+// mode and a block of 16 target rows, in one workgroup:
+//   Lambda_{j-1} = (Lambda_j (.) S_j) W_j,   j = k-1, ..., 1,   Lambda_k = rows of W_k,
+//   beta += sum_i (Lambda_j t_sel)_i + (Omega_j b_j),   eps += |Lambda_j| e_j,
+// with Lambda kept in LDS between the steps (never in HBM).  Modes: 0 upper, 1
+// lower, 2 Jacobian (S = 1[z^ > 0]).  The product is formed transposed on FP64
+// MFMA (v_mfma_f64_16x16x4): Lambda^T_{j-1} = W_j^T Omega^T, so the accumulator of
+// one step (lane l holds element [4i + l/16][l%16] of a 16 x 16 tile) is stored to
+// LDS in the layout the next step reads its B operand from (lane l supplies
+// B[l/16][l%16]).  A operands are W_j columns read from L2.
+// The neurons of layer j with slope 0 in the mode (stably inactive; z^ <= 0 in the
+// Jacobian) are listed out: a step runs over the other neurons only, and forms only
+// their columns for the next step; the state sits at list positions.
+// Wave w produces the output tiles w, w + 4, ... of each step; with one or two
+// tiles the waves split the k-steps instead (partial tiles added in slice order).
+//
+// What bounds it: FP64 MFMA, three workgroups a compute unit hiding the L2 reads and
+// the barriers between the steps.  Output pass of the 16-256-256-256-12 network, three
+// modes, 3,200 boxes: 475 us (every column of Lambda formed, one k-step in flight:
+// 740 us); 40 boxes of 16-128-128-128-12: 17 us (22 us).  The adjoint's output pass
+// with the Jacobian's rows: 469 us (in the general pass: 680 us and, in its reverse
+// launch, another 660 us for the Jacobian).
+struct ChainArgs {
+    const double* WTt;             // target layer k, transposed: [w_{k-1}][M] (shared by every box)
+    const double* bt;              // [M]
+    const double* W[NN_MAXL];      // layer j at W[j-1]: [w_j][w_{j-1}]
+    const double* b[NN_MAXL];
+    int w[NN_MAXL + 1];
+    int k, M, nbox;
+    // per-box vectors of hidden layer j (1-based) at base + (j - 1) * lstride + box * bstride
+    // (adjoint: the bounds only); D (adjoint: z^) with strides of its own
+    const double* lo; const double* hi;
+    const double* s; const double* t; const double* a; const double* e; const double* D;
+    size_t bstride, lstride, dbstride, dlstride;
+    double* C;                     // bound: [mode][box][M][w_0]
+    double* beta; double* eps;     // bound: [mode][box][M]
+    // adjoint: levels j = 0 .. k - 2 of mode 0, 1 at lv + (2 box + mode) lv_bm + off[j], [M][w_j];
+    // the Jacobian's rows at jac + box * jstride, [M][w_0]
+    double* lv; size_t lv_bm; int off[NN_MAXL];
+    double* jac; size_t jstride;
+    const uint32_t* ok;
+};
+
+constexpr size_t CHAIN_STATE_BYTES = (size_t)NN_MAXW * 16 * sizeof(double);
+constexpr int CHAIN_PAD = NN_MAXW + 8;               // listed neurons, padded past the last k-step read
+constexpr int CHAIN_PAD2 = NN_MAXW + 40;             // ... and past the last k-step fetched ahead
+
+struct ChainLists {
+    double v[5][CHAIN_PAD];        // slope x >= 0, slope x < 0, intercept, bias, e (list order)
+    int k[2][CHAIN_PAD2];          // listed neurons of the step's layer and of the layer below
+};
+
+// The k-loop of one step for one wave: NT tiles of output columns (col8: byte offsets
+// of the lane's columns in a row of W), k-steps 4 slice, 4 slice + 4 nslice, ... of the
+// list; x of the rows from W_k^T (FIRST) or from the state in LDS.
+template <bool FIRST, bool SUMS, int NT>
+__device__ __forceinline__ void chain_steps(const double* W, unsigned N8, const double* WTt, unsigned M8, unsigned row8,
+                                            const double* cst, const ChainLists& L, const int* kl, int Kc,
+                                            const unsigned (&col8)[4], int slice, int nslice, int turn, int g, int r,
+                                            bool t_on_pos, bool t_on_neg, d4 (&acc)[4], double& pb, double& pe) {
+    double wn[2][4], xn[2];
+    const int stride = 4 * nslice;
+    auto fetch = [&](int p, int c) {
+        const unsigned k = kl[c];
+        const unsigned kw = __umul24(k, N8);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) wn[p][i] = *(const double*)((const char*)W + (kw + col8[i]));
+        double x;
+        if (FIRST) x = *(const double*)((const char*)WTt + (__umul24(k, M8) + row8));
+        else x = cst[(c < NN_MAXW ? c : 0) * 16 + r];
+        xn[p] = c < Kc ? x : 0.0;
+    };
+    auto step = [&](int p, int c0, int n) {
+        const int c = c0 + g;
+        double w[4];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) w[i] = wn[p][i];
+        const double x = xn[p];
+        fetch(p, c + 2 * stride);                         // past the end: padding
+        const bool pos = x >= 0.0;
+        const double om = x * (pos ? L.v[0][c] : L.v[1][c]);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i], om, acc[i], 0, 0, 0);
+        if (SUMS && (turn < 0 || (n & 3) == turn)) {
+            const double xt = x * L.v[2][c];
+            pb = __builtin_fma(om, L.v[3][c], pb + ((pos ? t_on_pos : t_on_neg) ? xt : 0.0));
+            pe = __builtin_fma(fabs(x), L.v[4][c], pe);
+        }
+    };
+    int c0 = 4 * slice, n = 0;
+    if (c0 >= Kc) return;
+    fetch(0, c0 + g);
+    fetch(1, c0 + stride + g);
+    for (; c0 + stride < Kc; c0 += 2 * stride, n += 2) {
+        step(0, c0, n);
+        step(1, c0 + stride, n + 1);
+    }
+    if (c0 < Kc) step(0, c0, n);
+}
+
+template <bool ADJ>
+__global__ void __launch_bounds__(256, 3) nn_chain_kernel(ChainArgs A) {
+    extern __shared__ double cst[];                    // [list position or input][16]: Lambda^T of this block
+    __shared__ ChainLists L;
+    __shared__ int scnt[4];
+    __shared__ double spart[768];                      // partial tiles of the k-slices; then the row sums
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mode = blockIdx.y, box = blockIdx.z;
+    if (ADJ && !A.ok[box]) return;
+    // intercept of the selected line: upper mode on x >= 0, lower mode on x < 0
+    const bool t_on_pos = mode == 0, t_on_neg = mode == 1;
+    // list the neurons of layer j with a slope in this mode into L.k[p] and keep this
+    // lane's neuron's vectors and list position in registers until stage() (the list
+    // of the step above is still in use)
+    int Kc = 0, pos_ = -1;
+    double vr[5];
+    auto prepare = [&](int j, int p) {
+        const int K = A.w[j];
+        const size_t o = (size_t)(j - 1) * A.lstride + (size_t)box * A.bstride + tid;
+        bool keep = false;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) vr[q] = 0.0;
+        if (tid < K) {
+            if (mode == 2) {
+                keep = A.D[(size_t)(j - 1) * A.dlstride + (size_t)box * A.dbstride + tid] > 0.0;
+                vr[0] = vr[1] = 1.0;
+            } else {
+                const double l = A.lo[o], h = A.hi[o];
+                double s_, t_, a_, e_ = 0.0;
+                keep = h > 0.0 || (ADJ && l >= 0.0);
+                if (ADJ) nb_relax(l, h, s_, t_, a_);
+                else { s_ = A.s[o]; t_ = A.t[o]; a_ = A.a[o]; e_ = A.e[o]; }
+                vr[0] = mode == 0 ? s_ : a_;
+                vr[1] = mode == 0 ? a_ : s_;
+                vr[2] = t_;
+                vr[4] = e_;
+            }
+            vr[3] = ADJ ? 0.0 : A.b[j - 1][tid];
+        }
+        const uint64_t bal = __ballot(keep);
+        if (lane == 0) scnt[wave] = __popcll(bal);
+        __syncthreads();
+        int off = 0;
+        Kc = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { off += q < wave ? scnt[q] : 0; Kc += scnt[q]; }
+        pos_ = keep ? off + __popcll(bal & ((1ull << lane) - 1ull)) : -1;
+        if (keep) L.k[p][pos_] = tid;
+        if (tid >= Kc) L.k[p][tid] = 0;                // padding (its x is forced to 0)
+        if (tid < CHAIN_PAD2 - 256) L.k[p][256 + tid] = 0;
+        __syncthreads();
+    };
+    auto stage = [&]() {                               // the vectors, in list order (0 in the padding)
+        if (pos_ >= 0) {
+#pragma unroll
+            for (int q = 0; q < 5; ++q) L.v[q][pos_] = vr[q];
+        }
+        if (tid < 8) {
+#pragma unroll
+            for (int q = 0; q < 5; ++q) L.v[q][Kc + tid] = 0.0;
+        }
+    };
+    const int M = A.M;
+    // a target with one step (k = 2) runs every 16-row block in this workgroup with
+    // one list; deeper targets run one block per workgroup
+    const bool single = A.k == 2;
+    const int nrb = (M + 15) / 16;
+    int buf = 0;
+    for (int rb = single ? 0 : blockIdx.x; rb < (single ? nrb : blockIdx.x + 1); ++rb) {
+        const int row0 = 16 * rb;
+        if (!single || rb == 0) {
+            prepare(A.k - 1, buf);
+            stage();
+        }
+        __syncthreads();
+        double pb = 0.0, pe = 0.0;
+        for (int j = A.k - 1; j >= 1; --j) {
+            const int N = A.w[j - 1], kc = Kc;
+            const int* kl = L.k[buf];
+            int ncol = N;
+            if (j > 1) {
+                prepare(j - 1, buf ^ 1);               // columns of the layer below (registers until stage())
+                ncol = Kc;
+            }
+            // work split: ntile >= 3: wave w owns tiles w, w + 4, ... over all k; ntile 2 or
+            // 1: the waves split the k-steps of the tile(s) into 2 or 4 slices
+            const int ntile = (ncol + 15) >> 4;
+            const int nslice = ntile >= 3 || ntile == 0 ? 1 : 4 / ntile;
+            const int slice = wave / (4 / nslice);
+            const int tfirst = ntile >= 3 ? wave : (ntile == 2 ? wave & 1 : 0);
+            const int nmine = ntile >= 3 ? (ntile - wave + 3) >> 2 : (ntile > 0 ? 1 : 0);
+            // row sums: k-steps in turn over the waves, or each slice's by the wave of its first tile
+            const int turn = nslice == 1 ? wave : (tfirst == 0 ? -1 : 4);
+            d4 acc[4];
+            unsigned col8[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[i] = d4{0.0, 0.0, 0.0, 0.0};
+                const int c = i < nmine ? 16 * (tfirst + 4 * i) + r : 0;
+                col8[i] = 8u * (j > 1 ? L.k[buf ^ 1][c] : c);
+            }
+            const unsigned N8 = 8u * N, M8 = 8u * M, row8 = 8u * min(row0 + r, M - 1);
+            auto run = [&](auto first, auto nt) {
+                chain_steps<decltype(first)::value, !ADJ, decltype(nt)::value>(
+                    A.W[j - 1], N8, A.WTt, M8, row8, cst, L, kl, kc, col8, slice, nslice, turn, g, r, t_on_pos, t_on_neg,
+                    acc, pb, pe);
+            };
+            using T_ = std::integral_constant<bool, true>;
+            using F_ = std::integral_constant<bool, false>;
+#define CHAIN_NT(F)                                                      \
+    if (nmine == 4) run(F{}, std::integral_constant<int, 4>{});          \
+    else if (nmine == 3) run(F{}, std::integral_constant<int, 3>{});     \
+    else if (nmine == 2) run(F{}, std::integral_constant<int, 2>{});     \
+    else if (nmine == 1) run(F{}, std::integral_constant<int, 1>{});     \
+    else run(F{}, std::integral_constant<int, 0>{});
+            if (j == A.k - 1) { CHAIN_NT(T_) } else { CHAIN_NT(F_) }
+#undef CHAIN_NT
+            // slices 1.. hand their partial tiles to slice 0 (added in slice order); every
+            // read of the state and of the vectors is done before they are overwritten
+            const int pidx = nslice == 4 ? slice - 1 : tfirst;
+            if (nslice > 1 && slice > 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) spart[pidx * 256 + q * 64 + lane] = acc[0][q];
+            }
+            __syncthreads();
+            if (nslice > 1 && slice == 0) {
+                for (int sl = 1; sl < nslice; ++sl) {
+                    const int pi = nslice == 4 ? sl - 1 : tfirst;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[0][q] += spart[pi * 256 + q * 64 + lane];
+                }
+            }
+            if (j > 1) stage();
+            if (slice == 0) {
+                double* lv = ADJ && mode < 2 ? A.lv + ((size_t)box * 2 + mode) * A.lv_bm + A.off[j - 1] : nullptr;
+                if (ADJ && j == 1 && mode == 2) lv = A.jac + (size_t)box * A.jstride;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (i >= nmine) break;
+                    const int tt = tfirst + 4 * i;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = 16 * tt + 4 * q + g;
+                        if (!ADJ || j > 1) cst[c * 16 + r] = acc[i][q];
+                        if (ADJ && lv && c < ncol && row0 + r < M)
+                            lv[(size_t)(row0 + r) * N + (j > 1 ? L.k[buf ^ 1][c] : c)] = acc[i][q];
+                    }
+                }
+            }
+            __syncthreads();                           // the next step reads the state just written
+            if (j > 1) buf ^= 1;
+        }
+        if (!ADJ) {
+            // Lambda_0 rows of this block, and the bias and rounding sums of each row
+            const int n0 = A.w[0];
+            const size_t cbase = ((size_t)mode * A.nbox + box) * M;
+            for (int q = tid; q < 16 * n0; q += 256) {
+                const int rr = q / n0, n = q - rr * n0;
+                if (row0 + rr < M) A.C[(cbase + row0 + rr) * n0 + n] = cst[n * 16 + rr];
+            }
+            spart[wave * 64 + lane] = pb;
+            spart[256 + wave * 64 + lane] = pe;
+            __syncthreads();
+            if (tid < 16 && row0 + tid < M) {
+                double b_ = 0.0, e_ = 0.0;
+                for (int w = 0; w < 4; ++w)
+                    for (int q = 0; q < 4; ++q) { b_ += spart[w * 64 + tid + 16 * q]; e_ += spart[256 + w * 64 + tid + 16 * q]; }
+                const double bt = A.bt[row0 + tid];
+                A.beta[cbase + row0 + tid] = bt + b_;
+                A.eps[cbase + row0 + tid] = e_ + fabs(bt);
+            }
+            __syncthreads();                           // the next block reuses the state and sums
+        }
+    }
+}
+
+template <bool ADJ>
+static int launch_nn_chain(const ChainArgs& c, int nmode, int nact, hipStream_t st) {
+    static bool attr = false;
+    if (!attr) {
+        if (hipFuncSetAttribute((const void*)nn_chain_kernel<ADJ>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)CHAIN_STATE_BYTES) != hipSuccess)
+            return LEB_EDEVICE;
+        attr = true;
+    }
+    const unsigned rbs = c.k == 2 ? 1u : (unsigned)((c.M + 15) / 16);
+    hipLaunchKernelGGL(nn_chain_kernel<ADJ>, dim3(rbs, nmode, nact), dim3(256), CHAIN_STATE_BYTES, st, c);
+    return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 
 }  // namespace leb

@@ -134,7 +134,7 @@ def test_nn_bound_two_chunks(gpu):
 
 
 @pytest.mark.parametrize("widths", [[16, 16, 16, 16, 4], [16, 48, 80, 112, 12], [16, 256, 240, 32, 12],
-                                    [16, 64, 256, 256, 16, 8]])
+                                    [16, 64, 256, 256, 16, 8], [16, 256, 12]])
 @pytest.mark.parametrize("shift", [0.0, 50.0, -50.0])
 def test_nn_hidden_targets_tiles(gpu, widths, shift):
     """The 16-input hidden-layer passes: fewer tiles than waves, a ragged last
@@ -164,4 +164,35 @@ def test_nn_hidden_targets_tiles(gpu, widths, shift):
     assert (lo[zero] <= 0.0).all() and (hi[zero] >= 0.0).all()
     assert (np.maximum(-lo, hi)[zero] <= 8.0 * 2.0 ** -40 * m[zero]).all()
     check_bounds(lo[~zero], hi[~zero], o["r_lo"][~zero], o["r_hi"][~zero], "hidden targets")
+    mlp.close()
+
+
+@pytest.mark.parametrize("widths", [[32, 256, 240, 12], [48, 16, 32, 16, 48, 8], [240, 96, 20], [32, 32, 64, 256, 64]])
+@pytest.mark.parametrize("shift", [0.0, 50.0, -50.0])
+def test_nn_chain_tiles(gpu, widths, shift):
+    """The chain of a target layer over listed neurons and columns: inputs wider
+    than a tile, none to sixteen listed tiles, every slicing of the k-steps, ragged
+    outputs, layers mixed, all stably active or all stably inactive."""
+    import torch
+    import paper_2607_01203_amd as leb
+    rng = W.rng_for(1210 + widths[1] + len(widths))
+    Wl, bl = W.mlp_weights(rng, widths)
+    bl = [x + np.float32(shift) if 0 < i < len(bl) - 1 else x for i, x in enumerate(bl)]
+    nx = widths[0] - 4
+    a = rng.uniform(-1, 1, (2, 3, widths[0]))
+    sg = rng.uniform(0.005, 0.1, (2, 3, widths[0]))
+    print("case: nn chain %s shift %g" % (widths, shift), flush=True)
+    mlp = leb.MLP(Wl, bl, nx, False)
+    out = leb.nn_bound(mlp, _t(a[..., :nx], gpu), _t(a[..., nx:], gpu), _t(sg, gpu))
+    torch.cuda.synchronize()
+    o = _oracle(W.MLPNet(Wl, bl, nx, 4, False), a[..., :nx], a[..., nx:], sg)
+    lo, hi = out["r_lo"].cpu().numpy(), out["r_hi"].cpu().numpy()
+    # rows whose exact bound is 0 (a constant network): the rounding allowance, as above
+    zero = (o["r_lo"] == 0.0) & (o["r_hi"] == 0.0)
+    m = np.abs(a) + 2.0 * sg
+    for w, x in zip(Wl, bl):
+        m = m @ np.abs(np.asarray(w, np.float64)).T + np.abs(np.asarray(x, np.float64))
+    assert (lo[zero] <= 0.0).all() and (hi[zero] >= 0.0).all()
+    assert (np.maximum(-lo, hi)[zero] <= 8.0 * 2.0 ** -40 * m[zero]).all()
+    check_bounds(lo[~zero], hi[~zero], o["r_lo"][~zero], o["r_hi"][~zero], "nn chain")
     mlp.close()
