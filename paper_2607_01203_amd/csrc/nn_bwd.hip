@@ -60,6 +60,7 @@
 #include <mutex>
 #include <vector>
 
+#include "dpp.hpp"
 #include "leb.h"
 #include "leb_internal.hpp"
 #include "nn_hid.hpp"
@@ -93,7 +94,7 @@ struct NbArgs {
     double* ub;                    // [box][NN_MAXL][2][NN_MAXW] u-bar, l-bar of hidden layer j
     double* cg;                    // [box][2][2][NN_MAXW]       c-bar, rho-bar per pass direction
     uint32_t* ok;                  // [box] 1: valid input
-    double* jac;                   // NULL, or [box][w[L]][w[0]] the Jacobian's rows (chain form of the output pass)
+    double* jac;                   // 16 inputs: [box][w[L]][16] the Jacobian's rows
     double* lv;                    // [box][2][lv_bm] levels Lambda^(j) of the hidden-layer passes
     size_t lv_bm;                  // doubles per (box, direction)
     int lv_off[NN_MAXL][NN_MAXL];  // offset of level j of pass k: [row][column], w[k] x w[j]
@@ -700,13 +701,7 @@ __global__ void __launch_bounds__(NB_T) __attribute__((amdgpu_waves_per_eu(2))) 
         double jv[NBM_R];
 #pragma unroll
         for (int r = 0; r < NBM_R; ++r) jv[r] = 0.0;
-        if (k == L && A.jac) {
-            if (q < n0) {
-#pragma unroll
-                for (int r = 0; r < NBM_R; ++r)
-                    jv[r] = r < nr ? A.jac[((size_t)box * rows_k + sRow[r0 + r]) * n0 + q] : 0.0;
-            }
-        } else if (k == L) {
+        if (k == L) {
             // rows of J = W_L D_{L-1} W_{L-1} ... D_1 W_1 (D = [z^ > 0]) for this block
             for (int j = L - 1; j >= 1; --j) {
                 const int nj = A.w[j];
@@ -801,6 +796,326 @@ __global__ void __launch_bounds__(NB_T) __attribute__((amdgpu_waves_per_eu(2))) 
         if (q < n0) {
             A.cg[ix_cg(box, mode, 0) + q] += cacc;
             A.cg[ix_cg(box, mode, 1) + q] += racc;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- reverse passes, 16 inputs
+//
+// The adjoint of one pass for networks with 16 inputs and at most three hidden layers,
+// both directions of one box in a workgroup, 16 target rows at a time.  The products
+// are formed transposed (A: weights of listed neurons, B: 16 rows), so that the
+// accumulator of one level (lane l: neuron [4 i + l/16] of row [l%16]) becomes, after
+// the relaxation's selection, the B operand of the next without leaving the registers:
+//   level 1     Omega-bar_1 = W_1 Lambda-bar_0, four k-steps a tile;
+//   last level  (j = k - 1) only enters through s-bar = sum_r sel Omega-bar Lambda, which is
+//               linear in Omega-bar: each wave contracts the part of Omega-bar that its own
+//               tiles of the level below contribute, and only the sums s-bar meet;
+//   k = 3       a wave owns every fourth tile of level 1 and takes the last level's k-steps
+//               of those tiles;
+//   k = 4       every wave forms all of level 1 (a tenth of the pass), owns every fourth tile
+//               of level 2 and takes the last level's k-steps of those.
+// No barrier between the lists and the final sums.  Lists: the neurons that are not stably
+// inactive of the levels below the last one, the unstable ones of the last (nothing is
+// propagated past it, and s-bar and t-bar are used for those only), and the target rows
+// with an adjoint (unstable neurons of a hidden target).
+//
+// What bounds it: the latency of the operand reads (the levels' rows from memory, the
+// weights from L2) between short runs of MFMA (about 100 us of them at k = 3 and at
+// k = 4), two waves a SIMD.  3,200 boxes of 16-256-256-256-12, k = 2, 3, 4: 69, 590,
+// 385 us (one direction at a time through LDS with barriers at each level: 390, 1,126,
+// 678; one direction a workgroup and three waves a SIMD: 99, 899, 568; the next rows and
+// the next tile read ahead: 80, 590-680, 395).
+constexpr int NR_PAD = NN_MAXW + 16;
+
+struct RevLevel {                    // listed neurons of one level, zero past the end
+    int idx[NR_PAD];
+    double v[4][NR_PAD];             // s, t, a, bias (last level: bias only)
+};
+
+// Lists the kept neurons (one per lane, 256 lanes); returns their number.  Contains barriers.
+__device__ __forceinline__ int rev_list(bool keep, int* idx, int* cnt, int& pos) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t bal = __ballot(keep);
+    if (lane == 0) cnt[wave] = __popcll(bal);
+    __syncthreads();
+    int off = 0, n = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        off += q < wave ? cnt[q] : 0;
+        n += cnt[q];
+    }
+    pos = keep ? off + __popcll(bal & ((1ull << lane) - 1ull)) : -1;
+    if (keep) idx[pos] = tid;
+    __syncthreads();                                     // cnt read
+    return n;
+}
+
+template <int K>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) nn_rev_kernel(NbArgs A) {
+    __shared__ RevLevel lev[K - 1];
+    __shared__ int srow[NR_PAD], cnt[4];
+    // s-bar, t-bar of levels with one owner a tile; the last level's s-bar one part a wave (k > 2)
+    __shared__ double sst[K - 1][2][NR_PAD];
+    __shared__ double spart[K > 2 ? 4 : 1][NR_PAD];
+    const int box = blockIdx.x, tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (!A.ok[box]) return;
+    const int L = A.L, M = A.w[K], wl = A.w[K - 1];
+    const bool top = K == L;
+    int pos, nrows, nlev[K - 1];
+    {
+        const double lo = !top && tid < M ? A.bd[ix_bd(box, K, 0) + tid] : 0.0;
+        const double hi = !top && tid < M ? A.bd[ix_bd(box, K, 1) + tid] : 0.0;
+        const int n = rev_list(tid < M && (top || (lo < 0.0 && hi > 0.0)), srow, cnt, pos);
+        if (n == 0) return;                              // the same for every lane
+        nrows = n;
+    }
+#pragma unroll
+    for (int j = 1; j < K; ++j) {
+        const int nj = A.w[j];
+        const double lo = tid < nj ? A.bd[ix_bd(box, j, 0) + tid] : -1.0;
+        const double hi = tid < nj ? A.bd[ix_bd(box, j, 1) + tid] : -1.0;
+        RevLevel& v = lev[j - 1];
+        const int n = rev_list(j == K - 1 ? lo < 0.0 && hi > 0.0 : lo >= 0.0 || hi > 0.0, v.idx, cnt, pos);
+        if (pos >= 0) {
+            double s, t, a;
+            nb_relax(lo, hi, s, t, a);
+            v.v[0][pos] = s; v.v[1][pos] = t; v.v[2][pos] = a; v.v[3][pos] = A.b[j - 1][tid];
+        }
+        if (tid < 16) {
+            v.idx[n + tid] = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v.v[q][n + tid] = 0.0;
+        }
+        for (int q = tid; q < NR_PAD; q += 256) {
+            sst[j - 1][0][q] = sst[j - 1][1][q] = 0.0;
+            if (j == K - 1) {
+#pragma unroll
+                for (int w = 0; w < (K > 2 ? 4 : 1); ++w) spart[w][q] = 0.0;
+            }
+        }
+        nlev[j - 1] = n;
+    }
+    __syncthreads();
+    const int nlast = nlev[K - 2], nut = (nlast + 15) >> 4, nt1 = (nlev[0] + 15) >> 4;
+    const RevLevel& last = lev[K - 2];
+    const double* WTk = A.WT[K - 1];                     // rows of W_k, transposed: [w_{k-1}][M]
+    double* const lv = A.lv + (size_t)box * 2 * A.lv_bm;
+    double cv[4], rv[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        cv[s] = A.cr[ix_cr(box, 0) + 4 * s + g];
+        rv[s] = A.cr[ix_cr(box, 1) + 4 * s + g];
+    }
+    double cacc[4] = {0.0, 0.0, 0.0, 0.0}, racc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int r0 = 0; r0 < nrows; r0 += 16) {
+        const int row = srow[r0 + r < nrows ? r0 + r : 0];
+        // row seeds (0 past the last row), seeds of Lambda^(0), direct c and rho terms
+        double y[2], seed[2][4];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            double v = top ? (m == 0 ? A.g_hi : A.g_lo)[(A.u0 + box) * M + row] : A.ub[ix_ub(box, K, m) + row];
+            y[m] = r0 + r < nrows ? v : 0.0;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double jv = top ? A.jac[((size_t)box * M + row) * 16 + 4 * s + g] : 0.0;
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const double sgn = m == 0 ? 1.0 : -1.0;
+                const double d = lv[m * A.lv_bm + A.lv_off[K][0] + (size_t)row * 16 + 4 * s + g] - jv;
+                const double sd = d > 0.0 ? 1.0 : (d < 0.0 ? -1.0 : 0.0);
+                cacc[s] += y[m] * d;
+                racc[s] += sgn * y[m] * fabs(d);
+                seed[m][s] = y[m] * (cv[s] + sgn * sd * rv[s]);
+            }
+        }
+        // Omega-bar of one tile of level 1 (listed neurons 16 t + 4 i + g)
+        auto level1 = [&](const RevLevel& v, int t, nbd4 (&D)[2]) {
+            const double* w = A.W[0] + (size_t)v.idx[16 * t + r] * 16 + g;
+            double a[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) a[s] = w[4 * s];
+            D[0] = D[1] = nbd4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) D[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], seed[m][s], D[m], 0, 0, 0);
+        };
+        // Lambda-bar of a tile of level j from its Omega-bar (in place), and, where `sums`, its
+        // part of s-bar and t-bar
+        auto select = [&](int j, const RevLevel& v, int t, nbd4 (&D)[2], bool sums) {
+            const double* l0 = lv + A.lv_off[K][j] + (size_t)row * A.w[j];
+            double lm[2][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = v.idx[16 * t + 4 * i + g];
+#pragma unroll
+                for (int m = 0; m < 2; ++m) lm[m][i] = l0[m * A.lv_bm + n];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = 16 * t + 4 * i + g;
+                const double s = v.v[0][n], tt = v.v[1][n], a = v.v[2][n], b = v.v[3][n];
+                double sa = 0.0, ta = 0.0;
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const bool sel = m == 0 ? lm[m][i] >= 0.0 : lm[m][i] < 0.0;
+                    const double ob = D[m][i] + y[m] * b;
+                    sa += sel ? ob * lm[m][i] : 0.0;
+                    ta += sel ? y[m] * lm[m][i] : 0.0;
+                    D[m][i] = ob * (sel ? s : a) + (sel ? y[m] * tt : 0.0);
+                }
+                if (sums) {
+                    sa = sum16(sa);
+                    ta = sum16(ta);
+                    if (r == 0) {
+                        sst[j - 1][0][n] += sa;
+                        sst[j - 1][1][n] += ta;
+                    }
+                }
+            }
+        };
+        // s-bar and t-bar of a tile of the last level from (this wave's part of) its Omega-bar;
+        // whole: also the bias and t-bar terms
+        auto finish = [&](int t, const nbd4 (&D)[2], bool whole, double* part) {
+            double lm[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lm[i] = WTk[(size_t)last.idx[16 * t + 4 * i + g] * M + row];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = 16 * t + 4 * i + g;
+                const double yb = whole ? last.v[3][n] : 0.0;
+                // upper pass selects lm >= 0, lower pass lm < 0
+                const bool up = lm[i] >= 0.0;
+                const double sa = sum16(((up ? D[0][i] : D[1][i]) + (up ? y[0] : y[1]) * yb) * lm[i]);
+                if (whole) {
+                    const double ta = sum16((up ? y[0] : y[1]) * lm[i]);
+                    if (r == 0) sst[K - 2][1][n] += ta;
+                }
+                if (r == 0) part[n] += sa;
+            }
+        };
+        if constexpr (K == 2) {
+            for (int t = wave; t < nut; t += 4) {
+                nbd4 D[2];
+                level1(last, t, D);
+                finish(t, D, true, sst[0][0]);
+            }
+        } else if constexpr (K == 3) {
+            // own tiles of level 1, up to four tiles of the last level at a time (once even
+            // if it has none, for the sums of level 1)
+            const double* WT2 = A.WT[1];
+            for (int t0 = 0; t0 == 0 || t0 < nut; t0 += 4) {
+                nbd4 acc[4][2];
+                int uc[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[q][0] = acc[q][1] = nbd4{0.0, 0.0, 0.0, 0.0};
+                    uc[q] = last.idx[t0 + q < nut ? 16 * (t0 + q) + r : 0];
+                }
+                for (int t = wave; t < nt1; t += 4) {
+                    nbd4 D[2];
+                    level1(lev[0], t, D);
+                    double a[4][4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const double* w = WT2 + (size_t)lev[0].idx[16 * t + 4 * i + g] * wl;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) a[i][q] = w[uc[q]];
+                    }
+                    select(1, lev[0], t, D, t0 == 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (t0 + q >= nut) break;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+#pragma unroll
+                            for (int m = 0; m < 2; ++m)
+                                acc[q][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][q], D[m][i], acc[q][m], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (t0 + q < nut) finish(t0 + q, acc[q], ((t0 + q) & 3) == wave, spart[wave]);
+            }
+        } else {
+            // own tiles of level 2 over all of level 1
+            const double* WT2 = A.WT[1];
+            const double* WT3 = A.WT[2];
+            const int w2 = A.w[2], nt2 = (nlev[1] + 15) >> 4, nmine = (nt2 - wave + 3) >> 2;
+            nbd4 acc[4][2];
+            int oc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc[q][0] = acc[q][1] = nbd4{0.0, 0.0, 0.0, 0.0};
+                oc[q] = lev[1].idx[q < nmine ? 16 * (wave + 4 * q) + r : 0];
+            }
+            for (int t = 0; t < nt1; ++t) {
+                nbd4 D[2];
+                level1(lev[0], t, D);
+                double a[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double* w = WT2 + (size_t)lev[0].idx[16 * t + 4 * i + g] * w2;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) a[i][q] = w[oc[q]];
+                }
+                select(1, lev[0], t, D, (t & 3) == wave);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (q >= nmine) break;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int m = 0; m < 2; ++m)
+                            acc[q][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][q], D[m][i], acc[q][m], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (q < nmine) select(2, lev[1], wave + 4 * q, acc[q], true);
+            for (int t = 0; t < nut; ++t) {
+                nbd4 D[2] = {nbd4{0.0, 0.0, 0.0, 0.0}, nbd4{0.0, 0.0, 0.0, 0.0}};
+                const int u = last.idx[16 * t + r];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (q >= nmine) break;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const double a = WT3[(size_t)lev[1].idx[16 * (wave + 4 * q) + 4 * i + g] * wl + u];
+#pragma unroll
+                        for (int m = 0; m < 2; ++m)
+                            D[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, acc[q][m][i], D[m], 0, 0, 0);
+                    }
+                }
+                finish(t, D, (t & 3) == wave, spart[wave]);
+            }
+        }
+    }
+    __syncthreads();
+    // the sums of both directions, into the upper direction's slots
+#pragma unroll
+    for (int j = 1; j < K; ++j) {
+        if (tid >= nlev[j - 1]) continue;
+        double s = sst[j - 1][0][tid];
+        if (K > 2 && j == K - 1) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s += spart[K > 2 ? w : 0][tid];
+        }
+        const int n = lev[j - 1].idx[tid];
+        A.st[ix_st(box, 0, j, 0) + n] += s;
+        A.st[ix_st(box, 0, j, 1) + n] += sst[j - 1][1][tid];
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double c = sum16(cacc[s]), h = sum16(racc[s]);
+            if (r == 0) {
+                A.cg[ix_cg(box, 0, 0) + 4 * s + g] += c;
+                A.cg[ix_cg(box, 0, 1) + 4 * s + g] += h;
+            }
         }
     }
 }
@@ -979,14 +1294,18 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
                 }
                 hipLaunchKernelGGL(nbm_pass_kernel<false>, grid, dim3(NB_T), 0, st, a);
             }
-            a.k = L;
-            hipLaunchKernelGGL(nbm_pass_kernel<true>, grid, dim3(NB_T), 0, st, a);
+            auto reverse = [&](int k) {
+                a.k = k;
+                if (!chain) hipLaunchKernelGGL(nbm_pass_kernel<true>, grid, dim3(NB_T), 0, st, a);
+                else if (k == 2) hipLaunchKernelGGL(nn_rev_kernel<2>, dim3((unsigned)nb), dim3(NB_T), 0, st, a);
+                else if (k == 3) hipLaunchKernelGGL(nn_rev_kernel<3>, dim3((unsigned)nb), dim3(NB_T), 0, st, a);
+                else hipLaunchKernelGGL(nn_rev_kernel<4>, dim3((unsigned)nb), dim3(NB_T), 0, st, a);
+            };
+            reverse(L);
             for (int j = L - 1; j >= 1; --j) {
                 a.k = j;
                 hipLaunchKernelGGL(nb_radj_kernel, dim3((unsigned)nb), dim3(NB_T), 0, st, a);
-                if (j >= 2) {
-                    hipLaunchKernelGGL(nbm_pass_kernel<true>, grid, dim3(NB_T), 0, st, a);
-                }
+                if (j >= 2) reverse(j);
             }
             hipLaunchKernelGGL(nb_out_kernel, dim3((unsigned)nb), dim3(NB_T), 0, st, a);
             continue;

@@ -41,6 +41,7 @@
 
 #include <mutex>
 
+#include "dpp.hpp"
 #include "leb.h"
 #include "leb_internal.hpp"
 #include "pbh_node.hpp"
@@ -1146,20 +1147,6 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_tube_kernel(TubeRowArgs a, do
 }
 
 typedef double sls_p2 __attribute__((ext_vector_type(2), aligned(8)));
-
-// x + x of the partner lane of a data-parallel-primitive pattern (no LDS):
-// 0xB1, 0x4E: lanes 1, 2 away within four; 0x141, 0x140: mirrored within eight, sixteen
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double x) {
-    union { double d; int w[2]; } u;
-    u.d = x;
-    u.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], CTRL, 0xf, 0xf, true);
-    u.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], CTRL, 0xf, 0xf, true);
-    return x + u.d;
-}
-__device__ __forceinline__ double sum4(double x) { return dpp_add<0x4E>(dpp_add<0xB1>(x)); }
-__device__ __forceinline__ double sum8(double x) { return dpp_add<0x141>(sum4(x)); }
-__device__ __forceinline__ double sum16(double x) { return dpp_add<0x140>(sum8(x)); }
 
 // M[row][col] of a matrix with rows of C elements, 0 outside (a row past its end is
 // out of the descriptor's range)

@@ -192,3 +192,30 @@ def test_nn_backward_unstable_rows(gpu, widths, scale):
     g = _gpu_grad(leb, net, z, v, sg, mu, g_lo, g_hi, gpu)
     for k in range(3):
         _check_box(net, g, 0, k, z, v, sg, mu, g_lo, g_hi, "rows %s %g" % (widths, scale))
+
+
+@pytest.mark.parametrize("widths", [[16, 16, 8], [16, 256, 16, 12], [16, 96, 256, 12], [16, 32, 256, 48, 64],
+                                    [16, 256, 16, 256, 20], [16, 80, 256, 256, 8]])
+@pytest.mark.parametrize("shift", [0.0, 20.0, -20.0])
+def test_nn_backward_reverse_tiles(gpu, widths, shift):
+    """Reverse passes of 16-input networks: one to three hidden layers, one to
+    sixteen tiles of every level (more than four of the last), several output
+    row blocks, layers above the first mixed, all active or all inactive."""
+    import paper_2607_01203_amd as leb
+    rng = W.rng_for(5200 + widths[1] + 3 * widths[2] + len(widths))
+    nx = min(widths[-1], 16)
+    net, z, v, sg, mu, g_lo, g_hi = _case(rng, widths, nx, 1, 2, 0.3, 1.5, True)
+    b = [x + np.float32(shift) if 0 < i < len(net.b) - 1 else x for i, x in enumerate(net.b)]
+    net = W.MLPNet(net.W, b, nx, 16 - nx, True)
+    print("case: nn backward reverse %s shift %g" % (widths, shift), flush=True)
+    if widths[-1] == nx:
+        g = _gpu_grad(leb, net, z, v, sg, mu, g_lo, g_hi, gpu)
+    else:
+        import torch
+        mlp = leb.MLP(net.W, net.b, nx, False)
+        g = leb.nn_backward(mlp, _t(z, gpu), _t(v, gpu), _t(sg, gpu), _t(g_lo, gpu), _t(g_hi, gpu), mu=_t(mu, gpu))
+        torch.cuda.synchronize()
+        g = {k: x.cpu().numpy() for k, x in g.items()}
+        mlp.close()
+    for k in range(2):
+        _check_box(net, g, 0, k, z, v, sg, mu, g_lo, g_hi, "reverse %s %g" % (widths, shift))
