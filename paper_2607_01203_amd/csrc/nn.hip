@@ -54,7 +54,7 @@ namespace leb {
 
 struct PrepArgs {
     const double* z; const double* v; const double* mu; const double* sigma;
-    int64_t u0; int nbox;
+    int64_t u0; int nbox, nact;                            // boxes of the chunk's buffers, of this launch
     int L; int w[NN_MAXL + 1]; int nx, nu;
     const double* W[NN_MAXL]; const double* WT[NN_MAXL]; const double* b[NN_MAXL];
     // outputs (chunk-local)
@@ -168,10 +168,24 @@ struct RelaxArgs {
     const double* WT;                       // layer l transposed [w[l-1]][w[l]]
     const double* b;                        // [w[l]]
     const double* zhat;                     // [box][W]
-    int in, out, n0;
+    int in, out, n0, nact;
     double* s; double* t; double* a; double* D; double* e; double* amax;   // [box][W]
     uint32_t* boxflags;                     // [box]
 };
+
+// Relaxation coefficients of one neuron with bounds [l, u] (s rounded up: the line stays above
+// relu on [l, u])
+__device__ __forceinline__ void relax_coeffs(double l, double u, double& s, double& t, double& a) {
+    if (l >= 0.0) { s = 1.0; t = 0.0; a = 1.0; }
+    else if (u <= 0.0) { s = 0.0; t = 0.0; a = 0.0; }
+    else {
+        s = u / (u - l);
+        s = s + s * 0x1p-50;
+        t = -s * l;
+        t = t + t * 0x1p-50;
+        a = (u >= -l) ? 1.0 : 0.0;
+    }
+}
 
 // sound relaxation coefficients and rounding weights e = zmax + |W| amax_prev + |b| + |t|
 __global__ void __launch_bounds__(256) nn_relax_kernel(RelaxArgs A) {
@@ -188,15 +202,7 @@ __global__ void __launch_bounds__(256) nn_relax_kernel(RelaxArgs A) {
     if (q >= A.out) return;
     const double l = A.lo[o], u = A.hi[o];
     double s, t, a;
-    if (l >= 0.0) { s = 1.0; t = 0.0; a = 1.0; }
-    else if (u <= 0.0) { s = 0.0; t = 0.0; a = 0.0; }
-    else {
-        s = u / (u - l);
-        s = s + s * 0x1p-50;             // rounded up: the line stays above relu on [l, u]
-        t = -s * l;
-        t = t + t * 0x1p-50;
-        a = (u >= -l) ? 1.0 : 0.0;
-    }
+    relax_coeffs(l, u, s, t, a);
     double wa = 0.0;
     int k = 0;
     for (; k + 8 <= A.in; k += 8) {           // the weight loads of a group issued before its sums
@@ -211,6 +217,203 @@ __global__ void __launch_bounds__(256) nn_relax_kernel(RelaxArgs A) {
     A.D[o] = A.zhat[o] > 0.0 ? 1.0 : 0.0;
     A.e[o] = fmax(fabs(l), fabs(u)) + wa + fabs(A.b[q]) + fabs(t);
     A.amax[o] = fmax(u, 0.0);
+}
+
+// ---------------------------------------------------------- 16 boxes a workgroup
+//
+// nn_prep_kernel and nn_relax_kernel read every weight of the network for one box; with
+// many boxes that is what they wait for (3,200 boxes of 16-256-256-256-12: 3.4 GB from
+// L2 for each).  The forms below take 16 boxes as the columns of FP64 MFMA
+// (v_mfma_f64_16x16x4: Y^T = W X^T, A: a weight tile from W^T, B: 16 boxes' inputs in
+// LDS).  The instruction adds its four products in order, each rounded, so every sum
+// is bitwise the fused-multiply-add chain of the one-box kernels.
+//
+// Eight waves, wave w the output tiles w and w + 8.  What bounds them: MFMA at one
+// workgroup a compute unit (three chains of 256 x 256 products, 41 us for prep at 200
+// workgroups).  3,200 boxes: prep 93 us (one box a workgroup: 250; four boxes on the
+// VALU, bound by broadcast reads of LDS: 197), relax 27 us (102; 47).  The whole bound with
+// the grouped and the one-box form: 235 and 144 us at 50 boxes, 452 and 391 at 400, 692
+// and 693 at 800, 1,138 and 1,228 at 1,600, 2,048 and 2,343 at 3,200.
+constexpr int NNG_BOXES = 16, NNG_T = 512, NNG_RS = 17;     // boxes, lanes, LDS row stride
+constexpr int NNG_MIN = 1024;                               // fewest boxes for the grouped form
+
+// Y[c][n][box] for the output tiles t = wave, wave + 8 (acc[q][c]): chain 0 by W, the others by
+// |W|; inputs X[c][k][box], RELU: of the neurons with X[0] > 0 (chains 0 and 2).
+template <int NC, bool RELU>
+__device__ __forceinline__ void group_products(const double* WT, int in, int out, const double* X, int wave, int r,
+                                               int g, d4 (&acc)[2][NC]) {
+    const int nt = (out + 15) >> 4;                          // a ragged last tile repeats its last output
+    if (wave >= nt) return;
+    const int t1 = wave + 8 < nt ? wave + 8 : wave;
+    const double* w0 = WT + (size_t)g * out + min(16 * wave + r, out - 1);
+    const double* w1 = WT + (size_t)g * out + min(16 * t1 + r, out - 1);
+    double wn[2][2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) { wn[p][0] = w0[(size_t)4 * p * out]; wn[p][1] = w1[(size_t)4 * p * out]; }
+    for (int s = 0; s < in >> 2; s += 2) {                  // widths are multiples of 16
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            double x[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[c] = X[(c * NN_MAXW + 4 * (s + p) + g) * NNG_RS + r];
+            if (RELU) {
+                const bool on = x[0] > 0.0;
+                x[0] = on ? x[0] : 0.0;
+                if (NC > 2) x[NC - 1] = on ? x[NC - 1] : 0.0;
+            }
+            const double a0 = wn[p][0], a1 = wn[p][1];
+            const size_t o = (size_t)4 * (s + p + 2 < in >> 2 ? s + p + 2 : s + p) * out;
+            wn[p][0] = w0[o];
+            wn[p][1] = w1[o];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                acc[0][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(c == 0 && NC > 1 ? a0 : fabs(a0), x[c], acc[0][c], 0, 0, 0);
+                acc[1][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(c == 0 && NC > 1 ? a1 : fabs(a1), x[c], acc[1][c], 0, 0, 0);
+            }
+        }
+    }
+}
+
+constexpr size_t NNG_LDS = (size_t)3 * NN_MAXW * NNG_RS * sizeof(double);
+
+__global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
+    extern __shared__ __attribute__((aligned(16))) double X[];       // [3][NN_MAXW][NNG_RS]
+    __shared__ uint32_t s_flag[NNG_BOXES];
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b0 = blockIdx.x * NNG_BOXES, nb = min(NNG_BOXES, A.nact - b0);
+    const int n0 = A.w[0], m = A.w[A.L];
+    auto X_ = [&](int c, int n, int b) -> double& { return X[(c * NN_MAXW + n) * NNG_RS + b]; };
+    // rows [box][n] of an array from LDS plane c
+    auto store = [&](double* dst, int c, int cols) {
+        for (int e = tid; e < nb * cols; e += NNG_T) {
+            const int b = e / cols, n = e - b * cols;
+            dst[(size_t)(b0 + b) * NN_MAXW + n] = X_(c, n, b);
+        }
+    };
+    if (tid < NNG_BOXES) s_flag[tid] = 0;
+    __syncthreads();
+    // box = hull({a~}, a~ + mu +/- sigma): centre and half-width, widened so the FP64 box
+    // encloses the exact one; planes: centre, its magnitude, half-width
+    for (int e = tid; e < NNG_BOXES * n0; e += NNG_T) {
+        const int b = e / n0, q = e - b * n0, box = b0 + min(b, nb - 1);
+        const int64_t unit = A.u0 + box;
+        const double x = q < A.nx ? A.z[unit * A.nx + q] : A.v[unit * A.nu + (q - A.nx)];
+        const double sg = A.sigma[unit * n0 + q];
+        const double mu = A.mu ? A.mu[unit * n0 + q] : 0.0;
+        uint32_t f = 0;
+        if (!isfinite(x) || !isfinite(sg) || !isfinite(mu) || !(sg >= 0.0)) f |= LEB_FLAG_BAD_INPUT;
+        if (fabs(mu) > sg) f |= LEB_FLAG_HULL_EXTENDED;
+        if (f) atomicOr(&s_flag[b], f);
+        const double dlo = fmin(mu - sg, 0.0), dhi = fmax(mu + sg, 0.0);
+        const double cc = x + 0.5 * (dlo + dhi);
+        double rr = 0.5 * (dhi - dlo);
+        rr = rr + rr * 0x1p-50 + (fabs(x) + fabs(dlo) + fabs(dhi)) * 0x1p-51;
+        X_(0, q, b) = cc; X_(1, q, b) = fabs(cc); X_(2, q, b) = rr;
+        if (b < nb) { A.alpha[box * n0 + q] = x; A.c[box * n0 + q] = cc; A.rho[box * n0 + q] = rr; }
+    }
+    __syncthreads();
+    // l = -1: first layer bounds, exact affine image of the box (planes lin, abs, mag);
+    // l >= 0: nominal forward pass, magnitude chains (nominal error, Jacobian error)
+    for (int l = -1; l < A.L; ++l) {
+        const int in = A.w[l < 0 ? 0 : l], out = A.w[l < 0 ? 1 : l + 1];
+        const double* W = A.WT[l < 0 ? 0 : l];
+        const double* bias = A.b[l < 0 ? 0 : l];
+        const bool last = l == A.L - 1;
+        d4 acc[2][3];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = 16 * (wave + 8 * q) + 4 * i + g;
+                const double b = n < out ? bias[n] : 0.0;
+                acc[q][0][i] = b;
+                acc[q][1][i] = fabs(b);
+                acc[q][2][i] = 0.0;
+            }
+        if (l <= 0) group_products<3, false>(W, in, out, X, wave, r, g, acc);
+        else group_products<3, true>(W, in, out, X, wave, r, g, acc);
+        __syncthreads();                                     // the inputs are read
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (16 * (wave + 8 * q) >= out) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = 16 * (wave + 8 * q) + 4 * i + g;
+                const double z = acc[q][0][i], mz = acc[q][1][i], vz = acc[q][2][i];
+                if (l < 0) {
+                    const double err = RT * (mz + vz + fabs(z));
+                    X_(0, n, r) = z - vz - err;
+                    X_(1, n, r) = z + vz + err;
+                } else if (!last) {
+                    X_(0, n, r) = z;
+                    X_(1, n, r) = mz;
+                    X_(2, n, r) = vz;
+                } else if (r < nb && n < out) {
+                    A.g[(b0 + r) * m + n] = z;
+                    // |g^ - g| and |(J^ - J)(a - a~)| allowances
+                    A.eg[(b0 + r) * m + n] = RT * (mz + vz);
+                }
+            }
+        }
+        __syncthreads();
+        if (l < 0) {
+            store(A.lo, 0, out);
+            store(A.hi, 1, out);
+            __syncthreads();
+            // planes of the forward pass: input, its magnitude, |a - a~| bound
+            for (int e = tid; e < NNG_BOXES * n0; e += NNG_T) {
+                const int b = e / n0, q = e - b * n0, box = b0 + min(b, nb - 1);
+                const double x = A.alpha[box * n0 + q];
+                X_(0, q, b) = x; X_(1, q, b) = fabs(x);
+                X_(2, q, b) = fabs(A.c[box * n0 + q] - x) + A.rho[box * n0 + q];
+            }
+            __syncthreads();
+        } else if (!last) {
+            store(A.zhat + (size_t)l * A.nbox * NN_MAXW, 0, out);
+        }
+    }
+    if (tid < nb) A.flags[b0 + tid] = s_flag[tid];
+}
+
+__global__ void __launch_bounds__(NNG_T) nn_relax_group_kernel(RelaxArgs A) {
+    __shared__ double X[NN_MAXW * NNG_RS];
+    __shared__ uint32_t s_uns[NNG_BOXES];
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b0 = blockIdx.x * NNG_BOXES, nb = min(NNG_BOXES, A.nact - b0);
+    if (tid < NNG_BOXES) s_uns[tid] = 0;
+    for (int e = tid; e < NNG_BOXES * A.in; e += NNG_T) {
+        const int b = e / A.in, q = e - b * A.in, box = b0 + min(b, nb - 1);
+        X[q * NNG_RS + b] = A.amax_prev ? A.amax_prev[(size_t)box * NN_MAXW + q]
+                                        : fabs(A.c[box * A.n0 + q]) + A.rho[box * A.n0 + q];
+    }
+    __syncthreads();
+    d4 acc[2][1];
+    acc[0][0] = acc[1][0] = d4{0.0, 0.0, 0.0, 0.0};
+    group_products<1, false>(A.WT, A.in, A.out, X, wave, r, g, acc);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (16 * (wave + 8 * q) >= A.out) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) X[(16 * (wave + 8 * q) + 4 * i + g) * NNG_RS + r] = acc[q][0][i];
+    }
+    __syncthreads();
+    for (int e = tid; e < nb * A.out; e += NNG_T) {
+        const int b = e / A.out, q = e - b * A.out;
+        const size_t o = (size_t)(b0 + b) * NN_MAXW + q;
+        const double l = A.lo[o], u = A.hi[o];
+        if (l < 0.0 && u > 0.0) s_uns[b] = 1u;
+        double s, t, a;
+        relax_coeffs(l, u, s, t, a);
+        A.s[o] = s; A.t[o] = t; A.a[o] = a;
+        A.D[o] = A.zhat[o] > 0.0 ? 1.0 : 0.0;
+        A.e[o] = fmax(fabs(l), fabs(u)) + X[q * NNG_RS + b] + fabs(A.b[q]) + fabs(t);
+        A.amax[o] = fmax(u, 0.0);
+    }
+    __syncthreads();
+    if (tid < nb && s_uns[tid]) A.boxflags[b0 + tid] |= NN_UNSTABLE;
 }
 
 // ----------------------------------------------------------- concretize
@@ -459,14 +662,27 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
     for (int64_t u0 = 0; u0 < units; u0 += CB) {
         const int nb = (int)((units - u0) < CB ? (units - u0) : CB);
         PrepArgs pa;
-        pa.z = z; pa.v = v; pa.mu = mu; pa.sigma = sigma; pa.u0 = u0; pa.nbox = CB;
+        pa.z = z; pa.v = v; pa.mu = mu; pa.sigma = sigma; pa.u0 = u0; pa.nbox = CB; pa.nact = nb;
         pa.L = L;
         for (int l = 0; l <= L; ++l) pa.w[l] = net->w[l];
         pa.nx = net->nx; pa.nu = net->nu;
         for (int l = 0; l < L; ++l) { pa.W[l] = net->W[l]; pa.WT[l] = net->WT[l]; pa.b[l] = net->b[l]; }
         pa.alpha = alpha; pa.c = c; pa.rho = rho; pa.zhat = zhat; pa.lo = lo; pa.hi = hi; pa.g = g; pa.eg = eg;
         pa.flags = fl;
-        hipLaunchKernelGGL(nn_prep_kernel, dim3(nb), dim3(256), 0, st, pa);
+        const bool groups = nb >= NNG_MIN;
+        const int ng = (nb + NNG_BOXES - 1) / NNG_BOXES;
+        if (groups) {
+            static bool attr = false;
+            if (!attr) {
+                if (hipFuncSetAttribute((const void*)nn_prep_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)NNG_LDS) != hipSuccess)
+                    return LEB_EDEVICE;
+                attr = true;
+            }
+            hipLaunchKernelGGL(nn_prep_group_kernel, dim3(ng), dim3(NNG_T), NNG_LDS, st, pa);
+        } else {
+            hipLaunchKernelGGL(nn_prep_kernel, dim3(nb), dim3(256), 0, st, pa);
+        }
         if (hipGetLastError() != hipSuccess) return LEB_EDEVICE;
         auto relax = [&](int l) -> int {     // hidden layer l+1 (0-based l)
             RelaxArgs ra;
@@ -478,7 +694,9 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
             ra.s = layer(s, l); ra.t = layer(t, l); ra.a = layer(a, l); ra.D = layer(D, l);
             ra.e = layer(e, l); ra.amax = layer(amax, l);
             ra.boxflags = fl;
-            hipLaunchKernelGGL(nn_relax_kernel, dim3(nb), dim3(256), 0, st, ra);
+            ra.nact = nb;
+            if (groups) hipLaunchKernelGGL(nn_relax_group_kernel, dim3(ng), dim3(NNG_T), 0, st, ra);
+            else hipLaunchKernelGGL(nn_relax_kernel, dim3(nb), dim3(256), 0, st, ra);
             return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
         };
         if ((rc = relax(0))) return rc;

@@ -196,3 +196,32 @@ def test_nn_chain_tiles(gpu, widths, shift):
     assert (np.maximum(-lo, hi)[zero] <= 8.0 * 2.0 ** -40 * m[zero]).all()
     check_bounds(lo[~zero], hi[~zero], o["r_lo"][~zero], o["r_hi"][~zero], "nn chain")
     mlp.close()
+
+
+@pytest.mark.parametrize("widths", [[16, 256, 256, 256, 12], [32, 48, 144, 64], [16, 16, 20], [48, 128, 16, 33]])
+def test_nn_groups_of_boxes(gpu, widths):
+    """From 1,024 boxes on, 16 boxes share a workgroup in the forward pass and the
+    relaxations: the same bits as a box alone, in every place of a ragged last
+    group, with an invalid box among them."""
+    import torch
+    import paper_2607_01203_amd as leb
+    rng = W.rng_for(1510 + widths[1] + len(widths))
+    Wl, bl = W.mlp_weights(rng, widths)
+    nx = widths[0] - 4
+    a = rng.uniform(-1, 1, (1, 1033, widths[0]))
+    sg = rng.uniform(0.0, 0.1, a.shape)
+    mu = sg * rng.uniform(-1.2, 1.2, a.shape)
+    a[0, 700, 1] = np.nan
+    print("case: nn groups %s" % widths, flush=True)
+    mlp = leb.MLP(Wl, bl, nx, False)
+
+    def run(sl):
+        out = leb.nn_bound(mlp, _t(a[:, sl, :nx], gpu), _t(a[:, sl, nx:], gpu), _t(sg[:, sl], gpu), _t(mu[:, sl], gpu))
+        torch.cuda.synchronize()
+        return [out[k].cpu().numpy() for k in ("r_lo", "r_hi", "flags")]
+
+    big = run(slice(0, 1033))
+    for s0, s1 in ((0, 40), (690, 710), (1020, 1033)):
+        for x, y in zip(big, run(slice(s0, s1))):
+            assert np.array_equal(x[:, s0:s1], y)
+    mlp.close()
