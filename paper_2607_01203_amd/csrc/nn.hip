@@ -234,46 +234,6 @@ __global__ void __launch_bounds__(256) nn_relax_kernel(RelaxArgs A) {
 // VALU, bound by broadcast reads of LDS: 197), relax 27 us (102; 47).  The whole bound with
 // the grouped and the one-box form: 235 and 144 us at 50 boxes, 452 and 391 at 400, 692
 // and 693 at 800, 1,138 and 1,228 at 1,600, 2,048 and 2,343 at 3,200.
-constexpr int NNG_BOXES = 16, NNG_T = 512, NNG_RS = 17;     // boxes, lanes, LDS row stride
-constexpr int NNG_MIN = 1024;                               // fewest boxes for the grouped form
-
-// Y[c][n][box] for the output tiles t = wave, wave + 8 (acc[q][c]): chain 0 by W, the others by
-// |W|; inputs X[c][k][box], RELU: of the neurons with X[0] > 0 (chains 0 and 2).
-template <int NC, bool RELU>
-__device__ __forceinline__ void group_products(const double* WT, int in, int out, const double* X, int wave, int r,
-                                               int g, d4 (&acc)[2][NC]) {
-    const int nt = (out + 15) >> 4;                          // a ragged last tile repeats its last output
-    if (wave >= nt) return;
-    const int t1 = wave + 8 < nt ? wave + 8 : wave;
-    const double* w0 = WT + (size_t)g * out + min(16 * wave + r, out - 1);
-    const double* w1 = WT + (size_t)g * out + min(16 * t1 + r, out - 1);
-    double wn[2][2];
-#pragma unroll
-    for (int p = 0; p < 2; ++p) { wn[p][0] = w0[(size_t)4 * p * out]; wn[p][1] = w1[(size_t)4 * p * out]; }
-    for (int s = 0; s < in >> 2; s += 2) {                  // widths are multiples of 16
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            double x[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) x[c] = X[(c * NN_MAXW + 4 * (s + p) + g) * NNG_RS + r];
-            if (RELU) {
-                const bool on = x[0] > 0.0;
-                x[0] = on ? x[0] : 0.0;
-                if (NC > 2) x[NC - 1] = on ? x[NC - 1] : 0.0;
-            }
-            const double a0 = wn[p][0], a1 = wn[p][1];
-            const size_t o = (size_t)4 * (s + p + 2 < in >> 2 ? s + p + 2 : s + p) * out;
-            wn[p][0] = w0[o];
-            wn[p][1] = w1[o];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                acc[0][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(c == 0 && NC > 1 ? a0 : fabs(a0), x[c], acc[0][c], 0, 0, 0);
-                acc[1][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(c == 0 && NC > 1 ? a1 : fabs(a1), x[c], acc[1][c], 0, 0, 0);
-            }
-        }
-    }
-}
-
 constexpr size_t NNG_LDS = (size_t)3 * NN_MAXW * NNG_RS * sizeof(double);
 
 __global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
@@ -331,8 +291,8 @@ __global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
                 acc[q][1][i] = fabs(b);
                 acc[q][2][i] = 0.0;
             }
-        if (l <= 0) group_products<3, false>(W, in, out, X, wave, r, g, acc);
-        else group_products<3, true>(W, in, out, X, wave, r, g, acc);
+        if (l <= 0) group_products<3, true, false>(W, in, out, X, wave, r, g, acc);
+        else group_products<3, true, true>(W, in, out, X, wave, r, g, acc);
         __syncthreads();                                     // the inputs are read
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -391,7 +351,7 @@ __global__ void __launch_bounds__(NNG_T) nn_relax_group_kernel(RelaxArgs A) {
     __syncthreads();
     d4 acc[2][1];
     acc[0][0] = acc[1][0] = d4{0.0, 0.0, 0.0, 0.0};
-    group_products<1, false>(A.WT, A.in, A.out, X, wave, r, g, acc);
+    group_products<1, false, false>(A.WT, A.in, A.out, X, wave, r, g, acc);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 2; ++q) {

@@ -529,6 +529,50 @@ __global__ void __launch_bounds__(256, 2) nn_hid2_kernel(HidArgs A) {
     }
 }
 
+// ---------------------------------------------------------- 16 boxes a workgroup
+//
+// A layer's products for 16 boxes (the forms of nn.hip and nn_bwd.hip for many boxes).
+constexpr int NNG_BOXES = 16, NNG_T = 512, NNG_RS = 17;     // boxes, lanes, LDS row stride
+constexpr int NNG_MIN = 1024;                               // fewest boxes for the grouped form
+
+// Y[c][n][box] for the output tiles t = wave, wave + 8 (acc[q][c]): chain 0 by W (SIGNED, else by
+// |W|), the others by |W|; inputs X[c][k][box], RELU: of the neurons with X[0] > 0 (chains 0 and 2).
+template <int NC, bool SIGNED, bool RELU>
+__device__ __forceinline__ void group_products(const double* WT, int in, int out, const double* X, int wave, int r,
+                                               int g, d4 (&acc)[2][NC]) {
+    const int nt = (out + 15) >> 4;                          // a ragged last tile repeats its last output
+    if (wave >= nt) return;
+    const int t1 = wave + 8 < nt ? wave + 8 : wave;
+    const double* w0 = WT + (size_t)g * out + min(16 * wave + r, out - 1);
+    const double* w1 = WT + (size_t)g * out + min(16 * t1 + r, out - 1);
+    double wn[2][2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) { wn[p][0] = w0[(size_t)4 * p * out]; wn[p][1] = w1[(size_t)4 * p * out]; }
+    for (int s = 0; s < in >> 2; s += 2) {                  // widths are multiples of 16
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            double x[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[c] = X[(c * NN_MAXW + 4 * (s + p) + g) * NNG_RS + r];
+            if (RELU) {
+                const bool on = x[0] > 0.0;
+                x[0] = on ? x[0] : 0.0;
+                if (NC > 2) x[NC - 1] = on ? x[NC - 1] : 0.0;
+            }
+            const double a0 = wn[p][0], a1 = wn[p][1];
+            const size_t o = (size_t)4 * (s + p + 2 < in >> 2 ? s + p + 2 : s + p) * out;
+            wn[p][0] = w0[o];
+            wn[p][1] = w1[o];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                acc[0][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(c == 0 && SIGNED ? a0 : fabs(a0), x[c], acc[0][c], 0, 0, 0);
+                acc[1][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(c == 0 && SIGNED ? a1 : fabs(a1), x[c], acc[1][c], 0, 0, 0);
+            }
+        }
+    }
+}
+
+
 // ---------------------------------------------------------- fused chain
 //
 // The whole backward substitution of one target layer k, for one box, one

@@ -219,3 +219,28 @@ def test_nn_backward_reverse_tiles(gpu, widths, shift):
         mlp.close()
     for k in range(2):
         _check_box(net, g, 0, k, z, v, sg, mu, g_lo, g_hi, "reverse %s %g" % (widths, shift))
+
+
+@pytest.mark.parametrize("widths", [[16, 256, 256, 12], [48, 16, 96, 20], [16, 32, 48, 64, 16, 12]])
+def test_nn_backward_groups_of_boxes(gpu, widths):
+    """From 1,024 boxes on, 16 boxes share a workgroup in the nominal pass: the same
+    bits as in a small call, in a ragged last group, with an invalid box."""
+    import paper_2607_01203_amd as leb
+    rng = W.rng_for(6100 + widths[1] + len(widths))
+    nx = 12
+    net, z, v, sg, mu, g_lo, g_hi = _case(rng, widths, nx, 1, 1030, 0.01, 0.3, True)
+    z[0, 500, 2] = np.inf
+    print("case: nn backward groups %s" % widths, flush=True)
+    import torch
+    mlp = leb.MLP(net.W, net.b, nx, False)
+
+    def run(s):
+        g = leb.nn_backward(mlp, *(_t(x[:, s], gpu) for x in (z, v, sg, g_lo, g_hi)), mu=_t(mu[:, s], gpu))
+        torch.cuda.synchronize()
+        return {k: x.cpu().numpy() for k, x in g.items()}
+
+    big = run(slice(0, 1030))
+    for s0, s1 in ((0, 20), (490, 505), (1020, 1030)):
+        for k, x in run(slice(s0, s1)).items():
+            assert np.array_equal(big[k][:, s0:s1], x), k
+    mlp.close()
