@@ -307,8 +307,8 @@ __device__ double kZero8[8];          // zero-initialised; stands in for Phi at 
 // and after the tube loads; the short form has no loop around a load.
 template <bool FP, bool LONG, int RT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) tube_map2_kernel(const double* __restrict__ phi, Tube2Args A, TubeFP P) {
-    // LDS: the affine table [N][8] and per-lag affine sums [N-1][8] (FP64), a
-    // spare [4]; then FP32: Phi rows' columns 3, 4 for lags -4..N-1 [(N+4)*16],
+    // LDS: the affine table [N][8], per-lag affine sums [N-1][8] and sums of eight of
+    // them (FP64), a spare [4]; then FP32: Phi rows' columns 3, 4 for lags -4..N-1 [(N+4)*16],
     // c and w [2(N-1)+8][16]
     extern __shared__ double lds2[];
     __shared__ uint32_t sbad[16];
@@ -321,7 +321,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     const int kfull = 2 * nst, kpad = kfull + 8;
     double* dtab = lds2;                                // [N][8]
     double* g = dtab + N * 8;                           // [N-1][8]
-    double* spare = g + nst * 8;                        // [4], written, never read
+    double* dsum = g + nst * 8;                         // [ceil((N-1)/8)][8]: sums of eight lags
+    double* spare = dsum + ((nst + 7) >> 3) * 8;        // [4], written, never read
     float* sp = reinterpret_cast<float*>(spare + 4);    // sp[(lag + 4) * 16 + r * 2 + q'], q' = row 3 + q'
     float* sc = sp + (N + 4) * 16;                      // [kpad][16]
     float* sw = sc + (size_t)kpad * 16;
@@ -486,20 +487,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     else if (tid < 80) sp[(nst + 4) * 16 + tid - 64] = 0.0f;
     if (tid < 128) { sc[kfull * 16 + tid] = 0.0f; sw[kfull * 16 + tid] = 0.0f; }   // 8 zero rows past the end
     __syncthreads();
-    // affine table: dtab[k][r] = sum_{d<k} g[d][r], summed in increasing d
-    for (int t = tid; t < N * 8; t += 256) {
-        const int k = t >> 3, r = t & 7;
-        double acc = 0.0;
-        for (int d0 = 0; d0 < k; d0 += 8) {      // eight loads in flight, then their sum in increasing d
-            double x[8];
+    // affine table: dtab[k][r] = sum_{d<k} g[d][r]: sums of eight lags first, then at most
+    // N / 8 of them and seven lags (one chain of up to N - 1 additions: 4,200 cycles)
+    const int nch = (nst + 7) >> 3;
+    for (int t = tid; t < nch * 8; t += 256) {
+        const int d0 = 8 * (t >> 3), r = t & 7;
+        double x[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = d0 + u < k ? g[(d0 + u) * 8 + r] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += x[u];
-        }
-        dtab[t] = acc;
+        for (int u = 0; u < 8; ++u) x[u] = d0 + u < nst ? g[(d0 + u) * 8 + r] : 0.0;
+        dsum[t] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
     }
     stage_store(0);
+    __syncthreads();
+    for (int t = tid; t < N * 8; t += 256) {
+        const int k = t >> 3, r = t & 7, kc = k & ~7;
+        double acc = 0.0, x[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) x[u] = kc + u < k ? g[(kc + u) * 8 + r] : 0.0;
+        for (int c = 0; c < kc >> 3; ++c) acc += dsum[c * 8 + r];
+        dtab[t] = acc + (((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + x[6]));
+    }
     if (LONG)
         for (int j0 = 64; j0 < nst; j0 += 64) {
             stage_load(j0);
@@ -525,29 +532,37 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
             const int rr4 = 16 * rt + 4 * lq + i;
             dt[i] = (rr4 >> 3) < N ? dtab[(rr4 >> 3) * 8 + (rr4 & 7)] : 0.0;
         }
-        float c0v = sc[lane], w0v = sw[lane], c1v = sc[64 + lane], w1v = sw[64 + lane];
-        float a0 = sp[abase], a1 = sp[abase - 32];
+        // fragments of two iterations in flight (an iteration's products last about as long
+        // as one read of LDS)
+        float cf[2][2], wf[2][2], af[2][2];
+        auto frag = [&](int u, int k4) {
+            const int kc = k4 < kmax ? k4 : kmax - 8 < 0 ? 0 : (kmax - 1) & ~7;      // past the end: re-read
+            cf[u][0] = sc[kc * 16 + lane]; wf[u][0] = sw[kc * 16 + lane];
+            cf[u][1] = sc[kc * 16 + 64 + lane]; wf[u][1] = sw[kc * 16 + 64 + lane];
+            af[u][0] = sp[abase - 8 * kc]; af[u][1] = sp[abase - 8 * kc - 32];
+        };
+        frag(0, 0);
+        frag(1, 8);
         // FP32 accumulators over chunks of 8 iterations (32 products each), the
         // chunks summed in FP64
         double md[4] = {0.0, 0.0, 0.0, 0.0}, vd[4] = {0.0, 0.0, 0.0, 0.0};
         for (int cs = 0; cs < kmax; cs += 64) {
             const int ce = cs + 64 < kmax ? cs + 64 : kmax;
             f4 m0 = f4{0.0f, 0.0f, 0.0f, 0.0f}, v0 = m0, m1 = m0, v1 = m0;
-            for (int k4 = cs; k4 < ce; k4 += 8) {
-                const int kn = k4 + 8 < kmax ? k4 + 8 : k4;    // the last prefetch re-reads this step
-                const float c0n = sc[kn * 16 + lane], w0n = sw[kn * 16 + lane];
-                const float c1n = sc[kn * 16 + 64 + lane], w1n = sw[kn * 16 + 64 + lane];
-                const float a0n = sp[abase - 8 * kn], a1n = sp[abase - 8 * kn - 32];
-                // the reads stay ahead of the MFMAs and their results are consumed
-                // only after all four are issued
-                __builtin_amdgcn_sched_barrier(0);
+            auto iter = [&](int u, int k4) {
+                const float a0 = af[u][0], a1 = af[u][1], c0v = cf[u][0], c1v = cf[u][1], w0v = wf[u][0], w1v = wf[u][1];
                 m0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, c0v, m0, 0, 0, 0);
                 v0 = __builtin_amdgcn_mfma_f32_16x16x4f32(fabsf(a0), w0v, v0, 0, 0, 0);
                 m1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, c1v, m1, 0, 0, 0);
                 v1 = __builtin_amdgcn_mfma_f32_16x16x4f32(fabsf(a1), w1v, v1, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                c0v = c0n; w0v = w0n; c1v = c1n; w1v = w1n; a0 = a0n; a1 = a1n;
+                frag(u, k4 + 16);
+            };
+            int k4 = cs;
+            for (; k4 + 8 < ce; k4 += 16) {
+                iter(0, k4);
+                iter(1, k4 + 8);
             }
+            if (k4 < ce) iter(0, k4);                // the last one (64 is an even number of iterations)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 md[i] += (double)m0[i] + (double)m1[i];
@@ -768,7 +783,7 @@ static int launch_tube2(int B, int N, int U, const double* phi, const double* e,
     const int gy = (nrt + 4 * rt - 1) / (4 * rt);
     if (gx > 0x7fffffff || cols > 0x7fffffff) return LEB_EINVAL;
     const size_t nst = N > 1 ? N - 1 : 0;
-    const size_t smem = ((size_t)N * 8 + nst * 8 + 4) * sizeof(double) +
+    const size_t smem = ((size_t)N * 8 + nst * 8 + (nst + 7) / 8 * 8 + 4) * sizeof(double) +
                         ((size_t)(N + 4) * 16 + 2 * (2 * nst + 8) * 16) * sizeof(float);
     const bool isfp = fp.state != nullptr, lng = N > 65;
     const int which = (isfp ? 6 : 0) + (lng ? 3 : 0) + rti;
