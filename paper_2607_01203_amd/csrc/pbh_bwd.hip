@@ -117,47 +117,28 @@ __device__ __forceinline__ void bwd_task(const SpringSetup& st, double K3, doubl
                     1.0, K3, K15, K1, K05, acc, acc);
 }
 
-// SPLIT = false: 256 lanes, each runs its spring's five passes one after the other.
-// SPLIT = true (launches that leave the chip idle): five waves over the same up
-// to 64 lanes, each wave runs phases 1 and 2 for itself and then one pass.
-//
-// What bounds it: VALU issue (about 11,000 instructions a lane, most of them in phase
-// 3) at two waves a SIMD when the chip is full, the serial chain of one lane
-// otherwise.  28 nodes, 256 x 40 steps: 103 us (337 us with ten one-direction passes
-// over every term, whose hoisted values took 430 registers, one wave a SIMD, and
-// with adjoints addressed through scratch); 1 x 40: 15 us (55 us).
+// The adjoint of the timesteps of one workgroup: lane ln of `copy` holds node i of
+// timestep lt (its inputs d, the adjoints of its own and the next node's rows).  Contains
+// four workgroup barriers; returns whether this lane holds a node's result.
+template <bool SPLIT> struct BwdShared {
+    static constexpr int LANES = SPLIT ? 64 : BWD_BLOCK, COPIES = SPLIT ? BWD_TASKS : 1;
+    BwdPass pass[COPIES][LANES];
+    uint32_t unb[COPIES][LANES];                               // row unbounded
+    uint32_t flag[COPIES][LANES];                              // per timestep
+    double grad[SPLIT ? LANES : 1][2 * BWD_TASKS];
+};
+struct BwdConsts { int U; double c, kL, L0; };
+struct BwdOut { double nom[8], mu[8], sigma[8]; };             // per coordinate of the node
+
 template <bool SPLIT>
-__global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 : 2) pbh_chain_bwd(BwdArgs A) {
-    constexpr int LANES = SPLIT ? 64 : BWD_BLOCK, COPIES = SPLIT ? BWD_TASKS : 1;
-    __shared__ BwdPass s_pass[COPIES][LANES];
-    __shared__ uint32_t s_unb[COPIES][LANES];                  // row unbounded
-    __shared__ uint32_t s_flag[COPIES][LANES];                 // per timestep
-    __shared__ double s_grad[SPLIT ? LANES : 1][2 * BWD_TASKS];
-    const int U = A.U, T = A.T, nx = 6 * U, nu = 2 * U, n = nx + nu;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int copy = SPLIT ? wave : 0, ln = SPLIT ? (threadIdx.x & 63) : threadIdx.x;
-    const int64_t u0 = (int64_t)blockIdx.x * T;
-    const int64_t left = A.units - u0;
-    const int nloc = left < T ? (int)left : T;
-    const int lt = ln / U, i = ln - lt * U;
-    const bool active = lt < nloc, right = active && i < U - 1;
-    s_flag[copy][ln] = 0u;
-    TileRef tr = {};
-    tr.Z = A.z + u0 * nx; tr.V = A.v + u0 * nu; tr.MU = A.mu ? A.mu + u0 * n : nullptr; tr.SG = A.sigma + u0 * n;
-    tr.nloc = nloc;
-    NodeIn d;
-    node_load(tr, U, lt, i, d);
-    RowAdj gi = {0.0, 0.0, 0.0, 0.0}, gj = {0.0, 0.0, 0.0, 0.0};
-    if (active) {
-        const double* gl = A.g_lo + (u0 + lt) * nx + 6 * i;
-        const double* gh = A.g_hi + (u0 + lt) * nx + 6 * i;
-        gi = RowAdj{gl[3], gh[3], gl[4], gh[4]};
-        if (right) gj = RowAdj{gl[9], gh[9], gl[10], gh[10]};
-    }
+__device__ __forceinline__ bool bwd_core(const BwdConsts& K, BwdShared<SPLIT>& H, const NodeIn& d, RowAdj gi, RowAdj gj,
+                                         int wave, int copy, int ln, int lt, int i, bool active, bool right,
+                                         BwdOut& out) {
+    const int U = K.U;
     const IV<float> Dx = disp_interval(d.ms[0], d.ss[0]), Dz = disp_interval(d.ms[1], d.ss[1]);
     __syncthreads();
-    if (active && (node_flags(d) & LEB_FLAG_BAD_INPUT)) atomicOr(&s_flag[copy][lt], LEB_FLAG_BAD_INPUT);
-    const double K3 = 3.0 * A.kL * A.c, K15 = 1.5 * A.kL * A.c, K1 = A.kL * A.c, K05 = 0.5 * A.kL * A.c;
+    if (active && (node_flags(d) & LEB_FLAG_BAD_INPUT)) atomicOr(&H.flag[copy][lt], LEB_FLAG_BAD_INPUT);
+    const double K3 = 3.0 * K.kL * K.c, K15 = 1.5 * K.kL * K.c, K1 = K.kL * K.c, K05 = 0.5 * K.kL * K.c;
 
     // ---- 1. spring i primal
     IV<float> R[5];
@@ -167,12 +148,12 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
     SpringSetup st;
     if (right) {
         spring_setup_v(d.zs[0], d.zs[1], d.zj[0], d.zj[1], Dx, Dz, disp_interval(d.mj[0], d.sj[0]),
-                       disp_interval(d.mj[1], d.sj[1]), A.L0, st);
+                       disp_interval(d.mj[1], d.sj[1]), K.L0, st);
         AccPrimal acc;
         SpringPieces pc;
         spring_ok = spring_core(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj, st.Dzj, 1.0, 1.0, 1.0,
                                 1.0, K3, K15, K1, K05, acc, pc);
-        BwdPass& o = s_pass[copy][ln];
+        BwdPass& o = H.pass[copy][ln];
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
             o.piece.L[q] = spring_ok ? pc.L[q] : iv(0.0f, 0.0f);
@@ -183,7 +164,7 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
     __syncthreads();
 
     // ---- 2. node i primal + reverse
-    const bool bad = active && (s_flag[copy][lt] & LEB_FLAG_BAD_INPUT);
+    const bool bad = active && (H.flag[copy][lt] & LEB_FLAG_BAD_INPUT);
     uint32_t row_unb = (right && !spring_ok) ? 1u : 0u;
     PieceAdj rbar;
 #pragma unroll
@@ -194,12 +175,12 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
 #pragma unroll
         for (int q = 0; q < 5; ++q) L[q] = iv(0.0f, 0.0f);
         if (i > 0) {
-            const BwdPass& o = s_pass[copy][ln - 1];
+            const BwdPass& o = H.pass[copy][ln - 1];
             row_unb |= o.piece.unbounded;
 #pragma unroll
             for (int q = 0; q < 5; ++q) L[q] = o.piece.L[q];
         }
-        s_unb[copy][ln] = row_unb;
+        H.unb[copy][ln] = row_unb;
         RowAdj g = gi;
         if (row_unb || bad) { g.xlo = g.xhi = g.zlo = g.zhi = 0.0; }
         const bool own = U > 1 && !row_unb;
@@ -207,7 +188,7 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
         const IV<float> Dth = disp_interval(d.ms[2], d.ss[2]), Du1 = disp_interval(d.ms[6], d.ss[6]),
                         Du2 = disp_interval(d.ms[7], d.ss[7]);
         const double thn = d.zs[2], sn = d.vs[0] + d.vs[1];
-        node_terms(thn, sn, Dth, Du1, Du2, Dx, Dz, R, L, own, A.c, K15, K1, K05, 1.0, 1.0, 1.0, 1.0, 1.0, nt);
+        node_terms(thn, sn, Dth, Du1, Du2, Dx, Dz, R, L, own, K.c, K15, K1, K05, 1.0, 1.0, 1.0, 1.0, 1.0, nt);
         // term adjoints
         double tlo[12], thi[12];
         double sbar = 0.0;
@@ -222,7 +203,7 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
                 // d kappa / d s~ = +-c/2 ; kappa enters through the selected endpoints
                 const float a = nt.neg[q] ? nt.T[q].hi : nt.T[q].lo;
                 const float b = nt.neg[q] ? nt.T[q].lo : nt.T[q].hi;
-                const double dk = (q == 0 ? 0.5 : -0.5) * A.c;
+                const double dk = (q == 0 ? 0.5 : -0.5) * K.c;
                 sbar += dk * (alo * (double)a + ahi * (double)b);
             }
         }
@@ -292,7 +273,7 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
                 lbar.hi[q] = -Gb_lo[q]; lbar.lo[q] = -Gb_hi[q];
             }
         }
-        if (i > 0) s_pass[copy][ln - 1].adj = lbar;
+        if (i > 0) H.pass[copy][ln - 1].adj = lbar;
     }
     __syncthreads();
 
@@ -301,9 +282,9 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
 #pragma unroll
     for (int q = 0; q < 2 * BWD_TASKS; ++q) sg[q] = 0.0;
     if (right && spring_ok) {
-        const PieceAdj lb = s_pass[copy][ln].adj;
+        const PieceAdj lb = H.pass[copy][ln].adj;
         if (bad || row_unb) gi = RowAdj{0.0, 0.0, 0.0, 0.0};
-        if (bad || s_unb[copy][ln + 1]) gj = RowAdj{0.0, 0.0, 0.0, 0.0};
+        if (bad || H.unb[copy][ln + 1]) gj = RowAdj{0.0, 0.0, 0.0, 0.0};
         AccTangent acc;
         // slot adjoints: row i takes C + B, row i+1 takes -(C + A)
         acc.alo[S_CX] = gi.xlo - gj.xhi; acc.ahi[S_CX] = gi.xhi - gj.xlo;
@@ -317,60 +298,231 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
             constexpr int Q = decltype(task)::value;
             if (SPLIT && wave != Q) return;
             bwd_task<Q>(st, K3, K15, K1, K05, acc);
-            if (SPLIT) { s_grad[ln][2 * Q] = acc.g; s_grad[ln][2 * Q + 1] = acc.h; }
+            if (SPLIT) { H.grad[ln][2 * Q] = acc.g; H.grad[ln][2 * Q + 1] = acc.h; }
             else { sg[2 * Q] = acc.g; sg[2 * Q + 1] = acc.h; }
         };
         run(std::integral_constant<int, 0>()); run(std::integral_constant<int, 1>());
         run(std::integral_constant<int, 2>()); run(std::integral_constant<int, 3>());
         run(std::integral_constant<int, 4>());
     } else if (SPLIT && active) {
-        s_grad[ln][2 * wave] = 0.0;
-        s_grad[ln][2 * wave + 1] = 0.0;
+        H.grad[ln][2 * wave] = 0.0;
+        H.grad[ln][2 * wave + 1] = 0.0;
     }
     if (SPLIT) {
         __syncthreads();
-        if (wave > 0) return;            // the first wave adds up
+        if (wave > 0) return false;      // the first wave adds up
         if (active) {
 #pragma unroll
-            for (int q = 0; q < 2 * BWD_TASKS; ++q) sg[q] = s_grad[ln][q];
+            for (int q = 0; q < 2 * BWD_TASKS; ++q) sg[q] = H.grad[ln][q];
         }
     } else {
         if (right) {
-            double* o = s_pass[0][ln].next;
+            double* o = H.pass[0][ln].next;
             o[0] = sg[0]; o[1] = sg[1];
 #pragma unroll
             for (int q = 0; q < 4; ++q) o[2 + q] = sg[6 + q];
         }
         __syncthreads();
     }
-    if (!active) return;
+    if (!active) return false;
 
     // ---- 4. per-coordinate sums (fixed order) and the box chain rule
     double lf[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};             // spring i-1: node i is its second node
     if (i > 0) {
 #pragma unroll
         for (int q = 0; q < 6; ++q)
-            lf[q] = SPLIT ? s_grad[ln - 1][q < 2 ? q : q + 4] : s_pass[0][ln - 1].next[q];
+            lf[q] = SPLIT ? H.grad[ln - 1][q < 2 ? q : q + 4] : H.pass[0][ln - 1].next[q];
     }
-    const double gnom[8] = {lf[0] - sg[0], lf[1] - sg[1], ng.th, 0.0, 0.0, 0.0, ng.s, ng.s};
-    const double glo[8] = {ng.dx[0] + sg[2] + lf[2], ng.dz[0] + sg[4] + lf[4], ng.dth[0], 0.0, 0.0, 0.0, ng.du1[0],
+    const double gn[8] = {lf[0] - sg[0], lf[1] - sg[1], ng.th, 0.0, 0.0, 0.0, ng.s, ng.s};
+    const double gl[8] = {ng.dx[0] + sg[2] + lf[2], ng.dz[0] + sg[4] + lf[4], ng.dth[0], 0.0, 0.0, 0.0, ng.du1[0],
                            ng.du2[0]};
-    const double ghi[8] = {ng.dx[1] + sg[3] + lf[3], ng.dz[1] + sg[5] + lf[5], ng.dth[1], 0.0, 0.0, 0.0, ng.du1[1],
+    const double gh[8] = {ng.dx[1] + sg[3] + lf[3], ng.dz[1] + sg[5] + lf[5], ng.dth[1], 0.0, 0.0, 0.0, ng.du1[1],
                            ng.du2[1]};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const double sgm = d.ss[c], mu = d.ms[c];
+        // Delta_lo = min(mu - sigma, 0), Delta_hi = max(mu + sigma, 0); first candidate on a tie
+        const double alo = !bad && (mu - sgm <= 0.0) ? gl[c] : 0.0;
+        const double ahi = !bad && (mu + sgm >= 0.0) ? gh[c] : 0.0;
+        out.sigma[c] = ahi - alo;
+        out.mu[c] = alo + ahi;
+        out.nom[c] = bad ? 0.0 : gn[c];
+    }
+    return true;
+}
+
+// SPLIT = false: 256 lanes, each runs its spring's five passes one after the other.
+// SPLIT = true (launches that leave the chip idle): five waves over the same up
+// to 64 lanes, each wave runs phases 1 and 2 for itself and then one pass.
+//
+// What bounds it: VALU issue (about 11,000 instructions a lane, most of them in phase
+// 3) at two waves a SIMD when the chip is full, the serial chain of one lane
+// otherwise.  28 nodes, 256 x 40 steps: 103 us (337 us with ten one-direction passes
+// over every term, whose hoisted values took 430 registers, one wave a SIMD, and
+// with adjoints addressed through scratch); 1 x 40: 15 us (55 us).
+template <bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 : 2) pbh_chain_bwd(BwdArgs A) {
+    __shared__ BwdShared<SPLIT> S;
+    const int U = A.U, T = A.T, nx = 6 * U, nu = 2 * U, n = nx + nu;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int copy = SPLIT ? wave : 0, ln = SPLIT ? (threadIdx.x & 63) : threadIdx.x;
+    const int64_t u0 = (int64_t)blockIdx.x * T;
+    const int64_t left = A.units - u0;
+    const int nloc = left < T ? (int)left : T;
+    const int lt = ln / U, i = ln - lt * U;
+    const bool active = lt < nloc, right = active && i < U - 1;
+    S.flag[copy][ln] = 0u;
+    TileRef tr = {};
+    tr.Z = A.z + u0 * nx; tr.V = A.v + u0 * nu; tr.MU = A.mu ? A.mu + u0 * n : nullptr; tr.SG = A.sigma + u0 * n;
+    tr.nloc = nloc;
+    NodeIn d;
+    node_load(tr, U, lt, i, d);
+    RowAdj gi = {0.0, 0.0, 0.0, 0.0}, gj = {0.0, 0.0, 0.0, 0.0};
+    if (active) {
+        const double* gl = A.g_lo + (u0 + lt) * nx + 6 * i;
+        const double* gh = A.g_hi + (u0 + lt) * nx + 6 * i;
+        gi = RowAdj{gl[3], gh[3], gl[4], gh[4]};
+        if (right) gj = RowAdj{gl[9], gh[9], gl[10], gh[10]};
+    }
+    BwdOut o;
+    const BwdConsts K{U, A.c, A.kL, A.L0};
+    if (!bwd_core<SPLIT>(K, S, d, gi, gj, wave, copy, ln, lt, i, active, right, o)) return;
     const int64_t u = u0 + lt;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const int64_t o = u * n + (c < 6 ? 6 * i + c : nx + 2 * i + c - 6);
-        const double sgm = d.ss[c], mu = d.ms[c];
-        // Delta_lo = min(mu - sigma, 0), Delta_hi = max(mu + sigma, 0); first candidate on a tie
-        const double alo = !bad && (mu - sgm <= 0.0) ? glo[c] : 0.0;
-        const double ahi = !bad && (mu + sgm >= 0.0) ? ghi[c] : 0.0;
-        A.gsigma[o] = ahi - alo;
-        if (A.gmu) A.gmu[o] = alo + ahi;
-        const double gn = bad ? 0.0 : gnom[c];
-        if (c < 6) A.gz[u * nx + 6 * i + c] = gn;
-        else A.gv[u * nu + 2 * i + c - 6] = gn;
+        const int64_t q = u * n + (c < 6 ? 6 * i + c : nx + 2 * i + c - 6);
+        A.gsigma[q] = o.sigma[c];
+        if (A.gmu) A.gmu[q] = o.mu[c];
+        if (c < 6) A.gz[u * nx + 6 * i + c] = o.nom[c];
+        else A.gv[u * nu + 2 * i + c - 6] = o.nom[c];
     }
+}
+
+// The whole descent on the nominal point (pgd.hip) of up to 64 / U timesteps in one
+// workgroup: timesteps are independent of each other, so nothing leaves it between the
+// steps.  Waves 0 .. 4: the adjoint (upstream -1 on the lower, +1 on the upper ends), the
+// first also the move; wave 5: the bound at the same iterate, for its width.
+//
+// What bounds it: the serial chain of the adjoint, 19 us an iteration.  28 nodes, 40
+// timesteps, 10 steps: 209 us (a launch each for the bound, the adjoint and the move:
+// 300 us).
+constexpr int PGD_WAVES = BWD_TASKS + 1;
+
+struct PgdChainArgs {
+    const double* z0; const double* v0; const double* mu0; const double* sigma;
+    double* zo; double* vo; double* width; double* width0;
+    int64_t units;
+    int U, T, steps, fixed_box;
+    double radius, lr;
+    double c, kL, L0, pad;
+    int compact;
+};
+
+__global__ void __launch_bounds__(64 * PGD_WAVES, 1) pgd_chain_kernel(PgdChainArgs A) {
+    __shared__ BwdShared<true> S;
+    // the iterate and its mu, sigma, the start, mu0, the best iterate; the bound's rows
+    __shared__ __attribute__((aligned(16))) double sz[64 * 6], sv[64 * 2], smu[64 * 8], ssg[64 * 8], sz0[64 * 6],
+        sv0[64 * 2], smu0[64 * 8], szb[64 * 6], svb[64 * 2], rlo[64 * 6], rhi[64 * 6], sg[64 * 8];
+    __shared__ uint32_t s_better[64];
+    __shared__ SpringOut s_sp[64];
+    __shared__ uint32_t s_fl[64];
+    const int U = A.U, T = A.T, nx = 6 * U, nu = 2 * U, n = nx + nu, tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ln = tid & 63;
+    const int64_t u0 = (int64_t)blockIdx.x * T, rest = A.units - u0;
+    const int nloc = rest < T ? (int)rest : T;
+    for (int q = tid; q < nloc * nx; q += 64 * PGD_WAVES) sz[q] = sz0[q] = szb[q] = A.z0[u0 * nx + q];
+    for (int q = tid; q < nloc * nu; q += 64 * PGD_WAVES) sv[q] = sv0[q] = svb[q] = A.v0[u0 * nu + q];
+    for (int q = tid; q < nloc * n; q += 64 * PGD_WAVES) {
+        smu[q] = smu0[q] = A.mu0 ? A.mu0[u0 * n + q] : 0.0;
+        ssg[q] = A.sigma[u0 * n + q];
+    }
+    double best = INFINITY;
+    const TileRef t0{sz, sv, smu, ssg, rlo, rhi, nullptr, nullptr, nullptr, nloc};
+    for (int st = 0; st <= A.steps; ++st) {
+        // (the lane's place is formed anew each time, or the addresses of everything it
+        // reads would be kept in registers over the loop)
+        int lp = ln, Up = U;
+        asm volatile("" : "+v"(lp), "+s"(Up));
+        const int lt = lp / Up, i = lp - lt * Up;
+        const bool active = lt < nloc, right = active && i < U - 1;
+        const RowAdj gi = active ? RowAdj{-1.0, 1.0, -1.0, 1.0} : RowAdj{0.0, 0.0, 0.0, 0.0};
+        const RowAdj gj = right ? RowAdj{-1.0, 1.0, -1.0, 1.0} : RowAdj{0.0, 0.0, 0.0, 0.0};
+        double c_ = A.c, kL_ = A.kL, L0_ = A.L0;
+        asm volatile("" : "+s"(c_), "+s"(kL_), "+s"(L0_));
+        const BwdConsts K{U, c_, kL_, L0_};
+        if (wave < BWD_TASKS) S.flag[wave][ln] = 0u;
+        else s_fl[ln] = 0u;
+        __syncthreads();                             // the iterate is written
+        if (wave == BWD_TASKS) {
+            NodeIn d;
+            node_load(t0, U, lt, i, d);
+            wave_lds_fence();                        // s_fl cleared
+            node_pass<true>(A, t0, d, lt, i, s_sp, s_fl);
+            if (st < A.steps) {                      // the barriers of bwd_core
+                __syncthreads();
+                __syncthreads();
+                __syncthreads();
+            }
+            __syncthreads();
+        } else if (st < A.steps) {
+            NodeIn d;
+            node_load(t0, U, lt, i, d);
+            BwdOut o;
+            if (bwd_core<true>(K, S, d, gi, gj, wave, wave, ln, lt, i, active, right, o)) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    sg[lt * n + (c < 6 ? 6 * i + c : nx + 2 * i + c - 6)] = A.fixed_box ? o.nom[c] - o.mu[c] : o.nom[c];
+                }
+            }
+        } else {
+            __syncthreads();
+        }
+        if (wave == 0) {
+            // the vx and vz rows' widths, summed in row order by the timestep's first lane
+            double w = 0.0;
+            if (active && i == 0) {
+                const double* lo = rlo + lt * nx;
+                const double* hi = rhi + lt * nx;
+                for (int q = 0; q < U; q += 4) {
+                    double x[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int nd = q + (e >> 1) < U ? q + (e >> 1) : 0;
+                        x[e] = hi[6 * nd + 3 + (e & 1)] - lo[6 * nd + 3 + (e & 1)];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (q + (e >> 1) < U) w += x[e];
+                }
+            }
+            if (active && i == 0) {
+                const bool better = w < best;
+                if (st == 0 && A.width0) A.width0[u0 + lt] = w;
+                if (better) best = w;
+                s_better[lt] = better ? 1u : 0u;
+            }
+            wave_lds_fence();
+            const double frac = st < A.steps ? A.lr * (1.0 - (double)st / A.steps) : 0.0;
+            for (int q = ln; q < nloc * n; q += 64) {
+                const int l = q / n, c = q - l * n;
+                double* ap = c < nx ? sz + l * nx + c : sv + l * nu + c - nx;
+                const double a0 = *(c < nx ? sz0 + l * nx + c : sv0 + l * nu + c - nx);
+                double x = *ap;
+                if (s_better[l]) *(c < nx ? szb + l * nx + c : svb + l * nu + c - nx) = x;
+                if (st == A.steps) continue;
+                const double g = sg[q], r = A.radius * ssg[q];
+                if (g > 0.0) x -= frac * r;
+                else if (g < 0.0) x += frac * r;
+                x = fmin(fmax(x, a0 - r), a0 + r);
+                *ap = x;
+                if (A.fixed_box) smu[q] = a0 + (A.mu0 ? smu0[q] : 0.0) - x;
+            }
+        }
+    }
+    __syncthreads();
+    for (int q = tid; q < nloc * nx; q += 64 * PGD_WAVES) A.zo[u0 * nx + q] = szb[q];
+    for (int q = tid; q < nloc * nu; q += 64 * PGD_WAVES) A.vo[u0 * nu + q] = svb[q];
+    if (wave == 0 && ln < nloc * U && ln % U == 0) A.width[u0 + ln / U] = best;
 }
 
 int launch_pbh_bwd(const leb_dynamics* dyn, int64_t units, const double* z, const double* v, const double* mu,
@@ -395,6 +547,29 @@ int launch_pbh_bwd(const leb_dynamics* dyn, int64_t units, const double* z, cons
     if (blocks > 0x7fffffff) return LEB_EINVAL;
     if (split) hipLaunchKernelGGL(pbh_chain_bwd<true>, dim3((unsigned)blocks), dim3(64 * BWD_TASKS), 0, stream, a);
     else hipLaunchKernelGGL(pbh_chain_bwd<false>, dim3((unsigned)blocks), dim3(BWD_BLOCK), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
+}
+
+// The fused descent while every workgroup has a compute unit of its own (28 nodes, 10 steps,
+// whole call: 40 timesteps 211 us and 309 by launches, 480 timesteps 218 and 320; from
+// then on the workgroups would take turns); *done = false: not that case, nothing launched.
+int launch_pgd_chain(const leb_dynamics* dyn, int64_t units, const double* z0, const double* v0, const double* mu0,
+                     const double* sigma, int fixed_box, double radius, int steps, double lr, double* z, double* v,
+                     double* width, double* width0, hipStream_t stream, bool* done) {
+    const int U = dyn->n_units, T = U <= 64 ? 64 / U : 0;
+    *done = T > 0 && (units + T - 1) / T <= BWD_SPLIT_BLOCKS;
+    if (!*done) return LEB_OK;
+    PgdChainArgs a;
+    a.z0 = z0; a.v0 = v0; a.mu0 = mu0; a.sigma = sigma;
+    a.zo = z; a.vo = v; a.width = width; a.width0 = width0;
+    a.units = units;
+    a.U = U; a.T = T; a.steps = steps; a.fixed_box = fixed_box;
+    a.radius = radius; a.lr = lr;
+    a.c = dyn->dt / dyn->m;
+    a.kL = dyn->k_spring * dyn->rest_len;
+    a.L0 = dyn->rest_len;
+    a.pad = 0.0; a.compact = 0;
+    hipLaunchKernelGGL(pgd_chain_kernel, dim3((unsigned)((units + T - 1) / T)), dim3(64 * PGD_WAVES), 0, stream, a);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 

@@ -28,6 +28,10 @@ int launch_pbh_bwd(const leb_dynamics* dyn, int64_t units, const double* z, cons
                    const double* sigma, const double* g_lo, const double* g_hi, double* gz, double* gv,
                    double* gmu, double* gsigma, hipStream_t stream);
 
+int launch_pgd_chain(const leb_dynamics* dyn, int64_t units, const double* z0, const double* v0, const double* mu0,
+                     const double* sigma, int fixed_box, double radius, int steps, double lr, double* z, double* v,
+                     double* width, double* width0, hipStream_t stream, bool* done);
+
 constexpr int PGD_MAX_ROWS = 512;        // 2 rows a node, up to 256 nodes
 
 struct PgdBufs {
@@ -136,6 +140,11 @@ extern "C" int leb_pgd_nominal(const leb_dynamics* dyn, int32_t batch, int32_t N
     const int nx = dyn->nx, nu = dyn->nu, n = nx + nu;
     if (units * n > ((int64_t)1 << 40)) return LEB_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    // few timesteps: the whole descent in one launch, without a workspace
+    bool done = false;
+    if ((rc = launch_pgd_chain(dyn, units, z0, v0, mu0, sigma, fixed_box, radius, steps, lr, z, v, width, width0, s,
+                               &done)) || done)
+        return rc;
     std::lock_guard<std::mutex> lock(g_pgd.mu);
     // z, v, mu, lo, hi, glo, ghi, gz, gv, gmu, gsigma, best
     const size_t need = (size_t)units * (nx + nu + n + nx + nx + nx + nx + nx + nu + n + n + 1);

@@ -168,3 +168,28 @@ def test_pgd_beats_sampling_at_equal_time(gpu, name):
     print("pgd %.3f ms, %d samples; mean width start %.6g sampling %.6g pgd %.6g"
           % (t_pgd * 1e3, K, w0.mean().item(), best.mean().item(), w.mean().item()))
     assert bool((w <= best).all())
+
+
+@pytest.mark.parametrize("U,few,many", [(28, 5, 600), (1, 130, 16500), (50, 3, 270), (64, 2, 300), (33, 256, 257)])
+@pytest.mark.parametrize("fixed_box,steps", [(False, 3), (True, 2), (True, 0)])
+def test_pgd_fused_and_by_launches_agree(gpu, U, few, many, fixed_box, steps):
+    """The descent in one launch (few timesteps) and by a launch for each part
+    (many): the same point and widths, bit for bit, also for a timestep with
+    invalid data, a springless unit and workgroups that are not full."""
+    import torch
+    import paper_2607_01203_amd as leb
+    b = W.chain_batch(90 + U, 1, many, U)
+    z, v, sg = b.z.copy(), b.v.copy(), b.sigma.copy()
+    z[0, 1, 2] = np.nan
+    mu = 0.4 * sg * np.random.default_rng(U).uniform(-1.0, 1.0, sg.shape)
+    dyn = leb.dynamics_like(b.dyn)
+    print("case: pgd fused U=%d few=%d many=%d fixed=%s steps=%d" % (U, few, many, fixed_box, steps), flush=True)
+
+    def run(k):
+        out = leb.pgd_nominal(dyn, _t(z[:, :k], gpu), _t(v[:, :k], gpu), _t(sg[:, :k], gpu), _t(mu[:, :k], gpu),
+                              radius=0.8, steps=steps, lr=0.4, fixed_box=fixed_box)
+        torch.cuda.synchronize()
+        return [x.cpu().numpy() for x in out]
+
+    for x, y in zip(run(few), run(many)):
+        assert np.array_equal(x, y[:, :few], equal_nan=True)
