@@ -110,9 +110,12 @@ struct SpringKeep {
     uint32_t unb;         // spring i has no finite bound
 };
 
-// Spring i (nodes i, i+1) when right; writes *out (right only) and returns
-// whether the spring is unbounded through k.unb.
-__device__ __forceinline__ void spring_step(const NodeConsts& K, const NodeIn& d, bool right, SpringKeep& k,
+// Spring i (nodes i, i+1); writes *out and returns whether the spring is unbounded through
+// k.unb.  Every lane evaluates it (the last node of a chain against itself) and a lane
+// without a spring drops the result: branches around it cost more in register moves
+// than they save (28 nodes, 2,560 x 40: 133 us, with the branches 136).  springs: the
+// chain has any.
+__device__ __forceinline__ void spring_step(const NodeConsts& K, const NodeIn& d, bool springs, bool right, SpringKeep& k,
                                             SpringOut* out) {
     k.Dx = disp_interval(d.ms[0], d.ss[0]); k.Dz = disp_interval(d.ms[1], d.ss[1]);
     k.Dth = disp_interval(d.ms[2], d.ss[2]);
@@ -121,30 +124,34 @@ __device__ __forceinline__ void spring_step(const NodeConsts& K, const NodeIn& d
 #pragma unroll
     for (int q = 0; q < 5; ++q) k.R[q] = iv(0.0f, 0.0f);
     k.unb = 0;
-    if (!right) return;
+    if (!springs) return;
     SpringSetup st;
     spring_setup_v(d.zs[0], d.zs[1], d.zj[0], d.zj[1], k.Dx, k.Dz, disp_interval(d.mj[0], d.sj[0]),
                    disp_interval(d.mj[1], d.sj[1]), K.L0, st);
     AccPrimal acc;
     SpringPieces pc;
-    const bool ok = spring_core(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj,
+    const bool ok = spring_core<false>(st.dxA, st.dxB, st.dz0, st.dz1, st.dz2, st.Dxi, st.Dzi, st.Dxj,
                                                   st.Dzj, maskv(st.Dxi), maskv(st.Dzi), maskv(st.Dxj),
                                                   maskv(st.Dzj), K.K3, K.K15, K.K1, K.K05, acc, pc);
-    SpringOut o = {};
-    if (ok) {
-        k.rx.lo = acc.a[S_CX].lo + acc.a[S_BX].lo; k.rx.hi = acc.a[S_CX].hi + acc.a[S_BX].hi;
-        k.rz.lo = acc.a[S_CZ].lo + acc.a[S_BZ].lo; k.rz.hi = acc.a[S_CZ].hi + acc.a[S_BZ].hi;
-        // row i+1 receives -(cross + node i's own pairs)
-        o.xlo = -(acc.a[S_CX].hi + acc.a[S_AX].hi); o.xhi = -(acc.a[S_CX].lo + acc.a[S_AX].lo);
-        o.zlo = -(acc.a[S_CZ].hi + acc.a[S_AZ].hi); o.zhi = -(acc.a[S_CZ].lo + acc.a[S_AZ].lo);
+    k.unb = right && !ok ? 1u : 0u;
+    // (an unbounded spring's values are never used: its rows are infinite)
+    const double rxl = acc.a[S_CX].lo + acc.a[S_BX].lo, rxh = acc.a[S_CX].hi + acc.a[S_BX].hi;
+    const double rzl = acc.a[S_CZ].lo + acc.a[S_BZ].lo, rzh = acc.a[S_CZ].hi + acc.a[S_BZ].hi;
+    k.rx.lo = right ? rxl : 0.0; k.rx.hi = right ? rxh : 0.0;
+    k.rz.lo = right ? rzl : 0.0; k.rz.hi = right ? rzh : 0.0;
 #pragma unroll
-        for (int q = 0; q < 5; ++q) { o.L[q] = pc.L[q]; k.R[q] = pc.R[q]; }
-        o.unbounded = 0;
-    } else {
-        k.unb = 1;
-        o.unbounded = 1;
+    for (int q = 0; q < 5; ++q) {
+        k.R[q].lo = right ? pc.R[q].lo : 0.0f;
+        k.R[q].hi = right ? pc.R[q].hi : 0.0f;
     }
-    *out = o;
+    if (right) {
+        // row i+1 receives -(cross + node i's own pairs)
+        out->xlo = -(acc.a[S_CX].hi + acc.a[S_AX].hi); out->xhi = -(acc.a[S_CX].lo + acc.a[S_AX].lo);
+        out->zlo = -(acc.a[S_CZ].hi + acc.a[S_AZ].hi); out->zhi = -(acc.a[S_CZ].lo + acc.a[S_AZ].lo);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) out->L[q] = pc.L[q];
+        out->unbounded = k.unb;
+    }
 }
 
 // Node i: attitude block, the left spring's terms (left == NULL for node 0),
@@ -222,7 +229,7 @@ __device__ __forceinline__ void node_pass(const Args& A, const TileRef& t, const
     }
     const NodeConsts K = node_consts(A.c, A.kL, A.L0);
     SpringKeep k;
-    spring_step(K, d, right, k, &s_sp[lt * U + i]);
+    spring_step(K, d, U > 1, right, k, &s_sp[lt * U + i]);
     if (k.unb) atomicOr(&s_flag[lt], LEB_FLAG_UNBOUNDED);
     if (ONE_WAVE) wave_lds_fence();
     else __syncthreads();      // spring terms and flags complete

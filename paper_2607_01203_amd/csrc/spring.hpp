@@ -32,7 +32,9 @@ enum { S_CX = 0, S_CZ = 1, S_BX = 2, S_BZ = 3, S_AX = 4, S_AZ = 5 };
 // The pieces leave through out.right(q, T) / out.left(q, T), q = 0 .. 4:
 //   right: Txxx V1, Txxz V1, Txzz V1, Txzz V2, Tzzz V2
 //   left:  Txxx V3, Txxz V3, Txzz V3, Txzz V4, Tzzz V4
-template <class XA, class XB, class Z0, class Z1, class Z2, class PXI, class PZI, class PXJ, class PZJ, class Acc,
+// EARLY: leave at once when the spring may vanish (else the same verdict comes with the
+// rest evaluated, to be dropped)
+template <bool EARLY = true, class XA, class XB, class Z0, class Z1, class Z2, class PXI, class PZI, class PXJ, class PZJ, class Acc,
           class Out>
 __device__ __forceinline__ bool spring_core(IV<XA> dxA, IV<XB> dxB, IV<Z0> dz0, IV<Z1> dz1, IV<Z2> dz2,
                                             IV<PXI> Dxi, IV<PZI> Dzi, IV<PXJ> Dxj, IV<PZJ> Dzj,
@@ -44,7 +46,8 @@ __device__ __forceinline__ bool spring_core(IV<XA> dxA, IV<XB> dxB, IV<Z0> dz0, 
     const auto s1 = t_add(aA, b0); const auto s2 = t_add(aA, b1);
     const auto s3 = t_add(aB, b1); const auto s4 = t_add(aB, b2);
     const float smin = fminf(fminf(val(s1.lo), val(s2.lo)), fminf(val(s3.lo), val(s4.lo)));
-    if (!(smin >= 0x1p-40f)) return false;
+    const bool ok = smin >= 0x1p-40f;
+    if (EARLY && !ok) return false;
     const auto q1 = t_rcp_pos(t_mul_nn(t_mul_nn(s1, s1), t_sqrt_pos(s1)));
     const auto q2 = t_rcp_pos(t_mul_nn(t_mul_nn(s2, s2), t_sqrt_pos(s2)));
     const auto q3 = t_rcp_pos(t_mul_nn(t_mul_nn(s3, s3), t_sqrt_pos(s3)));
@@ -90,7 +93,7 @@ __device__ __forceinline__ bool spring_core(IV<XA> dxA, IV<XB> dxB, IV<Z0> dz0, 
     acc.pos(S_AZ, K15 * mzi, t_mul_z(Tzzz2, Pzzi));
     out.right(0, Txxx1); out.right(1, Txxz1); out.right(2, Txzz1); out.right(3, Txzz2); out.right(4, Tzzz2);
     out.left(0, Txxx3); out.left(1, Txxz3); out.left(2, Txzz3); out.left(3, Txzz4); out.left(4, Tzzz4);
-    return true;
+    return ok;
 }
 
 struct SpringPieces {
