@@ -61,19 +61,45 @@ struct PrepArgs {
     double* alpha; double* c; double* rho;                 // [box][w0]
     double* zhat;                                          // [L-1][box][W]
     double* lo; double* hi;                                // [L-1][box][W] (layer 1 filled here)
+    double* s; double* t; double* a; double* D; double* e; double* amax;   // layer 1's relaxation, [box][W]
     double* g; double* eg;                                 // [box][m]
     uint32_t* flags;                                       // [box]
 };
+
+// Relaxation coefficients of one neuron with bounds [l, u] (s rounded up: the line stays above
+// relu on [l, u])
+__device__ __forceinline__ void relax_coeffs(double l, double u, double& s, double& t, double& a) {
+    if (l >= 0.0) { s = 1.0; t = 0.0; a = 1.0; }
+    else if (u <= 0.0) { s = 0.0; t = 0.0; a = 0.0; }
+    else {
+        s = u / (u - l);
+        s = s + s * 0x1p-50;
+        t = -s * l;
+        t = t + t * 0x1p-50;
+        a = (u >= -l) ? 1.0 : 0.0;
+    }
+}
+
+// Layer 1's relaxation of one neuron at offset o: bounds [l, u], wa = |W_1| (|c| + rho) + |b|
+// (the sums of its bounds; the layers above take nn_relax_kernel)
+__device__ __forceinline__ void relax1_store(const PrepArgs& A, size_t o, double l, double u, double wa) {
+    double s, t, a;
+    relax_coeffs(l, u, s, t, a);
+    A.lo[o] = l; A.hi[o] = u;
+    A.s[o] = s; A.t[o] = t; A.a[o] = a;
+    A.e[o] = fmax(fabs(l), fabs(u)) + wa + fabs(t);
+    A.amax[o] = fmax(u, 0.0);
+}
 
 // one workgroup (256 lanes) per box
 __global__ void __launch_bounds__(256) nn_prep_kernel(PrepArgs A) {
     __shared__ double s_a[NN_MAXW], s_m[NN_MAXW], s_v[NN_MAXW];
     __shared__ double s_c[NN_MAXW], s_r[NN_MAXW], s_al[NN_MAXW];
-    __shared__ uint32_t s_flag;
+    __shared__ uint32_t s_flag, s_uns;
     const int box = blockIdx.x, q = threadIdx.x;
     const int64_t unit = A.u0 + box;
     const int n0 = A.w[0], m = A.w[A.L];
-    if (q == 0) s_flag = 0;
+    if (q == 0) s_flag = s_uns = 0;
     __syncthreads();
     if (q < n0) {
         const double x = q < A.nx ? A.z[unit * A.nx + q] : A.v[unit * A.nu + (q - A.nx)];
@@ -108,8 +134,9 @@ __global__ void __launch_bounds__(256) nn_prep_kernel(PrepArgs A) {
                 abs_ = __builtin_fma(fabs(Wr[k]), fabs(s_c[k]), abs_);
             }
             const double err = RT * (abs_ + mag + fabs(lin));
-            A.lo[(size_t)box * NN_MAXW + q] = lin - mag - err;
-            A.hi[(size_t)box * NN_MAXW + q] = lin + mag + err;
+            const double l = lin - mag - err, u = lin + mag + err;
+            relax1_store(A, (size_t)box * NN_MAXW + q, l, u, abs_ + mag);
+            if (l < 0.0 && u > 0.0) s_uns = 1u;
         }
     }
     // nominal forward pass, magnitude chains (nominal error, Jacobian error)
@@ -145,6 +172,7 @@ __global__ void __launch_bounds__(256) nn_prep_kernel(PrepArgs A) {
             if (l < A.L - 1) {
                 const bool on = z > 0.0;
                 A.zhat[((size_t)l * A.nbox + box) * NN_MAXW + q] = z;
+                if (l == 0) A.D[(size_t)box * NN_MAXW + q] = on ? 1.0 : 0.0;
                 s_a[q] = on ? z : 0.0;
                 s_m[q] = mz;
                 s_v[q] = on ? vz : 0.0;
@@ -156,44 +184,28 @@ __global__ void __launch_bounds__(256) nn_prep_kernel(PrepArgs A) {
         }
         __syncthreads();
     }
-    if (q == 0) A.flags[box] = s_flag;
+    if (q == 0) A.flags[box] = s_flag | (s_uns ? NN_UNSTABLE : 0u);
 }
 
 // ---------------------------------------------------------------- relax
 
 struct RelaxArgs {
     const double* lo; const double* hi;     // [box][W] of layer l
-    const double* amax_prev;                // [box][W] of layer l-1, or NULL (input layer: |c| + rho)
-    const double* c; const double* rho;     // [box][w0]
+    const double* amax_prev;                // [box][W] of layer l-1
     const double* WT;                       // layer l transposed [w[l-1]][w[l]]
     const double* b;                        // [w[l]]
     const double* zhat;                     // [box][W]
-    int in, out, n0, nact;
+    int in, out, nact;
     double* s; double* t; double* a; double* D; double* e; double* amax;   // [box][W]
     uint32_t* boxflags;                     // [box]
 };
-
-// Relaxation coefficients of one neuron with bounds [l, u] (s rounded up: the line stays above
-// relu on [l, u])
-__device__ __forceinline__ void relax_coeffs(double l, double u, double& s, double& t, double& a) {
-    if (l >= 0.0) { s = 1.0; t = 0.0; a = 1.0; }
-    else if (u <= 0.0) { s = 0.0; t = 0.0; a = 0.0; }
-    else {
-        s = u / (u - l);
-        s = s + s * 0x1p-50;
-        t = -s * l;
-        t = t + t * 0x1p-50;
-        a = (u >= -l) ? 1.0 : 0.0;
-    }
-}
 
 // sound relaxation coefficients and rounding weights e = zmax + |W| amax_prev + |b| + |t|
 __global__ void __launch_bounds__(256) nn_relax_kernel(RelaxArgs A) {
     __shared__ double s_am[NN_MAXW];
     const int box = blockIdx.x, q = threadIdx.x;
     if (q < A.in) {
-        if (A.amax_prev) s_am[q] = A.amax_prev[(size_t)box * NN_MAXW + q];
-        else s_am[q] = fabs(A.c[box * A.n0 + q]) + A.rho[box * A.n0 + q];
+        s_am[q] = A.amax_prev[(size_t)box * NN_MAXW + q];
     }
     __syncthreads();
     const size_t o = (size_t)box * NN_MAXW + q;
@@ -238,20 +250,13 @@ constexpr size_t NNG_LDS = (size_t)3 * NN_MAXW * NNG_RS * sizeof(double);
 
 __global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
     extern __shared__ __attribute__((aligned(16))) double X[];       // [3][NN_MAXW][NNG_RS]
-    __shared__ uint32_t s_flag[NNG_BOXES];
+    __shared__ uint32_t s_flag[NNG_BOXES], s_uns[NNG_BOXES];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = blockIdx.x * NNG_BOXES, nb = min(NNG_BOXES, A.nact - b0);
     const int n0 = A.w[0], m = A.w[A.L];
     auto X_ = [&](int c, int n, int b) -> double& { return X[(c * NN_MAXW + n) * NNG_RS + b]; };
-    // rows [box][n] of an array from LDS plane c
-    auto store = [&](double* dst, int c, int cols) {
-        for (int e = tid; e < nb * cols; e += NNG_T) {
-            const int b = e / cols, n = e - b * cols;
-            dst[(size_t)(b0 + b) * NN_MAXW + n] = X_(c, n, b);
-        }
-    };
-    if (tid < NNG_BOXES) s_flag[tid] = 0;
+    if (tid < NNG_BOXES) s_flag[tid] = s_uns[tid] = 0;
     __syncthreads();
     // box = hull({a~}, a~ + mu +/- sigma): centre and half-width, widened so the FP64 box
     // encloses the exact one; planes: centre, its magnitude, half-width
@@ -305,6 +310,7 @@ __global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
                     const double err = RT * (mz + vz + fabs(z));
                     X_(0, n, r) = z - vz - err;
                     X_(1, n, r) = z + vz + err;
+                    X_(2, n, r) = mz + vz;
                 } else if (!last) {
                     X_(0, n, r) = z;
                     X_(1, n, r) = mz;
@@ -318,8 +324,12 @@ __global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
         }
         __syncthreads();
         if (l < 0) {
-            store(A.lo, 0, out);
-            store(A.hi, 1, out);
+            for (int e = tid; e < nb * out; e += NNG_T) {
+                const int b = e / out, n = e - b * out;
+                const double lo = X_(0, n, b), hi = X_(1, n, b);
+                relax1_store(A, (size_t)(b0 + b) * NN_MAXW + n, lo, hi, X_(2, n, b));
+                if (lo < 0.0 && hi > 0.0) s_uns[b] = 1u;
+            }
             __syncthreads();
             // planes of the forward pass: input, its magnitude, |a - a~| bound
             for (int e = tid; e < NNG_BOXES * n0; e += NNG_T) {
@@ -330,10 +340,15 @@ __global__ void __launch_bounds__(NNG_T) nn_prep_group_kernel(PrepArgs A) {
             }
             __syncthreads();
         } else if (!last) {
-            store(A.zhat + (size_t)l * A.nbox * NN_MAXW, 0, out);
+            for (int e = tid; e < nb * out; e += NNG_T) {
+                const int b = e / out, n = e - b * out;
+                const double z = X_(0, n, b);
+                A.zhat[((size_t)l * A.nbox + b0 + b) * NN_MAXW + n] = z;
+                if (l == 0) A.D[(size_t)(b0 + b) * NN_MAXW + n] = z > 0.0 ? 1.0 : 0.0;
+            }
         }
     }
-    if (tid < nb) A.flags[b0 + tid] = s_flag[tid];
+    if (tid < nb) A.flags[b0 + tid] = s_flag[tid] | (s_uns[tid] ? NN_UNSTABLE : 0u);
 }
 
 __global__ void __launch_bounds__(NNG_T) nn_relax_group_kernel(RelaxArgs A) {
@@ -345,8 +360,7 @@ __global__ void __launch_bounds__(NNG_T) nn_relax_group_kernel(RelaxArgs A) {
     if (tid < NNG_BOXES) s_uns[tid] = 0;
     for (int e = tid; e < NNG_BOXES * A.in; e += NNG_T) {
         const int b = e / A.in, q = e - b * A.in, box = b0 + min(b, nb - 1);
-        X[q * NNG_RS + b] = A.amax_prev ? A.amax_prev[(size_t)box * NN_MAXW + q]
-                                        : fabs(A.c[box * A.n0 + q]) + A.rho[box * A.n0 + q];
+        X[q * NNG_RS + b] = A.amax_prev[(size_t)box * NN_MAXW + q];
     }
     __syncthreads();
     d4 acc[2][1];
@@ -629,6 +643,7 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
         for (int l = 0; l < L; ++l) { pa.W[l] = net->W[l]; pa.WT[l] = net->WT[l]; pa.b[l] = net->b[l]; }
         pa.alpha = alpha; pa.c = c; pa.rho = rho; pa.zhat = zhat; pa.lo = lo; pa.hi = hi; pa.g = g; pa.eg = eg;
         pa.flags = fl;
+        pa.s = s; pa.t = t; pa.a = a; pa.D = D; pa.e = e; pa.amax = amax;
         const bool groups = nb >= NNG_MIN;
         const int ng = (nb + NNG_BOXES - 1) / NNG_BOXES;
         if (groups) {
@@ -644,13 +659,12 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
             hipLaunchKernelGGL(nn_prep_kernel, dim3(nb), dim3(256), 0, st, pa);
         }
         if (hipGetLastError() != hipSuccess) return LEB_EDEVICE;
-        auto relax = [&](int l) -> int {     // hidden layer l+1 (0-based l)
+        auto relax = [&](int l) -> int {     // hidden layer l+1 (0-based l >= 1)
             RelaxArgs ra;
             ra.lo = layer(lo, l); ra.hi = layer(hi, l);
-            ra.amax_prev = l == 0 ? nullptr : layer(amax, l - 1);
-            ra.c = c; ra.rho = rho;
+            ra.amax_prev = layer(amax, l - 1);
             ra.WT = net->WT[l]; ra.b = net->b[l]; ra.zhat = layer(zhat, l);
-            ra.in = net->w[l]; ra.out = net->w[l + 1]; ra.n0 = n0;
+            ra.in = net->w[l]; ra.out = net->w[l + 1];
             ra.s = layer(s, l); ra.t = layer(t, l); ra.a = layer(a, l); ra.D = layer(D, l);
             ra.e = layer(e, l); ra.amax = layer(amax, l);
             ra.boxflags = fl;
@@ -659,7 +673,6 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
             else hipLaunchKernelGGL(nn_relax_kernel, dim3(nb), dim3(256), 0, st, ra);
             return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
         };
-        if ((rc = relax(0))) return rc;
         // backward chain for target layer k (1-based, 2..L): modes 0 upper, 1 lower (, 2 Jacobian)
         auto chain = [&](int k, int nmode, double** lam_out, double** beta_out, double** eps_out) -> int {
             ChainArgs ca = {};
