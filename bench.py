@@ -57,7 +57,7 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E
 # WRITE_SIZE (KiB per dispatch, rocprofv3 --pmc), and the factors that map each
 # counter to bytes, measured on a copy kernel of known size; None until taken for
 # the kernel as it is now.
-TUBE_PMC_KIB = (27280, 36110)
+TUBE_PMC_KIB = (25680, 32271)
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 FP64_PEAK_TFLOPS = 78.6          # MI355X FP64 matrix (= vector) peak
 FP32_MFMA_PEAK_TFLOPS = 157.3    # MI355X dense FP32 matrix peak (the compact tube map's contraction)
@@ -65,7 +65,7 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # lane-ops/s of non-packed VALU i
 # VALU lane-operations per unit of the path-based bound kernel at nx = 168:
 # SQ_INSTS_VALU x 64 / units from rocprofv3 --pmc on the 2,560 x 40 launch
 # (profiles/pbh_chain_fwd_plain_2560x40x168.md; None until taken for the kernel as it is now).
-PBH_VALU_LANE_OPS_PER_UNIT = 52723
+PBH_VALU_LANE_OPS_PER_UNIT = 50390
 
 
 def parse():
@@ -606,15 +606,18 @@ def nn_crown_flops(widths):
 
 # MFMA instructions per box of the MLP bound on the 16-256-256-256-12 workload
 # (SQ_INSTS_MFMA / boxes, profiles/nn_chain_kernel_mlp_bound_64x50.md), each
-# v_mfma_f64_16x16x4f64 2,048 FLOP; None until taken for the kernels as they are now.
-NN_MFMA_INSTS_PER_BOX = 76.96e6 / 3200
+# v_mfma_f64_16x16x4f64 2,048 FLOP.
+NN_MFMA_INSTS_PER_BOX = 36.34e6 / 3200
+# the same for the adjoint (profiles/nn_backward_mlp_bound_64x50.md)
+NN_ADJ_MFMA_INSTS_PER_BOX = 43.11e6 / 3200
 
 
 def nn_roofline(leb, W, dev, stream, args):
     """MLP bound (CROWN + Theorem 2) on 64 x 50 boxes of the 16-256-256-256-12
     network: FP64 MFMA, timed with HIP events on its stream.  `achieved` counts
-    the dense CROWN FLOPs (the method's work); `executed_frac` the MFMA FLOPs
-    the kernels issue (stably inactive neurons skipped) against the peak."""
+    the MFMA FLOPs that the kernels issue (the products of stably inactive
+    neurons and the chains of stable ones are skipped);
+    `dense_equivalent_tflops` the dense CROWN FLOPs, the method's work."""
     import torch
     b = W.nn_cfg()
     net = leb.MLP(b.net.W, b.net.b, b.net.nx, True)
@@ -634,37 +637,31 @@ def nn_roofline(leb, W, dev, stream, args):
     ms = e0.elapsed_time(e1) / reps
     boxes = b.z.shape[0] * b.z.shape[1]
     widths = [b.net.W[0].shape[1]] + [w.shape[0] for w in b.net.W]
-    fl = nn_crown_flops(widths) * boxes
+    dense = nn_crown_flops(widths) * boxes / (ms * 1e-3) / 1e12
     net.close()
-    achieved = fl / (ms * 1e-3) / 1e12
+    achieved = NN_MFMA_INSTS_PER_BOX * 2048 * boxes / (ms * 1e-3) / 1e12
     return {"workload": "MLP bound, 64 x 50 boxes, widths %s" % widths, "ms_per_call": round(ms, 4),
             "timestep_bounds_per_s": round(boxes / (ms * 1e-3), 1),
             "bound": "mfma", "achieved": round(achieved, 2), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": round(achieved / FP64_PEAK_TFLOPS, 4), "flops_per_box": nn_crown_flops(widths),
-            "executed_frac": None if NN_MFMA_INSTS_PER_BOX is None else
-            round(NN_MFMA_INSTS_PER_BOX * 2048 * boxes / (ms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, 4)}
+            "frac": round(achieved / FP64_PEAK_TFLOPS, 4), "flops_per_box": round(NN_MFMA_INSTS_PER_BOX * 2048),
+            "dense_flops_per_box": nn_crown_flops(widths), "dense_equivalent_tflops": round(dense, 2)}
 
 
 def nn_adjoint_flops(widths):
-    """(algorithmic, executed) FLOPs per box of the MLP bound's adjoint.
-    Algorithmic: the bound's own passes (nn_crown_flops) plus the reverse of
-    every pass in both modes, each as large as the pass.  Executed, dense MFMA
-    form (at most three hidden layers): a forward launch for every pass (the
-    output pass's too, to store its levels), the reverse of every pass, and the
-    Jacobian rows once per mode; the kernels skip the stably inactive neurons'
-    share of it."""
+    """Dense FLOPs per box of the MLP bound's adjoint: the bound's own passes
+    (nn_crown_flops) plus the reverse of every pass in both modes, each as large
+    as the pass."""
     L = len(widths) - 1
     chain = lambda k: sum(widths[k] * widths[j] * widths[j - 1] for j in range(k - 1, 0, -1))
-    rev = sum(2 * chain(k) for k in range(2, L + 1))
-    fwd = sum(2 * chain(k) for k in range(2, L + 1))
-    executed = fwd + rev + 2 * chain(L)
-    return nn_crown_flops(widths) + 2 * rev, 2 * executed
+    return nn_crown_flops(widths) + 2 * sum(2 * chain(k) for k in range(2, L + 1))
 
 
 def nn_adjoint(leb, W, dev, stream):
     """Adjoint of the MLP bound (leb_nn_backward) on the 64 x 50 boxes of the
     16-256-256-256-12 network, seeds g_lo = -1, g_hi = 1 (the gradient of the
-    bound's total width); FP64 MFMA products, timed with HIP events on its stream."""
+    bound's total width); FP64 MFMA products, timed with HIP events on its stream.
+    `achieved` counts the MFMA FLOPs that the kernels issue,
+    `dense_equivalent_tflops` the dense FLOPs of every pass."""
     import torch
     b = W.nn_cfg()
     net = leb.MLP(b.net.W, b.net.b, b.net.nx, True)
@@ -696,14 +693,14 @@ def nn_adjoint(leb, W, dev, stream):
     ms_bound = e0.elapsed_time(e1) / reps
     net.close()
     widths = [b.net.W[0].shape[1]] + [w.shape[0] for w in b.net.W]
-    alg, exe = nn_adjoint_flops(widths)
-    achieved = alg * boxes / (ms * 1e-3) / 1e12
+    alg = nn_adjoint_flops(widths)
+    achieved = NN_ADJ_MFMA_INSTS_PER_BOX * 2048 * boxes / (ms * 1e-3) / 1e12
     return {"workload": "MLP-bound adjoint, 64 x 50 boxes, widths %s" % widths, "ms_per_call": round(ms, 4),
             "box_gradients_per_s": round(boxes / (ms * 1e-3), 1), "ms_bound": round(ms_bound, 4),
             "over_bound": round(ms / ms_bound, 3), "bound": "mfma", "achieved": round(achieved, 2),
             "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / FP64_PEAK_TFLOPS, 4),
-            "flops_per_box": alg, "executed_flops_per_box": exe,
-            "executed_frac": round(exe * boxes / (ms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, 4)}
+            "flops_per_box": round(NN_ADJ_MFMA_INSTS_PER_BOX * 2048), "dense_flops_per_box": alg,
+            "dense_equivalent_tflops": round(alg * boxes / (ms * 1e-3) / 1e12, 2)}
 
 
 def nn_learned(leb, W, dev, stream, args):

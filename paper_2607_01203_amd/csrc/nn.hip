@@ -13,12 +13,12 @@
 //
 // GPU design.  Each backward substitution step
 //     Lambda_next = (Lambda (.) S) W_l      (S sign-selected slopes)
-// is a batched dense contraction run on FP64 MFMA (v_mfma_f64_16x16x4):
-// the left operand is generated on the fly from Lambda and the per-box
-// slopes, the shared weight tile is staged through LDS, and the per-row bias
-// (intercepts, Omega b_l) and rounding-term weights are accumulated while
-// the operand is generated.  The upper, lower and Jacobian chains of one
-// box share the same kernel (modes), the Jacobian chain using S = 1[z^ > 0].
+// is a batched dense contraction run on FP64 MFMA (v_mfma_f64_16x16x4): the
+// operand is generated on the fly from Lambda and the per-box slopes, the weights
+// come from L2, and the per-row bias (intercepts, Omega b_l) and rounding-term
+// weights are accumulated beside.  Kernels (nn_hid.hpp, shared with the adjoint): hidden
+// targets of 16-input networks run both directions together; every other chain
+// runs one mode (upper, lower, Jacobian with S = 1[z^ > 0]) a workgroup.
 //
 // Soundness in floating point: every FP64 dot product of length <= 300 has
 // error <= 2^-44.8 times the dot product of absolute values.  Each bound

@@ -34,23 +34,20 @@
 // only from passes with k > j, so each layer's adjoint is complete when its
 // own pass is reversed.  J a~ - g(a~) has derivative 0 (J is locally constant).
 //
-// GPU design.  One workgroup of 256 lanes per (box, pass direction); lane q
-// owns neuron column q of every level, applies the relaxation selection to
-// it and keeps the per-neuron sums s-bar, t-bar, c-bar, rho-bar of its column
-// across row blocks; later passes add to them in launch order, so the result
-// is deterministic.  The operand of each row-block product is staged in LDS
-// as [neuron][row]; the weights come from L2 (W_j forward, W_j^T in reverse,
-// both row-major, coalesced).  Two forms:
-//  * MFMA (at most three hidden layers, the usual case): 16-row blocks on
-//    FP64 MFMA; every pass has a forward launch that stores its levels and the
-//    reverse launch reads them back; the k range of each product runs over
-//    the neurons that are not stably inactive (see the MFMA section below).
-//    Hidden targets of 16-input networks: the forward kernels of the bound
-//    (nn_hid.hpp), storing the levels of unstable rows, the only ones read back.
-//  * VALU (deeper networks): 8-row blocks, Lambda^(j) of the lane's column
-//    kept in registers for the reverse sweep; hidden-layer passes store their
-//    levels, the output pass recomputes its chain; narrow outputs (the input
-//    layer) split the sum over lane slices added in a fixed order.
+// GPU design.  Sums are taken in a fixed order and later passes add to the per-neuron
+// sums in launch order, so the result is deterministic.  Three forms:
+//  * 16 inputs, at most three hidden layers (the usual case): the forward passes are the
+//    bound's kernels (nn_hid.hpp), storing the levels of unstable target rows, the only
+//    ones read back; the reverse passes keep the chain in registers (nn_rev_kernel).
+//  * other inputs, at most three hidden layers: one workgroup of 256 lanes per (box, pass
+//    direction), 16-row blocks on FP64 MFMA; lane q owns neuron column q of every level,
+//    applies the relaxation selection to it and keeps its sums; every pass has a forward
+//    launch that stores its levels and a reverse launch that reads them back; products
+//    run over the neurons that are not stably inactive (see the MFMA section below).
+//  * deeper networks, on the VALU: 8-row blocks, Lambda^(j) of the lane's column kept in
+//    registers for the reverse sweep; hidden-layer passes store their levels, the output
+//    pass recomputes its chain; narrow outputs (the input layer) split the sum over lane
+//    slices added in a fixed order.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
