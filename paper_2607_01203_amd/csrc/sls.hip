@@ -6,10 +6,10 @@
 // Responses (appendix on solving for Phi, eqs. backward_prop and
 // forward_prop; reformulated problem eq. fastsls_qp_reform): the problem
 // splits over the disturbance time j, so every (trajectory, j) pair runs on its
-// own, by one of three kernels chosen by size (leb_sls_responses),
+// own, by one of two kernels chosen by size (leb_sls_responses),
 //   backward  P_{N,j} = diag(qx_{N,j}); for k = N-1 .. j+1:
 //             S = diag(qu_{k,j}) + B_k^T P B_k,  Bc = B_k^T P A_k,
-//             K_{k,j} = -S^-1 Bc (Cholesky),  P <- diag(qx_{k,j}) + A_k^T P A_k + K^T Bc
+//             K_{k,j} = -S^-1 Bc,  P <- diag(qx_{k,j}) + A_k^T P A_k + K^T Bc
 //   forward   X = I; for k = j+1 .. N-1: Phi^x_{k,j} = X, Phi^u_{k,j} = K_{k,j} X,
 //             X <- (A_k + B_k K_{k,j}) X.
 // All FP64: the gains define the controller, they are not enclosures.
@@ -84,215 +84,7 @@ __device__ void riccati_zero(const RiccatiArgs& a, int b, int j, int cnt) {
     }
 }
 
-template <int NUB, int PF>
-__global__ void __launch_bounds__(SLS_THREADS) sls_riccati_kernel(RiccatiArgs a) {
-    const int j = blockIdx.x, b = blockIdx.y;
-    const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
-    if (j >= N - 1) {                            // no k with j < k < N
-        if (a.zero) riccati_zero(a, b, j, 1);
-        return;
-    }
-    extern __shared__ double sm[];
-    double* P = sm;                              // nx*nx   cost-to-go, then X of the forward pass
-    double* Ak = P + nx * nx;                    // nx*nx
-    double* PA = Ak + nx * nx;                   // nx*nx   P A_k, then X' of the forward pass
-    double* Acl = PA + nx * nx;                  // nx*nx   A_k + B_k K
-    double* Bk = Acl + nx * nx;                  // nx*nu
-    double* PB = Bk + nx * nu;                   // nx*nu
-    double* Bc = PB + nx * nu;                   // nu*nx
-    double* Kk = Bc + nu * nx;                   // nu*nx
-    double* L = Kk + nu * nx;                    // nu*nu   S, then its Cholesky factor
-    double* sqx = L + nu * nu;                   // nx      diag(Q^x_{k,j})
-    double* squ = sqx + nx;                      // nu      diag(Q^u_{k,j})
-    __shared__ int bad;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const double* Ab = a.A + (size_t)b * N * nx * nx;
-    const double* Bb = a.B + (size_t)b * N * nx * nu;
-    const double* qxb = a.qx + (size_t)b * (N + 1) * N * nx;
-    const double* qub = a.qu + (size_t)b * N * N * nu;
-    double* Kb = a.K + (size_t)b * N * N * nu * nx;
-    double* phib = a.phi + (size_t)b * N * N * n * nx;
-    if (tid == 0) bad = 0;
-    for (int q = tid; q < nx * nx; q += nt) {
-        const int r = q / nx, c = q - r * nx;
-        P[q] = r == c ? qxb[((size_t)N * N + j) * nx + r] : 0.0;
-    }
-    // a step's (A_k, B_k, weights) -- or (A_k, B_k, K_k) in the forward pass --
-    // are loaded into registers two steps ahead (two buffers, the step loop
-    // taken two at a time so each buffer has a fixed role) and stored to LDS
-    // after the last barrier of the step before theirs
-    double pfa[PF], pfb[PF];
-    const int nab = nx * n;
-    auto fetch = [&](int k, bool fwd, double* pf) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            const int q = tid + u * nt;
-            double x = 0.0;
-            if (q < nx * nx) x = Ab[(size_t)k * nx * nx + q];
-            else if (q < nab) x = Bb[(size_t)k * nx * nu + (q - nx * nx)];
-            else if (fwd) { if (q < nab + nu * nx) x = Kb[((size_t)k * N + j) * nu * nx + (q - nab)]; }
-            else if (q < nab + nx) x = qxb[((size_t)k * N + j) * nx + (q - nab)];
-            else if (q < nab + n) x = qub[((size_t)k * N + j) * nu + (q - nab - nx)];
-            pf[u] = x;
-        }
-    };
-    auto stash = [&](bool fwd, const double* pf) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            const int q = tid + u * nt;
-            if (q < nx * nx) Ak[q] = pf[u];
-            else if (q < nab) Bk[q - nx * nx] = pf[u];
-            else if (fwd) { if (q < nab + nu * nx) Kk[q - nab] = pf[u]; }
-            else if (q < nab + nx) sqx[q - nab] = pf[u];
-            else if (q < nab + n) squ[q - nab - nx] = pf[u];
-        }
-    };
-    fetch(N - 1, false, pfa);
-    stash(false, pfa);
-    if (N - 2 > j) fetch(N - 2, false, pfb);
-    auto bstep = [&](int k, double* fb, const double* sb) {
-        lds_barrier();
-        if (k - 2 > j) fetch(k - 2, false, fb);
-        // P A_k and P B_k
-        for (int q = tid; q < nx * n; q += nt) {
-            double s = 0.0;
-            if (q < nx * nx) {
-                const int r = q / nx, c = q - r * nx;
-                for (int l = 0; l < nx; ++l) s = fma(P[r * nx + l], Ak[l * nx + c], s);
-                PA[q] = s;
-            } else {
-                const int q2 = q - nx * nx, r = q2 / nu, c = q2 - r * nu;
-                for (int l = 0; l < nx; ++l) s = fma(P[r * nx + l], Bk[l * nu + c], s);
-                PB[q2] = s;
-            }
-        }
-        lds_barrier();
-        // S = diag(qu) + B^T (P B),  Bc = B^T (P A)
-        for (int q = tid; q < nu * n; q += nt) {
-            if (q < nu * nu) {
-                const int r = q / nu, c = q - r * nu;
-                double s = 0.0;
-                for (int l = 0; l < nx; ++l) s = fma(Bk[l * nu + r], PB[l * nu + c], s);
-                L[q] = (r == c ? squ[r] : 0.0) + s;
-            } else {
-                const int q2 = q - nu * nu, r = q2 / nx, c = q2 - r * nx;
-                double s = 0.0;
-                for (int l = 0; l < nx; ++l) s = fma(Bk[l * nu + r], PA[l * nx + c], s);
-                Bc[q2] = s;
-            }
-        }
-        lds_barrier();
-        // Cholesky S = L L^T (lower triangle in place; diagonal holds 1/L_ii)
-        if (tid == 0) {
-            for (int c = 0; c < nu; ++c) {
-                double d = L[c * nu + c];
-                for (int m = 0; m < c; ++m) d -= L[c * nu + m] * L[c * nu + m];
-                if (!(d > 0.0) || !isfinite(d)) { bad = 1; d = 1.0; }
-                const double inv = 1.0 / sqrt(d);
-                L[c * nu + c] = inv;
-                for (int r = c + 1; r < nu; ++r) {
-                    double s = L[r * nu + c];
-                    for (int m = 0; m < c; ++m) s -= L[r * nu + m] * L[c * nu + m];
-                    L[r * nu + c] = s * inv;
-                }
-            }
-        }
-        lds_barrier();
-        // K = -S^-1 Bc, one column per thread: L y = Bc[:, c], then L^T x = y, in registers
-        for (int c = tid; c < nx; c += nt) {
-            double y[NUB];
-#pragma unroll
-            for (int r = 0; r < NUB; ++r) {
-                if (r < nu) {
-                    double s = Bc[r * nx + c];
-#pragma unroll
-                    for (int m = 0; m < r; ++m) s -= L[r * nu + m] * y[m];
-                    y[r] = s * L[r * nu + r];
-                }
-            }
-#pragma unroll
-            for (int r = NUB - 1; r >= 0; --r) {
-                if (r < nu) {
-                    double s = y[r];
-#pragma unroll
-                    for (int m = r + 1; m < NUB; ++m)
-                        if (m < nu) s -= L[m * nu + r] * y[m];
-                    y[r] = s * L[r * nu + r];
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < NUB; ++r)
-                if (r < nu) Kk[r * nx + c] = bad ? NAN : -y[r];
-        }
-        lds_barrier();
-        // P <- diag(qx) + A^T (P A) + K^T Bc; the gain goes out
-        for (int q = tid; q < nx * nx; q += nt) {
-            const int r = q / nx, c = q - r * nx;
-            double s = 0.0;
-            for (int l = 0; l < nx; ++l) s = fma(Ak[l * nx + r], PA[l * nx + c], s);
-            double t = 0.0;
-            for (int m = 0; m < nu; ++m) t = fma(Kk[m * nx + r], Bc[m * nx + c], t);
-            P[q] = (r == c ? sqx[r] : 0.0) + s + t;
-        }
-        for (int q = tid; q < nu * nx; q += nt) Kb[((size_t)k * N + j) * nu * nx + q] = Kk[q];
-        lds_barrier();
-        if (k - 1 > j) stash(false, sb);
-    };
-    for (int k = N - 1; k > j; k -= 2) {
-        bstep(k, pfa, pfb);
-        if (k - 1 > j) bstep(k - 1, pfb, pfa);
-    }
-    // forward propagation from Phi^x_{j+1,j} = I; the gains were stored by this
-    // workgroup above, and this full barrier orders those stores before the loads
-    __syncthreads();
-    double* X = P;
-    double* Xn = PA;
-    for (int q = tid; q < nx * nx; q += nt) X[q] = (q / nx == q % nx) ? 1.0 : 0.0;
-    fetch(j + 1, true, pfa);
-    stash(true, pfa);
-    if (j + 2 < N) fetch(j + 2, true, pfb);
-    auto fstep = [&](int k, double* fb, const double* sb) {
-        lds_barrier();
-        if (k + 2 < N) fetch(k + 2, true, fb);
-        double* out = phib + ((size_t)k * N + j) * n * nx;
-        for (int q = tid; q < n * nx; q += nt) {
-            const int r = q / nx, c = q - r * nx;
-            double s;
-            if (r < nx) {
-                s = X[q];
-            } else {
-                s = 0.0;
-                for (int m = 0; m < nx; ++m) s = fma(Kk[(r - nx) * nx + m], X[m * nx + c], s);
-            }
-            out[q] = s;
-        }
-        for (int q = tid; q < nx * nx; q += nt) {
-            const int r = q / nx, c = q - r * nx;
-            double s = 0.0;
-            for (int m = 0; m < nu; ++m) s = fma(Bk[r * nu + m], Kk[m * nx + c], s);
-            Acl[q] = Ak[q] + s;
-        }
-        lds_barrier();
-        if (k + 1 < N) {
-            for (int q = tid; q < nx * nx; q += nt) {
-                const int r = q / nx, c = q - r * nx;
-                double s = 0.0;
-                for (int l = 0; l < nx; ++l) s = fma(Acl[r * nx + l], X[l * nx + c], s);
-                Xn[q] = s;
-            }
-            lds_barrier();
-            double* t = X; X = Xn; Xn = t;
-            stash(true, sb);
-        }
-    };
-    for (int k = j + 1; k < N; k += 2) {
-        fstep(k, pfa, pfb);
-        if (k + 1 < N) fstep(k + 1, pfb, pfa);
-    }
-    if (a.zero) riccati_zero(a, b, j, 1);
-}
-
-// The same recursions for one small size (NX <= 8, NU = 2) with eight lanes per
+// One small size (NX <= 8, NU = 2) with eight lanes per
 // (trajectory, j): lane c of a group of eight holds column c of every matrix in
 // registers, so products with A_k and B_k from the left are local, and a wave
 // runs eight consecutive j of one trajectory in lockstep over k, sharing
@@ -485,194 +277,18 @@ __global__ void __launch_bounds__(64) sls_riccati_lane_kernel(RiccatiArgs a) {
     if (a.zero) riccati_zero(a, b, j0, 8);
 }
 
-// The same recursions on FP64 MFMA (v_mfma_f64_16x16x4f64) for nx <= 16,
-// nu <= 4: one wave per (trajectory, j), every matrix a zero-padded 16 x 16
-// tile held in registers in the accumulator layout (lane l holds element
-// [4i + l/16][l%16] of its tile, i = 0..3).  That layout is also the B operand
-// of a product and, read as the A operand, the transpose, so every product
-// takes the form X^T Y and stays in registers:
-//   P A = P^T A and P B = P^T B (P is symmetric), S = B^T (P B),
-//   Bc = B^T (P A), P' = diag(qx) + A^T (P A) + K^T Bc;
-//   forward: K X = (K^T)^T X, (A + B K)^T = A^T + K^T B^T, X' = ((A + B K)^T)^T X,
-// with A^T, B^T, K^T loaded straight into the accumulator layout.  Only S
-// and Bc pass through LDS, for the nu x nu Cholesky factor and the column
-// solves (lanes c < nx, each factoring S itself).
 typedef double sls_d4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ sls_d4 mm_tn(const sls_d4& X, const sls_d4& Y, sls_d4 acc) {   // acc + X^T Y
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[t], Y[t], acc, 0, 0, 0);
-    return acc;
-}
-
-// M (R x C, leading dimension ld) in the accumulator layout; tr: M^T instead
-__device__ __forceinline__ sls_d4 tile_load(const double* M, int R, int C, int ld, int lr, int lq, bool tr) {
-    sls_d4 v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = tr ? lr : 4 * i + lq, col = tr ? 4 * i + lq : lr;
-        v[i] = (row < R && col < C) ? M[row * ld + col] : 0.0;
-    }
-    return v;
-}
-
-template <int NUB>
-__global__ void __launch_bounds__(64) sls_riccati_mfma_kernel(RiccatiArgs a) {
-    const int j = blockIdx.x, b = blockIdx.y;
-    const int nx = a.nx, nu = a.nu, N = a.N, n = nx + nu;
-    if (j >= N - 1) {
-        if (a.zero) riccati_zero(a, b, j, 1);
-        return;
-    }
-    __shared__ double sS[NUB * NUB];
-    __shared__ double sBc[NUB * 16];
-    __shared__ double sK[16 * 16];
-    const int lane = threadIdx.x, lr = lane & 15, lq = lane >> 4;
-    const double* Ab = a.A + (size_t)b * N * nx * nx;
-    const double* Bb = a.B + (size_t)b * N * nx * nu;
-    const double* qxb = a.qx + (size_t)b * (N + 1) * N * nx;
-    const double* qub = a.qu + (size_t)b * N * N * nu;
-    double* Kb = a.K + (size_t)b * N * N * nu * nx;
-    double* phib = a.phi + (size_t)b * N * N * n * nx;
-    for (int q = lane; q < 256; q += 64) sK[q] = 0.0;          // rows >= nu stay 0
-    // element of this lane on the diagonal (row 4i + lq == lr), if any
-    const int di = (lr >= lq && ((lr - lq) & 3) == 0) ? (lr - lq) >> 2 : -1;
-    sls_d4 P;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) P[i] = (i == di && lr < nx) ? qxb[((size_t)N * N + j) * nx + lr] : 0.0;
-    auto wts = [&](int k, double* qx_d, double* qu_d) {
-        *qx_d = (di >= 0 && lr < nx) ? qxb[((size_t)k * N + j) * nx + lr] : 0.0;
-        *qu_d = (di >= 0 && lr < nu) ? qub[((size_t)k * N + j) * nu + lr] : 0.0;
-    };
-    sls_d4 An = tile_load(Ab + (size_t)(N - 1) * nx * nx, nx, nx, nx, lr, lq, false);
-    sls_d4 Bn = tile_load(Bb + (size_t)(N - 1) * nx * nu, nx, nu, nu, lr, lq, false);
-    double qxn, qun;
-    wts(N - 1, &qxn, &qun);
-    const sls_d4 z4 = {0.0, 0.0, 0.0, 0.0};
-    for (int k = N - 1; k > j; --k) {
-        const sls_d4 A = An, B = Bn;
-        const double qxd = qxn, qud = qun;
-        if (k - 1 > j) {
-            An = tile_load(Ab + (size_t)(k - 1) * nx * nx, nx, nx, nx, lr, lq, false);
-            Bn = tile_load(Bb + (size_t)(k - 1) * nx * nu, nx, nu, nu, lr, lq, false);
-            wts(k - 1, &qxn, &qun);
-        }
-        const sls_d4 PA = mm_tn(P, A, z4);
-        const sls_d4 PB = mm_tn(P, B, z4);
-        sls_d4 S = mm_tn(B, PB, z4);
-        const sls_d4 Bc = mm_tn(B, PA, z4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = 4 * i + lq;
-            if (row < nu) {
-                if (lr < nu) sS[row * NUB + lr] = S[i] + (i == di ? qud : 0.0);
-                sBc[row * 16 + lr] = Bc[i];
-            }
-        }
-        lds_barrier();
-        if (lane < nx) {
-            // S = L L^T (nu <= NUB) in registers, then L y = Bc[:, c], L^T x = y
-            double L[NUB][NUB], inv[NUB];         // inv: 1 / L_cc, one division per pivot
-            bool bad = false;
-#pragma unroll
-            for (int c = 0; c < NUB; ++c) {
-                if (c < nu) {
-                    double d = sS[c * NUB + c];
-#pragma unroll
-                    for (int m = 0; m < c; ++m) d -= L[c][m] * L[c][m];
-                    if (!(d > 0.0) || !isfinite(d)) { bad = true; d = 1.0; }
-                    inv[c] = 1.0 / sqrt(d);
-#pragma unroll
-                    for (int r = c + 1; r < NUB; ++r) {
-                        if (r < nu) {
-                            double t = sS[r * NUB + c];
-#pragma unroll
-                            for (int m = 0; m < c; ++m) t -= L[r][m] * L[c][m];
-                            L[r][c] = t * inv[c];
-                        }
-                    }
-                }
-            }
-            double y[NUB];
-#pragma unroll
-            for (int r = 0; r < NUB; ++r) {
-                if (r < nu) {
-                    double t = sBc[r * 16 + lane];
-#pragma unroll
-                    for (int m = 0; m < r; ++m) t -= L[r][m] * y[m];
-                    y[r] = t * inv[r];
-                }
-            }
-#pragma unroll
-            for (int r = NUB - 1; r >= 0; --r) {
-                if (r < nu) {
-                    double t = y[r];
-#pragma unroll
-                    for (int m = r + 1; m < NUB; ++m)
-                        if (m < nu) t -= L[m][r] * y[m];
-                    y[r] = t * inv[r];
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < NUB; ++r) {
-                if (r < nu) {
-                    const double kv = bad ? NAN : -y[r];
-                    sK[r * 16 + lane] = kv;
-                    Kb[((size_t)k * N + j) * nu * nx + r * nx + lane] = kv;
-                }
-            }
-        }
-        lds_barrier();
-        sls_d4 K;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) K[i] = sK[(4 * i + lq) * 16 + lr];
-        sls_d4 Pn;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) Pn[i] = i == di ? qxd : 0.0;
-        Pn = mm_tn(A, PA, Pn);
-        P = mm_tn(K, Bc, Pn);
-        lds_barrier();                         // sS, sBc, sK are rewritten by the next step
-    }
-    // forward propagation from Phi^x_{j+1,j} = I; the gains were stored above
-    // by this wave, and the full barrier orders those stores before the loads
-    __syncthreads();
-    sls_d4 X;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) X[i] = (i == di && lr < nx) ? 1.0 : 0.0;
-    auto fwd_load = [&](int k, sls_d4* AT, sls_d4* BT, sls_d4* Kt, sls_d4* KT) {
-        const double* Kp = Kb + ((size_t)k * N + j) * nu * nx;
-        *AT = tile_load(Ab + (size_t)k * nx * nx, nx, nx, nx, lr, lq, true);
-        *BT = tile_load(Bb + (size_t)k * nx * nu, nx, nu, nu, lr, lq, true);
-        *Kt = tile_load(Kp, nu, nx, nx, lr, lq, false);
-        *KT = tile_load(Kp, nu, nx, nx, lr, lq, true);
-    };
-    sls_d4 ATn, BTn, Kn, KTn;
-    fwd_load(j + 1, &ATn, &BTn, &Kn, &KTn);
-    for (int k = j + 1; k < N; ++k) {
-        const sls_d4 AT = ATn, BT = BTn, Kt = Kn, KT = KTn;
-        if (k + 1 < N) fwd_load(k + 1, &ATn, &BTn, &Kn, &KTn);
-        double* out = phib + ((size_t)k * N + j) * n * nx;
-        const sls_d4 U = mm_tn(KT, X, z4);          // K X
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = 4 * i + lq;
-            if (lr < nx) {
-                if (row < nx) out[row * nx + lr] = X[i];
-                if (row < nu) out[(nx + row) * nx + lr] = U[i];
-            }
-        }
-        if (k + 1 < N) {
-            const sls_d4 AclT = mm_tn(Kt, BT, AT);  // (A + B K)^T
-            X = mm_tn(AclT, X, z4);                 // (A + B K) X
-        }
-    }
-    if (a.zero) riccati_zero(a, b, j, 1);
-}
-
-// The same recursions for larger sizes (nx <= 32, nu <= 16) on FP64 MFMA: one
+// Every other size (nx <= 32, nu <= 16) on FP64 MFMA (v_mfma_f64_16x16x4f64): one
 // wave per (trajectory, j), every matrix in registers as TX x TX zero-padded
-// 16 x 16 tiles (TX = 2: nx > 16) in the layout of the kernel above, every product
-// a sum of X^T Y over tiles.  The gain solves S K = -Bc by elimination: lane c
+// 16 x 16 tiles (TX = 2: nx > 16) in the accumulator layout (lane l holds element
+// [4i + l/16][l%16] of its tile, i = 0..3).  That layout is also the B operand of a
+// product and, read as the A operand, the transpose, so every product is a sum of
+// X^T Y over tiles and stays in registers:
+//   P A = P^T A and P B = P^T B (P is symmetric), S = B^T (P B),
+//   Bc = B^T (P A), P' = diag(qx) + A^T (P A) + K^T Bc;
+//   forward: U = (K^T)^T X, X' = (A^T)^T X + (B^T)^T U,
+// with A^T, B^T, K^T loaded straight into the layout.  The gain solves S K = -Bc by elimination: lane c
 // holds column c of [S | Bc] (NUB rows, NUB >= nu), and the pivot column is read
 // from its lane by v_readlane, so the nu steps need no LDS; the pivots are
 // the squares of the Cholesky pivots' and are tested the same way.  Only the
@@ -689,7 +305,10 @@ __global__ void __launch_bounds__(64) sls_riccati_mfma_kernel(RiccatiArgs a) {
 // each); the first launched waves are the longest chains (j = 0 of every
 // trajectory), so the short ones fill the end of the launch.  64 x 40 steps:
 // 0.55 ms, 34 TFLOP/s of padded products (6.48 ms with a 256-lane workgroup per
-// (trajectory, j) and every matrix in LDS).
+// (trajectory, j) and every matrix in LDS).  Small sizes too: 256 x 40 steps at
+// nx = 12, nu = 4: 0.31 ms (0.55 ms with whole tiles multiplied and every lane
+// factoring S); at nx = 8, nu = 4: 0.30 ms and at nx = 1: 0.19 ms (0.60 and 0.30 ms
+// with the matrices in LDS on the VALU).
 // Tiles are read through a buffer descriptor of the one matrix: a row past the
 // end is out of its range and reads 0, so a lane needs one offset per tile and one
 // column test instead of an address and a test for every element.
@@ -960,13 +579,10 @@ __global__ void __launch_bounds__(64, 2) sls_riccati_tile_kernel(RiccatiArgs a) 
 template <int TX>
 static void launch_riccati_tile(const RiccatiArgs& a, int batch, hipStream_t st) {
     const dim3 grid((unsigned)batch, (unsigned)a.N);
-    if (a.nu <= 8) hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 8>), grid, dim3(64), 0, st, a);
+    if (a.nu <= 4) hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 4>), grid, dim3(64), 0, st, a);
+    else if (a.nu <= 8) hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 8>), grid, dim3(64), 0, st, a);
     else if (a.nu <= 12) hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 12>), grid, dim3(64), 0, st, a);
     else hipLaunchKernelGGL((sls_riccati_tile_kernel<TX, 16>), grid, dim3(64), 0, st, a);
-}
-
-static size_t riccati_smem(int nx, int nu) {
-    return sizeof(double) * (size_t)(4 * nx * nx + 4 * nx * nu + nu * nu + nx + nu);
 }
 
 // ------------------------------------------------------------ tube rows
@@ -1834,22 +1450,16 @@ static int sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t N, const
     RiccatiArgs a;
     a.A = A; a.B = B; a.qx = qx; a.qu = qu; a.K = K; a.phi = phi;
     a.nx = nx; a.nu = nu; a.N = N; a.zero = zero ? 1 : 0;
-    const dim3 grid((unsigned)N, (unsigned)batch);
-    const size_t sm = riccati_smem(nx, nu);
     hipStream_t st = (hipStream_t)stream;
-    // nx <= 8 and nu <= 4: a 16 x 16 tile would be mostly padding (19 times the work at
-    // nx = 6), so these stay on the VALU; everything else runs on the matrix cores
-    if (nx > 16)
-        launch_riccati_tile<2>(a, batch, st);
-    else if (nu > 4)
-        launch_riccati_tile<1>(a, batch, st);
-    else if (nx > 8)
-        hipLaunchKernelGGL((sls_riccati_mfma_kernel<4>), grid, dim3(64), 0, st, a);
-    else if (nx == 6 && nu == 2)
+    // the planar quadrotor has a kernel with eight lanes a chain (256 x 40: 0.088 ms
+    // against 0.27 ms of the tiles at nx = 7, nu = 3); all else runs on the matrix cores
+    if (nx == 6 && nu == 2)
         hipLaunchKernelGGL((sls_riccati_lane_kernel<6, 2>), dim3((unsigned)((N + 7) / 8), (unsigned)batch), dim3(64),
                            0, st, a);
+    else if (nx > 16)
+        launch_riccati_tile<2>(a, batch, st);
     else
-        hipLaunchKernelGGL((sls_riccati_kernel<4, 2>), grid, dim3(64), sm, st, a);
+        launch_riccati_tile<1>(a, batch, st);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }
 

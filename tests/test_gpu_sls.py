@@ -505,3 +505,48 @@ def test_responses_full_clears_every_entry(gpu, nx, nu, N):
     for a, f in zip(out["leb_sls_responses"], out["leb_sls_responses_full"]):
         assert torch.equal(a[:, late], f[:, late]) and torch.isfinite(f).all()
         assert torch.isnan(a[:, ~late]).all() and (f[:, ~late] == 0).all()
+
+
+def _responses_long(A, B, qx, qu):
+    """Gains and responses in long double, P made symmetric after each step (over
+    40 steps the FP64 oracle's own rounding reaches 1e-3 of a gain)."""
+    A, B, qx, qu = (x.astype(np.longdouble) for x in (A, B, qx, qu))
+    N, nx, nu = B.shape
+    K, phi = np.zeros((N, N, nu, nx), A.dtype), np.zeros((N, N, nx + nu, nx), A.dtype)
+    for j in range(N - 1):
+        P = np.diag(qx[N, j])
+        for k in range(N - 1, j, -1):
+            Bc = B[k].T @ P @ A[k]
+            M = np.concatenate([np.diag(qu[k, j]) + B[k].T @ P @ B[k], -Bc], 1)
+            for p in range(nu):
+                M[p] = M[p] / M[p, p]
+                for r in range(nu):
+                    if r != p:
+                        M[r] = M[r] - M[r, p] * M[p]
+            K[k, j] = M[:, nu:]
+            P = np.diag(qx[k, j]) + A[k].T @ P @ A[k] + K[k, j].T @ Bc
+            P = (P + P.T) / 2
+        X = np.eye(nx, dtype=A.dtype)
+        for k in range(j + 1, N):
+            phi[k, j] = np.concatenate([X, K[k, j] @ X])
+            X = (A[k] + B[k] @ K[k, j]) @ X
+    return K, phi
+
+
+@pytest.mark.parametrize("nx,nu", [(1, 1), (4, 4), (5, 2), (6, 1), (8, 3), (13, 4), (16, 1), (17, 4), (32, 4)])
+def test_responses_few_inputs(gpu, nx, nu):
+    """The tiled Riccati kernel's form for at most four inputs at the edges of its
+    tiles, and a chain of 40 steps whose weights lie 1e4 apart: gains and
+    responses within 1e-9 (the condition, below 1e6, times the rounding)."""
+    import paper_2607_01203_amd as leb
+    print("case: responses few inputs nx=%d nu=%d" % (nx, nu), flush=True)
+    for N, apart in ((3, 1.0), (40, 1e4)):
+        A, B, qx, qu = W.random_ltv(500 + nx + nu, 1, N, nx, nu, scale=0.2)
+        qx[:, :, :, ::3] *= apart
+        K, phi = (_np(t) for t in leb.sls_responses(_t(A, gpu), _t(B, gpu), _t(qx, gpu), _t(qu, gpu)))
+        Ko, Po = _responses_long(A[0], B[0], qx[0], qu[0])
+        for got, want in ((K[0], Ko), (phi[0], Po)):
+            for k in range(N):
+                for j in range(N):
+                    s = max(np.abs(want[k, j]).max(), 1e-300) if k > j else 0.0
+                    assert np.abs(got[k, j] - want[k, j]).max() <= 1e-9 * s, (N, k, j)
