@@ -550,3 +550,23 @@ def test_responses_few_inputs(gpu, nx, nu):
                 for j in range(N):
                     s = max(np.abs(want[k, j]).max(), 1e-300) if k > j else 0.0
                     assert np.abs(got[k, j] - want[k, j]).max() <= 1e-9 * s, (N, k, j)
+
+
+@pytest.mark.parametrize("apart", [1.0, 1e4])
+def test_quadrotor_gains_accuracy(gpu, apart):
+    """The planar quadrotor's Riccati kernel over 40 steps: 99 of 100 gains within 100
+    roundings of the ones in long double, with weights 1e4 apart too (P symmetric after
+    each step: 10 to 20 roundings; its antisymmetric part left to grow: 500 and more)."""
+    import paper_2607_01203_amd as leb
+    print("case: quadrotor gains accuracy apart=%g" % apart, flush=True)
+    b = W.sls_cfg(seed=77, batch=4, N=40)
+    b.qx[:, :, :, ::3] *= apart
+    A, B, _ = leb.linearize(leb.dynamics_like(b.dyn), _t(b.z, gpu), _t(b.v, gpu))
+    K = _np(leb.sls_responses(A, B, _t(b.qx, gpu), _t(b.qu, gpu))[0])
+    A, B = _np(A), _np(B)
+    err = []
+    for i in range(A.shape[0]):
+        Ko = _responses_long(A[i], B[i], b.qx[i], b.qu[i])[0]
+        err += [float(np.linalg.norm((K[i, k, j] - Ko[k, j]).astype(float)) / np.linalg.norm(Ko[k, j].astype(float)))
+                for k in range(1, 40) for j in range(k)]
+    assert np.quantile(err, 0.99) <= 100 * 2.0 ** -53, np.quantile(err, 0.99)
