@@ -62,6 +62,35 @@ int WsFence::leave(hipStream_t s) {
     return LEB_OK;
 }
 
+// this device's bit (0: more devices than bits, the attribute is set on every call)
+static int device_bit(uint64_t* bit) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return LEB_EDEVICE;
+    *bit = dev < 64 ? 1ull << dev : 0ull;
+    return LEB_OK;
+}
+
+int DynLds::raise(const void* kernel, size_t bytes) {
+    uint64_t bit;
+    if (int rc = device_bit(&bit)) return rc;
+    if (set.load(std::memory_order_acquire) & bit) return LEB_OK;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        return LEB_EDEVICE;
+    set.fetch_or(bit, std::memory_order_release);
+    return LEB_OK;
+}
+
+int DynLds::raise_rest(const void* kernel, size_t* bytes) {
+    *bytes = rest.load(std::memory_order_relaxed);
+    if (*bytes == 0) {
+        hipFuncAttributes fa;
+        if (hipFuncGetAttributes(&fa, kernel) != hipSuccess) return LEB_EDEVICE;
+        *bytes = 160 * 1024 - fa.sharedSizeBytes;
+        rest.store(*bytes, std::memory_order_relaxed);
+    }
+    return raise(kernel, *bytes);
+}
+
 }  // namespace leb
 
 using namespace leb;

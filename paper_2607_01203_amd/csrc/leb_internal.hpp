@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "leb.h"
 
 namespace leb {
@@ -127,6 +129,17 @@ struct WsFenceScope {
     WsFence& f;
     hipStream_t s;
     ~WsFenceScope() { (void)f.leave(s); }
+};
+
+// A kernel's limit of dynamic LDS (one object a kernel).  The attribute belongs to the
+// device, so there is a bit for each device that it is set on; calls come from any thread.
+struct DynLds {
+    std::atomic<uint64_t> set{0};
+    std::atomic<size_t> rest{0};                  // 160 KB less the kernel's static part
+    // to `bytes` on the current device
+    int raise(const void* kernel, size_t bytes);
+    // to all that the kernel's static part leaves of a compute unit's 160 KB (*bytes)
+    int raise_rest(const void* kernel, size_t* bytes);
 };
 
 // closed-form test dynamics (LINEAR, QUADRATIC, SINCOS): one thread per unit

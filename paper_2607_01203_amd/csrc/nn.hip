@@ -647,13 +647,8 @@ int nn_bound_run(const leb_mlp_s* net, int64_t units, const double* z, const dou
         const bool groups = nb >= NNG_MIN;
         const int ng = (nb + NNG_BOXES - 1) / NNG_BOXES;
         if (groups) {
-            static bool attr = false;
-            if (!attr) {
-                if (hipFuncSetAttribute((const void*)nn_prep_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)NNG_LDS) != hipSuccess)
-                    return LEB_EDEVICE;
-                attr = true;
-            }
+            static DynLds lds;
+            if ((rc = lds.raise((const void*)nn_prep_group_kernel, NNG_LDS))) return rc;
             hipLaunchKernelGGL(nn_prep_group_kernel, dim3(ng), dim3(NNG_T), NNG_LDS, st, pa);
         } else {
             hipLaunchKernelGGL(nn_prep_kernel, dim3(nb), dim3(256), 0, st, pa);

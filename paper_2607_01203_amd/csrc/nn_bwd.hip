@@ -1341,14 +1341,9 @@ extern "C" int leb_nn_backward(leb_mlp net, int32_t batch, int32_t N, const doub
         if (getenv("LEB_TEST_FAIL_ALLOC") || hipMalloc(&g_nbws.buf, need) != hipSuccess) return LEB_ENOMEM;
         g_nbws.cap = need;
     }
-    static bool attr = false;
-    if (!attr) {
-        if (hipFuncSetAttribute((const void*)nb_box_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)NBG_LDS) != hipSuccess)
-            return LEB_EDEVICE;
-        attr = true;
-    }
     int rc;
+    static DynLds lds;
+    if ((rc = lds.raise((const void*)nb_box_group_kernel, NBG_LDS))) return rc;
     if ((rc = g_nbws.fence.enter(st))) return rc;
     WsFenceScope leave{g_nbws.fence, st};
     a.L = net->L;

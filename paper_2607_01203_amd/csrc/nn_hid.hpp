@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "leb.h"
+#include "leb_internal.hpp"
 #include "nn_net.hpp"
 
 namespace leb {
@@ -854,13 +855,8 @@ __global__ void __launch_bounds__(256, 3) nn_chain_kernel(ChainArgs A) {
 
 template <bool ADJ>
 static int launch_nn_chain(const ChainArgs& c, int nmode, int nact, hipStream_t st) {
-    static bool attr = false;
-    if (!attr) {
-        if (hipFuncSetAttribute((const void*)nn_chain_kernel<ADJ>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)CHAIN_STATE_BYTES) != hipSuccess)
-            return LEB_EDEVICE;
-        attr = true;
-    }
+    static DynLds lds;
+    if (int rc = lds.raise((const void*)nn_chain_kernel<ADJ>, CHAIN_STATE_BYTES)) return rc;
     const unsigned rbs = c.k == 2 ? 1u : (unsigned)((c.M + 15) / 16);
     hipLaunchKernelGGL(nn_chain_kernel<ADJ>, dim3(rbs, nmode, nact), dim3(256), CHAIN_STATE_BYTES, st, c);
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;

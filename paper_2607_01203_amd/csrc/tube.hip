@@ -731,18 +731,11 @@ static int launch_tube(int B, int N, int U, const double* phi, const double* e, 
     // output of 8 steps (mu and sigma, 64 rows x 16 columns)
     const size_t nm1 = N > 1 ? N - 1 : 0;
     const size_t smem = std::max((size_t)(N + 4) * 48 + 8 + 2 * (6 * nm1 + 8) * 16, (size_t)2 * 64 * 16) * sizeof(double);
-    // the kernel may use all 160 KB of LDS, static part included (set once)
-    static size_t dyn_max = 0;
-    if (dyn_max == 0) {
-        hipFuncAttributes fa;
-        if (hipFuncGetAttributes(&fa, (const void*)tube_map_kernel) != hipSuccess) return LEB_EDEVICE;
-        const size_t cap = 160 * 1024 - fa.sharedSizeBytes;
-        if (hipFuncSetAttribute((const void*)tube_map_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cap) !=
-            hipSuccess)
-            return LEB_EDEVICE;
-        dyn_max = cap;
-    }
-    if (smem > dyn_max) return LEB_ENOTSUP;     // N <= 83
+    // the kernel may use all 160 KB of LDS, static part included
+    static DynLds lds;
+    size_t most;
+    if (int rc = lds.raise_rest((const void*)tube_map_kernel, &most)) return rc;
+    if (smem > most) return LEB_ENOTSUP;        // N <= 83
     if (ev0)        // timed: events at the kernel's start and end
         hipExtLaunchKernelGGL(tube_map_kernel, dim3((unsigned)gx, gy), dim3(256), smem, s, ev0, ev1, 0, phi, a);
     else
@@ -793,17 +786,10 @@ static int launch_tube2(int B, int N, int U, const double* phi, const double* e,
         tube_map2_kernel<false, true, 1>,  tube_map2_kernel<false, true, 3>,  tube_map2_kernel<false, true, TM_RT>,
         tube_map2_kernel<true, false, 1>,  tube_map2_kernel<true, false, 3>,  tube_map2_kernel<true, false, TM_RT>,
         tube_map2_kernel<true, true, 1>,   tube_map2_kernel<true, true, 3>,   tube_map2_kernel<true, true, TM_RT>};
-    static size_t dyn_max[12] = {};
-    if (dyn_max[which] == 0) {
-        hipFuncAttributes fa;
-        if (hipFuncGetAttributes(&fa, (const void*)kern[which]) != hipSuccess) return LEB_EDEVICE;
-        const size_t cap = 160 * 1024 - fa.sharedSizeBytes;
-        if (hipFuncSetAttribute((const void*)kern[which], hipFuncAttributeMaxDynamicSharedMemorySize, (int)cap) !=
-            hipSuccess)
-            return LEB_EDEVICE;
-        dyn_max[which] = cap;
-    }
-    if (smem > dyn_max[which]) return LEB_ENOTSUP;
+    static DynLds lds[12];
+    size_t most;
+    if (int rc = lds[which].raise_rest((const void*)kern[which], &most)) return rc;
+    if (smem > most) return LEB_ENOTSUP;
     if (ev0)        // timed: events at the kernel's start and end
         hipExtLaunchKernelGGL(kern[which], dim3((unsigned)gx, gy), dim3(256), smem, s, ev0, ev1, 0, phi, a, fp);
     else

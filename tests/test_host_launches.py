@@ -1,0 +1,66 @@
+"""What the entry points launch, seen from the host: the HIP runtime's place is taken by
+tests/hip_recorder.c in a process of its own, so nothing runs and no GPU is needed."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, os, sys
+import numpy as np
+rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+for f in ("lanes", "groups", "lds"):
+    getattr(rec, "recorder_" + f).restype = ctypes.c_uint64
+rec.recorder_kernel.restype = ctypes.c_char_p
+sys.path.insert(0, os.getcwd())
+import paper_2607_01203_amd as leb
+L = leb.lib()
+P = ctypes.c_void_p(1 << 40)                       # an aligned address; nothing reads it
+def ok(rc):
+    assert rc == 0, rc
+def mlp(widths, nx):
+    return leb.MLP([np.ones((b, a), np.float32) for a, b in zip(widths[:-1], widths[1:])],
+                   [np.zeros(b, np.float32) for b in widths[1:]], nx, False)
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("recorder") / "hip_recorder.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "hip_recorder.c"), "-ldl"],
+                   check=True)
+    return so
+
+
+def _run(recorder, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, recorder], cwd=ROOT, capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_dynamic_lds_limit_on_every_device(recorder):
+    """The limit of dynamic LDS is an attribute of the device: a kernel that uses more than
+    64 KB finds it raised on whichever device is current, not only on the first one."""
+    _run(recorder, """
+dyn = leb.chain_dynamics(1)
+net = mlp([16, 64, 64, 12], 12)
+e = (ctypes.c_double * 6)(*[0.01] * 6)
+opt = leb.FPOptions(1e-6, 2, 0.0, 1e-12, 0, 1e-6)
+n = ctypes.c_int32()
+big = 0
+for d in (0, 1, 0, 2):
+    rec.recorder_device(d)
+    rec.recorder_clear()
+    ok(L.leb_nn_bound(net.handle, 1, 1024, P, P, None, P, None, P, P, None, None, 0.0, None, None))
+    ok(L.leb_nn_backward(net.handle, 1, 1024, P, P, None, P, P, P, P, P, None, P, None))
+    ok(L.leb_tube_map(1, 83, 1, P, e, P, P, P, P, None))
+    ok(L.leb_fixed_point_solve_noalloc(ctypes.byref(dyn), 1, 200, P, P, P, e, ctypes.byref(opt), P, P, P,
+                                       ctypes.byref(n), None))
+    ok(L.leb_sls_fixed_point(ctypes.byref(dyn), 1, 300, P, P, P, 0, None, 0.0, 0.0, P, P, P, P, P, None))
+    big += sum(rec.recorder_lds(i) > 65536 for i in range(rec.recorder_launches()))
+    assert rec.recorder_refused() == 0, (d, rec.recorder_refused())
+assert big >= 4 * 5, big
+""")
