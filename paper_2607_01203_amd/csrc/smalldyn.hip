@@ -634,14 +634,15 @@ __global__ void __launch_bounds__(256, 2) sample_rem_kernel(SampleArgs P, int pa
     double lo[NX], hi[NX];
 #pragma unroll
     for (int l = 0; l < NX; ++l) { lo[l] = 0.0; hi[l] = 0.0; }
-    for (int s = blockIdx.y * blockDim.x + threadIdx.x; s < P.K; s += parts * blockDim.x) {
+    const int64_t stride = (int64_t)parts * blockDim.x;      // (K up to 2^31 - 1: 32 bits would wrap past it)
+    for (int64_t s = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; s < P.K; s += stride) {
         double a[SD_SAMPLE_N], d[NC];
         uint32_t wild = 0;               // coordinates with a non-finite offset
 #pragma unroll
         for (int i = 0; i < SD_SAMPLE_N; ++i) a[i] = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            a[i] = i < n ? ctr[i] + P.t[(int64_t)s * n + i] * sg[i] : 0.0;
+            a[i] = i < n ? ctr[i] + P.t[s * n + i] * sg[i] : 0.0;
             d[i] = a[i] - a0[i];
             wild |= isfinite(d[i]) ? 0u : 1u << i;
         }
@@ -791,7 +792,7 @@ extern "C" int leb_sample_remainder(const leb_dynamics* dyn, int32_t batch, int3
     P.t = t; P.K = K; P.s_lo = s_lo; P.s_hi = s_hi;
     // parts a unit: about four workgroups a compute unit in all (1,024), at least one
     // sample a thread; one part needs no clearing and no atomics
-    const int64_t most = (K + 255) / 256;
+    const int64_t most = ((int64_t)K + 255) / 256;
     const int64_t want = units >= 512 ? 1 : 1024 / units;
     const int parts = (int)(most < 1 ? 1 : (want < most ? want : most));
     hipStream_t st = (hipStream_t)stream;

@@ -210,3 +210,24 @@ def test_small_units_of_a_wave(gpu, orc, name, units, mode):
     olo, ohi, ofl = orc.leb(orc.Dyn.like(b.dyn), b.z, b.v, b.sigma, mode=mode)
     check_bounds(lo, hi, olo, ohi, "%s %s" % (name, mode))
     assert (fl == ofl.astype(np.int32)).all()
+
+
+def test_sampled_remainder_most_samples(gpu):
+    """As many samples as the call takes (2^31 - 1, 17 GB): the last one counts, and
+    the strides of a unit's workgroups end there."""
+    import torch
+    import paper_2607_01203_amd as leb
+    print("case: sampled remainder, 2^31 - 1 samples", flush=True)
+    if torch.cuda.mem_get_info(gpu)[0] < 24 << 30:
+        pytest.skip("less than 24 GB free")
+    dyn = leb.sincos_dynamics(1)
+    z, sg = _t(np.full((1, 1, 1), 0.7), gpu), _t(np.full((1, 1, 1), 0.3), gpu)
+    v = z.new_empty((1, 1, 0))
+    t = torch.zeros((2 ** 31 - 1, 1), dtype=torch.float64, device=gpu)
+    t[-1] = 1.0
+    lo, hi = leb.sample_remainder(dyn, z, v, sg, t)
+    one_lo, one_hi = leb.sample_remainder(dyn, z, v, sg, t[-1:].contiguous())
+    torch.cuda.synchronize()
+    assert torch.equal(lo, one_lo) and torch.equal(hi, one_hi) and float(lo) < -0.02
+    del t
+    torch.cuda.empty_cache()
