@@ -369,76 +369,88 @@ __global__ void __launch_bounds__(256) small_poly_kernel(SmallArgs A, int G) {
     if (active && lane_row == 0 && A.flags) A.flags[u] = f;
 }
 
-// SINCOS, SATELLITE and QUAD3D: a wave bounds one row of four units, lane (unit, c)
-// one Hessian entry of the row (at most nine), so the row's entries run side by side
-// and the rows of a unit on different waves; the row's trigonometric enclosures are
-// computed one a lane and shared through LDS.  CLASSIC sums v = [H]
-// Delta per coordinate: lane i of the unit's sixteen collects the entries that touch
-// coordinate i.  Latency bounds it (a serial chain of interval operations, one
-// wave a row): PATH, EXPAND, CLASSIC of one local set of the 3-D quadrotor: 9.3, 9.7
-// and 11 us (one thread per row, its entries one after the other and the rows of a
-// unit diverging within a wave: 24, 22 and 30 us).
-template <int MODE>
+// SINCOS, SATELLITE and QUAD3D: a wave bounds one row of 64 / G units, lane (unit, c)
+// one Hessian entry of the row, so the row's entries run side by side and the rows of a
+// unit on different waves; the 3-D quadrotor's trigonometric enclosures are computed one a
+// lane and shared through LDS.  CLASSIC sums v = [H] Delta per coordinate: lane c of the
+// unit's G collects the entries that touch coordinates c, c + G, ...
+//
+// G is the most entries that a row of the system has, up to a power of two: 16 for the 3-D
+// quadrotor (9), 4 for the satellite and SINCOS in two dimensions (3), 1 for SINCOS in
+// one.  What bounds it is latency up to some thousand units (a serial chain of interval
+// operations, one wave a row: PATH, EXPAND, CLASSIC of one local set of the 3-D quadrotor
+// 9.3, 9.7 and 11 us, one thread per row and its entries one after the other 24, 22 and
+// 30 us), then the instructions issued, of which lanes without an entry take their share.
+// Many units, PATH, whole call: satellite x 400,000 107 us (one thread per row 190, 16 lanes
+// a row 354), SINCOS x 1,000,000 in two dimensions 189 us (277, 725), in one 21 us (47, 224),
+// 3-D quadrotor x 400,000 1,080 us (1,190 and the same 1,080).
+template <int MODE, int KIND, int G>
 __global__ void __launch_bounds__(256) small_entry_kernel(SmallArgs A) {
+    constexpr bool Q3 = KIND == LEB_DYN_QUAD3D;
+    // (not a changed copy of A: J is indexed, and a copy would lie in scratch)
+    __builtin_assume(A.kind == KIND);
     __shared__ div_ s_v[4][64][2];           // CLASSIC: entry c's contributions to v_k and v_j
     __shared__ signed char s_kj[4][64][2];
-    __shared__ Q3Cache s_q3[4][4];
+    __shared__ Q3Cache s_q3[4][Q3 ? 64 / G : 1];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t wid = (int64_t)blockIdx.x * 4 + wave;
     const int64_t ug = wid / A.nx;
-    const int l = (int)(wid - ug * A.nx), c = lane & 15;
-    const int64_t u = 4 * ug + (lane >> 4);
+    const int l = (int)(wid - ug * A.nx), c = lane & (G - 1), first = lane & ~(G - 1);
+    const int64_t u = (64 / G) * ug + lane / G;
     const bool active = u < A.units;
     const int n = A.nx + A.nu, full = n - 1;          // X^(n-1) = X
-    Q3Cache& C = s_q3[wave][lane >> 4];
-    const uint64_t group = 0xffffull << (lane & 48);
-    // the unit's flags, one coordinate a lane
-    uint32_t mine = active && c < n ? sd_input_flags(A, u, c) : 0u;
+    Q3Cache& C = s_q3[wave][Q3 ? lane / G : 0];
+    const uint64_t group = ((1ull << G) - 1ull) << first;
+    // the unit's flags, the coordinates shared out over its lanes
+    uint32_t mine = 0u;
+    if (active)
+        for (int i = c; i < n; i += G) mine |= sd_input_flags(A, u, i);
     const bool bad = (__ballot(mine & LEB_FLAG_BAD_INPUT) & group) != 0;
     const bool hull = (__ballot(mine & LEB_FLAG_HULL_EXTENDED) & group) != 0;
     div_ acc{0.0, 0.0};
     bool unb = false, any = false;
     int k = 0, j = 0;
     const bool entry = active && !bad && sd_candidate(A, l, c, &k, &j);
-    if (A.kind == LEB_DYN_QUAD3D && active && !bad && (l == 0 || (l >= 3 && l <= 8))) q3_cache(A, u, c, C);
-    wave_lds_fence();
-    if (active && !bad) {
-        if (entry) {
-            Entry e;
-            unb = sd_entry(A, u, l, k, j, MODE == LEB_IH_PATH ? j : full, C, e) < 0;     // prefix of the smaller index
-            const fiv dk = sd_disp(A, u, k), dj = sd_disp(A, u, j);
-            if (MODE == LEB_IH_CLASSIC) {
-                // v = [H] Delta over the symmetric matrix: row k gets H Delta_j, row j gets H Delta_k
-                div_ vk{0.0, 0.0}, vj{0.0, 0.0};
-                if (!unb && !sd_zero(dj)) { sd_acc(vk, e, 1.0, dj); any = true; }
-                if (!unb && k != j && !sd_zero(dk)) { sd_acc(vj, e, 1.0, dk); any = true; }
-                s_v[wave][lane][0] = vk;
-                s_v[wave][lane][1] = vj;
-            } else if (!unb && !sd_zero(dk) && !sd_zero(dj)) {
-                if (j < k) sd_acc(acc, e, 1.0, mul_zz(dj, dk));
-                else sd_acc(acc, e, 0.5, sq_z(dk));
-                any = true;
-            }
+    if (Q3) {
+        if (active && !bad && (l == 0 || (l >= 3 && l <= 8))) q3_cache(A, u, c, C);
+        wave_lds_fence();
+    }
+    if (entry) {
+        Entry e;
+        unb = sd_entry(A, u, l, k, j, MODE == LEB_IH_PATH ? j : full, C, e) < 0;     // prefix of the smaller index
+        const fiv dk = sd_disp(A, u, k), dj = sd_disp(A, u, j);
+        if (MODE == LEB_IH_CLASSIC) {
+            // v = [H] Delta over the symmetric matrix: row k gets H Delta_j, row j gets H Delta_k
+            div_ vk{0.0, 0.0}, vj{0.0, 0.0};
+            if (!unb && !sd_zero(dj)) { sd_acc(vk, e, 1.0, dj); any = true; }
+            if (!unb && k != j && !sd_zero(dk)) { sd_acc(vj, e, 1.0, dk); any = true; }
+            s_v[wave][lane][0] = vk;
+            s_v[wave][lane][1] = vj;
+        } else if (!unb && !sd_zero(dk) && !sd_zero(dj)) {
+            if (j < k) sd_acc(acc, e, 1.0, mul_zz(dj, dk));
+            else sd_acc(acc, e, 0.5, sq_z(dk));
+            any = true;
         }
     }
     if (MODE == LEB_IH_CLASSIC) {
         s_kj[wave][lane][0] = entry ? (signed char)k : (signed char)-1;
         s_kj[wave][lane][1] = entry && k != j ? (signed char)j : (signed char)-1;
         wave_lds_fence();
-        if (active && !bad && c < n) {
-            div_ v{0.0, 0.0};
-            for (int q = 0; q < SD_MAX_CAND; ++q) {
-                const int o = (lane & 48) + q;
+        if (active && !bad)
+            for (int i = c; i < n; i += G) {
+                div_ v{0.0, 0.0};
+                for (int q = 0; q < (G < SD_MAX_CAND ? G : SD_MAX_CAND); ++q) {
+                    const int o = first + q;
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (s_kj[wave][o][h] == c) { v.lo += s_v[wave][o][h].lo; v.hi += s_v[wave][o][h].hi; }
+                    for (int h = 0; h < 2; ++h)
+                        if (s_kj[wave][o][h] == i) { v.lo += s_v[wave][o][h].lo; v.hi += s_v[wave][o][h].hi; }
+                }
+                sd_classic(sd_disp(A, u, i), v, acc);
             }
-            sd_classic(sd_disp(A, u, c), v, acc);
-        }
     }
-    // sums over the sixteen lanes of the unit (every lane takes part)
+    // sums over the lanes of the unit (every lane takes part)
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
+    for (int off = 1; off < G; off <<= 1) {
         acc.lo += __shfl_xor(acc.lo, off);
         acc.hi += __shfl_xor(acc.hi, off);
     }
@@ -448,11 +460,21 @@ __global__ void __launch_bounds__(256) small_entry_kernel(SmallArgs A) {
         // row 0's wave reports the unit: only the 3-D quadrotor's attitude rows can be
         // unbounded, where cos(theta) over the widest theta they see is not positive
         uint32_t f = (bad ? LEB_FLAG_BAD_INPUT : 0u) | (hull ? LEB_FLAG_HULL_EXTENDED : 0u);
-        if (!bad && A.kind == LEB_DYN_QUAD3D &&
-            (!(C.th[1].c.lo > 0.0f) || (MODE == LEB_IH_PATH && !(C.th[0].c.lo > 0.0f))))
+        if (Q3 && !bad && (!(C.th[1].c.lo > 0.0f) || (MODE == LEB_IH_PATH && !(C.th[0].c.lo > 0.0f))))
             f |= LEB_FLAG_UNBOUNDED;
         A.flags[u] = f;
     }
+}
+
+template <int KIND, int G>
+static int launch_small_entry(int mode, const SmallArgs& A, hipStream_t s) {
+    const int64_t blocks = ((A.units + 64 / G - 1) / (64 / G) * A.nx + 3) / 4;      // a wave per row of 64 / G units
+    if (blocks > 0x7fffffff) return LEB_EINVAL;
+    const dim3 g((unsigned)blocks), b(256);
+    if (mode == LEB_IH_PATH) hipLaunchKernelGGL((small_entry_kernel<LEB_IH_PATH, KIND, G>), g, b, 0, s, A);
+    else if (mode == LEB_IH_EXPAND) hipLaunchKernelGGL((small_entry_kernel<LEB_IH_EXPAND, KIND, G>), g, b, 0, s, A);
+    else hipLaunchKernelGGL((small_entry_kernel<LEB_IH_CLASSIC, KIND, G>), g, b, 0, s, A);
+    return LEB_OK;
 }
 
 // --------------------------------------------------- sampled remainder
@@ -733,12 +755,11 @@ int launch_small_dyn(const leb_dynamics* dyn, int mode, int64_t units, const dou
         else if (mode == LEB_IH_EXPAND) hipLaunchKernelGGL(small_poly_kernel<LEB_IH_EXPAND>, g, b, 0, s, A, G);
         else hipLaunchKernelGGL(small_poly_kernel<LEB_IH_CLASSIC>, g, b, 0, s, A, G);
     } else {
-        const int64_t blocks = ((units + 3) / 4 * dyn->nx + 3) / 4;      // a wave per row of four units
-        if (blocks > 0x7fffffff) return LEB_EINVAL;
-        const dim3 g((unsigned)blocks);
-        if (mode == LEB_IH_PATH) hipLaunchKernelGGL(small_entry_kernel<LEB_IH_PATH>, g, b, 0, s, A);
-        else if (mode == LEB_IH_EXPAND) hipLaunchKernelGGL(small_entry_kernel<LEB_IH_EXPAND>, g, b, 0, s, A);
-        else hipLaunchKernelGGL(small_entry_kernel<LEB_IH_CLASSIC>, g, b, 0, s, A);
+        const int rc = dyn->kind == LEB_DYN_QUAD3D      ? launch_small_entry<LEB_DYN_QUAD3D, 16>(mode, A, s)
+                       : dyn->kind == LEB_DYN_SATELLITE ? launch_small_entry<LEB_DYN_SATELLITE, 4>(mode, A, s)
+                       : dyn->nx == 2                   ? launch_small_entry<LEB_DYN_SINCOS, 4>(mode, A, s)
+                                                        : launch_small_entry<LEB_DYN_SINCOS, 1>(mode, A, s);
+        if (rc) return rc;
     }
     return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
 }

@@ -231,3 +231,34 @@ def test_sampled_remainder_most_samples(gpu):
     assert torch.equal(lo, one_lo) and torch.equal(hi, one_hi) and float(lo) < -0.02
     del t
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("name", ["satellite", "quad3d", "sincos1", "sincos2"])
+def test_small_groups_of_units(gpu, name, mode):
+    """A unit's bound and flags do not depend on the units beside it in a wave (64, 16 or 4
+    of them), at whole waves, at ragged ends and next to a unit with bad input: bit for bit
+    what a call with the unit alone gives."""
+    import torch
+    import paper_2607_01203_amd as leb
+    print("case: small groups of units %s %s" % (name, mode), flush=True)
+    rng = np.random.default_rng(61)
+    if name.startswith("sincos"):
+        n = int(name[-1])
+        dyn = leb.sincos_dynamics(n)
+        z, v = rng.uniform(-3.0, 3.0, (65, n)), np.zeros((65, 0))
+        mu, sg = rng.uniform(-0.1, 0.1, (65, n)), rng.uniform(0.01, 0.3, (65, n))
+    else:
+        b = W.small_batch(_sys(name), 62, 65, 0.1)
+        dyn = leb.dynamics_like(b.dyn)
+        z, v, sg = (x.reshape(65, -1).copy() for x in (b.z, b.v, b.sigma))
+        mu = rng.uniform(-0.15, 0.15, sg.shape)
+    sg[5, -1], z[64, 0] = -1.0, np.nan
+    sg[7] = 0.0
+    call = lambda s: [x[0] for x in leb.interval_hessian_bound(
+        dyn, *(_t(a[None, s], gpu) for a in (z, v, sg, mu)), mode=mode)]
+    alone = [torch.cat(x) for x in zip(*(call(slice(i, i + 1)) for i in range(65)))]
+    assert (alone[2][[5, 64]] & leb.FLAG_BAD_INPUT).all() and torch.isinf(alone[0][[5, 64]]).all()
+    for units in (3, 16, 17, 64, 65):
+        for got, want in zip(call(slice(0, units)), alone):
+            assert torch.equal(got, want[:units]), units

@@ -64,3 +64,21 @@ for d in (0, 1, 0, 2):
     assert rec.recorder_refused() == 0, (d, rec.recorder_refused())
 assert big >= 4 * 5, big
 """)
+
+
+def test_small_systems_lanes_per_row(recorder):
+    """A row of a small system takes about as many lanes as it has Hessian entries (9, 3, 3
+    and 1 of the 3-D quadrotor, the satellite and the two sine systems), whatever the form:
+    lanes without an entry are what a large batch would wait for."""
+    _run(recorder, """
+J3 = (1.0, 2.0, 3.0)
+for dyn, G in ((leb.quad3d_dynamics(0.05, 1.0, 9.81, J3), 16), (leb.satellite_dynamics(0.1), 4),
+               (leb.sincos_dynamics(2), 4), (leb.sincos_dynamics(1), 1)):
+    for mode in (0, 1, 2):
+        for units in (1, 1000, 1000003):
+            rec.recorder_clear()
+            ok(L.leb_interval_hessian_bound(ctypes.byref(dyn), mode, 1, units, P, P, P, P, P, P, P, None))
+            assert rec.recorder_launches() == 1
+            lanes = rec.recorder_lanes(0)
+            assert units * dyn.nx <= lanes <= (units + 64 // G) * dyn.nx * G + 256, (dyn.kind, units, lanes)
+""")
