@@ -1199,13 +1199,18 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_fp_row_kernel(FpRowArgs a, in
 //              added up per row, the block Phi_{k+1,k} to LDS
 // with one LDS barrier after each.
 //
+// FOLD: the stream's places are dealt to two waves, each thread takes several one after the
+// other (the same sums in the same order, bit for bit) and nothing is read ahead.  With its
+// 160 VGPRs a compute unit holds twelve waves: three workgroups of four instead of one of
+// seven (nx = 12) or eight, or two of six.
+//
 // What bounds it: 40 dependent steps, each the latency of A, of the slowest of B
 // (the bound at small nx, the stream of the row at nx = 30: up to 374 KB a step for
 // one compute unit) and of C.  256 x 40 steps at nx = 6: 0.095 ms (rows, bound and
 // disturbance error one after the other: 0.224 ms); at nx = 12 0.197 ms (0.378 ms);
 // 64 x 40 at nx = 30 0.303 ms (1.33 ms).
 constexpr int SLS_FP_PF = 8;             // blocks of the next row read one step ahead
-constexpr int SLS_FP_MAX_THREADS = 768;
+constexpr int SLS_FP_MAX_THREADS = 768, SLS_FOLD_THREADS = 256;
 
 struct FpChainArgs {
     const double* phi; const double* E; const double* sigE;
@@ -1221,11 +1226,12 @@ struct FpChainArgs {
     int compact;
 };
 
+template <bool FOLD>
 __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChainArgs a) {
     const int b = blockIdx.x;
     const int U = a.U, nx = 6 * U, nu = a.nu, n = nx + nu, N = a.N, nw = a.nw;
     extern __shared__ double sm[];
-    const int nst = a.npos * a.slots;
+    const int nst = a.npos * a.slots;            // places in the row stream
     double* mo = sm;                    // n
     double* so = mo + n;                // n
     double* rl = so + n;                // nx
@@ -1304,11 +1310,17 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
             lds_barrier();
         }
     } else {
-        // this thread's place in the row stream
-        const int st = tid - 128, hx = nx >> 1;
+        // this thread's place in the row stream (FOLD: its first one)
+        const int st = tid - 128, lanes = bs - 128, hx = nx >> 1, per = hx * a.slots;
         const bool streams = st < nst;
-        const int pos = streams ? st % a.npos : 0, slot = streams ? st / a.npos : 0, l2 = 2 * (pos % hx);
-        const int per = hx * a.slots, mine = (pos / hx) * per + slot * hx + pos % hx;   // partial sums, row by row
+        int pos, slot, l2, mine;
+        auto place = [&](int q) {
+            pos = q % a.npos;
+            slot = q / a.npos;
+            l2 = 2 * (pos % hx);
+            mine = (pos / hx) * per + slot * hx + pos % hx;                      // partial sums, row by row
+        };
+        place(streams ? st : 0);
         auto load = [&](int k, int j) {          // entries 2 pos, 2 pos + 1 of Phi_{k,j}
             return *reinterpret_cast<const sls_p2*>(phib + ((size_t)k * N + j) * n * nx + 2 * pos);
         };
@@ -1317,17 +1329,17 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
         for (int q = 0; q < SLS_FP_PF; ++q) pf[q] = sls_p2{0.0, 0.0};
         for (int k = 0; k < N; ++k) {
             // A: row k (four lanes a row)
-            if (st < 4 * n) {
-                const int i = st >> 2, q = st & 3;
+            auto row_k = [&](int w) {
+                const int i = w >> 2, q = w & 3;
                 double m = 0.0, s = 0.0, g = 0.0;
                 if (k > 0) {
                     const double* cb = cbl + (size_t)(k - 1) * nx;
                     const double* rb = rbl + (size_t)(k - 1) * nx;
                     for (int l = q; l < nx; l += 4) {
-                        const double r = blk[i * nx + l], ap = fabs(r), c = cb[l], w = rb[l];
+                        const double r = blk[i * nx + l], ap = fabs(r), c = cb[l], h = rb[l];
                         m = fma(r, c, m);
-                        s = fma(ap, w, s);
-                        g = fma(ap, fabs(c) + w, g);
+                        s = fma(ap, h, s);
+                        g = fma(ap, fabs(c) + h, g);
                     }
                 }
                 m = sum4(m);
@@ -1351,12 +1363,16 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
                     a.sigma[(b0 + k) * n + i] = s;
                     if (!isfinite(s)) s_flag[1] = 0u;
                 }
+            };
+            if constexpr (FOLD) {
+                for (int w = st; w < 4 * n; w += lanes) row_k(w);
+            } else if (st < 4 * n) {
+                row_k(st);
             }
             lds_barrier();
             // B: the next row over the residuals known before this step
             if (streams && k + 1 < N) {
-                if (slot == 0) nb = load(k + 1, k);
-                double m = 0.0, s = 0.0, g = 0.0;
+                double m, s, g;
                 auto add = [&](int j, sls_p2 r) {
                     const double* cb = cbl + (size_t)j * nx + l2;
                     const double* rb = rbl + (size_t)j * nx + l2;
@@ -1368,33 +1384,52 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
                         g = fma(ap, fabs(cb[e]) + rb[e], g);
                     }
                 };
-                int j = slot;
+                auto rest = [&](int j) {         // blocks j, j + slots, ... below k
+                    for (; j < k; j += SLS_FP_PF * a.slots) {
+                        sls_p2 r[SLS_FP_PF];
 #pragma unroll
-                for (int q = 0; q < SLS_FP_PF; ++q, j += a.slots)
-                    if (j < k) add(j, pf[q]);
-                for (; j < k; j += SLS_FP_PF * a.slots) {
-                    sls_p2 r[SLS_FP_PF];
+                        for (int q = 0; q < SLS_FP_PF; ++q) r[q] = load(k + 1, min(j + q * a.slots, k - 1));
 #pragma unroll
-                    for (int q = 0; q < SLS_FP_PF; ++q) r[q] = load(k + 1, min(j + q * a.slots, k - 1));
+                        for (int q = 0; q < SLS_FP_PF; ++q)
+                            if (j + q * a.slots < k) add(j + q * a.slots, r[q]);
+                    }
+                };
+                auto put = [&]() {
+                    part[mine] = m;
+                    part[nst + mine] = s;
+                    part[2 * nst + mine] = g;
+                };
+                if constexpr (FOLD) {
+                    for (int q = st; q < nst; q += lanes) {
+                        place(q);
+                        if (slot == 0) nb = load(k + 1, k);
+                        m = s = g = 0.0;
+                        rest(slot);
+                        put();
+                        if (slot == 0) { blk[2 * pos] = nb[0]; blk[2 * pos + 1] = nb[1]; }   // (A has read the last one)
+                    }
+                } else {
+                    if (slot == 0) nb = load(k + 1, k);
+                    m = s = g = 0.0;
+                    int j = slot;
 #pragma unroll
-                    for (int q = 0; q < SLS_FP_PF; ++q)
-                        if (j + q * a.slots < k) add(j + q * a.slots, r[q]);
+                    for (int q = 0; q < SLS_FP_PF; ++q, j += a.slots)
+                        if (j < k) add(j, pf[q]);
+                    rest(j);
+                    if (k + 2 < N) {
+#pragma unroll
+                        for (int q = 0; q < SLS_FP_PF; ++q) pf[q] = load(k + 2, min(slot + q * a.slots, k));
+                    }
+                    put();
                 }
-                if (k + 2 < N) {
-#pragma unroll
-                    for (int q = 0; q < SLS_FP_PF; ++q) pf[q] = load(k + 2, min(slot + q * a.slots, k));
-                }
-                part[mine] = m;
-                part[nst + mine] = s;
-                part[2 * nst + mine] = g;
             }
             lds_barrier();
             // C: eight lanes a row over its nx / 2 positions in every slot
             if (k + 1 < N) {
-                if (st < 8 * n) {
-                    const int i = st >> 3;
+                auto row_sums = [&](int w) {
+                    const int i = w >> 3;
                     double m = 0.0, s = 0.0, g = 0.0;
-                    for (int q = i * per + (st & 7); q < (i + 1) * per; q += 8) {
+                    for (int q = i * per + (w & 7); q < (i + 1) * per; q += 8) {
                         m += part[q];
                         s += part[nst + q];
                         g += part[2 * nst + q];
@@ -1402,9 +1437,14 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
                     m = sum8(m);
                     s = sum8(s);
                     g = sum8(g);
-                    if ((st & 7) == 0) { base[i] = m; base[n + i] = s; base[2 * n + i] = g; }
+                    if ((w & 7) == 0) { base[i] = m; base[n + i] = s; base[2 * n + i] = g; }
+                };
+                if constexpr (FOLD) {
+                    for (int w = st; w < 8 * n; w += lanes) row_sums(w);
+                } else if (st < 8 * n) {
+                    row_sums(st);
                 }
-                if (streams && slot == 0) { blk[2 * pos] = nb[0]; blk[2 * pos + 1] = nb[1]; }
+                if (!FOLD && streams && slot == 0) { blk[2 * pos] = nb[0]; blk[2 * pos + 1] = nb[1]; }
             }
             lds_barrier();
         }
@@ -1419,13 +1459,25 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
 // workgroups share a compute unit (256 / 1,024 trajectories of 40 steps: 95 / 194 us;
 // with five stream waves 101 / 396 us).  Larger blocks need the five waves to keep a
 // row's reads in flight (nx = 12: 197 us, with two waves 226 us); at least one slot.
-static size_t fp_chain_plan(int nx, int nu, int U, int N, int* npos, int* slots, int* threads) {
+// Fold: batches of more than a workgroup a compute unit, while a step's stream is short
+// enough for two waves (positions of a block times N; the longer, the more the reads ahead
+// matter).  No disturbance, us, unfolded and folded, in brackets a workgroup that took its
+// phases one after the other:
+//   nx = 12   512 x 40   552  498 (527)      nx = 18   2,048 x 25   1,763  1,478 (1,789)
+//             512 x 64 1,124 1,173 (1,160)             8,192 x 10   2,082  1,216 (1,516)
+//           2,048 x 40 2,162 1,668 (1,794)             1,024 x 40   2,061  2,037 (2,338)
+//           2,048 x 64 4,439 4,067 (4,110)   nx = 24   8,192 x 10   2,544  1,864 (2,209)
+//           8,192 x 10 1,747   863 (1,051)             2,048 x 30   3,394  3,369 (-)
+//             512 x 80 1,454 1,591 (1,548)   nx = 30   8,192 x 10   3,511  3,235 (3,983)
+static size_t fp_chain_plan(int nx, int nu, int U, int N, int batch, int* npos, int* slots, int* threads, bool* fold) {
     const int n = nx + nu;
     *npos = n * nx / 2;
     *slots = max(1, (*npos <= 24 ? 128 : 320) / *npos);
     const int stream = max(*npos * *slots, 8 * n);
     *threads = 128 + 64 * ((stream + 63) / 64);
     if (*threads > SLS_FP_MAX_THREADS) return 0;
+    *fold = batch > 256 && *npos * N <= (batch > 1024 ? 7680 : 5376) && *threads > SLS_FOLD_THREADS;
+    if (*fold) *threads = SLS_FOLD_THREADS;
     const size_t bytes = sizeof(double) * ((size_t)5 * n + 3 * nx + (size_t)N * (3 * nx + nu + n + 2 * U) + n * nx +
                                            (size_t)3 * *npos * *slots) +
                          sizeof(SpringOut) * U + 2 * sizeof(uint32_t);
@@ -1604,7 +1656,8 @@ extern "C" int leb_sls_fixed_point(const leb_dynamics* dyn, int32_t batch, int32
     a.U = chain ? dyn->n_units : 0;
     // chains whose trajectory data fits in LDS: the whole causal pass in one launch
     int npos = 0, slots = 0, threads = 0;
-    const size_t lds = chain ? fp_chain_plan(nx, nu, dyn->n_units, N, &npos, &slots, &threads) : 0;
+    bool fold = false;
+    const size_t lds = chain ? fp_chain_plan(nx, nu, dyn->n_units, N, batch, &npos, &slots, &threads, &fold) : 0;
     if (lds > 0) {
         FpChainArgs c = {};
         c.phi = phi; c.E = E; c.sigE = sigE; c.z = z; c.v = v;
@@ -1613,10 +1666,11 @@ extern "C" int leb_sls_fixed_point(const leb_dynamics* dyn, int32_t batch, int32
         c.nu = nu; c.nw = nw; c.N = N; c.npos = npos; c.slots = slots;
         c.U = dyn->n_units;
         c.c = dyn->dt / dyn->m; c.kL = dyn->k_spring * dyn->rest_len; c.L0 = dyn->rest_len; c.pad = pad;
-        if (hipFuncSetAttribute((const void*)sls_fp_chain_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)SLS_LDS_MAX) != hipSuccess)
+        const auto kern = fold ? sls_fp_chain_kernel<true> : sls_fp_chain_kernel<false>;
+        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SLS_LDS_MAX) !=
+            hipSuccess)
             return LEB_EDEVICE;
-        hipLaunchKernelGGL(sls_fp_chain_kernel, dim3((unsigned)batch), dim3((unsigned)threads), lds, s, c);
+        hipLaunchKernelGGL(kern, dim3((unsigned)batch), dim3((unsigned)threads), lds, s, c);
         return hipGetLastError() == hipSuccess ? LEB_OK : LEB_EDEVICE;
     }
     // otherwise one row launch and one bound launch per step

@@ -570,3 +570,27 @@ def test_quadrotor_gains_accuracy(gpu, apart):
         err += [float(np.linalg.norm((K[i, k, j] - Ko[k, j]).astype(float)) / np.linalg.norm(Ko[k, j].astype(float)))
                 for k in range(1, 40) for j in range(k)]
     assert np.quantile(err, 0.99) <= 100 * 2.0 ** -53, np.quantile(err, 0.99)
+
+
+@pytest.mark.parametrize("n_units,N", [(2, 1), (2, 2), (2, 11), (2, 40), (3, 13), (4, 9), (5, 8)])
+def test_causal_pass_large_batch_same_bits(gpu, n_units, N):
+    """The causal pass of a large batch (two stream waves, several places of the row stream a
+    thread) gives every trajectory the bits that a batch of one to a compute unit gives it,
+    with and without disturbance columns, tubes that blow up among them."""
+    import torch
+    import paper_2607_01203_amd as leb
+    print("case: causal pass large batch n_units=%d N=%d" % (n_units, N), flush=True)
+    b = W.sls_cfg(seed=91, batch=300, N=N, n_units=n_units)
+    b.z[7, 0, 0] = np.nan
+    b.qu[11] *= 1e6
+    dyn = leb.dynamics_like(b.dyn)
+    z, v = _t(b.z, gpu), _t(b.v, gpu)
+    A, Bm, E = leb.linearize(dyn, z, v, list(b.e), b.thrust)
+    K, phi = leb.sls_responses(A, Bm, _t(b.qx, gpu), _t(b.qu, gpu))
+    for e, thrust, pad in ((E, b.thrust, 1e-6), (None, 0.0, 1e-3)):
+        cut = lambda x, s: None if x is None else x[s].contiguous()
+        call = lambda s: leb.sls_fixed_point(dyn, cut(z, s), cut(v, s), cut(phi, s), cut(e, s), thrust=thrust, pad=pad)
+        large = call(slice(0, 300))
+        for s in (slice(0, 150), slice(150, 300)):
+            for got, want in zip(large, call(s)):
+                assert torch.equal(torch.nan_to_num(got[s].double(), nan=1e99), torch.nan_to_num(want.double(), nan=1e99))

@@ -82,3 +82,20 @@ for dyn, G in ((leb.quad3d_dynamics(0.05, 1.0, 9.81, J3), 16), (leb.satellite_dy
             lanes = rec.recorder_lanes(0)
             assert units * dyn.nx <= lanes <= (units + 64 // G) * dyn.nx * G + 256, (dyn.kind, units, lanes)
 """)
+
+
+def test_causal_pass_workgroups_of_large_batches(recorder):
+    """The one-launch causal pass of a batch that fills the chip more than once: workgroups
+    of four waves while the horizon is short, so that three share a compute unit; the wide
+    ones up to one a compute unit."""
+    _run(recorder, """
+for U in (2, 3, 4, 5):
+    dyn = leb.chain_dynamics(U)
+    for batch, narrow in ((1, False), (256, False), (257, True), (8192, True)):
+        rec.recorder_clear()
+        ok(L.leb_sls_fixed_point(ctypes.byref(dyn), batch, 8, P, P, P, 0, None, 0.0, 0.0, P, P, P, P, P, None))
+        i = rec.recorder_launches() - 1
+        assert b"sls_fp_chain" in rec.recorder_kernel(i)
+        lanes = rec.recorder_lanes(i) // rec.recorder_groups(i)
+        assert rec.recorder_groups(i) == batch and (lanes <= 256) == narrow, (U, batch, lanes)
+""")
