@@ -1030,12 +1030,19 @@ static void launch_tube(const TubeRowArgs& a, int batch, double* out_sig, hipStr
 // FP64 interval sine and cosine of [lo, hi] from the library values at its ends
 // (sa, sb = sin lo, sin hi; ca, cb = cos lo, cos hi): widened by 2^-40 relative
 // plus 2^-100 absolute, +-1 where a critical point may lie inside (tested
-// against an outward pi) and everywhere for wide or far-out intervals.
+// against an outward pi) and everywhere for wide or far-out intervals, whose library
+// values are not needed (far out they cost several times as much).
+constexpr double SLS_PI_LO = 3.141592653589793115997963468544185161590576171875;
+
+__device__ __forceinline__ bool sls_wide(double lo, double hi) {
+    return !(hi - lo < 2.0 * SLS_PI_LO) || fabs(lo) > 1024.0 || fabs(hi) > 1024.0;
+}
+
 __device__ void sls_sincos(double lo, double hi, double sa, double sb, double ca, double cb, double* sl, double* sh,
                            double* cl, double* ch) {
-    const double PI_LO = 3.141592653589793115997963468544185161590576171875;
+    const double PI_LO = SLS_PI_LO;
     const double PI_HI = 3.141592653589793560087173318606801331043243408203125;
-    if (!(hi - lo < 2.0 * PI_LO) || fabs(lo) > 1024.0 || fabs(hi) > 1024.0) {
+    if (sls_wide(lo, hi)) {
         *sl = -1.0; *sh = 1.0; *cl = -1.0; *ch = 1.0;
         return;
     }
@@ -1085,7 +1092,12 @@ __device__ double thrust_rdist_row(int l, double zt, double mut, double sgt, dou
     if (comp != 3 && comp != 4) return 0.0;
     double lo, hi;
     thrust_theta(zt, mut, sgt, &lo, &hi);
-    return thrust_rdist(comp, lo, hi, sin(lo), sin(hi), cos(lo), cos(hi), e0, c);
+    double sa = 0.0, sb = 0.0, ca = 0.0, cb = 0.0;
+    if (!sls_wide(lo, hi)) {
+        sincos(lo, &sa, &ca);
+        sincos(hi, &sb, &cb);
+    }
+    return thrust_rdist(comp, lo, hi, sa, sb, ca, cb, e0, c);
 }
 
 struct EDiag { double e[SLS_MAX_NX]; };
@@ -1299,9 +1311,9 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
         for (int k = 0; k < N; ++k) {
             lds_barrier();
             if (mine) {
-                double lo, hi, sx, cx;
+                double lo, hi, sx = 0.0, cx = 0.0;
                 thrust_theta(zl[(size_t)k * nx + th], mo[th], so[th], &lo, &hi);
-                sincos(e ? hi : lo, &sx, &cx);
+                if (!sls_wide(lo, hi)) sincos(e ? hi : lo, &sx, &cx);
                 const double sy = __shfl_xor(sx, 1), cy = __shfl_xor(cx, 1);
                 rd[6 * u + 3 + e] = thrust_rdist(3 + e, lo, hi, e ? sy : sx, e ? sx : sy, e ? cy : cx, e ? cx : cy,
                                                  eth[((size_t)k * U + u) * 2 + e], a.thrust_c);

@@ -594,3 +594,26 @@ def test_causal_pass_large_batch_same_bits(gpu, n_units, N):
         for s in (slice(0, 150), slice(150, 300)):
             for got, want in zip(large, call(s)):
                 assert torch.equal(torch.nan_to_num(got[s].double(), nan=1e99), torch.nan_to_num(want.double(), nan=1e99))
+
+
+def test_thrust_error_of_far_out_attitudes(gpu):
+    """Thrust disturbance error where theta lies beyond what the sine's enclosure takes from
+    the library (|theta| > 1024): the whole range of the column, c + |e|; just inside it, the
+    rounding of the two ends only; the same from the one-launch pass and step by step."""
+    import paper_2607_01203_amd as leb
+    print("case: thrust error of far-out attitudes", flush=True)
+    dyn = leb.chain_dynamics(1)
+    c = 0.2 * dyn.dt / dyn.m
+    theta = np.array([1000.0, -1023.0, 1025.0, -2e5, 1e300, 1.0])
+    for N in (1, 680):                                   # 680 steps do not fit the one-launch pass
+        z = np.zeros((6, N, 6))
+        z[:, :, 2] = theta[:, None]
+        z = _t(z, gpu)
+        v = _t(np.full((6, N, 2), 4.9), gpu)
+        E = leb.linearize(dyn, z, v, [0.0] * 6, 0.2)[2]
+        phi = z.new_zeros((6, N, N, 8, 6))
+        _, _, lo, hi, _ = leb.sls_fixed_point(dyn, z, v, phi, E, thrust=0.2)
+        lo, hi, e = _np(lo)[:, :, 3:5], _np(hi)[:, :, 3:5], np.abs(_np(E)[:, :, 3:5, 6])
+        far = np.abs(theta) > 1024.0
+        assert (np.abs(hi - (c + e))[far] <= 1e-12 * c).all() and (np.abs(lo + (c + e))[far] <= 1e-12 * c).all()
+        assert (hi[~far] >= 0.0).all() and (hi[~far] <= 1e-9 * c).all() and (lo[~far] >= -1e-9 * c).all()
