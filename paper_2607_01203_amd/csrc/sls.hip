@@ -1359,10 +1359,10 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
                 g = sum4(g);
                 if (q == 0) {
                     if (k > 1) { m += base[i]; s += base[n + i]; g += base[2 * n + i]; }
-                    // rounding of the sums: at most nx + k (nw + 1) + 72 additions deep, each
-                    // within 2^-53 of the magnitudes g; doubled for the centre's error and the
-                    // final additions
-                    const double coef = (double)(nx + k * (nw + 1) + 72) * 0x1p-52;
+                    // rounding of the sums: at most 2 k + nx + 72 additions deep (two entries a
+                    // block in the stream, one block a slot at least), each within 2^-53 of the
+                    // magnitudes g; doubled for the centre's error and the final additions
+                    const double coef = (double)(nx + k * max(nw + 1, 2) + 72) * 0x1p-52;
                     s = s + coef * g * (1.0 + 0x1p-50) + 0x1p-1000;
                     const double se = sel[(size_t)k * n + i];
                     s = s + se;

@@ -617,3 +617,22 @@ def test_thrust_error_of_far_out_attitudes(gpu):
         far = np.abs(theta) > 1024.0
         assert (np.abs(hi - (c + e))[far] <= 1e-12 * c).all() and (np.abs(lo + (c + e))[far] <= 1e-12 * c).all()
         assert (hi[~far] >= 0.0).all() and (hi[~far] <= 1e-9 * c).all() and (lo[~far] >= -1e-9 * c).all()
+
+
+def test_causal_pass_rounding_allowance(gpu):
+    """Without disturbance columns the tube's allowance covers the depth of the causal pass's
+    sums, two additions for each earlier step, at 2^-52 of the magnitudes each: row px of a
+    chain that sums up radii of 1, for 200 steps of three nodes."""
+    import paper_2607_01203_amd as leb
+    print("case: causal pass rounding allowance", flush=True)
+    dyn = leb.chain_dynamics(3, k_spring=0.0, rest_len=1e5)
+    N = 200
+    z = _t(np.zeros((1, N, 18)), gpu)
+    v = _t(np.zeros((1, N, 6)), gpu)
+    phi = z.new_zeros((1, N, N, 24, 18))
+    phi[:, :, :, 0, 0] = 1.0
+    _, sg, _, _, cert = leb.sls_fixed_point(dyn, z, v, phi, None, pad=1.0)
+    assert int(cert[0]) == 1
+    k = np.arange(1, N)
+    over = (_np(sg)[0, 1:, 0] - k) / k * 2.0 ** 52
+    assert (over >= 2 * (k - 1) + 9).all() and (over <= 4 * k + 200).all(), over[-1]
