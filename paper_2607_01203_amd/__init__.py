@@ -253,7 +253,11 @@ def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    try:
+        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    except AttributeError:              # not part of torch's public interface
+        return torch.cuda.current_stream().cuda_stream
+    return raw(device())
 
 
 def analytic_bound(dyn: Dynamics, z, v, sigma, mu=None, pad: float = 0.0, zonotope: bool = False,

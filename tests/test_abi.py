@@ -285,3 +285,16 @@ def test_sls_entry_points_reject_bad_arguments_without_launching(L):
     assert L.leb_linearize(ctypes.byref(d), 1, 4, vp, vp, None, 0.1, vp, vp, vp, None) == -1        # E without e
     assert L.leb_linearize(ctypes.byref(d), 1, 4, vp, vp, None, -1.0, vp, vp, None, None) == -1
     assert L.leb_linearize(ctypes.byref(sat), 1, 4, vp, vp, None, 0.0, vp, vp, None, None) == -4
+
+
+def test_current_stream_without_the_raw_query(monkeypatch):
+    """The raw stream query is no public part of torch: without it the current stream's
+    object gives the handle."""
+    import types
+
+    import torch
+    import paper_2607_01203_amd as leb
+    monkeypatch.setattr(torch, "_C", types.SimpleNamespace())
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert leb._stream(None) == 77
+    assert leb._stream(types.SimpleNamespace(cuda_stream=5)) == 5
