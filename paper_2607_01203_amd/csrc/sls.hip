@@ -91,22 +91,24 @@ __device__ void riccati_zero(const RiccatiArgs& a, int b, int j, int cnt) {
 // A_k and B_k (read as broadcasts from LDS, stored there one step ahead).
 // P is symmetric, so P A = (A^T P)^T: the step's only exchanges between lanes are
 // that transpose, the 2 x NX rows of B^T P, the gain and P's own transpose (LDS, padded
-// strides).  As in the tiled kernel below, P is made symmetric after each step: 99th
-// percentile of the gains' relative error against long double, 40 steps of the hover
-// workload, 1.4e-15, with weights 1e4 apart 2.1e-15 (P as it comes: 4.2e-14 and 4.8e-12).
+// strides).  As in the tiled kernel below, P is made symmetric, here after every second step:
+// 99th percentile of the gains' relative error against long double, 40 steps of the hover
+// workload, 1.4e-15, with weights 1e4 apart 2.4e-15 (after each step 1.4e-15 and 2.1e-15
+// at 7 us more; after every eighth 1.9e-15 and 1.9e-14; P as it comes 4.2e-14 and 4.8e-12).
 // The 2 x 2 system is solved as L D L^T; its pivots are the squares of the
 // Cholesky pivots and are tested the same way.
 //
 // What bounds it: the serial chain of a wave, 2 (N - j - 1) dependent steps; at
 // 256 trajectories a compute unit holds five waves.  Eight lanes per chain keep
 // one step's products (about 190 FMA) inside the latency that its exchanges cost
-// anyway.  256 x 40 steps at nx = 6: 0.091 ms (0.088 without the mean of P; one 64-lane workgroup per chain with
-// the matrices in LDS: 0.280 ms); 1,024 x 40: 0.25 ms (0.857 ms).
+// anyway.  256 x 40 steps at nx = 6: 0.089 ms (0.085 without the means of P; one 64-lane
+// workgroup per chain with the matrices in LDS: 0.280 ms); 1,024 x 40: 0.24 ms (0.857 ms).
 template <int NX, int NU>
 __global__ void __launch_bounds__(64) sls_riccati_lane_kernel(RiccatiArgs a) {
     static_assert(NX <= 8 && NU == 2, "eight lanes per chain, 2 x 2 gain system");
     constexpr int n = NX + NU, AB = NX * n;                    // A_k and B_k of one step
     constexpr int ST = NX * NX + 2, SN = NU * NX + 2;          // strides of a chain's blocks in LDS
+    constexpr int SYM = 2;                                     // steps from one mean of P to the next
     const int b = blockIdx.y, N = a.N;
     const int lane = threadIdx.x, ch = lane >> 3, c = lane & 7;
     const int j0 = 8 * blockIdx.x, j = min(j0 + ch, N - 1);   // j = N - 1 has no steps
@@ -217,12 +219,16 @@ __global__ void __launch_bounds__(64) sls_riccati_lane_kernel(RiccatiArgs a) {
             for (int l = 0; l < NX; ++l) s = fma(A[l * NX + r], PA[l], s);
             s = fma(sN[ch * SN + r], Bc[0], s);
             P[r] = fma(sN[ch * SN + NX + r], Bc[1], s);
-            if (own) sT[ch * ST + c * NX + r] = P[r];
         }
-        lds_barrier();
-        // the mean with the transpose (element (c, r) is in lane r's column)
+        if ((k & (SYM - 1)) == 0) {
+            // the mean with the transpose (element (c, r) is in lane r's column)
 #pragma unroll
-        for (int r = 0; r < NX; ++r) P[r] = 0.5 * (P[r] + sT[ch * ST + r * NX + cc]);
+            for (int r = 0; r < NX; ++r)
+                if (own) sT[ch * ST + c * NX + r] = P[r];
+            lds_barrier();
+#pragma unroll
+            for (int r = 0; r < NX; ++r) P[r] = 0.5 * (P[r] + sT[ch * ST + r * NX + cc]);
+        }
     }
     // forward: U = K X, X' = A X + B U from Phi^x_{j+1,j} = I.  The gains were stored
     // by this wave, and the full barrier orders those stores before the loads
