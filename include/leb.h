@@ -125,8 +125,8 @@ typedef struct {
  *            entry is written.
  * Kinds: CHAIN (nodes in one workgroup, FP32 outward intervals, FP64
  * accumulation); LINEAR ([0, 0] for valid data); QUADRATIC and SINCOS,
- * closed-form test dynamics, SATELLITE and QUAD3D (one thread per unit, the
- * same arithmetic; QUADRATIC reads Q through dyn->coeffs).  Invalid data (non-finite nominal, mu or sigma, negative
+ * closed-form test dynamics, SATELLITE and QUAD3D (the same arithmetic;
+ * QUADRATIC reads Q through dyn->coeffs).  Invalid data (non-finite nominal, mu or sigma, negative
  * sigma) gives [-inf, +inf] on every row of the unit and LEB_FLAG_BAD_INPUT
  * for every kind; z and sigma (and v when nu > 0) are required for every kind.
  * Returns LEB_OK or a negative leb_status.
@@ -164,8 +164,9 @@ int leb_interval_hessian_bound(const leb_dynamics* dyn, int32_t mode, int32_t ba
  *   t              DEVICE [K][nx+nu], shared by every unit
  *   s_lo, s_hi     [batch][N][nx] outputs
  * Kinds QUADRATIC, SINCOS, SATELLITE, QUAD3D with nx + nu <= 16 (else
- * LEB_ENOTSUP).  One workgroup per unit; the result is an estimate from
- * inside, not a bound.
+ * LEB_ENOTSUP).  The samples of a unit are shared by one workgroup or, for few
+ * units, several; the result does not depend on their number.  It is an estimate
+ * from inside, not a bound.
  */
 int leb_sample_remainder(const leb_dynamics* dyn, int32_t batch, int32_t N, const double* z, const double* v,
                          const double* mu, const double* sigma, int32_t K, const double* t, double* s_lo,
@@ -214,8 +215,10 @@ int leb_backward(const leb_dynamics* dyn, int32_t batch, int32_t N, const double
  *   z, v           outputs: the narrowest iterate seen (the start included)
  *   width [batch][N] output: its W; width0 [batch][N] optional: W(a0)
  * LEB_EINVAL for fixed_box not 0/1, radius outside [0, 1], lr not positive
- * and finite, steps < 0.  Uses a library-owned grow-only workspace, ordered
- * across streams like the other workspaces.
+ * and finite, steps < 0.  Few timesteps (up to 256 floor(64 / n_units), chains of up
+ * to 64 nodes) take one launch without a workspace; the others use a
+ * library-owned grow-only workspace, ordered across streams like the other
+ * workspaces.
  */
 int leb_pgd_nominal(const leb_dynamics* dyn, int32_t batch, int32_t N, const double* z0, const double* v0,
                     const double* mu0, const double* sigma, int32_t fixed_box, double radius, int32_t steps,
@@ -630,13 +633,14 @@ int leb_linearize(const leb_dynamics* dyn, int32_t batch, int32_t N, const doubl
  * leb_sls_responses -- closed-loop responses of the reformulated SLS problem
  * (eq. fastsls_qp_reform) by the parallel Riccati recursions (appendix on
  * solving for Phi, eqs. backward_prop and forward_prop, with the start
- * Phi^x_{j+1,j} = I of eq. fastsls_qp_cost_reform_init), one workgroup per
+ * Phi^x_{j+1,j} = I of eq. fastsls_qp_cost_reform_init), independently for every
  * (trajectory, disturbance time j):
  *   A [batch][N][nx][nx], B [batch][N][nx][nu]   the LTV pairs (A_k, B_k)
  *   qx [batch][N+1][N][nx], qu [batch][N][N][nu] diagonal weights Q^x_{k,j},
  *       Q^u_{k,j} (Q^{ux} = 0; box constraints make Q^T Q of eq.
- *       sls_cost_matrices_tau diagonal); qu > 0 and qx >= 0 make every
- *       Cholesky pivot positive, otherwise that (trajectory, j) gets NaN gains
+ *       sls_cost_matrices_tau diagonal); qu > 0 and qx >= 0 make every pivot
+ *       of the elimination of S_{k,j} (the squares of its Cholesky pivots)
+ *       positive, otherwise that (trajectory, j) gets NaN gains
  *   K [batch][N][N][nu][nx]     out: gains K_{k,j} for j < k < N
  *   phi [batch][N][N][nx+nu][nx] out: Phi_{k,j} = [Phi^x_{k,j}; Phi^u_{k,j}]
  *       for j < k < N (rows 0..nx-1 state, nx.. input responses)

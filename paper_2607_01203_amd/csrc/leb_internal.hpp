@@ -142,7 +142,7 @@ struct DynLds {
     int raise_rest(const void* kernel, size_t* bytes);
 };
 
-// closed-form test dynamics (LINEAR, QUADRATIC, SINCOS): one thread per unit
+// small systems (LINEAR, QUADRATIC, SINCOS, SATELLITE, QUAD3D) in one of the three forms
 int launch_small_dyn(const leb_dynamics* dyn, int mode, int64_t units, const double* z, const double* v,
                      const double* mu, const double* sigma, double* r_lo, double* r_hi, double* c_bar,
                      double* rho_bar, double pad, uint32_t* flags, hipStream_t s);

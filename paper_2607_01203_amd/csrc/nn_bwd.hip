@@ -919,7 +919,8 @@ __global__ void __launch_bounds__(NB_T) __attribute__((amdgpu_waves_per_eu(2))) 
 //
 // What bounds it: the latency of the operand reads (the levels' rows from memory, the
 // weights from L2) between short runs of MFMA (about 100 us of them at k = 3 and at
-// k = 4), two waves a SIMD.  3,200 boxes of 16-256-256-256-12, k = 2, 3, 4: 69, 590,
+// k = 4), two waves a SIMD (k = 4: 256 registers, one spilled).  3,200 boxes of
+// 16-256-256-256-12, k = 2, 3, 4: 69, 590,
 // 385 us (one direction at a time through LDS with barriers at each level: 390, 1,126,
 // 678; one direction a workgroup and three waves a SIMD: 99, 899, 568; the next rows and
 // the next tile read ahead: 80, 590-680, 395).

@@ -78,8 +78,8 @@ __device__ __forceinline__ TileRef tile_ref(const PbhTile& p) {
 // tube there does not (C_{t-1} = C_{t-2} up to step t - 3, as the tube at a step uses
 // earlier steps only), and those of the last step are never used: sweep t bounds the steps
 // t - 2 .. N - 2 and leaves the other residuals as they are.  28 nodes x 256 x 40: 21.8 us
-// in the first sweeps, 18.2 from 1,024 workgroups (four a compute unit) down, the fixed
-// point 440 us (every step in every sweep: 22.6 and 474 us).
+// in the first sweeps, 18.2 from 1,024 workgroups (four a compute unit) down; with every
+// step in every sweep 22.6, and the fixed point 34 us longer.
 enum { PBH_UNITS = 0, PBH_TILES = 1, PBH_SWEEP = 2 };
 template <int FORM>
 __global__ void __launch_bounds__(PBH_BLOCK) pbh_chain_fwd(ChainArgs A) {

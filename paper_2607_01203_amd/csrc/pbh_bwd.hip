@@ -355,9 +355,9 @@ __device__ __forceinline__ bool bwd_core(const BwdConsts& K, BwdShared<SPLIT>& H
 // SPLIT = true (launches that leave the chip idle): five waves over the same up
 // to 64 lanes, each wave runs phases 1 and 2 for itself and then one pass.
 //
-// What bounds it: VALU issue (about 11,000 instructions a lane, most of them in phase
-// 3) at two waves a SIMD when the chip is full, the serial chain of one lane
-// otherwise.  28 nodes, 256 x 40 steps: 103 us (337 us with ten one-direction passes
+// What bounds it: VALU issue (10,500 instructions a wave, most of them in phase
+// 3) at two waves a SIMD when the chip is full (256 registers, 24 of them spilled), the
+// serial chain of one lane otherwise.  28 nodes, 256 x 40 steps: 102 us (337 us with ten one-direction passes
 // over every term, whose hoisted values took 430 registers, one wave a SIMD, and
 // with adjoints addressed through scratch); 1 x 40: 15 us (55 us).
 template <bool SPLIT>
@@ -403,9 +403,9 @@ __global__ void __launch_bounds__(SPLIT ? 64 * BWD_TASKS : BWD_BLOCK, SPLIT ? 1 
 // steps.  Waves 0 .. 4: the adjoint (upstream -1 on the lower, +1 on the upper ends), the
 // first also the move; wave 5: the bound at the same iterate, for its width.
 //
-// What bounds it: the serial chain of the adjoint, 19 us an iteration.  28 nodes, 40
-// timesteps, 10 steps: 209 us (a launch each for the bound, the adjoint and the move:
-// 300 us).
+// What bounds it: the serial chain of the adjoint, 19 us an iteration (256 registers, 25
+// spilled).  28 nodes, 40 timesteps, 10 steps: 209 us (a launch each for the bound, the
+// adjoint and the move: 300 us).
 constexpr int PGD_WAVES = BWD_TASKS + 1;
 
 struct PgdChainArgs {

@@ -113,7 +113,8 @@ struct SpringKeep {
 // Spring i (nodes i, i+1); writes *out and returns whether the spring is unbounded through
 // k.unb.  Every lane evaluates it (the last node of a chain against itself) and a lane
 // without a spring drops the result: branches around it cost more in register moves
-// than they save (28 nodes, 2,560 x 40: 133 us, with the branches 136).  springs: the
+// than they save (28 nodes, 2,560 x 40, whole call: 135 us, with the branches 141; where
+// every spring is unbounded the branches would save 0.5 us of a launch).  springs: the
 // chain has any.
 __device__ __forceinline__ void spring_step(const NodeConsts& K, const NodeIn& d, bool springs, bool right, SpringKeep& k,
                                             SpringOut* out) {

@@ -52,7 +52,6 @@ constexpr int SLS_MAX_NX = 32;
 constexpr int SLS_MAX_NU = 16;
 constexpr int SLS_MAX_NW = 64;
 constexpr int SLS_THREADS = 256;
-constexpr int SLS_PF = 8;                      // prefetch registers per thread (nx^2 + 2 nx nu <= 8 threads)
 constexpr size_t SLS_ROW_LDS = 48 * 1024;      // LDS budget of a tube-row workgroup
 constexpr size_t SLS_LDS_MAX = 160 * 1024;     // LDS of the one-launch fixed point (a compute unit's)
 
@@ -318,7 +317,7 @@ typedef double sls_d4 __attribute__((ext_vector_type(4)));
 // nx = 30, nu = 10 a backward and a forward step issue 184 MFMA (64 cycles
 // each); the first launched waves are the longest chains (j = 0 of every
 // trajectory), so the short ones fill the end of the launch.  64 x 40 steps:
-// 0.55 ms, 34 TFLOP/s of padded products (6.48 ms with a 256-lane workgroup per
+// 0.61 ms, 29 TFLOP/s of padded products (6.48 ms with a 256-lane workgroup per
 // (trajectory, j) and every matrix in LDS).  Small sizes too: 256 x 40 steps at
 // nx = 12, nu = 4: 0.31 ms (0.55 ms with whole tiles multiplied and every lane
 // factoring S); at nx = 8, nu = 4: 0.30 ms and at nx = 1: 0.19 ms (0.60 and 0.30 ms
@@ -814,8 +813,8 @@ __device__ __forceinline__ double element_at(__amdgpu_buffer_rsrc_t M, int C, in
 // What bounds it: the padded products (72 MFMA a block at nx = 30: 94 us for 64 x 40
 // steps) with the address and masking work beside them, and reading Phi (479 MB
 // there: 98 us).  The fragments of the next group of states are read during this
-// group's products.  64 x 40 at nx = 30: 0.25 ms (VALU rows: 1.24 ms), at nx = 18
-// 0.091 ms (0.305 ms); 256 x 40 at nx = 12: 0.117 ms (0.120 ms with |Phi| |E| as a
+// group's products.  64 x 40 at nx = 30: 0.27 ms (VALU rows: 1.24 ms), at nx = 18
+// 0.09 ms (0.305 ms); 256 x 40 at nx = 12: 0.097 ms (3 us more with |Phi| |E| as a
 // second MFMA product).  Several rows k a workgroup, to share E_j, was slower
 // (0.28 and 0.33 ms with two and four rows at nx = 30).
 template <int RT, int CT>
@@ -944,7 +943,10 @@ static void launch_tube_e_mfma(const TubeRowArgs& a, int batch, double* out_sig,
 //
 // What bounds it: reading Phi (77 MB at 256 x 40: 16 us) and one wave's walk over
 // up to 39 blocks.  256 x 40: 0.036 ms (a workgroup per row k, two barriers a chunk
-// and the sums over its slots through LDS: 0.047 ms); 1,024 x 40: 0.125 ms (0.173 ms).
+// and the sums over its slots through LDS: 0.047 ms); 1,024 x 40: 0.108 ms (0.173 ms).
+// At other horizons, the whole fixed point with it and with a workgroup per row: 256 x 10
+// 41 and 41, 256 x 20 69 and 71, 256 x 80 305 and 341, 1,024 x 20 136 and 162 us; few long
+// trajectories leave it too few waves: 64 x 150 699 and 663, 16 x 300 2,107 and 1,942.
 template <int NX, int NU>
 __global__ void __launch_bounds__(320) sls_tube_e_lane_kernel(TubeRowArgs a, double* out_sig) {
     constexpr int n = NX + NU, NW = 8, KW = 40, CH = 40, JU = 4;   // k a workgroup, staged j, j read ahead
@@ -1224,9 +1226,9 @@ __global__ void __launch_bounds__(SLS_THREADS) sls_fp_row_kernel(FpRowArgs a, in
 //
 // What bounds it: 40 dependent steps, each the latency of A, of the slowest of B
 // (the bound at small nx, the stream of the row at nx = 30: up to 374 KB a step for
-// one compute unit) and of C.  256 x 40 steps at nx = 6: 0.095 ms (rows, bound and
-// disturbance error one after the other: 0.224 ms); at nx = 12 0.197 ms (0.378 ms);
-// 64 x 40 at nx = 30 0.303 ms (1.33 ms).
+// one compute unit) and of C.  256 x 40 steps at nx = 6: 0.092 ms (rows, bound and
+// disturbance error one after the other: 0.224 ms); at nx = 12 0.195 ms (0.378 ms);
+// 64 x 40 at nx = 30 0.300 ms (1.33 ms).
 constexpr int SLS_FP_PF = 8;             // blocks of the next row read one step ahead
 constexpr int SLS_FP_MAX_THREADS = 768, SLS_FOLD_THREADS = 256;
 
@@ -1475,7 +1477,9 @@ __global__ void __launch_bounds__(SLS_FP_MAX_THREADS) sls_fp_chain_kernel(FpChai
 // Slots: blocks side by side in the row stream.  At nx = 6 (24 positions a block) two
 // stream waves hold five, so that the blocks read ahead cover 40 steps and two
 // workgroups share a compute unit (256 / 1,024 trajectories of 40 steps: 95 / 194 us;
-// with five stream waves 101 / 396 us).  Larger blocks need the five waves to keep a
+// with five stream waves 101 / 396 us); at 20 steps the number does not matter (256: 61
+// us, with five waves 64), beyond the steps read ahead five waves are faster for few
+// trajectories (256 x 80 270 and 248, 64 x 150 605 and 436 us).  Larger blocks need the five waves to keep a
 // row's reads in flight (nx = 12: 197 us, with two waves 226 us); at least one slot.
 // Fold: batches of more than a workgroup a compute unit, while a step's stream is short
 // enough for two waves (positions of a block times N; the longer, the more the reads ahead
@@ -1529,8 +1533,9 @@ static int sls_responses(int32_t nx, int32_t nu, int32_t batch, int32_t N, const
     a.A = A; a.B = B; a.qx = qx; a.qu = qu; a.K = K; a.phi = phi;
     a.nx = nx; a.nu = nu; a.N = N; a.zero = zero ? 1 : 0;
     hipStream_t st = (hipStream_t)stream;
-    // the planar quadrotor has a kernel with eight lanes a chain (256 x 40: 0.088 ms
-    // against 0.27 ms of the tiles at nx = 7, nu = 3); all else runs on the matrix cores
+    // the planar quadrotor has a kernel with eight lanes a chain (whole calls, new buffers: 1 x 40
+    // steps 59 us, 256 x 40 89, 1,024 x 40 354; on the tiles 86, 244 and 964); all else runs
+    // on the matrix cores
     if (nx == 6 && nu == 2)
         hipLaunchKernelGGL((sls_riccati_lane_kernel<6, 2>), dim3((unsigned)((N + 7) / 8), (unsigned)batch), dim3(64),
                            0, st, a);

@@ -355,7 +355,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))
     // order it is needed: Phi (columns 3, 4 and the per-lag affine sums), the
     // residual rows of the first 64 steps, the tube C_{t-1}.  Phi and the
     // residuals wait only for themselves; the tube is used after the contraction.
-    const int nsp = (N + 4) * 16, ng = nst * 8;
+    const int ng = nst * 8;
     const double* ph = nst > 0 ? phi : kZero8;         // no Phi for a single step
     // Phi rows t = 8 lag + r (six columns) two per thread and pass: columns
     // 3, 4 go to sp, the others into the per-lag affine sums g
@@ -748,12 +748,14 @@ static int launch_tube(int B, int N, int U, const double* phi, const double* e, 
 // Row tiles a wave takes (RT): with one workgroup for all rows of 16 node columns a
 // small grid leaves compute units idle, with more every workgroup stages Phi and the
 // residuals again.  28 nodes, 40 steps, the whole fixed point (11 sweeps):
-//   batch        1    32    64   128   200   256   512
-//   RT = 1     183   228   278   387   500   564   972 us
-//   RT = 3     195   235   267   348   435   519   856
-//   RT = 5     224   269   300   352   443   488   793
+//   batch        1    32    64   128   180   200   220   256   512
+//   RT = 1     164   214   250   346   444   460   475   500   840 us
+//   RT = 3     180   220   240   308   375   389   425   452   737
+//   RT = 5     212   255   272   312   392   401   409   431   698
 // One tile a wave up to about one workgroup per compute unit, three up to 384 column
-// groups (219 trajectories of 28 nodes).
+// groups (219 trajectories of 28 nodes).  The same at 20 steps (64 trajectories 124, 129,
+// 131; 128: 143, 139, 141; 512: 289, 256, 269) and with 5 nodes (64: 178, 192, 223; 256:
+// 215, 218, 250; 1,024: 416, 380, 402; 2,000: 656, 579, 558).
 constexpr int TM2_GRID_1 = 320, TM2_GRID_3 = 384;
 
 static int launch_tube2(int B, int N, int U, const double* phi, const double* e, double pad, const double* c2,
@@ -939,7 +941,8 @@ int fp_check_args(const leb_fp_options* opt, const double* e, int N) {
     for (int q = 0; q < 6; ++q)
         if (!(e[q] >= 0.0) || !isfinite(e[q])) return LEB_EINVAL;
     // the compact tube map keeps Phi's two residual columns, the affine sums and
-    // the residuals of all steps of 16 node columns in LDS: 448 N + 990 bytes
+    // the residuals of all steps of 16 node columns in LDS: about 456 N + 1,000 bytes
+    // (97 KB at 210 steps)
     if (N > FP_MAX_N) return LEB_ENOTSUP;
     return LEB_OK;
 }

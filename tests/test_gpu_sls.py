@@ -636,3 +636,27 @@ def test_causal_pass_rounding_allowance(gpu):
     k = np.arange(1, N)
     over = (_np(sg)[0, 1:, 0] - k) / k * 2.0 ** 52
     assert (over >= 2 * (k - 1) + 9).all() and (over <= 4 * k + 200).all(), over[-1]
+
+
+@pytest.mark.parametrize("nx,nu", [(6, 2), (5, 4), (9, 8), (16, 12), (16, 16), (17, 4), (20, 7), (30, 12), (32, 16)])
+def test_responses_full_in_every_form(gpu, nx, nu):
+    """Each form of the Riccati recursions (the quadrotor's lanes; one and two tiles of states
+    with up to 4, 8, 12 and 16 inputs): the responses of long double where k > j, zeros
+    elsewhere, in arrays that held something else."""
+    import ctypes
+    import torch
+    import paper_2607_01203_amd as leb
+    print("case: responses full in every form nx=%d nu=%d" % (nx, nu), flush=True)
+    N = 7
+    A, B, qx, qu = W.random_ltv(700 + nx + nu, 2, N, nx, nu, scale=0.2)
+    t = [_t(x, gpu) for x in (A, B, qx, qu)]
+    K = torch.full((2, N, N, nu, nx), float("nan"), dtype=torch.float64, device=gpu)
+    phi = torch.full((2, N, N, nx + nu, nx), float("nan"), dtype=torch.float64, device=gpu)
+    vp = lambda x: ctypes.c_void_p(x.data_ptr())
+    leb._check(leb.lib().leb_sls_responses_full(nx, nu, 2, N, *(vp(x) for x in t), vp(K), vp(phi), None))
+    for i in range(2):
+        for got, want in zip((_np(K)[i], _np(phi)[i]), _responses_long(A[i], B[i], qx[i], qu[i])):
+            for k in range(N):
+                for j in range(N):
+                    s = max(np.abs(want[k, j]).max(), 1e-300) if k > j else 0.0
+                    assert np.abs(got[k, j] - want[k, j]).max() <= 1e-9 * s, (i, k, j)
