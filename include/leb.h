@@ -216,7 +216,7 @@ int leb_backward(const leb_dynamics* dyn, int32_t batch, int32_t N, const double
  *   width [batch][N] output: its W; width0 [batch][N] optional: W(a0)
  * LEB_EINVAL for fixed_box not 0/1, radius outside [0, 1], lr not positive
  * and finite, steps < 0.  Few timesteps (up to 256 floor(64 / n_units), chains of up
- * to 64 nodes) take one launch without a workspace; the others use a
+ * to 64 nodes, up to 4,096 steps) take one launch without a workspace; the others use a
  * library-owned grow-only workspace, ordered across streams like the other
  * workspaces.
  */

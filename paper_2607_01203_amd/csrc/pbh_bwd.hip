@@ -552,12 +552,16 @@ int launch_pbh_bwd(const leb_dynamics* dyn, int64_t units, const double* z, cons
 
 // The fused descent while every workgroup has a compute unit of its own (28 nodes, 10 steps,
 // whole call: 40 timesteps 211 us and 309 by launches, 480 timesteps 218 and 320; from
-// then on the workgroups would take turns); *done = false: not that case, nothing launched.
+// then on the workgroups would take turns) and the launch stays below 0.1 s (19 us a step: a
+// longer one would hold the device, and could not be ended); *done = false: not that case,
+// nothing launched.
+constexpr int PGD_FUSED_STEPS = 4096;
+
 int launch_pgd_chain(const leb_dynamics* dyn, int64_t units, const double* z0, const double* v0, const double* mu0,
                      const double* sigma, int fixed_box, double radius, int steps, double lr, double* z, double* v,
                      double* width, double* width0, hipStream_t stream, bool* done) {
     const int U = dyn->n_units, T = U <= 64 ? 64 / U : 0;
-    *done = T > 0 && (units + T - 1) / T <= BWD_SPLIT_BLOCKS;
+    *done = T > 0 && (units + T - 1) / T <= BWD_SPLIT_BLOCKS && steps <= PGD_FUSED_STEPS;
     if (!*done) return LEB_OK;
     PgdChainArgs a;
     a.z0 = z0; a.v0 = v0; a.mu0 = mu0; a.sigma = sigma;

@@ -12,7 +12,7 @@
 
 typedef struct { uint32_t x, y, z; } dim3_;
 
-enum { MAX_LAUNCHES = 4096, MAX_KERNELS = 256, MAX_DEVICES = 8, DEFAULT_LDS = 65536 };
+enum { MAX_LAUNCHES = 1 << 16, MAX_KERNELS = 256, MAX_DEVICES = 8, DEFAULT_LDS = 65536 };
 static struct { const void* f; uint64_t groups, lanes; uint32_t gx, gy, gz; size_t lds; } launches[MAX_LAUNCHES];
 static struct { const void* f; size_t lds[MAX_DEVICES]; } limits[MAX_KERNELS];
 static int n_launches, n_limits, device, refused;

@@ -99,3 +99,15 @@ for U in (2, 3, 4, 5):
         lanes = rec.recorder_lanes(i) // rec.recorder_groups(i)
         assert rec.recorder_groups(i) == batch and (lanes <= 256) == narrow, (U, batch, lanes)
 """)
+
+
+def test_descent_of_many_steps_in_many_launches(recorder):
+    """The descent of few timesteps is one launch while that launch is short; a call of any
+    number of steps does not hold the device in one."""
+    _run(recorder, """
+dyn = leb.chain_dynamics(2)
+for steps, one in ((0, True), (10, True), (1000, True), (10 ** 4, False)):
+    rec.recorder_clear()
+    ok(L.leb_pgd_nominal(ctypes.byref(dyn), 1, 40, P, P, None, P, 0, 1.0, steps, 0.25, P, P, P, P, None))
+    assert (rec.recorder_launches() == 1) == one, (steps, rec.recorder_launches())
+""")
